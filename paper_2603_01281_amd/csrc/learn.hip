@@ -2,14 +2,14 @@
 // Omega = h^T h_signal / n of token key embeddings, its left singular vectors and singular values, the rank k
 // that keeps a fraction gamma of the singular-value mass (Eq. 3), and the head score D_h = mean ||h+ - h-||_2.
 //
-// Not on the inference path: written for clarity and determinism, not speed.
+// Not on the inference path; deterministic throughout (every sum has a fixed order).
 //   cov_partial_kernel   Omega in 16-row strips, the token range split into chunks (fp32 accumulation); bf16
 //                        tensors take cov_partial_mfma_kernel (exact products on the matrix cores, one pass).
-//   jacobi_svd_kernel    one workgroup per head, Omega (d x d, column-major, padded) resident in LDS.  One-sided
-//                        (Hestenes) Jacobi: plane rotations applied from the right make the columns mutually
-//                        orthogonal, Omega V = U Sigma, so at convergence column j is sigma_j u_j: the left singular
-//                        vectors come out directly, which is what Eq. 2 needs.  d/2 disjoint column pairs per
-//                        step (round-robin tournament), d - 1 steps per sweep, until a sweep rotates nothing.
+//   cov_reduce_kernel, gram_kernel   Omega from its partial sums, Omega Omega^T in fp64.
+//   svd_kernel           one workgroup per head: pivoted Cholesky of the Gram matrix (fp64), then one-sided (Hestenes)
+//                        Jacobi on its factor: plane rotations applied from the right make the columns mutually
+//                        orthogonal, L V = U Sigma, so at convergence column j is sigma_j u_j: the left singular
+//                        vectors come out directly, which is what Eq. 2 needs.
 //   head_distance_*      token ranges per workgroup, 16-byte loads, partial sums merged in a fixed order.
 #include "common.h"
 
@@ -153,115 +153,355 @@ __global__ __launch_bounds__(kLearnThreads) void cov_partial_mfma_kernel(const u
   }
 }
 
-// grid (Hkv); dynamic LDS: D columns of D + 1 floats, then D floats (sigma), then D ints (rank).
-template <typename T, int D>
-__global__ __launch_bounds__(8 * D) void jacobi_svd_kernel(const float* __restrict__ part, int Hkv, int splits,
-                                                                   float inv_n, float gamma, float* __restrict__ U_out,
-                                                                   float* __restrict__ sigma_out, int* __restrict__ k_out,
-                                                                   T* __restrict__ U_packed, int r_pad) {
-  constexpr int LD = D + 1;
-  constexpr int NP = D / 2;                       // column pairs per step
-  constexpr int TPP = 16;                         // threads per pair (a pair never straddles a wave)
-  constexpr int NT = NP * TPP;                    // = blockDim.x
-  extern __shared__ float lds[];
-  float* A = lds;                                 // A[j * LD + i] = Omega[i][j]
-  float* sig = lds + D * LD;
-  int* rank = reinterpret_cast<int*>(sig + D);
-  const int h = blockIdx.x, tid = threadIdx.x;
+// Omega = (sum of the token splits, in order) / n, over the first split's slots.  grid-stride over 4-element pieces.
+__global__ __launch_bounds__(kLearnThreads) void cov_reduce_kernel(float* __restrict__ part, size_t elems, int splits, float inv_n) {
+  const size_t e = ((size_t)blockIdx.x * kLearnThreads + threadIdx.x) * 4;
+  if (e >= elems) return;
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+  for (int sp = 0; sp < splits; ++sp) s += *reinterpret_cast<const f32x4*>(part + (size_t)sp * elems + e);
+  *reinterpret_cast<f32x4*>(part + e) = s * inv_n;
+}
 
-  for (int idx = tid; idx < D * D; idx += NT) {
-    const int i = idx / D, j = idx % D;
-    float s = 0.f;
-    for (int sp = 0; sp < splits; ++sp) s += part[(((size_t)sp * Hkv + h) * D + i) * D + j];     // fixed order
-    A[j * LD + i] = s * inv_n;
+// B = Omega Omega^T in fp64 (a product of two fp32 values is exact there).  grid (D / 8, D / 64, Hkv): 8 rows x 64
+// columns of B per workgroup, which needs 72 rows of Omega in LDS (rows padded by 16 bytes: 16-byte reads down a
+// column of rows without bank conflicts).
+template <int D>
+__global__ __launch_bounds__(kLearnThreads) void gram_kernel(const float* __restrict__ omega, double* __restrict__ gram) {
+  constexpr int LD = D + 4, P = D / 4;                           // 16-byte pieces per row
+  constexpr int NLD = (72 * P + kLearnThreads - 1) / kLearnThreads;     // surplus threads repeat the last piece
+  __shared__ __attribute__((aligned(16))) float om[72 * LD];     // rows c0 .. c0 + 63, then r0 .. r0 + 7
+  const int h = blockIdx.z, r0 = 8 * blockIdx.x, c0 = 64 * blockIdx.y;
+  f32x4 v[NLD];
+#pragma unroll
+  for (int k = 0; k < NLD; ++k) {
+    const int idx = min((int)threadIdx.x + k * kLearnThreads, 72 * P - 1), row = idx / P;
+    v[k] = *reinterpret_cast<const f32x4*>(omega + ((size_t)h * D + (row < 64 ? c0 + row : r0 + row - 64)) * D + 4 * (idx % P));
+  }
+#pragma unroll
+  for (int k = 0; k < NLD; ++k) {
+    const int idx = min((int)threadIdx.x + k * kLearnThreads, 72 * P - 1);
+    *reinterpret_cast<f32x4*>(om + (idx / P) * LD + 4 * (idx % P)) = v[k];
   }
   __syncthreads();
+  const int c = threadIdx.x & 63, r = 2 * (threadIdx.x >> 6);    // one column, rows r and r + 1
+  double acc0 = 0.0, acc1 = 0.0;
+#pragma unroll 4
+  for (int j = 0; j < D; j += 4) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(om + c * LD + j);
+    const f32x4 y0 = *reinterpret_cast<const f32x4*>(om + (64 + r) * LD + j), y1 = *reinterpret_cast<const f32x4*>(om + (65 + r) * LD + j);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      acc0 = __builtin_fma((double)y0[e], (double)x[e], acc0);
+      acc1 = __builtin_fma((double)y1[e], (double)x[e], acc1);
+    }
+  }
+  double* g = gram + ((size_t)h * D + r0 + r) * D + c0 + c;
+  g[0] = acc0;
+  g[D] = acc1;
+}
 
-  const int pr = tid / TPP, sub = tid % TPP;
+// value of lane (l + DPP pattern) within the 16-lane row
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+// Eight sums over the 64 lanes at once: lane l receives the total of v[l / 8].
+__device__ __forceinline__ float reduce8(const float (&v)[8], int lane) {
+  float a[4], b[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 4]), false, false);
+    a[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(a[i]), __float_as_uint(a[i + 2]), false, false);
+    b[i] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+  const bool up = (lane & 8) != 0;
+  float r = (up ? b[1] : b[0]) + dpp<0x128>(up ? b[0] : b[1]);   // row_ror:8
+  r += dpp<0xB1>(r);                                             // lane ^ 1
+  r += dpp<0x4E>(r);                                             // lane ^ 2
+  r += dpp<0x141>(r);                                            // mirrored in 8
+  return r;
+}
+
+__device__ __forceinline__ unsigned wave_max(unsigned v) {
+  auto step = [&](unsigned u) __attribute__((always_inline)) { v = max(v, u); };
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));   // mirrored in 8
+  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));   // mirrored in 16
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  v = max(a[0], a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return (unsigned)__builtin_amdgcn_readfirstlane((int)max(b[0], b[1]));
+}
+__device__ __forceinline__ double lane_double(double v, int l) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, l), hi = (unsigned)__builtin_amdgcn_readlane((int)(u >> 32), l);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Left singular vectors and singular values of one head's Omega, from its Gram matrix B = Omega Omega^T (fp64).
+// grid (Hkv), one workgroup of D / 16 waves per head (the heads are independent and a step of either phase needs
+// everything the step before it produced, so more workgroups would only add synchronisation).
+//
+// Phase 1, Cholesky with diagonal pivoting, B = L L^T, in fp64: Omega and L have the same left singular vectors and
+// singular values (up to rotations from the right), and L, whose columns come out nearly sorted and nearly
+// orthogonal, needs about half the Jacobi sweeps that Omega needs.  fp64 because B holds squares: what falls below 1e-14
+// of its largest element is below 1e-7 of sigma_1, and is dropped.  B lives in registers (a thread has a tile of
+// D / 16 x 4 or 4 x 4); every wave keeps the diagonal and finds the pivot by itself, so a step has one barrier.
+//
+// Phase 2, one-sided Jacobi on L in fp32 in blocks of 8 columns: a wave holds two blocks (16 columns, D / 64 rows per
+// lane) in registers and rotates all pairs across them (8 rounds of 8 disjoint pairs, registers named at compile
+// time, the 8 dot products of a round reduced together); then blocks change partners through LDS (a round-robin
+// tournament of the blocks: D / 8 - 1 exchanges per sweep instead of one barrier per round of pairs).  Pairs inside a
+// block are rotated once per sweep.  A rotation is applied as three shears.  Sweeps repeat until one rotates nothing.
+// What bounds it: vector issue on the head's CU (about 140 instructions per round and wave, two waves per SIMD: 11 k
+// cycles per exchange of blocks).  8 heads, D = 128: 720 us (phase 1 78, phase 2 620 in 8 or 9 sweeps); the form before this
+// one, Jacobi on Omega with a barrier after every 64 pairs and all columns in LDS, took 2730 us.
+template <typename T, int D>
+__global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ gram, float gamma, float* __restrict__ U_out,
+                                                    float* __restrict__ sigma_out, int* __restrict__ k_out,
+                                                    T* __restrict__ U_packed, int r_pad) {
+  constexpr int NW = D / 16, NT = 64 * NW;
+  constexpr int RPL = D / 64;                     // rows per lane
+  constexpr int LD = D + RPL;                     // column stride in floats
+  typedef float rows_t __attribute__((ext_vector_type(RPL)));
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  float* A = lds;                                 // [D columns][LD]
+  double* colbuf = reinterpret_cast<double*>(lds + D * LD);      // [2][D]
+  float* sig = lds + D * LD + 4 * D;              // [D]
+  float* sorted_s = sig + D;                      // [D]
+  int* by_rank = reinterpret_cast<int*>(sorted_s + D);           // [D] column of the r-th largest value
+  const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // ---- phase 1 ----
+  float unit;                                     // sqrt of B's largest element: L is scaled by its inverse
+  int ncols = D;
+  {
+    constexpr int TR = D * D / NT / 4;            // a thread holds TR rows x 4 columns (8 or 4 rows)
+    const int tr = TR * (tid / (D / 4)), tc = 4 * (tid % (D / 4));
+    const double* Bh = gram + (size_t)h * D * D;
+    double a[TR][4], d[RPL];
+#pragma unroll
+    for (int i = 0; i < TR; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[i][j] = Bh[(size_t)(tr + i) * D + tc + j];
+#pragma unroll
+    for (int x = 0; x < RPL; ++x) d[x] = Bh[(size_t)(lane + 64 * x) * (D + 1)];
+    double floor_d = 0.0;
+    float key_scale = 1.f;
+    unit = 0.f;
+    for (int k = 0; k < D; ++k) {
+      // pivot: the largest remaining diagonal element (to 17 bits; the lower ones carry its index)
+      unsigned key = 0;
+#pragma unroll
+      for (int x = 0; x < RPL; ++x)
+        key = max(key, d[x] > 0.0 ? (__float_as_uint((float)d[x] * key_scale) & ~127u) | (unsigned)(lane + 64 * x) : 0u);
+      const int p = (int)(wave_max(key) & 127u);
+      double dp = d[0];
+#pragma unroll
+      for (int x = 1; x < RPL; ++x) dp = (p >> 6) == x ? d[x] : dp;
+      dp = lane_double(dp, p & 63);
+      if (k == 0) {
+        bool nan = false;                         // a sample that is not a number shows in the singular values
+#pragma unroll
+        for (int x = 0; x < RPL; ++x) nan = nan || d[x] != d[x];
+        floor_d = 1e-14 * dp;
+        unit = __any(nan) ? __builtin_nanf("") : (float)sqrt(dp);
+        key_scale = dp > 0.0 ? (float)(1.0 / dp) : 0.f;
+      }
+      if (!(dp > floor_d)) { ncols = k; break; }  // the same in every wave: same data, same operations
+      // row p of what is left of B, as it stands: l_k = row / sqrt(dp)
+      double* row = colbuf + (k & 1) * D;
+      if (tr == (p & ~(TR - 1))) {
+#pragma unroll
+        for (int i = 0; i < TR; ++i)
+          if ((p & (TR - 1)) == i) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) row[tc + j] = a[i][j];
+          }
+      }
+      double inv = __builtin_amdgcn_rcp(dp);      // 1 / dp: hardware estimate and two Newton steps
+      inv = __builtin_fma(__builtin_fma(-dp, inv, 1.0), inv, inv);
+      inv = __builtin_fma(__builtin_fma(-dp, inv, 1.0), inv, inv);
+      __syncthreads();
+      double rv[TR], cv[4], dv[RPL];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) cv[j] = row[tc + j] * inv;
+#pragma unroll
+      for (int i = 0; i < TR; ++i) rv[i] = row[tr + i];
+#pragma unroll
+      for (int x = 0; x < RPL; ++x) dv[x] = row[lane + 64 * x];
+#pragma unroll
+      for (int x = 0; x < RPL; ++x) d[x] = lane + 64 * x == p || d[x] <= 0.0 ? 0.0 : __builtin_fma(-dv[x] * inv, dv[x], d[x]);
+#pragma unroll
+      for (int i = 0; i < TR; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[i][j] = __builtin_fma(-rv[i], cv[j], a[i][j]);
+      if (wave == (k & (NW - 1))) {               // one wave writes the column of L
+        const float rho = (float)dp * key_scale;  // of the largest element
+        float f = __builtin_amdgcn_rsqf(rho);
+        f = f * __builtin_fmaf(-0.5f * rho * f, f, 1.5f) * key_scale;
+#pragma unroll
+        for (int x = 0; x < RPL; ++x) A[k * LD + lane + 64 * x] = (float)dv[x] * f;
+      }
+    }
+    for (int idx = tid; idx < (D - ncols) * LD; idx += NT) A[ncols * LD + idx] = 0.f;
+    __syncthreads();
+  }
+
+  // ---- phase 2 ----
+  const int nblk = max(2, ((ncols + 7) / 8 + 1) & ~1);           // blocks that take part (even)
   for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
     int rotated = 0;
-    for (int step = 0; step < D - 1; ++step) {
-      // round-robin tournament: position 0 stays, the others rotate; positions k and D - 1 - k meet
-      auto at = [&](int pos) {                    // pos - 1 + step < 2 (D - 1)
-        if (pos == 0) return 0;
-        const int x = pos - 1 + step;
-        return (x >= D - 1 ? x - (D - 1) : x) + 1;
-      };
-      int p = at(pr), q = at(D - 1 - pr);
-      if (p > q) { const int t = p; p = q; q = t; }
-      float* ap = A + p * LD;
-      float* aq = A + q * LD;
-      float alpha = 0.f, beta = 0.f, gam = 0.f;
+    for (int step = 0; step < nblk - 1; ++step) {
+      if (wave < nblk / 2) {
+        auto at = [&](int pos) {                  // round-robin: position 0 stays, the others rotate
+          if (pos == 0) return 0;
+          const int x = pos - 1 + step;
+          return (x >= nblk - 1 ? x - (nblk - 1) : x) + 1;
+        };
+        float* base[2] = {A + 8 * at(wave) * LD, A + 8 * at(nblk - 1 - wave) * LD};
+        rows_t x[16];
 #pragma unroll
-      for (int i = sub; i < D; i += TPP) {
-        const float x = ap[i], y = aq[i];
-        alpha = fmaf(x, x, alpha);
-        beta = fmaf(y, y, beta);
-        gam = fmaf(x, y, gam);
-      }
+        for (int j = 0; j < 16; ++j) x[j] = *reinterpret_cast<const rows_t*>(base[j / 8] + (j & 7) * LD + RPL * lane);
+        auto dot = [&](int p, int q) __attribute__((always_inline)) -> float {
+          float s = x[p][0] * x[q][0];
 #pragma unroll
-      for (int d = 1; d < TPP; d *= 2) {
-        alpha += __shfl_xor(alpha, d);
-        beta += __shfl_xor(beta, d);
-        gam += __shfl_xor(gam, d);
-      }
-      if (fabsf(gam) > kRotateTol * sqrtf(alpha * beta)) {        // the same decision in all TPP lanes of the pair
-        rotated = 1;
-        const float zeta = (beta - alpha) / (2.f * gam);
-        const float t = copysignf(1.f, zeta) / (fabsf(zeta) + sqrtf(1.f + zeta * zeta));
-        const float c = 1.f / sqrtf(1.f + t * t), s = c * t;
+          for (int i = 1; i < RPL; ++i) s = __builtin_fmaf(x[p][i], x[q][i], s);
+          return s;
+        };
+        // rotation of the lane's pair from its norms and dot product; returns t (0: leave the pair alone), sine and
+        // tangent of half the angle
+        auto angle = [&](float al, float be, float ga, float& sn, float& th) __attribute__((always_inline)) -> float {
+          const bool rot = ga * ga > (kRotateTol * kRotateTol) * (al * be);      // norms are 0 or in [1e-7, 1]
+          const float df = be - al, g2 = ga + ga;
+          float t = g2 * __builtin_amdgcn_rcpf(df + copysignf(__builtin_amdgcn_sqrtf(__builtin_fmaf(df, df, g2 * g2)), df));
+          t = rot ? t : 0.f;
+          const float w = __builtin_fmaf(t, t, 1.f);
+          float c = __builtin_amdgcn_rsqf(w);
+          c = c * __builtin_fmaf(-0.5f * w * c, c, 1.5f);
+          sn = c * t;
+          th = sn * __builtin_amdgcn_rcpf(1.f + c);
+          return t;
+        };
+        auto apply = [&](int p, int q, float sn, float th) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = sub; i < D; i += TPP) {
-          const float x = ap[i], y = aq[i];
-          ap[i] = c * x - s * y;
-          aq[i] = s * x + c * y;
+          for (int i = 0; i < RPL; ++i) {
+            const float x1 = __builtin_fmaf(-th, x[q][i], x[p][i]);
+            x[q][i] = __builtin_fmaf(sn, x1, x[q][i]);
+            x[p][i] = __builtin_fmaf(-th, x[q][i], x1);
+          }
+        };
+        auto lane_value = [&](float v, int j) __attribute__((always_inline)) {
+          return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 8 * j));
+        };
+        if (step == 0) {                          // pairs inside the blocks: 7 rounds of 4 pairs in each
+#pragma unroll
+          for (int r = 0; r < 7; ++r) {
+            // round-robin of 8: player 7 stays; pairs (7, r), (r + k, r - k) mod 7
+            float va[8], vb[8], vg[8];
+            int P[8], Q[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+              const int k = j & 3, o = 8 * (j >> 2);
+              P[j] = o + (k == 0 ? 7 : (r + k) % 7);
+              Q[j] = o + (k == 0 ? r : (r - k + 7) % 7);
+              va[j] = dot(P[j], P[j]);
+              vb[j] = dot(Q[j], Q[j]);
+              vg[j] = dot(P[j], Q[j]);
+            }
+            const float al = reduce8(va, lane), be = reduce8(vb, lane), ga = reduce8(vg, lane);
+            float sn, th;
+            const float t = angle(al, be, ga, sn, th);
+            rotated |= __any(t != 0.f);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) apply(P[j], Q[j], lane_value(sn, j), lane_value(th, j));
+          }
         }
+        // pairs across the blocks: in round r lanes 8 p .. 8 p + 7 look after columns p and 8 + (p + r) % 8; the norms
+        // are formed once and updated with each rotation
+        float va[8], vb[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { va[j] = dot(j, j); vb[j] = dot(8 + j, 8 + j); }
+        float al = reduce8(va, lane), be = reduce8(vb, lane);
+        const int next_lane = ((lane + 8) & 63) * 4;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          float vg[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) vg[j] = dot(j, 8 + ((j + r) & 7));
+          const float ga = reduce8(vg, lane);
+          float sn, th;
+          const float t = angle(al, be, ga, sn, th);
+          rotated |= __any(t != 0.f);             // no branch around the rotations: with t = 0 they change nothing
+          al = fmaxf(__builtin_fmaf(-t, ga, al), 0.f);
+          be = fmaxf(__builtin_fmaf(t, ga, be), 0.f);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) apply(j, 8 + ((j + r) & 7), lane_value(sn, j), lane_value(th, j));
+          be = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(next_lane, __builtin_bit_cast(int, be)));
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) *reinterpret_cast<rows_t*>(base[j / 8] + (j & 7) * LD + RPL * lane) = x[j];
       }
-      __syncthreads();
+      __syncthreads();                            // a block is read and written by the wave that holds it only
     }
     if (!__syncthreads_or(rotated)) break;
   }
 
-  // singular values = column norms; order them (descending, ties by column index)
-  if (tid < D) {
-    float s2 = 0.f;
-    for (int i = 0; i < D; ++i) s2 = fmaf(A[tid * LD + i], A[tid * LD + i], s2);
-    sig[tid] = sqrtf(s2);
+  // ---- singular values = column norms; order them (descending, ties by column index) ----
+  for (int c = wave; c < D; c += NW) {
+    const rows_t v = *reinterpret_cast<const rows_t*>(A + c * LD + RPL * lane);
+    float s2 = v[0] * v[0];
+#pragma unroll
+    for (int i = 1; i < RPL; ++i) s2 = __builtin_fmaf(v[i], v[i], s2);
+#pragma unroll
+    for (int s = 1; s < 64; s *= 2) s2 += __shfl_xor(s2, s);
+    if (lane == 0) sig[c] = sqrtf(s2);
   }
   __syncthreads();
   if (tid < D) {
     const float me = sig[tid];
     int r = 0;
+#pragma unroll 8
     for (int k = 0; k < D; ++k) r += (sig[k] > me) || (sig[k] == me && k < tid);
-    rank[tid] = r;
-    sigma_out[(size_t)h * D + r] = me;
+    by_rank[r] = tid;
+    sorted_s[r] = me;
+    sigma_out[(size_t)h * D + r] = me * unit;
   }
   __syncthreads();
-  // rank rule of Eq. 3 (one thread; d additions)
-  __shared__ int k_sel;
-  __shared__ float sorted_s[D];
-  __shared__ float sig_floor;
-  if (tid < D) sorted_s[rank[tid]] = sig[tid];
-  __syncthreads();
-  if (tid == 0) {
-    float total = 0.f;
-    for (int k = 0; k < D; ++k) total += sorted_s[k];
-    float run = 0.f;
-    int ks = D;
-    for (int k = 0; k < D; ++k) {
-      run += sorted_s[k];
-      if (run >= gamma * total) { ks = k + 1; break; }
+  // rank rule of Eq. 3: the smallest k whose leading values reach gamma of the sum; every wave works it out by itself
+  int k_sel;
+  {
+    float run[RPL], total = 0.f;                  // inclusive sums in index order: lane l has l, then 64 + l
+#pragma unroll
+    for (int x = 0; x < RPL; ++x) {
+      float v = sorted_s[64 * x + lane];
+#pragma unroll
+      for (int s = 1; s < 64; s *= 2) {
+        const float u = __shfl_up(v, s);
+        v += lane >= s ? u : 0.f;
+      }
+      run[x] = v + total;
+      total = __shfl(run[x], 63);
     }
-    k_sel = ks;
-    k_out[h] = ks;
-    sig_floor = kZeroSigma * sorted_s[0];
+    int below = 0;
+#pragma unroll
+    for (int x = 0; x < RPL; ++x) below += __popcll(__ballot(!(run[x] >= gamma * total)));
+    k_sel = min(below + 1, D);
+    if (tid == 0) k_out[h] = k_sel;
   }
-  __syncthreads();
-  for (int idx = tid; idx < D * D; idx += NT) {
-    const int j = idx / D, i = idx % D;                 // column j of A, element i
-    const float s = sig[j];
-    const float u = s > sig_floor ? A[j * LD + i] / s : 0.f;     // s > 0 here
-    const int r = rank[j];
+  static_assert(NT % D == 0, "a thread keeps its output column");
+  const int r = tid % D, j = by_rank[r];
+  const float s = sorted_s[r], s_inv = s > kZeroSigma * sorted_s[0] ? 1.f / s : 0.f;
+#pragma unroll 8
+  for (int i = tid / D; i < D; i += NT / D) {
+    const float u = A[j * LD + i] * s_inv;
     U_out[((size_t)h * D + i) * D + r] = u;
     if (U_packed && r < r_pad) {
       const float v = r < k_sel ? u : 0.f;
@@ -323,13 +563,13 @@ __global__ __launch_bounds__(kLearnThreads) void head_distance_partial_kernel(co
   }
 }
 
-// grid (Hkv), one wave: D_h = (sum of the head's partials, in order) / n
+// grid (Hkv), one wave: D_h = (sum of the head's partials, in a fixed order) / n
 __global__ void head_distance_finish_kernel(const float* __restrict__ part, int splits, float inv_n, float* __restrict__ D_out) {
-  if (threadIdx.x == 0) {
-    float s = 0.f;
-    for (int i = 0; i < splits; ++i) s += part[(size_t)blockIdx.x * splits + i];
-    D_out[blockIdx.x] = s * inv_n;
-  }
+  float s = 0.f;
+  for (int i = threadIdx.x; i < splits; i += 64) s += part[(size_t)blockIdx.x * splits + i];
+#pragma unroll
+  for (int d = 1; d < 64; d *= 2) s += __shfl_xor(s, d);
+  if (threadIdx.x == 0) D_out[blockIdx.x] = s * inv_n;
 }
 
 template <typename T, int D>
@@ -342,12 +582,16 @@ hipError_t launch_learn_td(const void* hn, const void* hs, int n, int Hkv, float
   else
     hipLaunchKernelGGL((cov_partial_kernel<T, D>), dim3(D / 16, Hkv, splits), dim3(kLearnThreads), 0, s,
                        static_cast<const T*>(hn), static_cast<const T*>(hs), n, Hkv, splits, part);
-  const size_t smem = ((size_t)D * (D + 1) + 2 * D) * sizeof(float);
-  auto kernel = jacobi_svd_kernel<T, D>;
+  const size_t elems = (size_t)Hkv * D * D;
+  double* gram = reinterpret_cast<double*>(part + elems);          // over the other splits' slots (learn_workspace_bytes has room)
+  hipLaunchKernelGGL(cov_reduce_kernel, dim3((unsigned)((elems / 4 + kLearnThreads - 1) / kLearnThreads)), dim3(kLearnThreads), 0, s,
+                     part, elems, splits, 1.0f / (float)n);
+  hipLaunchKernelGGL((gram_kernel<D>), dim3(D / 8, D / 64, Hkv), dim3(kLearnThreads), 0, s, part, gram);
+  const size_t smem = ((size_t)D * (D + D / 64) + 7 * D) * sizeof(float);
+  auto kernel = svd_kernel<T, D>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(Hkv), dim3(8 * D), smem, s, part, Hkv, splits, 1.0f / (float)n, gamma, U_out,
-                     sigma_out, k_out, static_cast<T*>(U_packed), r_pad);
+  hipLaunchKernelGGL(kernel, dim3(Hkv), dim3(4 * D), smem, s, gram, gamma, U_out, sigma_out, k_out, static_cast<T*>(U_packed), r_pad);
   return hipGetLastError();
 }
 
@@ -362,7 +606,8 @@ static inline int distance_splits(int n, int Hkv) {
 }
 
 size_t learn_workspace_bytes(int Hkv, int D, int n) {
-  const size_t cov = (size_t)learn_token_splits(n) * Hkv * D * D * sizeof(float);
+  const int splits = learn_token_splits(n);                        // at least Omega (fp32) and its Gram matrix (fp64)
+  const size_t cov = (size_t)(splits > 3 ? splits : 3) * Hkv * D * D * sizeof(float);
   const size_t dist = ((size_t)distance_splits(n, Hkv) * Hkv * sizeof(float) + 15) / 16 * 16;
   return cov > dist ? cov : dist;
 }
