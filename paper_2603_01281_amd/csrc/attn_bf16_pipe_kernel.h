@@ -84,6 +84,68 @@ __device__ __forceinline__ void pipe_load_16B(const void* base, uint32_t lane_of
                : "memory", "m0");
 }
 
+// Sum / maximum over the 64 lanes (all active), the same value in all of them.
+__device__ __forceinline__ float pipe_wave_sum(float v) {
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) v += __shfl_xor(v, m);
+  return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(v)));
+}
+__device__ __forceinline__ int pipe_wave_max(int v) {
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) v = max(v, __shfl_xor(v, m));
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
+// What a block of query rows and a workgroup cost beside their key tiles, in units of one 64-key tile (2700 cycles):
+// a block waits for its first tiles, runs its last ones outside the unrolled loop and writes its output; a workgroup
+// starts and prepares the edit.
+constexpr float PIPE_BLOCK_TILES = 4.f, PIPE_START_TILES = 3.f;
+
+// Workgroup `item` of the a.width that a batch of prompts of different lengths (at most 64) gets per head chunk.
+// Lane i looks after prompt i: its n_i blocks of query rows are T_i = sum over them of (tiles + PIPE_BLOCK_TILES) of
+// work, which W_i = floor(T_i / L) + 1 workgroups share.  L is the load of a workgroup if the batch is to take R
+// rounds of the a.slots workgroups that run at a time, T / (R slots - B), and no less than the longest block;
+// R = 1 .. PIPE_RAGGED_ROUNDS is the one with the smallest R (L + PIPE_START_TILES).  The longest prompts come first,
+// so the last workgroups to start are the shortest.  Returns false past the last workgroup.
+constexpr int PIPE_RAGGED_ROUNDS = 6;
+template <int BQ>
+__device__ __forceinline__ bool pipe_ragged_item(const AttnArgs& a, int item, int& b, int& slot, int& W) {
+  const int lane = threadIdx.x & 63;
+  size_t tok0;
+  int len = 0;
+  if (lane < a.B) prompt_extent(a, lane, tok0, len);
+  const int nb = (len + BQ - 1) / BQ;
+  constexpr float T = BQ / 64.f;                 // key tiles per block of query rows
+  const float work = (float)nb * (0.5f * T * (float)(nb + 1) + PIPE_BLOCK_TILES);
+  const float total = pipe_wave_sum(work);
+  const float longest = T * (float)pipe_wave_max(nb) + PIPE_BLOCK_TILES;
+  float best = 0.f, load = longest;
+#pragma unroll
+  for (int R = 1; R <= PIPE_RAGGED_ROUNDS; ++R) {
+    const int share = R * a.slots - a.B;
+    const float L = fmaxf(longest, total / (float)max(share, 1));
+    const float cost = (float)R * (L + PIPE_START_TILES);
+    if (share > 0 && (best == 0.f || cost < best)) {
+      best = cost;
+      load = L;
+    }
+  }
+  int w = min(nb, (int)(work / load) + 1);
+  // sum of w <= total / load + B <= R slots <= a.width; should rounding ever break this, one workgroup per prompt
+  if (pipe_wave_sum((float)w) > (float)a.width) w = min(nb, 1);
+  int first = 0;                                 // this prompt's first workgroup
+  for (int j = 0; j < a.B; ++j) {
+    const int nj = __builtin_amdgcn_readlane(nb, j), wj = __builtin_amdgcn_readlane(w, j);
+    first += (nj > nb || (nj == nb && j < lane)) ? wj : 0;
+  }
+  const unsigned long long hit = __ballot(item >= first && item < first + w);
+  if (hit == 0ull) return false;
+  b = __builtin_ctzll(hit);
+  slot = item - __builtin_amdgcn_readlane(first, b);
+  W = __builtin_amdgcn_readlane(w, b);
+  return true;
+}
+
 // HPW heads x RBW row groups = waves per workgroup; every wave owns RPW blocks of 32 consecutive query rows.
 // RPW = 2 (four waves, one per SIMD, 512-register budget) reads every K / V fragment once for two products.
 // NKR: rank of the concatenated basis in blocks of 32 columns (compile-time so that the edit is straight-line code).
@@ -124,30 +186,32 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   const int Scap = a.S;                      // tokens per prompt in memory (strides, launch grid)
   const int G = a.Hq / a.Hkv;
   const int nHC = a.Hq / HPW;
-  const int nQB = (Scap + BQ - 1) / BQ;
-  // A workgroup handles two blocks of query rows of one (batch, head group), one after the other: block
-  // nQB - 1 - p and block p.  Every workgroup then scans nQB + 1 key tiles (no imbalance from causality), the
-  // steering set-up is done once for both, and the first loads of the second block overlap the first block's
-  // output stores.  (With nQB odd the middle block is on its own.)
-  // blockIdx = (prompt, pair, head chunk), head chunk fastest: workgroups are dispatched round-robin over the
+  // A workgroup handles several blocks of query rows of one (batch, head group), one after the other.  A prompt's
+  // blocks, latest (longest) first, are dealt to its W workgroups back and forth: slot 0 .. W-1, then W-1 .. 0 and so
+  // on.  Two deals give every slot the same number of key tiles, so there is no imbalance from causality; the
+  // steering set-up is done once for all of a workgroup's blocks, and a block's first loads overlap the output stores
+  // of the one before.  W comes from the launcher (see pipe_width there).
+  // blockIdx = (prompt, slot, head chunk), head chunk fastest: workgroups are dispatched round-robin over the
   // XCDs in index order, so with 8 head chunks an XCD's L2 serves one KV head, and the workgroups resident at the
   // same time walk the K / V tiles of the same prompt from tile 0 on, at the same pace.
-  const int npairs = (nQB + 1) / 2;
   const int hc = (int)(blockIdx.x % nHC);
-  const int bp = (int)(blockIdx.x / nHC);
-  const int b = bp / npairs, pair = bp % npairs;
+  const int item = (int)(blockIdx.x / nHC);
   const int hq0 = hc * HPW;
   const int h = hq0 / G;
+  int b, slot, W = a.width;
+  if (a.slots) {
+    if (!pipe_ragged_item<BQ>(a, item, b, slot, W)) return;
+  } else {
+    b = item / a.width;
+    slot = item % a.width;
+  }
   size_t tok0;                               // first token of this prompt in the tensors
   int S;                                     // this prompt's length: rows and keys beyond it do not exist
   prompt_extent(a, b, tok0, S);
-  int npass = (nQB - 1 - pair != pair) ? 2 : 1;
-  int qb = nQB - 1 - pair;
-  if (qb * BQ >= S) {                        // the later block lies beyond this prompt's end
-    qb = pair;
-    npass = 1;
-  }
-  if (qb * BQ >= S) return;                  // workgroup-uniform, before any barrier
+  const int nblocks = (S + BQ - 1) / BQ;
+  if (!a.slots && (a.cu || a.lens)) W = (nblocks + 1) / 2;
+  if (slot >= W || slot >= nblocks) return;  // workgroup-uniform, before any barrier
+  int qb = nblocks - 1 - slot;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -232,6 +296,19 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   auto issue_k = [&](int t) __attribute__((always_inline)) { issue_k_to(std::false_type{}, t, kst_base + (t % 3) * TB); };
   auto issue_v = [&](int t) __attribute__((always_inline)) { issue_v_to(std::false_type{}, t, vpos(2 * t - 1), vpos(2 * t)); };
 
+  // 4 KB per wave for turning Q rows into operands and the output accumulators into rows: the third stage of the K
+  // ring and positions 3 and 4 of the V ring, which a block's first loads do not touch.  32 rows x 128 bytes; the
+  // 16-byte chunk of a row is swizzled with the row (chunk ^ row % 8).
+  static_assert(RPW == 1 && NW <= 8, "one 4 KB staging area per wave");
+  unsigned char* const stg = wave < 4 ? Kst + 2 * TB + 4096 * wave : Vst + 3 * HB + 4096 * (wave - 4);
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+  auto stg_line = [&](int i) __attribute__((always_inline)) -> u32x4* {     // chunk lane % 8 of row 8 i + lane / 8
+    return reinterpret_cast<u32x4*>(stg + 1024 * i + 128 * (lane >> 3) + 16 * ((lane & 7) ^ (lane >> 3)));
+  };
+  auto stg_row = [&](int chunk) __attribute__((always_inline)) -> unsigned char* {     // of row l32
+    return stg + 128 * l32 + 16 * (chunk ^ (l32 & 7));
+  };
+
   // ---- Q fragments: B operand of S^T = K Q^T, lane (col = row qi, k = 16 ks + 8 hf + e) ----
   bf16x8 qf[RPW][KS];
   // First loads of a block of query rows: K tiles 0 and 1, V blocks -1 (a copy of row 0: the first step's PV
@@ -241,15 +318,30 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     issue_v(0);
     if (ntiles > 1) issue_k(1);
     issue_v(1);
+    // Raw order: register i of lane l holds 16-byte chunk (l % 8) + 8 (i / 4) of row 8 (i % 4) + l / 8, so every load
+    // covers eight whole 128-byte lines; q_operands() turns them into operands through LDS.  (Fetched in operand
+    // order, 32 rows x 32 bytes per load, the address unit took 3 cycles per row: 6000 cycles per block.)
 #pragma unroll
-    for (int rp = 0; rp < RPW; ++rp) {
-      const int qi = qi0 + 32 * rp;
-      const bool ok = qi < S;
-      const uint16_t* qp = Qg + ((tok0 + (ok ? qi : 0)) * a.Hq + hq) * D + 8 * hf;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)     // rows past the end read row 0 (finite data, results never stored):
-        qf[rp][ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qp + 16 * ks));   // no branch, no wait here
+    for (int i = 0; i < KS; ++i) {        // rows past the end read row 0 (finite data, results never stored):
+      const int qi = qw + 8 * (i & 3) + (lane >> 3);                                          // no branch, no wait here
+      const uint16_t* qp = Qg + ((tok0 + (qi < S ? qi : 0)) * a.Hq + hq) * D + 64 * (i >> 2) + 8 * (lane & 7);
+      qf[0][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qp));
     }
+  };
+  auto q_operands = [&]() __attribute__((always_inline)) {
+    bf16x8 qn[KS];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) *stg_line(i) = __builtin_bit_cast(u32x4, qf[0][4 * half + i]);
+      asm volatile("" ::: "memory");       // a wave's LDS accesses complete in program order: no wait needed
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        qn[4 * half + ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(stg_row(2 * ks + hf)));
+      asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[0][ks] = qn[ks];
   };
   begin_block();
 
@@ -673,6 +765,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
 
   // ---- prologue: wait for the first tiles, edit K(0) and K(1), first block of S^T ----
   dma_wait_vmcnt<0>();   // also covers the Q, U and mask loads issued after the tile loads
+  q_operands();
 #pragma unroll
   for (int rp = 0; rp < RPW; ++rp)
 #pragma unroll
@@ -1004,38 +1097,44 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
 
   // ---- next block's first loads (after a barrier: the last PV product above still read the V ring), then this
   // block's output ----
-  const int qi_out = qi0;
-  const bool more = pass + 1 < npass;
+  const int qw_out = qw;
+  const int dealt = (pass + 1) * W + (pass & 1 ? slot : W - 1 - slot);    // the next deal's block for this slot
+  const bool more = dealt < nblocks;
   if (more) {
     dma_barrier();
-    qb = pair;
+    qb = nblocks - 1 - dealt;
     qw = qb * BQ + WR * (wave % RBW);
     qi0 = qw + l32;
     last_key = min(S, qb * BQ + BQ) - 1;
     ntiles = last_key / BK + 1;
     begin_block();
   }
+  if (!more) dma_barrier();    // the staging areas belong to the rings
+  // Output: through the staging area, 64 of the 128 columns at a time, so that every store covers eight whole
+  // 128-byte lines (straight from the accumulators a store is 32 pieces of 16 bytes: 13000 cycles per block).
+  const float l_tot = l_run[0] + __shfl_xor(l_run[0], 32);
+  const float inv = 1.f / l_tot;
 #pragma unroll
-  for (int rp = 0; rp < RPW; ++rp) {
-    const int qi = qi_out + 32 * rp;
-    const float l_tot = l_run[rp] + __shfl_xor(l_run[rp], 32);
-    if (qi < S) {
-      const float inv = 1.f / l_tot;
-      uint16_t* op = Og + ((tok0 + qi) * a.Hq + hq) * D + 4 * hf;
+  for (int half = 0; half < 2; ++half) {
 #pragma unroll
-      for (int db = 0; db < DB; ++db) {
+    for (int c4 = 0; c4 < 8; ++c4) {       // columns 64 half + 8 c4 + 4 hf .. + 3
+      bf16x4 o4;
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          bf16x4 o4;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[rp][db][4 * q4 + e] * inv);
-          *reinterpret_cast<uint2*>(op + 32 * db + 8 * q4) = __builtin_bit_cast(uint2, o4);
-        }
-      }
-      // m_run is the reference exponent in units of s * scale * log2(e); l_tot is relative to it
-      if (a.lse && hf == 0) a.lse[lse_index(a, b, hq, tok0, qi)] = m_run[rp] * 0.6931471805599453f + logf(l_tot);
+      for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[0][2 * half + c4 / 4][4 * (c4 & 3) + e] * inv);
+      *reinterpret_cast<uint2*>(stg_row(c4) + 8 * hf) = __builtin_bit_cast(uint2, o4);
     }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int qi = qw_out + 8 * i + (lane >> 3);
+      const u32x4 line = *stg_line(i);
+      if (qi < S) *reinterpret_cast<u32x4*>(Og + ((tok0 + qi) * a.Hq + hq) * D + 64 * half + 8 * (lane & 7)) = line;
+    }
+    asm volatile("" ::: "memory");
   }
+  // m_run is the reference exponent in units of s * scale * log2(e); l_tot is relative to it
+  if (a.lse && hf == 0 && qw_out + l32 < S)
+    a.lse[lse_index(a, b, hq, tok0, qw_out + l32)] = m_run[0] * 0.6931471805599453f + logf(l_tot);
   if (!more) break;
   }   // for pass
 }
