@@ -217,7 +217,9 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
   const int hq = hq0 + wave / RBW;
-  int qw = qb * BQ + WR * (wave % RBW);    // first query row of this wave
+  // Waves w and w + 4 share a SIMD: their row blocks are chosen to end on different tiles or halves of a tile.
+  const int rb = RBW == 1 ? 0 : RBW == 2 ? (wave ^ (wave >> 2)) & 1 : RBW == 4 ? (wave & 3) ^ (wave >> 2 ? 3 : 0) : wave < 4 ? wave : 11 - wave;
+  int qw = qb * BQ + WR * rb;    // first query row of this wave
   int qi0 = qw + l32;                      // this lane's query row in row block 0 (block rp: + 32 rp)
 
   const float gain = STEER ? st.gain[h] : 0.f;
@@ -930,10 +932,10 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     for (int rp = 0; rp < RPW; ++rp) sn[rp] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, qf[rp][ks], sn[rp], 0, 0, 0);
   };
   constexpr float kSumLimit = 4096.f;          // probabilities stay below 2^12
-  auto step = [&](auto koff_c, auto knext_c, auto voff_c, f32x16 (&cur)[RPW], f32x16 (&next)[RPW], bf16x8 (&pb)[RPW][2],
+  auto step = [&](auto koff_c, uint32_t knext0, uint32_t knext1, auto voff_c, f32x16 (&cur)[RPW], f32x16 (&next)[RPW], bf16x8 (&pb)[RPW][2],
                   bf16x8 (&kpre)[2]) __attribute__((always_inline)) {
     static_assert(KS == 8 && RPW == 1, "the schedule below is written for eight k-slices and one row block per wave");
-    const int KOFF = koff_c, KNEXT = knext_c, VOFF = voff_c;
+    const int KOFF = koff_c, VOFF = voff_c;
     bf16x8 pn[2];
     float lb;
 #pragma unroll
@@ -950,8 +952,8 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     qk_one(6, k6, next);
     qk_one(7, k7, next);
     pv_half(VOFF, pb);
-    kpre[0] = kfrag(0, KNEXT);
-    kpre[1] = kfrag(1, KNEXT);
+    kpre[0] = *(pipe_lds_bf16x8_ptr)(uintptr_t)knext0;
+    kpre[1] = *(pipe_lds_bf16x8_ptr)(uintptr_t)knext1;
     block_exp_sum(cur[0], pn, lb);
     // Program order: every MFMA is followed by its share of the 24 LDS reads, two plain vector instructions and
     // (from the second MFMA on, when the first multiply-adds have been issued) one exponential: the transcendental
@@ -994,12 +996,36 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(kaddr[ks]));
 #pragma unroll
     for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(vaddr[db]));
-    step(integral_constant<int, ST * TB + HB>{}, integral_constant<int, ((ST + 1) % 3) * TB>{}, integral_constant<int, ((2 * ST + 5) % 6) * HB>{}, sc0, sc1, pb, kpre);
+    step(integral_constant<int, ST * TB + HB>{}, kaddr[0] + ((ST + 1) % 3) * TB, kaddr[1] + ((ST + 1) % 3) * TB, integral_constant<int, ((2 * ST + 5) % 6) * HB>{}, sc0, sc1, pb, kpre);
     if (STEER && !DENSE && __builtin_expect(ztile == t, 0)) corr(t, 32, sc1);
     top(std::true_type{}, st_c, t);
     if (kEventsInHot) events(t, ((ST + 1) % 3) * TB, kpre);
-    step(integral_constant<int, ((ST + 1) % 3) * TB>{}, integral_constant<int, ((ST + 1) % 3) * TB + HB>{}, integral_constant<int, 2 * ST * HB>{}, sc1, sc0, pb, kpre);
+    step(integral_constant<int, ((ST + 1) % 3) * TB>{}, kaddr[0] + ((ST + 1) % 3) * TB + HB, kaddr[1] + ((ST + 1) % 3) * TB + HB, integral_constant<int, 2 * ST * HB>{}, sc1, sc0, pb, kpre);
     bottom(std::true_type{}, t);
+  };
+
+  // A step at run-time ring offsets.  The operand addresses are moved there before the step and back after it: an
+  // address formed inside the step is a vector instruction that the order asked for has no place for, and the
+  // step's MFMAs then end up in a row in front of its exponentials (4100 cycles per tile instead of the loop's 2700).
+  auto move_addr = [&](uint32_t dk, uint32_t dv) __attribute__((always_inline)) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      kaddr[ks] += dk;
+      asm volatile("" : "+v"(kaddr[ks]));
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      vaddr[db] += dv;
+      asm volatile("" : "+v"(vaddr[db]));
+    }
+  };
+  auto ring_step = [&](int koff, int knext, int voff, f32x16 (&cur)[RPW], f32x16 (&next)[RPW]) __attribute__((always_inline)) {
+    uint32_t k0 = kaddr[0] + knext, k1 = kaddr[1] + knext;
+    asm volatile("" : "+v"(k0), "+v"(k1));
+    move_addr(koff, voff);
+    __builtin_amdgcn_sched_barrier(0);
+    step(IC0{}, k0, k1, IC0{}, cur, next, pb, kpre);
+    move_addr(-koff, -voff);
   };
 
   // Hot iterations: tile t is seen in full by every row of this wave and tile t + 2 exists and is complete.  They
@@ -1026,24 +1052,12 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     top(std::false_type{}, IC0{}, t);
     const int off = (t % 3) * TB, offn = ((t + 1) % 3) * TB;
     if (STEER && !DENSE && ztile == t) corr(t, 0, sc0);
-    step(off + HB, offn, (int)vpos(2 * t - 1), sc0, sc1, pb, kpre);
+    ring_step(off + HB, offn, (int)vpos(2 * t - 1), sc0, sc1);
     if (STEER && !DENSE && ztile == t) corr(t, 32, sc1);
     events(t, offn, kpre);
-    step(offn, offn + HB, (int)vpos(2 * t), sc1, sc0, pb, kpre);
+    ring_step(offn, offn + HB, (int)vpos(2 * t), sc1, sc0);
     bottom(std::false_type{}, t);
     ++t;
-  }
-  // ---- up to two more full tiles before the wave's last one: same pipelined step, ring stage known at run time ----
-#pragma nounroll
-  for (; t < tw_last; ++t) {
-    top(std::false_type{}, IC0{}, t);
-    const int off = (t % 3) * TB, offn = ((t + 1) % 3) * TB;
-    if (STEER && !DENSE && ztile == t) corr(t, 0, sc0);
-    step(off + HB, offn, (int)vpos(2 * t - 1), sc0, sc1, pb, kpre);
-    if (STEER && !DENSE && ztile == t) corr(t, 32, sc1);
-    events(t, offn, kpre);
-    step(offn, offn + HB, (int)vpos(2 * t), sc1, sc0, pb, kpre);
-    bottom(std::false_type{}, t);
   }
   // ---- the wave's last tile (causal mask, nothing further to score), then idle turns while other waves finish.
   // The second block of that tile may still be in flight during its own iteration (V runs half a tile behind), so
@@ -1060,34 +1074,31 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
       owed = false;
     }
     if (t == tw_last) {
+      // A wave whose rows are the first 32 of the tile sees nothing of its second block; one whose rows are the
+      // last 32 sees all of its first.
       const int off = (t % 3) * TB;
-      qk_part(IC0{}, ICK{}, off + HB, sc1);
+      const bool second = (qw & 32) != 0;      // wave-uniform
+      if (second) qk_part(IC0{}, ICK{}, off + HB, sc1);
       if (zt) {
         corr(t, 0, sc0);
-        corr(t, 32, sc1);
+        if (second) corr(t, 32, sc1);
       }
       if (t > 0) pv_half((int)vpos(2 * t - 1), pb);      // the block before this tile (its softmax ran in the last step)
-#pragma unroll
-      for (int rp = 0; rp < RPW; ++rp) {
-        pipe_mfma_result_guard(sc0[rp]);
-        causal_mask(t * BK, rp, sc0[rp]);
-        raise_reference(rp, block_max(sc0[rp]));
-      }
+      pipe_mfma_result_guard(sc0[0]);
+      if (!second) causal_mask(t * BK, 0, sc0[0]);
+      raise_reference(0, block_max(sc0[0]));
       rescale_outputs();
-#pragma unroll
-      for (int rp = 0; rp < RPW; ++rp) block_exp(rp, sc0[rp], pb[rp]);
+      block_exp(0, sc0[0], pb[0]);
       pv_half((int)vpos(2 * t), pb);
-#pragma unroll
-      for (int rp = 0; rp < RPW; ++rp) {
-        pipe_mfma_result_guard(sc1[rp]);
-        causal_mask(t * BK + 32, rp, sc1[rp]);
-        raise_reference(rp, block_max(sc1[rp]));
+      if (second) {
+        pipe_mfma_result_guard(sc1[0]);
+        causal_mask(t * BK + 32, 0, sc1[0]);
+        raise_reference(0, block_max(sc1[0]));
+        rescale_outputs();
+        block_exp(0, sc1[0], pb[0]);
+        owed = true;
+        owed_off = (int)vpos(2 * t + 1);
       }
-      rescale_outputs();
-#pragma unroll
-      for (int rp = 0; rp < RPW; ++rp) block_exp(rp, sc1[rp], pb[rp]);
-      owed = true;
-      owed_off = (int)vpos(2 * t + 1);
     }
     bottom(std::false_type{}, t);
   }
@@ -1103,7 +1114,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   if (more) {
     dma_barrier();
     qb = nblocks - 1 - dealt;
-    qw = qb * BQ + WR * (wave % RBW);
+    qw = qb * BQ + WR * rb;
     qi0 = qw + l32;
     last_key = min(S, qb * BQ + BQ) - 1;
     ntiles = last_key / BK + 1;
