@@ -6,7 +6,10 @@
 // so a token contributes one contiguous G*D run) and writes D fp32 partial sums to the
 // workspace.  Stage 2 (one small workgroup per (batch, KV head)) adds the partials in a fixed
 // order, so the result is deterministic, then forms the M alignments and normalises them.
+#include <type_traits>
+
 #include "common.h"
+#include "project_wide.h"
 
 namespace seka {
 
@@ -197,6 +200,7 @@ __global__ __launch_bounds__(kFinishThreads) void route_finish_kernel(const floa
 // ---- query projection with the routing sums in its epilogue (Sec. 3.3: the routing query is a by-product of the
 // projection that produces Q, so it need not be read back) ----
 //
+// The sizes that project_route_wide_kernel does not take (rule in launch_project_route):
 // Q[t, n] = sum_e X[t, e] W[n, e]  (bf16 in, fp32 accumulate, bf16 out; W is the projection weight with one row per
 // output feature, the layout of a linear layer).  One workgroup = 128 tokens x 128 output features (one head at
 // D = 128), four waves of 64 x 64, v_mfma_f32_32x32x16_bf16; 64-wide slices of E go through two LDS stages, the
@@ -363,18 +367,32 @@ hipError_t launch_project_route(const void* X, const void* W, int E, void* Qout,
                                 const float* proto, int M, int mode, float tau, float* w_out, void* workspace,
                                 hipStream_t s) {
   const int N = Hq * 128, G = Hq / Hkv;
-  const dim3 grid(N / kProjTile, (unsigned)(((size_t)B * S) / kProjTile));
+  const long long tokens = (long long)B * S;
+  const dim3 grid(N / kProjTile, (unsigned)(tokens / kProjTile));
   float* ws = static_cast<float*>(workspace);
+  const uint16_t *x = static_cast<const uint16_t*>(X), *wq = static_cast<const uint16_t*>(W);
+  uint16_t* q = static_cast<uint16_t*>(Qout);
+  const long long wide = ((tokens + kWideTile - 1) / kWideTile) * ((N + kWideTile - 1) / kWideTile);
+  // 128 x 128 tiles while there is at most one per compute unit (4 times as many as 256 x 256 ones), us for E = 4096,
+  // N = 4096, 128 / 256: 512 tokens 52 / 69, 1024 55 / 71, 2048 90 / 78, 4096 173 / 119, 32768 1336 / 811; 5120 x
+  // 1024 x 1024 (80 tiles) 33 / 29.  The lane offsets of the wide kernel are 32 bits: E below 2^22.
+  if (wide > 64 && E < (1 << 22)) {
+    auto kernel = w_out ? project_route_wide_kernel<true> : project_route_wide_kernel<false>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       8 * kWideHalf);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((wide + 7) / 8 * 8)), dim3(512), 8 * kWideHalf, s, x, wq, q, E, tokens, N, S, G,
+                       Hkv, ws);
+  } else if (w_out != nullptr) {
+    hipLaunchKernelGGL((project_route_kernel<true>), grid, dim3(256), 0, s, x, wq, q, E, N, S, G, Hkv, ws);
+  } else {
+    hipLaunchKernelGGL((project_route_kernel<false>), grid, dim3(256), 0, s, x, wq, q, E, N, S, G, Hkv, ws);
+  }
   if (w_out != nullptr) {
-    hipLaunchKernelGGL((project_route_kernel<true>), grid, dim3(256), 0, s, static_cast<const uint16_t*>(X),
-                       static_cast<const uint16_t*>(W), static_cast<uint16_t*>(Qout), E, N, S, G, Hkv, ws);
     const float inv_count = 1.0f / ((float)S * (float)G);
     hipLaunchKernelGGL((route_finish_kernel<128>), dim3(B * Hkv), dim3(kFinishThreads), 0, s, ws, (S / 64) * G, inv_count,
                        proto, Hkv, M, mode, tau, static_cast<const int*>(nullptr), static_cast<const int*>(nullptr), 0, S, 0, G,
                        w_out);
-  } else {
-    hipLaunchKernelGGL((project_route_kernel<false>), grid, dim3(256), 0, s, static_cast<const uint16_t*>(X),
-                       static_cast<const uint16_t*>(W), static_cast<uint16_t*>(Qout), E, N, S, G, Hkv, ws);
   }
   return hipGetLastError();
 }
