@@ -95,17 +95,13 @@ def _check(status):
         raise SekaError(status)
 
 
-def _torch():
-    return torch
-
-
 def _dtype_code(t):
-    torch = _torch()
-    if t.dtype == torch.float32:
+    dtype = t.dtype
+    if dtype == torch.float32:
         return SEKA_F32
-    if t.dtype == torch.bfloat16:
+    if dtype == torch.bfloat16:
         return SEKA_BF16
-    raise TypeError(f"unsupported tensor dtype {t.dtype}")
+    raise TypeError(f"unsupported tensor dtype {dtype}")
 
 
 def _dev(t, name):
@@ -118,7 +114,9 @@ def _dev(t, name):
 
 def _stream(stream):
     if stream is None:
-        return _torch().cuda.current_stream().cuda_stream
+        # the handle of torch.cuda.current_stream() without building a Stream object: 3 us less on every call, which for
+        # the shortest prompts is a third of it
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return stream
 
 
@@ -130,10 +128,10 @@ def _steer(U, gain, mask, w, Hkv, key_scale=None, tokens=None, D=None, dtype=Non
     """U [Hkv,M,D,r] device tensor; gain: host sequence of Hkv floats; mask [B,S] (or [total]) uint8 device; w [B,Hkv,M]
     fp32 device or None; key_scale: host sequence of Hkv floats or None (all ones).  tokens: the number of mask
     bytes the call will index; D, dtype, B: what U, mask and w must agree with."""
-    torch = _torch()
     if U.dim() != 4:
         raise ValueError("U must be [Hkv, M, D, r]")
-    if U.shape[0] != Hkv or (D is not None and U.shape[2] != D):
+    heads, M, rows, r = U.shape
+    if heads != Hkv or (D is not None and rows != D):
         raise ValueError(f"U is {tuple(U.shape)}, expected [Hkv={Hkv}, M, D={D}, r]")
     if dtype is not None and U.dtype != dtype:
         raise TypeError(f"U must have the tensors' dtype {dtype}, got {U.dtype}")
@@ -144,14 +142,14 @@ def _steer(U, gain, mask, w, Hkv, key_scale=None, tokens=None, D=None, dtype=Non
     if len(gain) != Hkv or (key_scale is not None and len(key_scale) != Hkv):
         raise ValueError(f"gain / key_scale must have one entry per KV head ({Hkv})")
     if w is not None:
-        if w.dtype != torch.float32 or w.dim() != 3 or w.shape[1] != Hkv or w.shape[2] != U.shape[1] or \
+        if w.dtype != torch.float32 or w.dim() != 3 or w.shape[1] != Hkv or w.shape[2] != M or \
                 (B is not None and w.shape[0] != B):
-            raise ValueError(f"w must be fp32 [B={B}, Hkv={Hkv}, M={U.shape[1]}], got {w.dtype} {tuple(w.shape)}")
+            raise ValueError(f"w must be fp32 [B={B}, Hkv={Hkv}, M={M}], got {w.dtype} {tuple(w.shape)}")
     gains = (ctypes.c_float * Hkv)(*[float(g) for g in gain])
     scales = None
     if key_scale is not None:
         scales = (ctypes.c_float * Hkv)(*[float(a) for a in key_scale])
-    st = seka_steer(int(U.shape[1]), int(U.shape[3]), _dev(U, "U"), _dev(w, "w"), gains, _dev(mask, "mask"), scales)
+    st = seka_steer(M, r, _dev(U, "U"), _dev(w, "w"), gains, _dev(mask, "mask"), scales)
     st._keepalive = (gains, scales)
     return st
 
@@ -163,14 +161,13 @@ def seka_route_workspace_bytes(B, S, Hq, Hkv, D, dtype, t0, t1):
 
 def seka_route(Q, proto, t0, t1, mode=SEKA_ROUTE_SOFTMAX_COS, tau=10.0, w_out=None, workspace=None, stream=None):
     """Q [B,S,Hq,D] (fp32|bf16), proto [Hkv,M,D] fp32 -> w_out [B,Hkv,M] fp32 (allocated if None)."""
-    torch = _torch()
     B, S, Hq, D = Q.shape
     Hkv, M, _ = proto.shape
     sh = _shape(B, S, Hq, Hkv, D, _dtype_code(Q), 0.0)
     if w_out is None:
         w_out = torch.empty((B, Hkv, M), dtype=torch.float32, device=Q.device)
-    need = lib.seka_route_workspace_bytes(ctypes.byref(sh), t0, t1)
     if workspace is None:
+        need = lib.seka_route_workspace_bytes(ctypes.byref(sh), t0, t1)
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=Q.device)
     _check(lib.seka_route(_dev(Q, "Q"), ctypes.byref(sh), _dev(proto, "proto"), M, t0, t1, mode, float(tau),
                           _dev(w_out, "w_out"), _dev(workspace, "workspace"), workspace.numel() * workspace.element_size(),
@@ -182,7 +179,6 @@ def seka_route_ragged(Q, proto, window, seq_lens=None, cu_seqlens=None, max_len=
                       tau=10.0, w_out=None, workspace=None, stream=None):
     """Per-prompt routing over the last `window` tokens of each prompt.  Padded: Q [B,S,Hq,D] with seq_lens [B]
     int32 device tensor.  Packed: Q [total,Hq,D] with cu_seqlens [B+1] int32 device tensor and max_len."""
-    torch = _torch()
     Hkv, M, _ = proto.shape
     if cu_seqlens is not None:
         total, Hq, D = Q.shape
@@ -193,8 +189,8 @@ def seka_route_ragged(Q, proto, window, seq_lens=None, cu_seqlens=None, max_len=
     sh = _shape(B, S, Hq, Hkv, D, _dtype_code(Q), 0.0)
     if w_out is None:
         w_out = torch.empty((B, Hkv, M), dtype=torch.float32, device=Q.device)
-    need = lib.seka_route_ragged_workspace_bytes(ctypes.byref(sh), window)
     if workspace is None:
+        need = lib.seka_route_ragged_workspace_bytes(ctypes.byref(sh), window)
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=Q.device)
     _check(lib.seka_route_ragged(_dev(Q, "Q"), ctypes.byref(sh), _dev(proto, "proto"), M, _dev(seq_lens, "seq_lens"),
                                  _dev(cu_seqlens, "cu_seqlens"), total, window, mode, float(tau), _dev(w_out, "w_out"),
@@ -212,7 +208,6 @@ def seka_project_route(X, Wq, Q_out, Hkv, proto=None, mode=SEKA_ROUTE_SOFTMAX_CO
                        workspace=None, stream=None):
     """X [B,S,E] bf16, Wq [Hq*D,E] bf16 -> Q_out [B,S,Hq,D] bf16 and, with proto [Hkv,M,D], the routing weights
     w_out [B,Hkv,M] of the whole prompt (allocated if None).  Returns w_out (None without proto)."""
-    torch = _torch()
     B, S, Hq, D = Q_out.shape
     E = X.shape[2]
     sh = _shape(B, S, Hq, Hkv, D, _dtype_code(Q_out), 0.0)
@@ -282,12 +277,11 @@ def seka_decode_workspace_bytes(B, S, Hq, Hkv, D, dtype):
 
 def seka_attention_decode(q, K, V, O, seq_lens=None, lse=None, scale=0.0, workspace=None, stream=None):
     """q/O [B,Hq,D]; K/V [B,S,Hkv,D] caches; seq_lens [B] int32 device tensor or None."""
-    torch = _torch()
     B, Hq, D = q.shape
     S, Hkv = K.shape[1], K.shape[2]
     sh = _shape(B, S, Hq, Hkv, D, _dtype_code(q), scale)
-    need = lib.seka_decode_workspace_bytes(ctypes.byref(sh))
     if workspace is None:
+        need = lib.seka_decode_workspace_bytes(ctypes.byref(sh))
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=q.device)
     _check(lib.seka_attention_decode(_dev(q, "q"), _dev(K, "K"), _dev(V, "V"), _dev(O, "O"), _dev(lse, "lse"),
                                      _dev(seq_lens, "seq_lens"), ctypes.byref(sh), _dev(workspace, "workspace"),
@@ -323,11 +317,10 @@ def seka_attention_prefill_ragged(Q, K, V, O, seq_lens, U=None, gain=None, mask=
 def seka_learn_projection(h_neutral, h_signal, gamma, U_out, sigma_out, k_out, U_packed=None, workspace=None,
                           stream=None):
     """h_* [B,S,Hkv,D]; U_out [Hkv,D,D] fp32, sigma_out [Hkv,D] fp32, k_out [Hkv] int32; U_packed [Hkv,D,r_pad]."""
-    torch = _torch()
     B, S, Hkv, D = h_neutral.shape
     sh = _shape(B, S, Hkv, Hkv, D, _dtype_code(h_neutral), 0.0)
-    need = lib.seka_learn_workspace_bytes(ctypes.byref(sh))
     if workspace is None:
+        need = lib.seka_learn_workspace_bytes(ctypes.byref(sh))
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=h_neutral.device)
     r_pad = U_packed.shape[2] if U_packed is not None else 0
     _check(lib.seka_learn_projection(_dev(h_neutral, "h_neutral"), _dev(h_signal, "h_signal"), ctypes.byref(sh),
@@ -340,7 +333,6 @@ def seka_learn_projection(h_neutral, h_signal, gamma, U_out, sigma_out, k_out, U
 
 def seka_head_distance(h_pos, h_neg, D_out, workspace=None, stream=None):
     """h_* [B,S,Hkv,D]; D_out [Hkv] fp32."""
-    torch = _torch()
     B, S, Hkv, D = h_pos.shape
     sh = _shape(B, S, Hkv, Hkv, D, _dtype_code(h_pos), 0.0)
     if workspace is None:
