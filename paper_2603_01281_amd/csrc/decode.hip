@@ -253,8 +253,8 @@ __host__ __device__ inline int decode_heads_per_group_mfma(int G) {
   return 1;
 }
 
-template <int D>
-__global__ __launch_bounds__(kDecThreads, 2) void decode_partial_mfma_kernel(const uint16_t* __restrict__ q,
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const uint16_t* __restrict__ q,
                                                                           const uint16_t* __restrict__ K,
                                                                           const uint16_t* __restrict__ V,
                                                                           const int* __restrict__ lens, int S, int Hq,
@@ -271,8 +271,8 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_partial_mfma_kernel(con
   constexpr int CPR = D / 8, RPI = 64 / CPR, NV = BK / RPI;   // V rows: 16-byte chunks per row, rows per load, loads
   constexpr int kTileBytes = BK * LD * 2;
   constexpr int kMergeBytes = kDecMfmaMaxHeads * OLD * 4;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[kDecWaves * (kTileBytes > kMergeBytes ? kTileBytes : kMergeBytes)];
-  __shared__ float sm_ml[kDecWaves][kDecMfmaMaxHeads][2];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[NW * (kTileBytes > kMergeBytes ? kTileBytes : kMergeBytes)];
+  __shared__ float sm_ml[NW][kDecMfmaMaxHeads][2];
 
   const int G = Hq / Hkv;
   const int chunks = G / HP;
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_partial_mfma_kernel(con
 
   int kb = k0 + wave * BK;
   if (kb < k1) fetch(kb);
-  for (; kb < k1; kb += kDecWaves * BK) {
+  for (; kb < k1; kb += NW * BK) {
     // K rows to the wave's tile, back as A fragments (lane (key l32, hf): 16 bytes at d = 16 s + 8 hf); then the V
     // rows take the tile over.  A wave's LDS operations execute in program order; the fences are for the compiler.
 #pragma unroll
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_partial_mfma_kernel(con
     for (int i = 0; i < NV; ++i)
       *reinterpret_cast<u32x4*>(vt + (RPI * i + lane / CPR) * LD + 8 * (lane % CPR)) = vr[i];
     asm volatile("" ::: "memory");
-    const int kb_next = kb + kDecWaves * BK;
+    const int kb_next = kb + NW * BK;
     const bool full = kb + BK <= k1;
     if (kb_next < k1) fetch(kb_next);      // the registers are free again: next block's loads fly during the softmax
 
@@ -412,14 +412,14 @@ __global__ __launch_bounds__(kDecThreads, 2) void decode_partial_mfma_kernel(con
   }
   __syncthreads();
   const float* sm_all = reinterpret_cast<const float*>(smem);
-  for (int idx = threadIdx.x; idx < HP * D; idx += kDecThreads) {
+  for (int idx = threadIdx.x; idx < HP * D; idx += 64 * NW) {
     const int g = idx / D, d = idx % D;
     float mm = sm_ml[0][g][0];
 #pragma unroll
-    for (int w = 1; w < kDecWaves; ++w) mm = fmaxf(mm, sm_ml[w][g][0]);
+    for (int w = 1; w < NW; ++w) mm = fmaxf(mm, sm_ml[w][g][0]);
     float ll = 0.f, oo = 0.f;
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
+    for (int w = 0; w < NW; ++w) {
       const float aw = __builtin_amdgcn_exp2f(sm_ml[w][g][0] - mm);
       ll += sm_ml[w][g][1] * aw;
       oo += sm_all[((size_t)w * kDecMfmaMaxHeads + g) * OLD + d] * aw;
@@ -552,15 +552,25 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
     const dim3 grid(splits, Hkv * (G / hp), B);
     const uint16_t *q16 = static_cast<const uint16_t*>(q), *K16 = static_cast<const uint16_t*>(K), *V16 = static_cast<const uint16_t*>(V);
     uint16_t* O16 = static_cast<uint16_t*>(O);
-    if (D == 128) {
-      hipLaunchKernelGGL(decode_partial_mfma_kernel<128>, grid, dim3(kDecThreads), 0, s, q16, K16, V16, lens, S, Hq, Hkv, hp, c2, splits, part, O16, lse);
-      if (splits > 1)
+#define SEKA_DEC_LAUNCH(DD, NW)                                                                                              \
+    hipLaunchKernelGGL((decode_partial_mfma_kernel<DD, NW>), grid, dim3(64 * NW), 0, s, q16, K16, V16, lens, S, Hq, Hkv, hp, \
+                       c2, splits, part, O16, lse)
+    if (splits > 1) {
+      if (D == 128) {
+        SEKA_DEC_LAUNCH(128, 4);
         hipLaunchKernelGGL((decode_finish_kernel<uint16_t, 128>), dim3(Hq, B), dim3(kFinThreads), 0, s, part, Hq, splits, O16, lse);
-    } else {
-      hipLaunchKernelGGL(decode_partial_mfma_kernel<64>, grid, dim3(kDecThreads), 0, s, q16, K16, V16, lens, S, Hq, Hkv, hp, c2, splits, part, O16, lse);
-      if (splits > 1)
+      } else {
+        SEKA_DEC_LAUNCH(64, 4);
         hipLaunchKernelGGL((decode_finish_kernel<uint16_t, 64>), dim3(Hq, B), dim3(kFinThreads), 0, s, part, Hq, splits, O16, lse);
+      }
+    } else if (S > 128 && (long long)B * Hkv * (G / hp) <= 256) {
+      // A short cache is one workgroup's chain of blocks, half as long with twice the waves: 12.0 -> 10.3 us at S = 1000,
+      // 32 / 8 heads.  Only one such workgroup fits a compute unit (LDS): at 512 workgroups 17.5 us became 20.1.
+      if (D == 128) SEKA_DEC_LAUNCH(128, 8); else SEKA_DEC_LAUNCH(64, 8);
+    } else {
+      if (D == 128) SEKA_DEC_LAUNCH(128, 4); else SEKA_DEC_LAUNCH(64, 4);
     }
+#undef SEKA_DEC_LAUNCH
     return hipGetLastError();
   }
   return D == 128 ? launch_decode_td<float, 128>(q, K, V, O, lse, lens, B, S, Hq, Hkv, scale, part, splits, s)

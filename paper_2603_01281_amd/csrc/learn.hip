@@ -439,11 +439,13 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
           const float ga = reduce8(vg, lane);
           float sn, th;
           const float t = angle(al, be, ga, sn, th);
-          rotated |= __any(t != 0.f);             // no branch around the rotations: with t = 0 they change nothing
-          al = fmaxf(__builtin_fmaf(-t, ga, al), 0.f);
-          be = fmaxf(__builtin_fmaf(t, ga, be), 0.f);
+          if (__any(t != 0.f)) {                  // the last sweeps rotate few pairs, the very last none
+            rotated = 1;
+            al = fmaxf(__builtin_fmaf(-t, ga, al), 0.f);
+            be = fmaxf(__builtin_fmaf(t, ga, be), 0.f);
 #pragma unroll
-          for (int j = 0; j < 8; ++j) apply(j, 8 + ((j + r) & 7), lane_value(sn, j), lane_value(th, j));
+            for (int j = 0; j < 8; ++j) apply(j, 8 + ((j + r) & 7), lane_value(sn, j), lane_value(th, j));
+          }
           be = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(next_lane, __builtin_bit_cast(int, be)));
         }
 #pragma unroll
