@@ -18,6 +18,7 @@ namespace {
 constexpr int kRouteThreads = 256;
 constexpr int kMaxChunks = 256;
 constexpr int kFinishThreads = 512;
+constexpr int kRouteAllRows = 128;
 
 // Chunks per (batch, KV head): enough workgroups for the whole chip (about 2048) even when B * Hkv is small,
 // at least 32 tokens per chunk, at most kMaxChunks partial sums for the second stage to add.
@@ -50,13 +51,120 @@ template <> struct Vec16<uint16_t> {
   }
 };
 
+// Sum over the 64 lanes, the same value in all of them.
+__device__ __forceinline__ float wave_total(float v) {
+  v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0xB1, 0xf, 0xf, true));    // lane ^ 1
+  v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x4E, 0xf, 0xf, true));    // lane ^ 2
+  v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x141, 0xf, 0xf, true));   // mirrored in 8
+  v += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x140, 0xf, 0xf, true));   // mirrored in 16
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Tokens [t0, t1) that prompt b contributes, and the tensor row of its first token.  With length arrays: its last
+// `window` tokens.
+__device__ __forceinline__ size_t route_range(int b, int S, const int* lens, const int* cu, int total, int window, int& t0, int& t1) {
+  if (lens == nullptr && cu == nullptr) return (size_t)b * S;
+  size_t row_base = (size_t)b * S;
+  int len;
+  if (cu != nullptr) {
+    const int start = min(max(cu[b], 0), total);
+    len = min(cu[b + 1] - start, total - start);
+    row_base = (size_t)start;
+  } else {
+    len = lens[b];
+  }
+  t1 = min(max(len, 0), S);
+  t0 = max(0, t1 - window);
+  return row_base;
+}
+
+// The expert prototypes of a KV head as the waves of a workgroup take them: wave w has experts w, w + NW, ...,
+// element lane + 64 x.  Loaded ahead of the sums they are multiplied with.
+template <int D, int NW>
+struct RouteProto {
+  static constexpr int N = (SEKA_MAX_EXPERTS + NW - 1) / NW, X = D / 64;
+  float p[N][X];
+  __device__ __forceinline__ void load(const float* proto, int h, int M, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int x = 0; x < X; ++x) {
+        const int m = wave + NW * i;
+        p[i][x] = m < M ? proto[((size_t)h * M + m) * D + lane + 64 * x] : 0.f;
+      }
+  }
+};
+
+// Expert coefficients from the mean query (qbar, in LDS behind a barrier).  Every dot product is one wave's, the rule
+// is 16 lanes' of wave 0; sums are trees of a fixed shape.  (One thread per expert and one for the rule: 3 us.)
+template <int D, int NW>
+__device__ __forceinline__ void route_weights(const float* qbar, const RouteProto<D, NW>& pr, int M, int mode, float tau,
+                                              float (&dots)[SEKA_MAX_EXPERTS], float (&pnorm2)[SEKA_MAX_EXPERTS], int wave,
+                                              int lane, float* out) {
+  float q[D / 64], q2 = 0.f;
+#pragma unroll
+  for (int x = 0; x < D / 64; ++x) {
+    q[x] = qbar[lane + 64 * x];
+    q2 += q[x] * q[x];
+  }
+  q2 = wave_total(q2);
+#pragma unroll
+  for (int i = 0; i < RouteProto<D, NW>::N; ++i) {
+    const int m = wave + NW * i;
+    if (m < M) {                                 // wave-uniform
+      float d = 0.f, n2 = 0.f;
+#pragma unroll
+      for (int x = 0; x < D / 64; ++x) {
+        d += q[x] * pr.p[i][x];
+        n2 += pr.p[i][x] * pr.p[i][x];
+      }
+      d = wave_total(d);
+      n2 = wave_total(n2);
+      if (lane == 0) {
+        dots[m] = d;
+        pnorm2[m] = n2;
+      }
+    }
+  }
+  __syncthreads();
+  if (wave != 0) return;
+  const bool live = lane < M;
+  const float dot = live ? dots[lane] : 0.f;
+  float value;
+  if (mode == SEKA_ROUTE_SOFTMAX_COS) {
+    const float nn = live ? sqrtf(q2) * sqrtf(pnorm2[lane]) : 0.f;
+    const float z = live ? tau * (nn >= 1e-30f ? dot / nn : 0.f) : -INFINITY;
+    float zmax = z;
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, m));
+    const float e = live ? expf(z - zmax) : 0.f;
+    float den = e;
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) den += __shfl_xor(den, m);
+    value = e / den;
+  } else {
+    float big = fabsf(dot);
+#pragma unroll
+    for (int m = 1; m < 16; m <<= 1) big = fmaxf(big, __shfl_xor(big, m));
+    value = big >= 1e-30f ? dot / big : 0.f;
+  }
+  if (live) out[lane] = value;
+}
+static_assert(SEKA_MAX_EXPERTS <= 16, "the rule runs in 16 lanes");
+
 // grid = (chunks, B*Hkv); workspace[(bh*chunks + c)*D + d] = sum over the chunk's tokens and the G heads.
-template <typename T, int D>
+// ALL: one chunk, and the workgroup goes on to the coefficients itself (no second kernel; the workspace is not used).
+template <typename T, int D, bool ALL>
 __global__ __launch_bounds__(kRouteThreads) void route_partial_kernel(const T* __restrict__ Q, int S, int Hq, int Hkv,
                                                                        int t0, int t1, int chunks,
                                                                        const int* __restrict__ lens,
                                                                        const int* __restrict__ cu, int total, int window,
-                                                                       float* __restrict__ workspace) {
+                                                                       float* __restrict__ workspace,
+                                                                       const float* __restrict__ proto, int M, int mode,
+                                                                       float tau, float* __restrict__ w_out) {
   constexpr int VE = Vec16<T>::N;
   constexpr int VPR = D / VE;                    // 16-byte vectors per (token, head) row
   constexpr int RPP = kRouteThreads / VPR;       // rows per pass
@@ -64,20 +172,9 @@ __global__ __launch_bounds__(kRouteThreads) void route_partial_kernel(const T* _
   const int G = Hq / Hkv;
   const int bh = blockIdx.y, b = bh / Hkv, h = bh % Hkv;
   const int c = blockIdx.x;
-  size_t row_base = (size_t)b * S;               // first token row of the prompt
-  if (lens != nullptr || cu != nullptr) {        // per-prompt range: the last `window` tokens of the prompt
-    int len;
-    if (cu != nullptr) {
-      const int start = min(max(cu[b], 0), total);
-      len = min(cu[b + 1] - start, total - start);
-      row_base = (size_t)start;
-    } else {
-      len = lens[b];
-    }
-    len = min(max(len, 0), S);
-    t1 = len;
-    t0 = max(0, len - window);
-  }
+  RouteProto<D, kRouteThreads / 64> pr;
+  if (ALL) pr.load(proto, h, M, threadIdx.x >> 6, threadIdx.x & 63);
+  const size_t row_base = route_range(b, S, lens, cu, total, window, t0, t1);
   const int T_total = t1 - t0;
   const int per = (T_total + chunks - 1) / chunks;
   const int ta = t0 + c * per;
@@ -109,11 +206,20 @@ __global__ __launch_bounds__(kRouteThreads) void route_partial_kernel(const T* _
 #pragma unroll
   for (int i = 0; i < VE; ++i) red[lane_row][col * VE + i] = acc[i];
   __syncthreads();
+  __shared__ float qbar[ALL ? D : 1], dots[SEKA_MAX_EXPERTS], pnorm2[SEKA_MAX_EXPERTS];
   if (threadIdx.x < D) {
     float s = 0.f;
 #pragma unroll
     for (int r = 0; r < RPP; ++r) s += red[r][threadIdx.x];
-    workspace[((size_t)bh * chunks + c) * D + threadIdx.x] = s;
+    if (ALL)
+      qbar[threadIdx.x] = nrows > 0 ? s * (1.0f / (float)nrows) : 0.f;
+    else
+      workspace[((size_t)bh * chunks + c) * D + threadIdx.x] = s;
+  }
+  if (ALL) {
+    __syncthreads();
+    route_weights<D, kRouteThreads / 64>(qbar, pr, M, mode, tau, dots, pnorm2, threadIdx.x >> 6, threadIdx.x & 63,
+                                         w_out + (size_t)bh * M);
   }
 }
 
@@ -124,28 +230,22 @@ __global__ __launch_bounds__(kFinishThreads) void route_finish_kernel(const floa
                                                            const float* __restrict__ proto, int Hkv, int M, int mode,
                                                            float tau, const int* __restrict__ lens, const int* __restrict__ cu,
                                                            int total, int S, int window, int G, float* __restrict__ w_out) {
-  __shared__ float qbar[D];
-  __shared__ float dots[SEKA_MAX_EXPERTS];
-  __shared__ float pnorm2[SEKA_MAX_EXPERTS];
+  __shared__ float qbar[D], dots[SEKA_MAX_EXPERTS], pnorm2[SEKA_MAX_EXPERTS];
   constexpr int NJ = kFinishThreads / D;
   __shared__ float part[NJ][D];
   const int bh = blockIdx.x, h = bh % Hkv;
+  RouteProto<D, kFinishThreads / 64> pr;
+  pr.load(proto, h, M, threadIdx.x >> 6, threadIdx.x & 63);
   if (lens != nullptr || cu != nullptr) {        // tokens this prompt contributed (the partial kernel's range)
-    const int b = bh / Hkv;
-    int len;
-    if (cu != nullptr) {
-      const int start = min(max(cu[b], 0), total);
-      len = min(cu[b + 1] - start, total - start);
-    } else {
-      len = lens[b];
-    }
-    len = min(max(len, 0), S);
-    const int count = (len - max(0, len - window)) * G;
+    int t0 = 0, t1 = 0;
+    route_range(bh / Hkv, S, lens, cu, total, window, t0, t1);
+    const int count = (t1 - t0) * G;
     inv_count = count > 0 ? 1.0f / (float)count : 0.f;
   }
   {
     const int d = threadIdx.x % D, j = threadIdx.x / D;
     float s = 0.f;
+#pragma unroll 8
     for (int c = j; c < chunks; c += NJ) s += workspace[((size_t)bh * chunks + c) * D + d];
     part[j][d] = s;
   }
@@ -157,43 +257,8 @@ __global__ __launch_bounds__(kFinishThreads) void route_finish_kernel(const floa
     qbar[threadIdx.x] = s * inv_count;
   }
   __syncthreads();
-  if (threadIdx.x < M) {
-    const float* p = proto + ((size_t)h * M + threadIdx.x) * D;
-    float d = 0.f, n2 = 0.f;
-    for (int i = 0; i < D; ++i) {
-      d += qbar[i] * p[i];
-      n2 += p[i] * p[i];
-    }
-    dots[threadIdx.x] = d;
-    pnorm2[threadIdx.x] = n2;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float* out = w_out + (size_t)bh * M;
-    if (mode == SEKA_ROUTE_SOFTMAX_COS) {
-      float q2 = 0.f;
-      for (int i = 0; i < D; ++i) q2 += qbar[i] * qbar[i];
-      const float qn = sqrtf(q2);
-      float z[SEKA_MAX_EXPERTS];
-      float zmax = -INFINITY;
-      for (int m = 0; m < M; ++m) {
-        const float nn = qn * sqrtf(pnorm2[m]);
-        const float c = nn >= 1e-30f ? dots[m] / nn : 0.f;
-        z[m] = tau * c;
-        zmax = fmaxf(zmax, z[m]);
-      }
-      float den = 0.f;
-      for (int m = 0; m < M; ++m) {
-        z[m] = expf(z[m] - zmax);
-        den += z[m];
-      }
-      for (int m = 0; m < M; ++m) out[m] = z[m] / den;
-    } else {
-      float big = 0.f;
-      for (int m = 0; m < M; ++m) big = fmaxf(big, fabsf(dots[m]));
-      for (int m = 0; m < M; ++m) out[m] = big >= 1e-30f ? dots[m] / big : 0.f;
-    }
-  }
+  route_weights<D, kFinishThreads / 64>(qbar, pr, M, mode, tau, dots, pnorm2, threadIdx.x >> 6, threadIdx.x & 63,
+                                        w_out + (size_t)bh * M);
 }
 
 
@@ -342,12 +407,22 @@ hipError_t launch_route(const void* Q, int B, int S, int Hq, int Hkv, int D, int
   const dim3 grid(chunks, B * Hkv);
   float* ws = static_cast<float*>(workspace);
   const float inv_count = 1.0f / ((float)(t1 - t0) * (float)(Hq / Hkv));
+  // Up to 128 rows (the last-token rule: G of them) one workgroup per (prompt, KV head) does everything: a second kernel
+  // would cost what the first does (8.2 us for the two at 64 tokens x 4 heads, 4.4 in one).
+  const bool all = (long long)(t1 - t0) * (Hq / Hkv) <= kRouteAllRows;
 #define SEKA_ROUTE_CASE(T, DD)                                                                                       \
   do {                                                                                                               \
-    hipLaunchKernelGGL((route_partial_kernel<T, DD>), grid, dim3(kRouteThreads), 0, s, static_cast<const T*>(Q), S,  \
-                       Hq, Hkv, t0, t1, chunks, lens, cu, total, window, ws);                                        \
-    hipLaunchKernelGGL((route_finish_kernel<DD>), dim3(B * Hkv), dim3(kFinishThreads), 0, s, ws, chunks, inv_count, proto, Hkv, \
-                       M, mode, tau, lens, cu, total, S, window, Hq / Hkv, w_out);                                   \
+    if (all) {                                                                                                       \
+      hipLaunchKernelGGL((route_partial_kernel<T, DD, true>), dim3(1, B * Hkv), dim3(kRouteThreads), 0, s,           \
+                         static_cast<const T*>(Q), S, Hq, Hkv, t0, t1, 1, lens, cu, total, window, ws, proto, M,     \
+                         mode, tau, w_out);                                                                          \
+    } else {                                                                                                         \
+      hipLaunchKernelGGL((route_partial_kernel<T, DD, false>), grid, dim3(kRouteThreads), 0, s,                      \
+                         static_cast<const T*>(Q), S, Hq, Hkv, t0, t1, chunks, lens, cu, total, window, ws, proto, M, \
+                         mode, tau, w_out);                                                                          \
+      hipLaunchKernelGGL((route_finish_kernel<DD>), dim3(B * Hkv), dim3(kFinishThreads), 0, s, ws, chunks, inv_count, \
+                         proto, Hkv, M, mode, tau, lens, cu, total, S, window, Hq / Hkv, w_out);                     \
+    }                                                                                                                \
   } while (0)
   if (dtype == SEKA_BF16) {
     if (D == 128) SEKA_ROUTE_CASE(uint16_t, 128); else SEKA_ROUTE_CASE(uint16_t, 64);
