@@ -430,14 +430,13 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const u
 
 // grid (Hq, B), block kFinThreads: thread (j, d) merges splits j, j + NJ, ... in that order, then the NJ partial
 // states are merged in index order: a fixed order, whatever the launch.  The kernel is pure latency (a few tens of
-// kilobytes per workgroup), so every load of a thread is issued before the first is used, and a thread has at most
-// kDecMaxSplits / NJ of them.
+// kilobytes per workgroup), so every load of a thread is issued before the first is used; NI, the states a thread
+// takes, is what the number of splits needs.
 constexpr int kFinThreads = 1024;
-template <typename T, int D>
+template <typename T, int D, int NI>
 __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(const float* __restrict__ part, int Hq, int splits,
                                                                     T* __restrict__ O, float* __restrict__ lse) {
   constexpr int NJ = kFinThreads / D;
-  constexpr int NI = (kDecMaxSplits + NJ - 1) / NJ;        // splits per thread, at most
   __shared__ float sm[NJ][D + 2];
   const int hq = blockIdx.x, b = blockIdx.y, d = threadIdx.x % D, j = threadIdx.x / D;
   const float* src = part + ((size_t)b * Hq + hq) * splits * (D + 2);
@@ -484,6 +483,15 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(const float*
   }
 }
 
+template <typename T, int D>
+void launch_decode_finish(const float* part, int B, int Hq, int splits, T* O, float* lse, hipStream_t s) {
+  constexpr int NJ = kFinThreads / D;
+  const dim3 grid(Hq, B), block(kFinThreads);
+  if (splits <= NJ) hipLaunchKernelGGL((decode_finish_kernel<T, D, 1>), grid, block, 0, s, part, Hq, splits, O, lse);
+  else if (splits <= 2 * NJ) hipLaunchKernelGGL((decode_finish_kernel<T, D, 2>), grid, block, 0, s, part, Hq, splits, O, lse);
+  else hipLaunchKernelGGL((decode_finish_kernel<T, D, (kDecMaxSplits + NJ - 1) / NJ>), grid, block, 0, s, part, Hq, splits, O, lse);
+}
+
 template <typename T, int D, int GP>
 hipError_t launch_decode_gp(const void* q, const void* K, const void* V, void* O, float* lse, const int* lens, int B,
                             int S, int Hq, int Hkv, float scale, float* part, int splits, hipStream_t s) {
@@ -493,7 +501,7 @@ hipError_t launch_decode_gp(const void* q, const void* K, const void* V, void* O
                      static_cast<const T*>(q), static_cast<const T*>(K), static_cast<const T*>(V), lens, S, Hq, Hkv, c2,
                      splits, part, static_cast<T*>(O), lse);
   if (splits > 1)
-    hipLaunchKernelGGL((decode_finish_kernel<T, D>), dim3(Hq, B), dim3(kFinThreads), 0, s, part, Hq, splits, static_cast<T*>(O), lse);
+    launch_decode_finish<T, D>(part, B, Hq, splits, static_cast<T*>(O), lse, s);
   return hipGetLastError();
 }
 
@@ -558,10 +566,10 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
     if (splits > 1) {
       if (D == 128) {
         SEKA_DEC_LAUNCH(128, 4);
-        hipLaunchKernelGGL((decode_finish_kernel<uint16_t, 128>), dim3(Hq, B), dim3(kFinThreads), 0, s, part, Hq, splits, O16, lse);
+        launch_decode_finish<uint16_t, 128>(part, B, Hq, splits, O16, lse, s);
       } else {
         SEKA_DEC_LAUNCH(64, 4);
-        hipLaunchKernelGGL((decode_finish_kernel<uint16_t, 64>), dim3(Hq, B), dim3(kFinThreads), 0, s, part, Hq, splits, O16, lse);
+        launch_decode_finish<uint16_t, 64>(part, B, Hq, splits, O16, lse, s);
       }
     } else if (S > 128 && (long long)B * Hkv * (G / hp) <= 256) {
       // A short cache is one workgroup's chain of blocks, half as long with twice the waves: 12.0 -> 10.3 us at S = 1000,
