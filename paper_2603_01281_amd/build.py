@@ -13,7 +13,8 @@ PROBES = ["mfma_rate_probe", "hbm_read_probe"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["api.hip", "route.hip", "edit.hip", "decode.hip", "learn.hip", "attn_f32.hip", "attn_bf16.hip", "attn_bf16_d128.hip", "attn_bf16_d64.hip",
-           "attn_bf16_pipe_plain.hip", "attn_bf16_pipe_r32.hip", "attn_bf16_pipe_r64.hip", "attn_bf16_pipe_r128.hip"]
+           "attn_bf16_pipe_plain.hip", "attn_bf16_pipe_r32.hip", "attn_bf16_pipe_r64.hip", "attn_bf16_pipe_r128.hip",
+           "attn_bf16_pipe64_plain.hip", "attn_bf16_pipe64_r32.hip", "attn_bf16_pipe64_r64.hip", "attn_bf16_pipe64_r128.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffast-math", "-fno-finite-math-only",

@@ -26,22 +26,27 @@ hipError_t launch_attention_bf16_cfg(const AttnArgs& a, const SteerArgs* steer, 
   return hipGetLastError();
 }
 
-// software-pipelined direct-to-LDS kernels (head dimension 128 only; defined in attn_bf16_pipe_*.hip)
+// software-pipelined direct-to-LDS kernels (defined in attn_bf16_pipe_*.hip and, for head dimension 64, attn_bf16_pipe64_*.hip)
 hipError_t launch_attention_bf16_pipe_plain(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attention_bf16_pipe_r32(const AttnArgs& a, const SteerArgs* steer, hipStream_t s);
 hipError_t launch_attention_bf16_pipe_r64(const AttnArgs& a, const SteerArgs* steer, hipStream_t s);
 hipError_t launch_attention_bf16_pipe_r128(const AttnArgs& a, const SteerArgs* steer, hipStream_t s);
+hipError_t launch_attention_bf16_pipe64_plain(const AttnArgs& a, hipStream_t s);
+hipError_t launch_attention_bf16_pipe64_r32(const AttnArgs& a, const SteerArgs* steer, hipStream_t s);
+hipError_t launch_attention_bf16_pipe64_r64(const AttnArgs& a, const SteerArgs* steer, hipStream_t s);
+hipError_t launch_attention_bf16_pipe64_r128(const AttnArgs& a, const SteerArgs* steer, hipStream_t s);
 
-inline hipError_t launch_attention_bf16_pipe(const AttnArgs& a, const SteerArgs* steer, hipStream_t s) {
-  if (!steer) return launch_attention_bf16_pipe_plain(a, s);
+template <int D>
+hipError_t launch_attention_bf16_pipe(const AttnArgs& a, const SteerArgs* steer, hipStream_t s) {
+  if (!steer) return D == 128 ? launch_attention_bf16_pipe_plain(a, s) : launch_attention_bf16_pipe64_plain(a, s);
   const int R = steer->M * steer->r;
   // The rank <= 32 kernel applies the edit to the scores and has no place for a key scale other than 1 (Eq. 4's
   // negative-side gain): such calls take the dense form, which edits the keys themselves.
   bool unit_scale = true;
   for (int h = 0; h < a.Hkv; ++h) unit_scale = unit_scale && (steer->gain[h] == 0.f || steer->kscale[h] == 1.f);
-  if (R <= 32 && unit_scale) return launch_attention_bf16_pipe_r32(a, steer, s);
-  if (R <= 64) return launch_attention_bf16_pipe_r64(a, steer, s);
-  return launch_attention_bf16_pipe_r128(a, steer, s);
+  if (R <= 32 && unit_scale) return D == 128 ? launch_attention_bf16_pipe_r32(a, steer, s) : launch_attention_bf16_pipe64_r32(a, steer, s);
+  if (R <= 64) return D == 128 ? launch_attention_bf16_pipe_r64(a, steer, s) : launch_attention_bf16_pipe64_r64(a, steer, s);
+  return D == 128 ? launch_attention_bf16_pipe_r128(a, steer, s) : launch_attention_bf16_pipe64_r128(a, steer, s);
 }
 
 template <int D, bool STEER>
@@ -55,8 +60,13 @@ hipError_t launch_attention_bf16_group(const AttnArgs& a, const SteerArgs* steer
 
 template <int D, bool STEER>
 hipError_t launch_attention_bf16_any(const AttnArgs& a, const SteerArgs* steer, hipStream_t s) {
-  if (D == 128) {
-    const hipError_t e = launch_attention_bf16_pipe(a, steer, s);
+  // Many prompts of one block of rows of one or two heads: the register-staged kernel at D = 64 runs two workgroups per
+  // compute unit and hides their starts behind each other (32 / 32 heads, rank 32, us, this / pipelined: B=64 S=64
+  // 34 / 49, B=64 S=203 123 / 130, B=14 S=203 31 / 35; at S=300 the other way, 237 / 201; four heads x 64 rows never).
+  const int G = a.Hq / a.Hkv, heads = G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
+  const bool staged = D == 64 && heads < 4 && a.S <= 256 / heads && (long long)a.B * (a.Hq / heads) > 256;
+  if (!staged) {
+    const hipError_t e = launch_attention_bf16_pipe<D>(a, steer, s);
     if (e != hipErrorNotSupported) return e;     // highlight bitmap too large for LDS at this S: register-staged kernel
   }
   return launch_attention_bf16_group<D, STEER>(a, steer, s);

@@ -1,19 +1,16 @@
-// Tile transport shared by the direct-to-LDS bf16 attention kernels (gfx950, head dimension 128):
-//   * K/V tiles (64 keys x 128) go from global memory straight into LDS with global_load_lds
+// Tile transport of the direct-to-LDS kernels (gfx950):
+//   * K/V tiles (64 keys) go from global memory straight into LDS with global_load_lds
 //     (16 bytes per lane, no register staging), two tiles ahead of the math, into rings of three
 //     stages.  Completion is tracked with an explicit vmcnt wait followed by the per-tile barrier.
 //   * A direct-to-LDS load writes 64 lanes x 16 bytes contiguously, so rows cannot be padded; bank
 //     conflicts are avoided by choosing WHICH 16-byte chunk of a row each lane fetches (an XOR
-//     swizzle of the chunk index with the row index): K chunks are swizzled by row & 15 (conflict-free
-//     16-byte row reads), V chunks by 4 * (row & 3) (conflict-free transposing reads).
+//     swizzle of the chunk index with the row index; see pipe_k_swizzle / pipe_v_swizzle).
 #pragma once
 #include "common.h"
 
 namespace seka {
 
 constexpr int DMA_BK = 64;                       // keys per tile
-constexpr int DMA_D = 128;
-constexpr int DMA_TILE_BYTES = DMA_BK * DMA_D * 2;   // 16 KB
 constexpr int DMA_STAGES = 3;
 
 typedef __attribute__((address_space(3))) s16x4* dma_lds_s16x4_ptr;

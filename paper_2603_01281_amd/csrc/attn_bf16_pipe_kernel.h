@@ -50,11 +50,12 @@ namespace seka {
 constexpr int PIPE_Z_LD = 80;                       // bytes per key in a coordinate buffer
 constexpr int PIPE_Z_BYTES = DMA_BK * PIPE_Z_LD;    // one buffer
 constexpr int PIPE_QT_BYTES = 2048;                 // U^T q of one wave: [2 k-slices][64 lanes][8] bf16
-inline size_t attention_bf16_pipe_smem_bytes(int S, bool steer, int nkr, int nwaves) {
-  size_t n = (size_t)2 * DMA_STAGES * DMA_TILE_BYTES;
+inline size_t attention_bf16_pipe_smem_bytes(int D, int S, bool steer, int nkr, int nwaves) {
+  size_t n = (size_t)2 * DMA_STAGES * DMA_BK * D * 2;
+  if (D == 64) n += (size_t)4096 * nwaves;             // staging areas (at D = 128 the rings have room for them)
   if (steer) {
     const int Rpad = 32 * nkr;
-    n += nkr == 1 ? (size_t)DMA_D * Rpad * 2 : (size_t)DMA_D * DMA_D * 2;
+    n += nkr == 1 ? (size_t)D * Rpad * 2 : (size_t)D * D * 2;
     n += (size_t)Rpad * 4;
     if (nkr == 1) n += (size_t)2 * PIPE_Z_BYTES + (size_t)nwaves * PIPE_QT_BYTES;
     n += (size_t)((S + DMA_BK - 1) / DMA_BK) * 8;
@@ -96,19 +97,21 @@ __device__ __forceinline__ int pipe_wave_max(int v) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
-// What a block of query rows and a workgroup cost beside their key tiles, in units of one 64-key tile (2700 cycles):
+// What a block of query rows and a workgroup cost beside their key tiles, in units of one 64-key tile (2700 cycles at
+// D = 128):
 // a block waits for its first tiles, runs its last ones outside the unrolled loop and writes its output; a workgroup
 // starts and prepares the edit.
-constexpr float PIPE_BLOCK_TILES = 4.f, PIPE_START_TILES = 3.f;
+constexpr float pipe_block_tiles(int D) { return 4.f * 128 / D; }
+constexpr float pipe_start_tiles(int D) { return 3.f * 128 / D; }
 
 // Workgroup `item` of the a.width that a batch of prompts of different lengths (at most 64) gets per head chunk.
-// Lane i looks after prompt i: its n_i blocks of query rows are T_i = sum over them of (tiles + PIPE_BLOCK_TILES) of
+// Lane i looks after prompt i: its n_i blocks of query rows are T_i = sum over them of (tiles + pipe_block_tiles) of
 // work, which W_i = floor(T_i / L) + 1 workgroups share.  L is the load of a workgroup if the batch is to take R
 // rounds of the a.slots workgroups that run at a time, T / (R slots - B), and no less than the longest block;
-// R = 1 .. PIPE_RAGGED_ROUNDS is the one with the smallest R (L + PIPE_START_TILES).  The longest prompts come first,
+// R = 1 .. PIPE_RAGGED_ROUNDS is the one with the smallest R (L + pipe_start_tiles).  The longest prompts come first,
 // so the last workgroups to start are the shortest.  Returns false past the last workgroup.
 constexpr int PIPE_RAGGED_ROUNDS = 6;
-template <int BQ>
+template <int BQ, int D>
 __device__ __forceinline__ bool pipe_ragged_item(const AttnArgs& a, int item, int& b, int& slot, int& W) {
   const int lane = threadIdx.x & 63;
   size_t tok0;
@@ -116,15 +119,15 @@ __device__ __forceinline__ bool pipe_ragged_item(const AttnArgs& a, int item, in
   if (lane < a.B) prompt_extent(a, lane, tok0, len);
   const int nb = (len + BQ - 1) / BQ;
   constexpr float T = BQ / 64.f;                 // key tiles per block of query rows
-  const float work = (float)nb * (0.5f * T * (float)(nb + 1) + PIPE_BLOCK_TILES);
+  const float work = (float)nb * (0.5f * T * (float)(nb + 1) + pipe_block_tiles(D));
   const float total = pipe_wave_sum(work);
-  const float longest = T * (float)pipe_wave_max(nb) + PIPE_BLOCK_TILES;
+  const float longest = T * (float)pipe_wave_max(nb) + pipe_block_tiles(D);
   float best = 0.f, load = longest;
 #pragma unroll
   for (int R = 1; R <= PIPE_RAGGED_ROUNDS; ++R) {
     const int share = R * a.slots - a.B;
     const float L = fmaxf(longest, total / (float)max(share, 1));
-    const float cost = (float)R * (L + PIPE_START_TILES);
+    const float cost = (float)R * (L + pipe_start_tiles(D));
     if (share > 0 && (best == 0.f || cost < best)) {
       best = cost;
       load = L;
@@ -146,12 +149,20 @@ __device__ __forceinline__ bool pipe_ragged_item(const AttnArgs& a, int item, in
   return true;
 }
 
+// The 16-byte chunk of tile row `row` that lies at position p is p ^ swizzle: conflict-free 16-byte reads of one chunk
+// of 16 consecutive rows (K), and conflict-free transposing reads of four consecutive rows x 64 bytes (V).
+template <int D>
+__host__ __device__ constexpr int pipe_k_swizzle(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
+template <int D>
+__host__ __device__ constexpr int pipe_v_swizzle(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+
 // HPW heads x RBW row groups = waves per workgroup; every wave owns RPW blocks of 32 consecutive query rows.
 // RPW = 2 (four waves, one per SIMD, 512-register budget) reads every K / V fragment once for two products.
 // NKR: rank of the concatenated basis in blocks of 32 columns (compile-time so that the edit is straight-line code).
-template <int HPW, int RBW, int RPW, bool STEER, int NKR>
-__global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
-  constexpr int D = DMA_D;
+template <int D, int HPW, int RBW, int RPW, bool STEER, int NKR>
+__global__ __launch_bounds__(64 * HPW * RBW) __attribute__((amdgpu_waves_per_eu(2, D == 64 ? 2 : 8))) void
+attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
+  static_assert(D == 64 || D == 128, "head dimensions of the tile layouts");
   constexpr int NW = HPW * RBW;
   constexpr int NT = 64 * NW;
   constexpr int WR = 32 * RPW;
@@ -159,9 +170,11 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   constexpr int BK = DMA_BK;
   constexpr int KS = D / 16;
   constexpr int DB = D / 32;
-  constexpr int SLOTS = DMA_TILE_BYTES / 1024;
+  constexpr int KS2 = D / 32;
+  constexpr int RB = 2 * D, CH = D / 8;                  // bytes and 16-byte chunks of a tile row
+  constexpr int TB = BK * RB;                            // bytes of a tile
+  constexpr int SLOTS = TB / 1024;
   constexpr int SPW = (SLOTS + NW - 1) / NW;             // load instructions per wave per tensor per tile
-  constexpr int TB = DMA_TILE_BYTES;
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* Kst = smem;                                     // [3][16 KB] swizzled K tiles
@@ -169,7 +182,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   constexpr int Rpad = 32 * NKR;
   constexpr bool DENSE = NKR >= 2;         // edit with the dense matrix g P (see attention_bf16_pipe_smem_bytes)
   constexpr bool kEventsInHot = STEER && (!DENSE || NW == 8);   // steering events handled inside the hot loop (see the tile loop)
-  uint16_t* UN = reinterpret_cast<uint16_t*>(smem + 2 * DMA_STAGES * TB);
+  uint16_t* UN = reinterpret_cast<uint16_t*>(smem + 2 * DMA_STAGES * TB + (D == 64 ? 4096 * NW : 0));
   uint16_t* U1 = UN;                       // low rank: operand (rb, s) of U_cat^T K^T: [2][4][64 lanes][8]
   uint16_t* AP = UN;                       // dense: operand (s_out, half, ks) of (g P) K^T: [4][2][4][64 lanes][8]
   float* cvec = reinterpret_cast<float*>(UN + (DENSE ? (size_t)D * D : (size_t)D * Rpad));   // [Rpad]
@@ -200,7 +213,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   const int h = hq0 / G;
   int b, slot, W = a.width;
   if (a.slots) {
-    if (!pipe_ragged_item<BQ>(a, item, b, slot, W)) return;
+    if (!pipe_ragged_item<BQ, D>(a, item, b, slot, W)) return;
   } else {
     b = item / a.width;
     slot = item % a.width;
@@ -230,8 +243,8 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   int ntiles = last_key / BK + 1;          // the first block is the later one: its tile count bounds the second's
 
   // ---- tile loads: scalar tile base + per-lane offset fixed for the whole kernel ----
-  // Slot s of a tile is LDS bytes [1024 s, 1024 s + 1024) = rows 4s..4s+3; lane l lands at row 4s + l/16,
-  // chunk position l%16, and fetches the logical chunk that the swizzle assigns to that position.
+  // Slot s of a tile is LDS bytes [1024 s, 1024 s + 1024) = 4 rows (8 at D = 64); lane l lands at row l / CH of them,
+  // chunk position l % CH, and fetches the logical chunk that the swizzle assigns to that position.
   const uint32_t rowbytes = (uint32_t)a.Hkv * D * 2;
   const uint32_t kst_base = (uint32_t)(uintptr_t)(dma_lds_void_ptr)Kst;
   const uint32_t vst_base = (uint32_t)(uintptr_t)(dma_lds_void_ptr)Vst;
@@ -247,13 +260,13 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
 #pragma unroll
   for (int n = 0; n < SPW; ++n) {
     const int slot = min(wave + NW * n, SLOTS - 1);      // surplus slots repeat the last one (same bytes)
-    const int row = 4 * slot + (lane >> 4);
+    const int row = (64 / CH) * slot + lane / CH;
     slot_row[n] = row;
     slot_lds[n] = 1024u * slot;
     vslot_lds[n] = 1024u * (slot & (SLOTS / 2 - 1));
     vslot_hi[n] = slot >= SLOTS / 2;
-    koff[n] = row * rowbytes + 16u * ((lane & 15) ^ (row & 15));
-    voff[n] = row * rowbytes + 16u * ((lane & 15) ^ (4 * (row & 3)));
+    koff[n] = row * rowbytes + 16u * ((lane & (CH - 1)) ^ pipe_k_swizzle<D>(row));
+    voff[n] = row * rowbytes + 16u * ((lane & (CH - 1)) ^ pipe_v_swizzle<D>(row));
   }
   const size_t head_off = (tok0 * a.Hkv + h) * D * 2;          // bytes to this (batch, KV head), token 0
   const unsigned char* Kbytes = reinterpret_cast<const unsigned char*>(Kg) + head_off;
@@ -299,10 +312,12 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   auto issue_v = [&](int t) __attribute__((always_inline)) { issue_v_to(std::false_type{}, t, vpos(2 * t - 1), vpos(2 * t)); };
 
   // 4 KB per wave for turning Q rows into operands and the output accumulators into rows: the third stage of the K
-  // ring and positions 3 and 4 of the V ring, which a block's first loads do not touch.  32 rows x 128 bytes; the
+  // ring and positions 3 and 4 of the V ring, which a block's first loads do not touch (at D = 64 an area of its own).  32 rows x 128 bytes; the
   // 16-byte chunk of a row is swizzled with the row (chunk ^ row % 8).
   static_assert(RPW == 1 && NW <= 8, "one 4 KB staging area per wave");
-  unsigned char* const stg = wave < 4 ? Kst + 2 * TB + 4096 * wave : Vst + 3 * HB + 4096 * (wave - 4);
+  unsigned char* const stg = D == 64    ? smem + 2 * DMA_STAGES * TB + 4096 * wave
+                             : wave < 4 ? Kst + 2 * TB + 4096 * wave
+                                        : Vst + 3 * HB + 4096 * (wave - 4);
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
   auto stg_line = [&](int i) __attribute__((always_inline)) -> u32x4* {     // chunk lane % 8 of row 8 i + lane / 8
     return reinterpret_cast<u32x4*>(stg + 1024 * i + 128 * (lane >> 3) + 16 * ((lane & 7) ^ (lane >> 3)));
@@ -333,7 +348,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   auto q_operands = [&]() __attribute__((always_inline)) {
     bf16x8 qn[KS];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
+    for (int half = 0; half < D / 64; ++half) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) *stg_line(i) = __builtin_bit_cast(u32x4, qf[0][4 * half + i]);
       asm volatile("" ::: "memory");       // a wave's LDS accesses complete in program order: no wait needed
@@ -446,7 +461,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const int r = r0 + i;
-          U1[((((r >> 4) * 4 + s1) * 64) + g1 * 16 + (r & 15)) * 8 + e1] = e16[i];
+          U1[((((r >> 4) * KS2 + s1) * 64) + g1 * 16 + (r & 15)) * 8 + e1] = e16[i];
         }
       }
     };
@@ -497,7 +512,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
           }
           // this lane holds T[y = 16 strip + 4 g + i][x = 16 ct + j], i = 0..3
           const int x = 16 * ct + j, xl = x & 31, y0 = 16 * strip + 4 * g;
-          const int frag = ((x >> 5) * 2 + ((xl >> 2) & 1)) * 4 + (y0 >> 5);           // (s_out, half, ks)
+          const int frag = ((x >> 5) * 2 + ((xl >> 2) & 1)) * KS2 + (y0 >> 5);           // (s_out, half, ks)
           const int flane = 16 * ((y0 & 31) >> 3) + 4 * (xl >> 3) + (xl & 3);          // lane (g', j') of the edit
           bf16x4 o4;
 #pragma unroll
@@ -505,7 +520,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
           *reinterpret_cast<uint2*>(AP + (frag * 64 + flane) * 8 + (y0 & 7)) = __builtin_bit_cast(uint2, o4);
         }
       }
-      dma_barrier();           // q_operands() stages its rows where the staged U_cat lies
+      if (D == 128) dma_barrier();           // q_operands() stages its rows where the staged U_cat lies
     }
   }
   // Which of the 64 tiles [tile0, tile0 + 64) hold a highlighted key: kept in scalar registers so that the common
@@ -525,14 +540,13 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int j = ln & 15, g = ln >> 4;
-    constexpr int KS2 = D / 32;
     const int kblk = wave;
     const unsigned bits16 = (unsigned)((bits >> (16 * (kblk & 3))) & 0xffffull);
     if (kblk >= BK / 16 || bits16 == 0) return;           // wave-uniform
-    unsigned char* krow = Kb + (16 * kblk + j) * 256;     // row & 15 == j
+    unsigned char* krow = Kb + (16 * kblk + j) * RB;
     bf16x8 kreg[KS2];   // K^T as B operand: lane (col = key j, k = d = 32 s + 8 g + e) = logical chunk 4 s + g
 #pragma unroll
-    for (int s = 0; s < KS2; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ j));
+    for (int s = 0; s < KS2; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j)));
     const float mbit = ((bits16 >> j) & 1u) ? 1.f : 0.f;
     const float ksc = 1.f + mbit * (kscale - 1.f);        // a for highlighted keys, exactly 1 otherwise
     // k' = a k + mask (g P) k: output rows d are permuted so that each result lands in the lane that holds that
@@ -545,7 +559,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
         f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int ks = 0; ks < KS2; ++ks) {
-          const bf16x8 ua = *reinterpret_cast<const bf16x8*>(AP + (((s * 2 + half) * 4 + ks) * 64 + ln) * 8);
+          const bf16x8 ua = *reinterpret_cast<const bf16x8*>(AP + (((s * 2 + half) * KS2 + ks) * 64 + ln) * 8);
           acc[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua, kreg[ks], acc[ks & 1], 0, 0, 0);
         }
 #pragma unroll
@@ -556,7 +570,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
       bf16x8 o;
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[e] = (__bf16)outv[e];
-      *reinterpret_cast<bf16x8*>(krow + 16 * ((4 * s + g) ^ j)) = o;
+      *reinterpret_cast<bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j))) = o;
     }
   };
 
@@ -569,7 +583,6 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int j = ln & 15, g = ln >> 4;
-    constexpr int KS2 = D / 32;
     const int kblk = wave;
     if (kblk >= BK / 16) return;                          // wave-uniform
     const unsigned bits16 = (unsigned)((bits >> (16 * kblk)) & 0xffffull);
@@ -580,17 +593,17 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
       *reinterpret_cast<uint2*>(zrow + 32) = make_uint2(0, 0);
       return;
     }
-    const unsigned char* krow = Kb + (16 * kblk + j) * 256;     // row & 15 == j
+    const unsigned char* krow = Kb + (16 * kblk + j) * RB;
     bf16x8 kreg[KS2];   // K^T as B operand: lane (col = key j, k = d = 32 s + 8 g + e) = logical chunk 4 s + g
 #pragma unroll
-    for (int s = 0; s < KS2; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ j));
+    for (int s = 0; s < KS2; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j)));
     const float mbit = ((bits16 >> j) & 1u) ? 1.f : 0.f;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // two chains: even and odd slices of d
 #pragma unroll
       for (int s = 0; s < KS2; ++s) {
-        const bf16x8 ua = *reinterpret_cast<const bf16x8*>(U1 + ((half * 4 + s) * 64 + ln) * 8);
+        const bf16x8 ua = *reinterpret_cast<const bf16x8*>(U1 + ((half * KS2 + s) * 64 + ln) * 8);
         acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua, kreg[s], acc[s & 1], 0, 0, 0);
       }
       const f32x4 c4 = *reinterpret_cast<const f32x4*>(cvec + 16 * half + 4 * g);
@@ -627,11 +640,11 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   // V: row 16 kb + 4 hf + (li >> 2) (+8), logical chunk 4 db + 2 (grp & 1) + ((li & 3) >> 1), physical chunk 4 (db ^ q) + low
   uint32_t kaddr[KS], vaddr[DB];
   {
-    const int kfix = l32 * 256 + 16 * (hf ^ (l32 & 1)) + 32 * ((l32 & 15) >> 1);
+    const int kfix = l32 * RB + 16 * (hf ^ pipe_k_swizzle<D>(l32));
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) kaddr[ks] = kst_base + (uint32_t)(kfix ^ (ks << 5));
     const int li = lane & 15, grp = lane >> 4;
-    const int vfix = (4 * hf + (li >> 2)) * 256 + 64 * ((li >> 2) & 3) + 16 * (2 * (grp & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
+    const int vfix = (4 * hf + (li >> 2)) * RB + 16 * (pipe_v_swizzle<D>(li >> 2) + 2 * (grp & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
 #pragma unroll
     for (int db = 0; db < DB; ++db) vaddr[db] = vst_base + (uint32_t)(vfix ^ (db << 6));
   }
@@ -752,8 +765,8 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)(vaddr[db] + off + (16 * kb) * 256));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)(vaddr[db] + off + (16 * kb + 8) * 256));
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)(vaddr[db] + off + (16 * kb) * RB));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)(vaddr[db] + off + (16 * kb + 8) * RB));
         const bf16x4 lo4 = __builtin_bit_cast(bf16x4, lo), hi4 = __builtin_bit_cast(bf16x4, hi);
         const bf16x8 va = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
@@ -797,7 +810,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         const bf16x8 ua = *reinterpret_cast<const bf16x8*>(
-            U1 + ((((l32 >> 4) * 4 + (ks >> 1)) * 64) + (2 * (ks & 1) + hf) * 16 + (l32 & 15)) * 8);
+            U1 + ((((l32 >> 4) * KS2 + (ks >> 1)) * 64) + (2 * (ks & 1) + hf) * 16 + (l32 & 15)) * 8);
         qt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ua, qf[0][ks], qt, 0, 0, 0);
       }
       bf16x8 q8[2];
@@ -935,7 +948,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   constexpr float kSumLimit = 4096.f;          // probabilities stay below 2^12
   auto step = [&](auto koff_c, uint32_t knext0, uint32_t knext1, auto voff_c, f32x16 (&cur)[RPW], f32x16 (&next)[RPW], bf16x8 (&pb)[RPW][2],
                   bf16x8 (&kpre)[2]) __attribute__((always_inline)) {
-    static_assert(KS == 8 && RPW == 1, "the schedule below is written for eight k-slices and one row block per wave");
+    static_assert(RPW == 1, "the schedule below is written for one row block per wave");
     const int KOFF = koff_c, VOFF = voff_c;
     bf16x8 pn[2];
     float lb;
@@ -946,12 +959,14 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     const bf16x8 k2 = kfrag(2, KOFF), k3 = kfrag(3, KOFF);
     qk_one(2, k2, next);
     qk_one(3, k3, next);
-    const bf16x8 k4 = kfrag(4, KOFF), k5 = kfrag(5, KOFF);
-    qk_one(4, k4, next);
-    qk_one(5, k5, next);
-    const bf16x8 k6 = kfrag(6, KOFF), k7 = kfrag(7, KOFF);
-    qk_one(6, k6, next);
-    qk_one(7, k7, next);
+    if constexpr (KS == 8) {
+      const bf16x8 k4 = kfrag(4, KOFF), k5 = kfrag(5, KOFF);
+      qk_one(4, k4, next);
+      qk_one(5, k5, next);
+      const bf16x8 k6 = kfrag(6, KOFF), k7 = kfrag(7, KOFF);
+      qk_one(6, k6, next);
+      qk_one(7, k7, next);
+    }
     pv_half(VOFF, pb);
     kpre[0] = *(pipe_lds_bf16x8_ptr)(uintptr_t)knext0;
     kpre[1] = *(pipe_lds_bf16x8_ptr)(uintptr_t)knext1;
@@ -961,15 +976,27 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
     // unit takes one instruction about every ten cycles, and a run of exponentials stalls the wave in front of
     // the next MFMA.
     __builtin_amdgcn_sched_group_barrier(0x100, 2, 2);          // fragments 2 and 3
+    if constexpr (KS == 8) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 2);
-      if (i < 14 && !(i & 1)) __builtin_amdgcn_sched_group_barrier(0x100, 2, 2);
-      if (i < 15 && ((i & 1) || i == 14)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 2);
-      __builtin_amdgcn_sched_group_barrier(0x002, 2, 2);
-      if (i >= 1) __builtin_amdgcn_sched_group_barrier(0x400, 1, 2);
+      for (int i = 0; i < 16; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 2);
+        if (i < 14 && !(i & 1)) __builtin_amdgcn_sched_group_barrier(0x100, 2, 2);
+        if (i < 15 && ((i & 1) || i == 14)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 2);
+        __builtin_amdgcn_sched_group_barrier(0x002, 2, 2);
+        if (i >= 1) __builtin_amdgcn_sched_group_barrier(0x400, 1, 2);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x400, 1, 2);
+    } else {       // half the MFMAs for the same softmax: twice the vector work beside each
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 2);
+        if (i < 4) __builtin_amdgcn_sched_group_barrier(0x100, 2, 2);
+        if (i == 4 || i == 5) __builtin_amdgcn_sched_group_barrier(0x100, 1, 2);
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 2);
+        if (i >= 1) __builtin_amdgcn_sched_group_barrier(0x400, 2, 2);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x400, 2, 2);
     }
-    __builtin_amdgcn_sched_group_barrier(0x400, 1, 2);
     // The probabilities are first used by the next step: without a use here their whole computation is sunk
     // into that step, away from the MFMAs it is meant to share the issue port with.
     asm volatile("" : "+v"(pn[0]), "+v"(pn[1]), "+v"(lb));
@@ -1127,7 +1154,7 @@ __global__ __launch_bounds__(64 * HPW * RBW) void attention_bf16_pipe_kernel(Att
   const float l_tot = l_run[0] + __shfl_xor(l_run[0], 32);
   const float inv = 1.f / l_tot;
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
+  for (int half = 0; half < D / 64; ++half) {
 #pragma unroll
     for (int c4 = 0; c4 < 8; ++c4) {       // columns 64 half + 8 c4 + 4 hf .. + 3
       bf16x4 o4;

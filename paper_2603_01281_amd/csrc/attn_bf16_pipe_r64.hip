@@ -2,6 +2,6 @@
 #include "attn_bf16_pipe_launch.h"
 namespace seka {
 hipError_t launch_attention_bf16_pipe_r64(const AttnArgs& a, const SteerArgs* steer, hipStream_t s) {
-  return launch_attention_bf16_pipe_group<true, 2>(a, steer, s);
+  return launch_attention_bf16_pipe_group<128, true, 2>(a, steer, s);
 }
 }  // namespace seka
