@@ -50,12 +50,16 @@ namespace seka {
 constexpr int PIPE_Z_LD = 80;                       // bytes per key in a coordinate buffer
 constexpr int PIPE_Z_BYTES = DMA_BK * PIPE_Z_LD;    // one buffer
 constexpr int PIPE_QT_BYTES = 2048;                 // U^T q of one wave: [2 k-slices][64 lanes][8] bf16
+// bf16 parts of an element of g P (dense form).  One part rounds it to 2^-9, at D = 128 less than the edited key's own
+// rounding adds; a full-rank projector at D = 64 (whose diagonal is g) was further from the exact result than the form with
+// two low-rank products (4.2e-3 against 3.3e-3, 2-norms), so there a second part carries the remainder.
+constexpr int pipe_edit_parts(int D) { return D == 64 ? 2 : 1; }
 inline size_t attention_bf16_pipe_smem_bytes(int D, int S, bool steer, int nkr, int nwaves) {
   size_t n = (size_t)2 * DMA_STAGES * DMA_BK * D * 2;
   if (D == 64) n += (size_t)4096 * nwaves;             // staging areas (at D = 128 the rings have room for them)
   if (steer) {
     const int Rpad = 32 * nkr;
-    n += nkr == 1 ? (size_t)D * Rpad * 2 : (size_t)D * D * 2;
+    n += nkr == 1 ? (size_t)D * Rpad * 2 : (size_t)pipe_edit_parts(D) * D * D * 2;
     n += (size_t)Rpad * 4;
     if (nkr == 1) n += (size_t)2 * PIPE_Z_BYTES + (size_t)nwaves * PIPE_QT_BYTES;
     n += (size_t)((S + DMA_BK - 1) / DMA_BK) * 8;
@@ -179,13 +183,13 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* Kst = smem;                                     // [3][16 KB] swizzled K tiles
   unsigned char* Vst = smem + DMA_STAGES * TB;                   // [3][16 KB] swizzled V tiles
-  constexpr int Rpad = 32 * NKR;
+  constexpr int Rpad = 32 * NKR, NP = pipe_edit_parts(D);
   constexpr bool DENSE = NKR >= 2;         // edit with the dense matrix g P (see attention_bf16_pipe_smem_bytes)
   constexpr bool kEventsInHot = STEER && (!DENSE || NW == 8);   // steering events handled inside the hot loop (see the tile loop)
   uint16_t* UN = reinterpret_cast<uint16_t*>(smem + 2 * DMA_STAGES * TB + (D == 64 ? 4096 * NW : 0));
   uint16_t* U1 = UN;                       // low rank: operand (rb, s) of U_cat^T K^T: [2][4][64 lanes][8]
-  uint16_t* AP = UN;                       // dense: operand (s_out, half, ks) of (g P) K^T: [4][2][4][64 lanes][8]
-  float* cvec = reinterpret_cast<float*>(UN + (DENSE ? (size_t)D * D : (size_t)D * Rpad));   // [Rpad]
+  uint16_t* AP = UN;                       // dense: operand (s_out, half, ks) of (g P) K^T: [NP][D/32][2][D/32][64 lanes][8]
+  float* cvec = reinterpret_cast<float*>(UN + (DENSE ? (size_t)NP * D * D : (size_t)D * Rpad));   // [Rpad]
   unsigned char* zbuf = reinterpret_cast<unsigned char*>(cvec + Rpad);     // low rank: [2][64 keys][80 B] coordinates
   unsigned char* qtbuf = zbuf + 2 * PIPE_Z_BYTES;                          // low rank: [NW][2][64 lanes][8] U^T q
   unsigned long long* hlbits = reinterpret_cast<unsigned long long*>(      // [tiles] (STEER)
@@ -490,16 +494,17 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
       // element T[y][x] is stored where the edit expects (g P)[d_out = x][d' = y] (T is symmetric up to rounding).
       const int j = lane & 15, g = lane >> 4;
       for (int strip = wave; strip < D / 16; strip += NW) {
-        bf16x8 af[NKR];      // A operand: lane (row = 16 strip + j, k = r = 32 kk + 8 g + e), scaled by c_r
+        bf16x8 af[NKR], al[NKR];      // A operand: lane (row = 16 strip + j, k = r = 32 kk + 8 g + e), scaled by c_r; al: its remainder
 #pragma unroll
         for (int kk = 0; kk < NKR; ++kk) {
           const bf16x8 u = *reinterpret_cast<const bf16x8*>(ustage(16 * strip + j, 4 * kk + g));
           const f32x4 c0 = *reinterpret_cast<const f32x4*>(cvec + 32 * kk + 8 * g);
           const f32x4 c1 = *reinterpret_cast<const f32x4*>(cvec + 32 * kk + 8 * g + 4);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            af[kk][e] = (__bf16)((float)u[e] * c0[e]);
-            af[kk][4 + e] = (__bf16)((float)u[4 + e] * c1[e]);
+          for (int e = 0; e < 8; ++e) {
+            const float x = (float)u[e] * (e < 4 ? c0[e & 3] : c1[e & 3]);
+            af[kk][e] = (__bf16)x;
+            if (NP == 2) al[kk][e] = (__bf16)(x - (float)af[kk][e]);
           }
         }
 #pragma unroll
@@ -509,6 +514,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
           for (int kk = 0; kk < NKR; ++kk) {
             const bf16x8 bfr = *reinterpret_cast<const bf16x8*>(ustage(16 * ct + j, 4 * kk + g));
             acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[kk], bfr, acc, 0, 0, 0);
+            if (NP == 2) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[kk], bfr, acc, 0, 0, 0);
           }
           // this lane holds T[y = 16 strip + 4 g + i][x = 16 ct + j], i = 0..3
           const int x = 16 * ct + j, xl = x & 31, y0 = 16 * strip + 4 * g;
@@ -518,6 +524,11 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) o4[i] = (__bf16)acc[i];
           *reinterpret_cast<uint2*>(AP + (frag * 64 + flane) * 8 + (y0 & 7)) = __builtin_bit_cast(uint2, o4);
+          if (NP == 2) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o4[i] = (__bf16)(acc[i] - (float)o4[i]);
+            *reinterpret_cast<uint2*>(AP + D * D + (frag * 64 + flane) * 8 + (y0 & 7)) = __builtin_bit_cast(uint2, o4);
+          }
         }
       }
       if (D == 128) dma_barrier();           // q_operands() stages its rows where the staged U_cat lies
@@ -561,6 +572,10 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
         for (int ks = 0; ks < KS2; ++ks) {
           const bf16x8 ua = *reinterpret_cast<const bf16x8*>(AP + (((s * 2 + half) * KS2 + ks) * 64 + ln) * 8);
           acc[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua, kreg[ks], acc[ks & 1], 0, 0, 0);
+          if (NP == 2) {
+            const bf16x8 ul = *reinterpret_cast<const bf16x8*>(AP + D * D + (((s * 2 + half) * KS2 + ks) * 64 + ln) * 8);
+            acc[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ul, kreg[ks], acc[ks & 1], 0, 0, 0);
+          }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
