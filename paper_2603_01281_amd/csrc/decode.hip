@@ -92,6 +92,16 @@ __device__ __forceinline__ void merge_state(float& m, float& l, float (&o)[N], f
   for (int i = 0; i < N; ++i) o[i] = o[i] * a1 + o2[i] * a2;
 }
 
+// The range of the cache that a stage-1 workgroup takes.  Workgroups go to the eight XCDs in index order, so with a
+// multiple of four ranges an XCD has the same ranges of every prompt and head, and the first ranges, the only ones that
+// short caches have, pile up on a few (16 caches of 536 to 8192 tokens, 8 KV heads: 23 ranges per head on one XCD, 8 on
+// another; 68 -> 53 us with nothing cached).  Ragged batches therefore turn the order with the head and the prompt; equal
+// lengths keep it (an XCD then reads all heads of the same tokens).
+__device__ __forceinline__ int decode_split_index(const int* lens, int splits) {
+  const unsigned turn = lens && splits % 4 == 0 ? blockIdx.y + blockIdx.z : 0u;
+  return (int)((blockIdx.x + turn) % (unsigned)splits);
+}
+
 // What a stage-1 workgroup does with the merged state (mm, ll, oo) of output element d of query head hq: with
 // several splits it goes to the partial-state buffer for stage 2; with a single split it IS the result, and the
 // workgroup writes the output and the log-sum-exp itself (the same arithmetic as stage 2 on one split, which is
@@ -131,10 +141,11 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const T* __
   const int G = Hq / Hkv;
   const int chunks = G / GP;
   const int b = blockIdx.z, h = blockIdx.y / chunks, hq0 = h * G + (blockIdx.y % chunks) * GP;
-  const int split = blockIdx.x;
+  const int split = decode_split_index(lens, splits);
   const int n = lens ? min(max(lens[b], 0), S) : S;
   const int per = (S + splits - 1) / splits;
   const int k0 = split * per, k1 = min(n, k0 + per);
+  if (k0 >= k1 && splits > 1) return;      // workgroup-uniform; stage 2 knows which ranges are empty
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int c = lane % LPR, kk = lane / LPR;
@@ -277,10 +288,11 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const u
   const int G = Hq / Hkv;
   const int chunks = G / HP;
   const int b = blockIdx.z, h = blockIdx.y / chunks, hq0 = h * G + (blockIdx.y % chunks) * HP;
-  const int split = blockIdx.x;
+  const int split = decode_split_index(lens, splits);
   const int n = lens ? min(max(lens[b], 0), S) : S;
   const int per = (S + splits - 1) / splits;
   const int k0 = split * per, k1 = min(n, k0 + per);
+  if (k0 >= k1 && splits > 1) return;      // workgroup-uniform; stage 2 knows which ranges are empty
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int l32 = lane & 31, hf = lane >> 5, li = lane & 15, grp = lane >> 4;
@@ -434,12 +446,15 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const u
 // takes, is what the number of splits needs.
 constexpr int kFinThreads = 1024;
 template <typename T, int D, int NI>
-__global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(const float* __restrict__ part, int Hq, int splits,
-                                                                    T* __restrict__ O, float* __restrict__ lse) {
+__global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(const float* __restrict__ part, const int* __restrict__ lens,
+                                                                    int S, int Hq, int splits, T* __restrict__ O,
+                                                                    float* __restrict__ lse) {
   constexpr int NJ = kFinThreads / D;
   __shared__ float sm[NJ][D + 2];
   const int hq = blockIdx.x, b = blockIdx.y, d = threadIdx.x % D, j = threadIdx.x / D;
   const float* src = part + ((size_t)b * Hq + hq) * splits * (D + 2);
+  const int per = (S + splits - 1) / splits;             // tokens per range, as in stage 1; a shorter cache has fewer
+  const int live = lens ? (min(max(lens[b], 0), S) + per - 1) / per : splits;
   float mv[NI], lv[NI], ov[NI];
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
@@ -452,11 +467,11 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(const float*
   float mm = kNegBig;
 #pragma unroll
   for (int i = 0; i < NI; ++i)
-    if (j + NJ * i < splits) mm = fmaxf(mm, mv[i]);
+    if (j + NJ * i < live) mm = fmaxf(mm, mv[i]);
   float ll = 0.f, oo = 0.f;
 #pragma unroll
   for (int i = 0; i < NI; ++i)
-    if (j + NJ * i < splits) {
+    if (j + NJ * i < live) {
       const float aw = __builtin_amdgcn_exp2f(mv[i] - mm);
       ll += lv[i] * aw;
       oo += ov[i] * aw;
@@ -484,12 +499,12 @@ __global__ __launch_bounds__(kFinThreads) void decode_finish_kernel(const float*
 }
 
 template <typename T, int D>
-void launch_decode_finish(const float* part, int B, int Hq, int splits, T* O, float* lse, hipStream_t s) {
+void launch_decode_finish(const float* part, const int* lens, int B, int S, int Hq, int splits, T* O, float* lse, hipStream_t s) {
   constexpr int NJ = kFinThreads / D;
   const dim3 grid(Hq, B), block(kFinThreads);
-  if (splits <= NJ) hipLaunchKernelGGL((decode_finish_kernel<T, D, 1>), grid, block, 0, s, part, Hq, splits, O, lse);
-  else if (splits <= 2 * NJ) hipLaunchKernelGGL((decode_finish_kernel<T, D, 2>), grid, block, 0, s, part, Hq, splits, O, lse);
-  else hipLaunchKernelGGL((decode_finish_kernel<T, D, (kDecMaxSplits + NJ - 1) / NJ>), grid, block, 0, s, part, Hq, splits, O, lse);
+  if (splits <= NJ) hipLaunchKernelGGL((decode_finish_kernel<T, D, 1>), grid, block, 0, s, part, lens, S, Hq, splits, O, lse);
+  else if (splits <= 2 * NJ) hipLaunchKernelGGL((decode_finish_kernel<T, D, 2>), grid, block, 0, s, part, lens, S, Hq, splits, O, lse);
+  else hipLaunchKernelGGL((decode_finish_kernel<T, D, (kDecMaxSplits + NJ - 1) / NJ>), grid, block, 0, s, part, lens, S, Hq, splits, O, lse);
 }
 
 template <typename T, int D, int GP>
@@ -501,7 +516,7 @@ hipError_t launch_decode_gp(const void* q, const void* K, const void* V, void* O
                      static_cast<const T*>(q), static_cast<const T*>(K), static_cast<const T*>(V), lens, S, Hq, Hkv, c2,
                      splits, part, static_cast<T*>(O), lse);
   if (splits > 1)
-    launch_decode_finish<T, D>(part, B, Hq, splits, static_cast<T*>(O), lse, s);
+    launch_decode_finish<T, D>(part, lens, B, S, Hq, splits, static_cast<T*>(O), lse, s);
   return hipGetLastError();
 }
 
@@ -566,10 +581,10 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
     if (splits > 1) {
       if (D == 128) {
         SEKA_DEC_LAUNCH(128, 4);
-        launch_decode_finish<uint16_t, 128>(part, B, Hq, splits, O16, lse, s);
+        launch_decode_finish<uint16_t, 128>(part, lens, B, S, Hq, splits, O16, lse, s);
       } else {
         SEKA_DEC_LAUNCH(64, 4);
-        launch_decode_finish<uint16_t, 64>(part, B, Hq, splits, O16, lse, s);
+        launch_decode_finish<uint16_t, 64>(part, lens, B, S, Hq, splits, O16, lse, s);
       }
     } else if (S > 128 && (long long)B * Hkv * (G / hp) <= 256) {
       // A short cache is one workgroup's chain of blocks, half as long with twice the waves: 12.0 -> 10.3 us at S = 1000,
