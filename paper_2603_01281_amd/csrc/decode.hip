@@ -11,6 +11,7 @@
 // bf16 caches (decode_partial_mfma_kernel), on the vector unit for fp32 ones (decode_partial_kernel).  Partial
 // states are merged across lanes, waves (LDS) and splits (stage 2, fixed order, so the result does not depend on
 // scheduling).
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -29,7 +30,7 @@ constexpr int kDecWaves = kDecThreads / 64;
 constexpr float kDecSlack = 8.f;        // a head's reference exponent trails its maximum by at most this
 constexpr float kNegBig = -1e30f;
 // split policy (measured on MI355X: more, smaller splits lose to the merge stage; fewer leave CUs idle)
-constexpr int kDecTargetWG = 4096, kDecMinRows = 512, kDecMaxSplits = 64;
+constexpr int kDecTargetWG = 4096, kDecMinRows = 512, kDecMinElemsF32 = 8192, kDecMaxSplits = 64;
 
 __host__ __device__ inline int decode_heads_per_group(int G) {
   if (G <= 8) return G;
@@ -38,11 +39,10 @@ __host__ __device__ inline int decode_heads_per_group(int G) {
   return 1;
 }
 
-// Splits of the cached range per (prompt, head group): about kDecTargetWG workgroups in all, at least kDecMinRows tokens each.
-__host__ __device__ inline int decode_splits(int B, int Hkv, int G, int S, int heads_per_wg) {
-  const int groups = B * Hkv * (G / heads_per_wg);
+// Splits of the cached range per (prompt, head group): about kDecTargetWG workgroups in all, at least min_rows tokens each.
+inline int decode_splits(int groups, int S, int min_rows) {
   int want = (kDecTargetWG + groups - 1) / groups;
-  const int cap = S / kDecMinRows > 1 ? S / kDecMinRows : 1;
+  const int cap = S / min_rows > 1 ? S / min_rows : 1;
   if (want > cap) want = cap;
   if (want > kDecMaxSplits) want = kDecMaxSplits;
   return want < 1 ? 1 : want;
@@ -560,15 +560,26 @@ static int decode_heads_per_wg(int G, int dtype) {
   return dtype == SEKA_BF16 ? decode_heads_per_group_mfma(G) : decode_heads_per_group(G);
 }
 
+// The fp32 kernel multiplies on the vector unit, about 60 ns per token and workgroup at seven heads: ranges of 64 tokens
+// (128 at D = 64) where there are workgroups to spare (B=3 S=1408 28 / 4 heads 69 -> 15 us, B=1 S=4864 32 / 4 63 -> 19, B=8 S=700 32 / 8
+// 40 -> 13; nothing changes where the groups alone are enough).  Not more than the library's own buffer holds, unless
+// the 512-token ranges need that much.
+static int decode_splits_of(int B, int S, int Hq, int Hkv, int D, int dtype) {
+  const int G = Hq / Hkv, groups = B * Hkv * (G / decode_heads_per_wg(G, dtype));
+  const int splits = decode_splits(groups, S, kDecMinRows);
+  if (dtype == SEKA_BF16) return splits;
+  const size_t fit = kDecodeStaticScratchBytes / ((size_t)B * Hq * (D + 2) * sizeof(float));
+  return std::max(splits, (int)std::min((size_t)decode_splits(groups, S, kDecMinElemsF32 / D), fit));
+}
+
 size_t decode_workspace_bytes(int B, int S, int Hq, int Hkv, int D, int dtype) {
-  const int G = Hq / Hkv;
-  return (size_t)B * Hq * decode_splits(B, Hkv, G, S, decode_heads_per_wg(G, dtype)) * (D + 2) * sizeof(float);
+  return (size_t)B * Hq * decode_splits_of(B, S, Hq, Hkv, D, dtype) * (D + 2) * sizeof(float);
 }
 
 hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, float* lse, const int* lens, int B, int S,
                          int Hq, int Hkv, int D, int dtype, float scale, void* workspace, hipStream_t s) {
   const int G = Hq / Hkv, hp = decode_heads_per_wg(G, dtype);
-  const int splits = decode_splits(B, Hkv, G, S, hp);
+  const int splits = decode_splits_of(B, S, Hq, Hkv, D, dtype);
   float* part = static_cast<float*>(workspace);
   if (dtype == SEKA_BF16) {
     const float c2 = scale * 1.4426950408889634f;
