@@ -1,4 +1,4 @@
-// bf16 attention kernels for head dimension 64.
+// bf16 attention at head dimension 64: dispatch and the register-staged kernels.
 #include <cstring>
 #include "attn_bf16_launch.h"
 namespace seka {

@@ -1,4 +1,4 @@
-// bf16 causal GQA prefill attention for gfx950, head dimension 128, with the spectral key edit fused in
+// bf16 causal GQA prefill attention for gfx950, head dimensions 64 and 128, with the spectral key edit fused in
 // (paper Sec. 2: logits q_i . k'_j / sqrt(d_k), k'_j = k_j + g P k_j for highlighted j; Sec. 3.3 for the
 // blended P of AdaSEKA).  Flash-style: scores and edited keys never leave the CU.  Software-pipelined,
 // 32 query rows per wave; attn_bf16_lds_dma.h describes how the tiles travel.
