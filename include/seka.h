@@ -271,6 +271,8 @@ seka_status seka_attention_decode_static(const void* q, const void* K, const voi
  *            fp32 and the column is all zero; vectors of equal singular values span the right subspace only.
  * sigma_out  dev [Hkv,D] fp32, descending.
  * k_out      dev [Hkv] int32, in [1, D].
+ *            A head whose Omega is not finite (samples that are not, or products beyond fp32) gets NaN in all of U_out,
+ *            sigma_out and U_packed, and k = D; the other heads are not touched by it.
  * U_packed   dev [Hkv,D,r_pad] tensor dtype or NULL: the first min(k_h, r_pad) columns of U_out[h], the remaining
  *            columns zero, ready to be seka_steer.U with M = 1, r = r_pad (1 <= r_pad <= D).
  * workspace  dev scratch of at least seka_learn_workspace_bytes(sh) bytes, 16-byte aligned.

@@ -278,6 +278,15 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
   int* by_rank = reinterpret_cast<int*>(sorted_s + D);           // [D] column of the r-th largest value
   const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  auto store_packed = [&](int i, int r, float v) __attribute__((always_inline)) {      // row i, column r < r_pad
+    const size_t at = ((size_t)h * D + i) * r_pad + r;
+    if (sizeof(T) == 2) {
+      const __bf16 bv = (__bf16)v;
+      reinterpret_cast<uint16_t*>(U_packed)[at] = __builtin_bit_cast(uint16_t, bv);
+    } else {
+      reinterpret_cast<float*>(U_packed)[at] = v;
+    }
+  };
 
   // ---- phase 1 ----
   float unit;                                     // sqrt of B's largest element: L is scaled by its inverse
@@ -293,6 +302,19 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
       for (int j = 0; j < 4; ++j) a[i][j] = Bh[(size_t)(tr + i) * D + tc + j];
 #pragma unroll
     for (int x = 0; x < RPL; ++x) d[x] = Bh[(size_t)(lane + 64 * x) * (D + 1)];
+    unsigned top = 0;                             // high word of the largest diagonal element (they are sums of squares)
+#pragma unroll
+    for (int x = 0; x < RPL; ++x) top = max(top, (unsigned)(__builtin_bit_cast(unsigned long long, d[x]) >> 32) & 0x7fffffffu);
+    top = wave_max(top);
+    if (top >= 0x7ff00000u) {                     // Omega is not finite: neither is what is made of it (the same in every wave)
+      const float nan = __builtin_nanf("");
+      for (int idx = tid; idx < D * D; idx += NT) U_out[(size_t)h * D * D + idx] = nan;
+      if (tid < D) sigma_out[(size_t)h * D + tid] = nan;
+      if (tid == 0) k_out[h] = D;
+      if (U_packed)
+        for (int idx = tid; idx < D * r_pad; idx += NT) store_packed(idx / r_pad, idx % r_pad, nan);
+      return;
+    }
     double floor_d = 0.0;
     float key_scale = 1.f;
     unit = 0.f;
@@ -308,11 +330,8 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
       for (int x = 1; x < RPL; ++x) dp = (p >> 6) == x ? d[x] : dp;
       dp = lane_double(dp, p & 63);
       if (k == 0) {
-        bool nan = false;                         // a sample that is not a number shows in the singular values
-#pragma unroll
-        for (int x = 0; x < RPL; ++x) nan = nan || d[x] != d[x];
         floor_d = 1e-14 * dp;
-        unit = __any(nan) ? __builtin_nanf("") : (float)sqrt(dp);
+        unit = (float)sqrt(dp);
         key_scale = dp > 0.0 ? (float)(1.0 / dp) : 0.f;
       }
       if (!(dp > floor_d)) { ncols = k; break; }  // the same in every wave: same data, same operations
@@ -468,13 +487,18 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
   }
   __syncthreads();
   if (tid < D) {
-    const float me = sig[tid];
+    // compared as bits, which order non-negative values and leave no two of them unordered: every rank is written,
+    // whatever the values are
+    const unsigned me = __float_as_uint(sig[tid]);
     int r = 0;
 #pragma unroll 8
-    for (int k = 0; k < D; ++k) r += (sig[k] > me) || (sig[k] == me && k < tid);
+    for (int k = 0; k < D; ++k) {
+      const unsigned other = __float_as_uint(sig[k]);
+      r += (other > me) || (other == me && k < tid);
+    }
     by_rank[r] = tid;
-    sorted_s[r] = me;
-    sigma_out[(size_t)h * D + r] = me * unit;
+    sorted_s[r] = sig[tid];
+    sigma_out[(size_t)h * D + r] = sig[tid] * unit;
   }
   __syncthreads();
   // rank rule of Eq. 3: the smallest k whose leading values reach gamma of the sum; every wave works it out by itself
@@ -505,15 +529,7 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
   for (int i = tid / D; i < D; i += NT / D) {
     const float u = A[j * LD + i] * s_inv;
     U_out[((size_t)h * D + i) * D + r] = u;
-    if (U_packed && r < r_pad) {
-      const float v = r < k_sel ? u : 0.f;
-      if (sizeof(T) == 2) {
-        const __bf16 bv = (__bf16)v;
-        reinterpret_cast<uint16_t*>(U_packed)[((size_t)h * D + i) * r_pad + r] = __builtin_bit_cast(uint16_t, bv);
-      } else {
-        reinterpret_cast<float*>(U_packed)[((size_t)h * D + i) * r_pad + r] = v;
-      }
-    }
+    if (U_packed && r < r_pad) store_packed(i, r, r < k_sel ? u : 0.f);
   }
 }
 

@@ -37,3 +37,37 @@ def test_low_rank_samples(seka, D, n, scale):
         want = int(np.sum(frac < gamma)) + 1
         if np.abs(frac - gamma).min() > 1e-4:
             assert got_k[h] == want
+
+
+def _learn(seka, ha, hb, gamma, dtype, r_pad=16):
+    """U, sigma, k and the packed basis of [n, Hkv, D] samples; every output buffer starts as a value no result has."""
+    import torch
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    _, Hkv, D = ha.shape
+    U = torch.full((Hkv, D, D), 7.0, device="cuda")
+    sig = torch.full((Hkv, D), -7.0, device="cuda")
+    k = torch.full((Hkv,), -1, dtype=torch.int32, device="cuda")
+    Up = torch.full((Hkv, D, r_pad), 7.0, device="cuda", dtype=dt)
+    seka.seka_learn_projection(torch.from_numpy(ha)[None].cuda().to(dt), torch.from_numpy(hb)[None].cuda().to(dt), gamma, U, sig, k,
+                               U_packed=Up)
+    torch.cuda.synchronize()
+    return U, sig, k, Up
+
+
+# one sample of the middle head: in the neutral view a row of Omega is lost, in the other a column, so every row
+@pytest.mark.parametrize("dtype,D,view,value", [("f32", 128, 0, np.nan), ("bf16", 128, 1, np.nan), ("bf16", 64, 0, np.nan),
+                                                ("f32", 64, 1, np.inf), ("f32", 128, 0, -np.inf), ("f32", 64, 0, 3e38)])
+def test_samples_that_are_not_finite(seka, dtype, D, view, value):
+    import torch
+    print(f"learn not finite {dtype} D={D} view={view} value={value}", flush=True)
+    g = np.random.default_rng(D + view)
+    ha, hb = (g.standard_normal((300, 3, D)).astype(np.float32) for _ in range(2))
+    clean = _learn(seka, ha, hb, 0.9, dtype)
+    (ha, hb)[view][137:139, 1, D // 2] = value                    # two: 3e38 is finite, the sum of its products is not
+    (hb, ha)[view][137:139, 1] = np.where(np.arange(D) % 2, 4.0, -4.0)
+    U, sig, k, Up = _learn(seka, ha, hb, 0.9, dtype)
+    for out in (U, sig, Up):
+        assert torch.isnan(out[1].float()).all()
+    assert int(k[1]) == D
+    for got, want in zip((U, sig, k, Up), clean):                 # the other heads: the same bits as without it
+        assert torch.equal(got[[0, 2]], want[[0, 2]]) and torch.isfinite(got[[0, 2]].float()).all()
