@@ -315,6 +315,17 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
         for (int idx = tid; idx < D * r_pad; idx += NT) store_packed(idx / r_pad, idx % r_pad, nan);
       return;
     }
+    // The factorisation runs on 2^-e B, e even, whose largest element lies in [1, 4): B's own, from 2^-298 to 2^263, and
+    // their reciprocals leave fp32, in which the pivots are compared and L is stored.  Powers of two: no bit changes.
+    const int e = top ? ((int)(top >> 20) - 1023) & ~1 : 0;
+    const double down = __builtin_bit_cast(double, (unsigned long long)(1023 - e) << 52);
+    const double up_half = __builtin_bit_cast(double, (unsigned long long)(1023 + e / 2) << 52);
+#pragma unroll
+    for (int i = 0; i < TR; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[i][j] *= down;
+#pragma unroll
+    for (int x = 0; x < RPL; ++x) d[x] *= down;
     double floor_d = 0.0;
     float key_scale = 1.f;
     unit = 0.f;
@@ -331,7 +342,7 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
       dp = lane_double(dp, p & 63);
       if (k == 0) {
         floor_d = 1e-14 * dp;
-        unit = (float)sqrt(dp);
+        unit = (float)(sqrt(dp) * up_half);
         key_scale = dp > 0.0 ? (float)(1.0 / dp) : 0.f;
       }
       if (!(dp > floor_d)) { ncols = k; break; }  // the same in every wave: same data, same operations

@@ -71,3 +71,31 @@ def test_samples_that_are_not_finite(seka, dtype, D, view, value):
     assert int(k[1]) == D
     for got, want in zip((U, sig, k, Up), clean):                 # the other heads: the same bits as without it
         assert torch.equal(got[[0, 2]], want[[0, 2]]) and torch.isfinite(got[[0, 2]].float()).all()
+
+
+# squares of Omega's elements, and their reciprocals, beyond fp32 at either end
+@pytest.mark.parametrize("dtype,D,n,scale_a,scale_b", [("f32", 128, 300, 1e-10, 1e-10), ("bf16", 128, 300, 1e-10, 1e-10),
+                                                       ("f32", 64, 20, 1e-18, 1e-12), ("bf16", 64, 300, 1e-17, 1e-17), ("f32", 128, 9, 1e10, 1e10),
+                                                       ("bf16", 128, 300, 1e15, 1e20)])
+def test_small_and_large_samples(seka, dtype, D, n, scale_a, scale_b):
+    import torch
+    print(f"learn scale {dtype} D={D} n={n} {scale_a} {scale_b}", flush=True)
+    g = np.random.default_rng(n)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    ha, hb = (torch.from_numpy((s * g.standard_normal((n, 2, D))).astype(np.float32)).to(dt).float().numpy() for s in (scale_a, scale_b))
+    U, sig, k, Up = _learn(seka, ha, hb, 0.9, dtype)
+    got_U, got_S = H.to_f64(U), H.to_f64(sig)
+    assert torch.isfinite(U).all() and torch.isfinite(Up.float()).all()
+    for h in range(2):
+        omega = ha[:, h].astype(np.float64).T @ hb[:, h].astype(np.float64) / n
+        s = np.linalg.svd(omega, compute_uv=False)
+        rank = min(n, D)
+        assert np.abs(got_S[h] - s).max() <= 2e-5 * s[0] and np.all(np.diff(got_S[h]) <= 0)       # bounds as above
+        live = got_S[h] > 1e-5 * got_S[h, 0]
+        assert live[:rank // 2].all() and np.all(got_U[h][:, ~live] == 0.0)
+        G = got_U[h][:, live].T @ got_U[h][:, live]
+        assert np.abs(G - np.eye(int(live.sum()))).max() <= 1e-4
+        assert np.abs(np.linalg.norm(got_U[h][:, live].T @ omega, axis=1) - s[live]).max() <= 1e-4 * s[0]
+        frac = np.cumsum(s) / s.sum()
+        if np.abs(frac - 0.9).min() > 1e-4:
+            assert int(k[h]) == int(np.sum(frac < 0.9)) + 1
