@@ -512,20 +512,18 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
     sigma_out[(size_t)h * D + r] = sig[tid] * unit;
   }
   __syncthreads();
-  // rank rule of Eq. 3: the smallest k whose leading values reach gamma of the sum; every wave works it out by itself
+  // Rank rule of Eq. 3: the smallest k whose leading values reach gamma of the sum; every wave works it out by itself.
+  // One chain of additions in index order: its sums never decrease and stay at the total from the last value that counts
+  // on, so at gamma = 1 the zeros behind it are not asked for.  (Sums in another association differ in the last bit.)
   int k_sel;
   {
-    float run[RPL], total = 0.f;                  // inclusive sums in index order: lane l has l, then 64 + l
+#pragma clang fp reassociate(off)
+    float run[RPL], total = 0.f;                  // lane l keeps the sums up to l and up to 64 + l
+#pragma unroll 8
+    for (int k = 0; k < D; ++k) {
+      total += sorted_s[k];
 #pragma unroll
-    for (int x = 0; x < RPL; ++x) {
-      float v = sorted_s[64 * x + lane];
-#pragma unroll
-      for (int s = 1; s < 64; s *= 2) {
-        const float u = __shfl_up(v, s);
-        v += lane >= s ? u : 0.f;
-      }
-      run[x] = v + total;
-      total = __shfl(run[x], 63);
+      for (int x = 0; x < RPL; ++x) run[x] = k == 64 * x + lane ? total : run[x];
     }
     int below = 0;
 #pragma unroll

@@ -99,3 +99,17 @@ def test_small_and_large_samples(seka, dtype, D, n, scale_a, scale_b):
         frac = np.cumsum(s) / s.sum()
         if np.abs(frac - 0.9).min() > 1e-4:
             assert int(k[h]) == int(np.sum(frac < 0.9)) + 1
+
+
+@pytest.mark.parametrize("D,n", [(128, 1), (128, 9), (128, 60), (64, 5), (64, 33), (64, 64), (128, 300)])
+def test_all_of_the_mass(seka, D, n):
+    """gamma = 1: values that are exactly zero are not asked for, and what is left out is lost in the sum's rounding."""
+    print(f"learn gamma 1 D={D} n={n}", flush=True)
+    g = np.random.default_rng(D + n)
+    ha, hb = (g.standard_normal((n, 12, D)).astype(np.float32) for _ in range(2))
+    U, sig, k, Up = _learn(seka, ha, hb, 1.0, "f32")
+    got_S, got_k = H.to_f64(sig), k.cpu().numpy()
+    for h in range(12):
+        assert 1 <= got_k[h] <= np.count_nonzero(got_S[h]), (h, got_k[h], np.count_nonzero(got_S[h]))
+        # a value is absorbed if it is below half an ulp of the sum so far, at most 2^-24 of the total; D of them at most
+        assert got_S[h, got_k[h]:].sum() <= D * 2.0 ** -24 * got_S[h].sum()
