@@ -229,7 +229,8 @@ seka_status seka_attention_prefill_packed(const void* Q, const void* K, const vo
  * seq_lens  dev [B] int32 or NULL (= S for every prompt); values are clamped to [0, S]; a prompt with no
  *           cached token gets O = 0 and lse = -inf.
  * workspace dev scratch of at least seka_decode_workspace_bytes(sh) bytes, 16-byte aligned; contents on return
- *           are unspecified; calls sharing it must be ordered by their stream.  (Caches short enough to be
+ *           are unspecified; calls sharing it must be ordered by their stream.  The size never falls with B or S:
+ *           one allocated for the largest batch and cache serves the smaller ones.  (Caches short enough to be
  *           taken in one piece per head group, S < 1024 in bf16, are one kernel that does not touch it.)
  */
 size_t seka_decode_workspace_bytes(const seka_shape* sh);
@@ -243,9 +244,9 @@ seka_status seka_attention_decode(const void* q, const void* K, const void* V, v
  * results and errors, without the workspace pair: the partial states go to a buffer of
  * SEKA_DECODE_STATIC_MAX_BYTES (8 MiB) that the library owns in device memory (one per GPU that loads the
  * library, held until the process ends).  The call allocates and frees nothing.
- *   - Problems whose partial states exceed the buffer (seka_decode_workspace_bytes(sh) > SEKA_DECODE_STATIC_MAX_BYTES;
- *     B * Hq * splits * (D + 2) * 4 bytes with at most 64 splits, e.g. more than 256 (prompt, query head) pairs
- *     of a long cache at D = 128) return SEKA_ERR_WORKSPACE and launch nothing: use seka_attention_decode.
+ *   - Problems whose partial states exceed the buffer (B * Hq * splits * (D + 2) * 4 bytes with at most 64 splits, e.g.
+ *     more than 256 (prompt, query head) pairs of a long cache at D = 128) return SEKA_ERR_WORKSPACE and launch
+ *     nothing: use seka_attention_decode.  Whatever seka_decode_workspace_bytes(sh) <= SEKA_DECODE_STATIC_MAX_BYTES fits.
  *   - Every call on a GPU shares that GPU's buffer.  Calls on one stream are ordered by it; calls that overlap
  *     in time on one GPU (different streams, no dependency) race on the buffer and give wrong results.  Nothing
  *     in the buffer has to start at zero: every slot a launch reads is written earlier in the same call.

@@ -572,8 +572,17 @@ static int decode_splits_of(int B, int S, int Hq, int Hkv, int D, int dtype) {
   return std::max(splits, (int)std::min((size_t)decode_splits(groups, S, kDecMinElemsF32 / D), fit));
 }
 
-size_t decode_workspace_bytes(int B, int S, int Hq, int Hkv, int D, int dtype) {
+size_t decode_partial_bytes(int B, int S, int Hq, int Hkv, int D, int dtype) {
   return (size_t)B * Hq * decode_splits_of(B, S, Hq, Hkv, D, dtype) * (D + 2) * sizeof(float);
+}
+
+// A workspace that serves any smaller batch and any shorter cache too.  Fewer prompts may be cut into so many more ranges that
+// they need more than B do (fp32, 32 / 8 heads, D = 128, S = 1408: 22 prompts more than 23), hence the largest
+// need up to B; beyond kDecTargetWG prompts it only grows with B.  The need never falls with S.
+size_t decode_workspace_bytes(int B, int S, int Hq, int Hkv, int D, int dtype) {
+  size_t most = decode_partial_bytes(B, S, Hq, Hkv, D, dtype);
+  for (int b = std::min(B - 1, kDecTargetWG); b > 0; --b) most = std::max(most, decode_partial_bytes(b, S, Hq, Hkv, D, dtype));
+  return most;
 }
 
 hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, float* lse, const int* lens, int B, int S,

@@ -176,6 +176,21 @@ def test_decode_rejects_bad_arguments(B):
     assert L.seka_decode_workspace_bytes(ctypes.byref(_shape(B, Hq=5))) == 0
 
 
+def test_decode_workspace_serves_smaller_calls(B):
+    """A workspace sized for the largest batch and cache is large enough for every smaller one."""
+    L = B.lib
+    for dtype in (B.SEKA_F32, B.SEKA_BF16):
+        for Hq, Hkv, D in ((32, 8, 128), (28, 4, 128), (32, 4, 64), (12, 12, 128), (8, 1, 64), (40, 2, 128)):
+            size = lambda b, s: L.seka_decode_workspace_bytes(ctypes.byref(B.seka_shape(b, s, Hq, Hkv, D, dtype, 0.0)))
+            by_s = []
+            for S in (1, 63, 64, 127, 200, 700, 1023, 1024, 1408, 2048, 3000, 4096, 9000, 16384, 40000):
+                sizes = [size(b, S) for b in range(1, 140)]
+                assert sizes == sorted(sizes), (dtype, Hq, Hkv, D, S)
+                by_s.append(sizes)
+            assert all(a <= b for lo, hi in zip(by_s, by_s[1:]) for a, b in zip(lo, hi)), (dtype, Hq, Hkv, D)
+            assert size(4096, 2048) <= size(4097, 2048) <= size(5000, 2048) and size(65535, 64) > 0
+
+
 def test_learn_rejects_bad_arguments(B):
     L = B.lib
     ok = _shape(B)
