@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_f32_kernel(AttnArgs a, 
       for (int nb = 0; nb < NB; ++nb) {
         const unsigned bits = (unsigned)(__ballot(s.m[nb] != 0) & 0xffffull);
         if (__builtin_expect(bits != 0, 0)) {
-          const float mbit = s.m[nb] != 0 ? 1.f : 0.f;               // key l % 16
+          const f32x4 as_stored = acc[nb];
           if (kscale != 1.f) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[nb][i] *= (bits >> (4 * g + i)) & 1u ? kscale : 1.f;
@@ -196,8 +196,11 @@ __global__ __launch_bounds__(kThreads, 2) void attention_f32_kernel(AttnArgs a, 
             const f32x4 t = qt[blk * 64 + lane];
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-              acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32((z0[i] + z1[i]) * (c4[i] * mbit), t[i], acc[nb], 0, 0, 0);
+              acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32((z0[i] + z1[i]) * c4[i], t[i], acc[nb], 0, 0, 0);
           }
+          // the other keys of the block keep their scores, whatever the correction came to (weights that are not finite)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[nb][i] = (bits >> (4 * g + i)) & 1u ? acc[nb][i] : as_stored[i];
         }
       }
     }

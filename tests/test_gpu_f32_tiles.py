@@ -34,3 +34,29 @@ def test_f32_tile_edges(seka, B, S, Hq, Hkv, D, M, r):
     # error is below sqrt(128) * 5 * 2^-24 * 3 / sqrt(64) < 2e-6, and an output moves by at most 2 max|V| (4) of that
     H.assert_close_f32(H.to_f64(O), ref_O, "O", tol=1e-5)
     H.assert_close_f32(H.to_f64(lse), ref_L, "LSE", tol=1e-5)
+
+
+@pytest.mark.parametrize("B,S,D,r,bad", [(1, 90, 64, 8, "weight"), (1, 90, 128, 20, "basis"), (64, 90, 128, 8, "weight"), (64, 90, 64, 20, "basis")])
+def test_f32_edit_touches_highlighted_keys_only(seka, B, S, D, r, bad):
+    """A weight or a basis that is not finite reaches the highlighted keys and no other key of their block: rows that see
+    none of them have the bits of plain attention."""
+    import torch
+    print(f"f32 not finite B={B} S={S} D={D} r={r} {bad}", flush=True)
+    Hq, Hkv = 4, 2
+    inp = inputs.make_layer("f32edges", "f32", B=B, S=S, Hq=Hq, Hkv=Hkv, D=D, M=2, r=r, gain=1.0, mask_recipe=("cover", 0.3, 0.3, 1),
+                            seed=S, qkv_mult=0.5)
+    dev = H.DeviceInputs(inp)
+    first = 37                                                    # inside a 16-key block
+    mask = torch.zeros((B, S), dtype=torch.uint8, device="cuda")
+    mask[:, first:first + 9] = 1
+    w = torch.full((B, Hkv, 2), 0.5, device="cuda")
+    if bad == "weight":
+        w[:, 0, 1], w[:, 1, 0] = float("nan"), float("inf")
+    else:
+        dev.U[:, 1, 5, 3] = float("nan")
+    P, O = torch.full_like(dev.Q, 7.0), torch.full_like(dev.Q, 7.0)
+    seka.seka_attention_plain(dev.Q, dev.K, dev.V, P, scale=inp.scale)
+    seka.seka_attention_prefill(dev.Q, dev.K, dev.V, O, dev.U, [1.0] * Hkv, mask, w=w, scale=inp.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(O[:, :first], P[:, :first])
+    assert not torch.isfinite(O[:, first:]).all(-1).any()
