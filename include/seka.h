@@ -179,6 +179,9 @@ seka_status seka_edit_keys_packed(const void* K_in, void* K_out, const seka_shap
  * lse   dev [B,Hq,S] fp32 or NULL: natural log of the softmax denominator (row maximum included).
  * st == NULL, st->mask == NULL or all gains zero gives exactly seka_attention_plain.
  * bf16 tensors: products on the matrix cores with fp32 accumulation, softmax in fp32.
+ * A prompt's rows have the same bits whatever batch it is in, padded, packed or alone.  Where sizes choose another kernel
+ * they agree within rounding only: bf16 at D = 64 with S <= 256 and Hq / Hkv no multiple of 4, by the number of
+ * prompts; steered bf16 with S in the hundreds of thousands, whose highlight words leave LDS no room.
  */
 seka_status seka_attention_prefill(const void* Q, const void* K, const void* V, void* O,
                                    float* lse, const seka_shape* sh, const seka_steer* st,

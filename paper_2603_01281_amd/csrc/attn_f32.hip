@@ -15,7 +15,8 @@
 //
 // What bounds it: small problems, latency: few waves exist, so the keys of a unit are split over the four waves of
 // a workgroup (KSPLIT = 4) and merged through LDS at the end.  Large ones, the operand loads from L1 / L2 (16 KB per 64
-// products): four units that share their keys form a workgroup (KSPLIT = 1).  The form before this one (scalar FMAs, keys
+// products): four units that share their keys form a workgroup (KSPLIT = 1), and a wave takes the four parts of its keys
+// one after the other, which gives the bits of the split form (0 to 5 % of a short launch, none of a long one).  The form before this one (scalar FMAs, keys
 // and probabilities broadcast from LDS, the edit as dependent global loads) took 134 us at B=1 S=256 Hq=4 D=64 (one
 // call among others), this one 10; B=15 S=549 Hq=32 D=64 1898 -> 320 us; B=2 S=1446 Hq=6 D=128 1706 -> 144 us.
 #include "common.h"
@@ -41,14 +42,29 @@ __device__ __forceinline__ float row_sum(float v) {
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// x a1 + y a2 with the roundings fixed: the two ways of handing out units have to give the same bits.
+__device__ __forceinline__ float fold(float x, float a1, float y, float a2) {
+#pragma clang fp reassociate(off) contract(off)
+  const float t = y * a2;
+  return __builtin_fmaf(x, a1, t);
+}
+// log-sum-exp of a row from its reference exponent (base 2) and its sum, likewise
+__device__ __forceinline__ float row_lse(float m, float l) {
+#pragma clang fp reassociate(off) contract(off)
+  const float log_l = logf(l);
+  return __builtin_fmaf(m, 0.6931471805599453f, log_l);
+}
+
 __host__ __device__ inline int f32_rank_blocks(const SteerArgs& st) { return (st.M * st.r + 15) / 16; }
 
 // LDS: U_cat as operands [rank block][D/16][64 lanes] of four floats, U^T q [wave][rank block][64 lanes] of four floats, the column
-// coefficients; after the key loop the same memory merges the waves' states.
+// coefficients; then a state per wave.  KSPLIT = 4: the states take the place of the rest after the key loop.
+__host__ __device__ inline size_t attention_f32_steer_bytes(int D, int rank_blocks) {
+  return (size_t)rank_blocks * (D / 16 + 4) * 1024 + (size_t)rank_blocks * 64;
+}
 inline size_t attention_f32_smem_bytes(int D, int rank_blocks, int ksplit) {
-  const size_t steer = (size_t)rank_blocks * (D / 16 + 4) * 1024 + (size_t)rank_blocks * 64;
-  const size_t merge = ksplit > 1 ? (size_t)4 * (D / 4 + 2) * 256 : 0;
-  return steer > merge ? steer : merge;
+  const size_t steer = attention_f32_steer_bytes(D, rank_blocks), states = (size_t)4 * (D / 4 + 2) * 256;
+  return ksplit == 1 ? steer + states : steer > states ? steer : states;
 }
 
 template <int D, bool STEER, int KSPLIT>
@@ -160,6 +176,7 @@ __global__ __launch_bounds__(kThreads, 2) void attention_f32_kernel(AttnArgs a, 
   const float c2 = a.scale * 1.4426950408889634f;
 
   auto process = [&](int step, const Step& s) __attribute__((always_inline)) {
+#pragma clang fp reassociate(off)
     f32x4 acc[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -236,14 +253,65 @@ __global__ __launch_bounds__(kThreads, 2) void attention_f32_kernel(AttnArgs a, 
       }
     }
   };
-  for (int step = step0; step < nsteps; step += 2 * KSPLIT) {
-    if (step + KSPLIT < nsteps) fetch(step + KSPLIT, s1);
-    process(step, s0);
-    if (step + KSPLIT >= nsteps) break;
-    if (step + 2 * KSPLIT < nsteps) fetch(step + 2 * KSPLIT, s0);
-    process(step + KSPLIT, s1);
+  // A state, this lane's part: D/16 x 4 values, m, l; value v of lane l at [v][l].
+  constexpr int RS = D / 4 + 2;
+  auto keep_state = [&](float* st) __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < D / 16; ++x)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) st[(4 * x + i) * 64] = o[x][i];
+    st[(RS - 2) * 64] = m_run;
+    st[(RS - 1) * 64] = l_run;
+  };
+  if (KSPLIT == 1) {
+    // The steps of a row are four chains, w, w + 4, w + 8 ... for w = 0 .. 3, and the result is their states folded in
+    // that order.  With KSPLIT = 4 each chain is a wave's; here the wave takes them one after the other.  So a row
+    // has the same bits in either form, and they do not depend on the batch it is in.
+    float* kept = lds + attention_f32_steer_bytes(D, NR) / 4 + (size_t)wave * RS * 64 + lane;
+    auto after = [&](int step) __attribute__((always_inline)) {       // nsteps: none
+      return step + 4 < nsteps ? step + 4 : (step & 3) < 3 ? min((step & 3) + 1, nsteps) : nsteps;
+    };
+    auto end_chain = [&](int step, bool last) __attribute__((always_inline)) {
+      if (step + 4 < nsteps) return;
+      l_run = row_sum(l_run);
+      if ((step & 3) != 0) {
+        const float m1 = kept[(RS - 2) * 64], l1 = kept[(RS - 1) * 64], mm = fmaxf(m1, m_run);
+        const float a1 = __builtin_amdgcn_exp2f(m1 - mm), a2 = __builtin_amdgcn_exp2f(m_run - mm);
+        m_run = mm;
+        l_run = fold(l1, a1, l_run, a2);
+#pragma unroll
+        for (int x = 0; x < D / 16; ++x)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) o[x][i] = fold(kept[(4 * x + i) * 64], a1, o[x][i], a2);
+      }
+      if (last) return;
+      keep_state(kept);                          // read back by the lane that wrote it
+#pragma unroll
+      for (int x = 0; x < D / 16; ++x) o[x] = f32x4{0.f, 0.f, 0.f, 0.f};
+      m_run = -1e30f;
+      l_run = 0.f;
+    };
+    for (int step = 0; step < nsteps;) {
+      const int next = after(step);
+      if (next < nsteps) fetch(next, s1);
+      process(step, s0);
+      end_chain(step, next >= nsteps);
+      if (next >= nsteps) break;
+      step = after(next);
+      if (step < nsteps) fetch(step, s0);
+      process(next, s1);
+      end_chain(next, step >= nsteps);
+    }
+  } else {
+    for (int step = step0; step < nsteps; step += 2 * KSPLIT) {
+      if (step + KSPLIT < nsteps) fetch(step + KSPLIT, s1);
+      process(step, s0);
+      if (step + KSPLIT >= nsteps) break;
+      if (step + 2 * KSPLIT < nsteps) fetch(step + 2 * KSPLIT, s0);
+      process(step + KSPLIT, s1);
+    }
+    l_run = row_sum(l_run);
   }
-  l_run = row_sum(l_run);
 
   // ---- output: lane (row l % 16, g) holds d = 64 hh + 16 g + 4 i + db in o[4 hh + db][i] ----
   if (KSPLIT == 1) {
@@ -255,44 +323,33 @@ __global__ __launch_bounds__(kThreads, 2) void attention_f32_kernel(AttnArgs a, 
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         *reinterpret_cast<f32x4*>(op + 64 * hh + 4 * i) = f32x4{o[4 * hh][i], o[4 * hh + 1][i], o[4 * hh + 2][i], o[4 * hh + 3][i]} * inv;
-    if (a.lse && g == 0) a.lse[lse_index(a, b, hq, tok0, qi)] = m_run * 0.6931471805599453f + logf(l_run);
+    if (a.lse && g == 0) a.lse[lse_index(a, b, hq, tok0, qi)] = row_lse(m_run, l_run);
     return;
   }
-  // merge the four waves' states: [wave][D/16 x 4 values, m, l][64 lanes]; wave w then finishes the values i = w
-  constexpr int RS = D / 4 + 2;
+  // fold the four waves' states; wave w finishes the values i = w
   __syncthreads();                               // the steering operands are dead
-  float* mine = lds + (size_t)wave * RS * 64 + lane;
-#pragma unroll
-  for (int x = 0; x < D / 16; ++x)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) mine[(4 * x + i) * 64] = o[x][i];
-  mine[(RS - 2) * 64] = m_run;
-  mine[(RS - 1) * 64] = l_run;
+  keep_state(lds + (size_t)wave * RS * 64 + lane);
   __syncthreads();
-  float mw[4], m_all = -1e30f, l_all = 0.f;
+  float m_all = lds[(size_t)(RS - 2) * 64 + lane], l_all = lds[(size_t)(RS - 1) * 64 + lane], r[D / 16];
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    mw[w] = lds[(size_t)(w * RS + RS - 2) * 64 + lane];
-    m_all = fmaxf(m_all, mw[w]);
-  }
+  for (int x = 0; x < D / 16; ++x) r[x] = lds[(size_t)(4 * x + wave) * 64 + lane];
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    mw[w] = __builtin_amdgcn_exp2f(mw[w] - m_all);
-    l_all += mw[w] * lds[(size_t)(w * RS + RS - 1) * 64 + lane];
+  for (int w = 1; w < 4; ++w) {                  // a wave without a step changes nothing: its a2 is zero and so is its state
+    const float* other = lds + (size_t)w * RS * 64 + lane;
+    const float m2 = other[(RS - 2) * 64], mm = fmaxf(m_all, m2);
+    const float a1 = __builtin_amdgcn_exp2f(m_all - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
+    m_all = mm;
+    l_all = fold(l_all, a1, other[(RS - 1) * 64], a2);
+#pragma unroll
+    for (int x = 0; x < D / 16; ++x) r[x] = fold(r[x], a1, other[(4 * x + wave) * 64], a2);
   }
   if (qi >= Sb) return;
   const float inv = 1.f / l_all;
   float* op = O + ((tok0 + qi) * a.Hq + hq) * D + 16 * g + 4 * wave;
 #pragma unroll
-  for (int hh = 0; hh < VH; ++hh) {
-    f32x4 r = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) r[db] += mw[w] * lds[(size_t)(w * RS + 4 * (4 * hh + db) + wave) * 64 + lane];
-    *reinterpret_cast<f32x4*>(op + 64 * hh) = r * inv;
-  }
-  if (a.lse && wave == 0 && g == 0) a.lse[lse_index(a, b, hq, tok0, qi)] = m_all * 0.6931471805599453f + logf(l_all);
+  for (int hh = 0; hh < VH; ++hh)
+    *reinterpret_cast<f32x4*>(op + 64 * hh) = f32x4{r[4 * hh], r[4 * hh + 1], r[4 * hh + 2], r[4 * hh + 3]} * inv;
+  if (a.lse && wave == 0 && g == 0) a.lse[lse_index(a, b, hq, tok0, qi)] = row_lse(m_all, l_all);
 }
 
 template <int D, bool STEER, int KSPLIT>
@@ -309,9 +366,10 @@ hipError_t launch_cfg(const AttnArgs& a, const SteerArgs& st, int units, hipStre
 template <int D, bool STEER>
 hipError_t launch_d(const AttnArgs& a, const SteerArgs& st, hipStream_t s) {
   const int units = (a.S + kUnitRows - 1) / kUnitRows * (a.Hq / a.Hkv);      // per (prompt, KV head)
-  // One wave per unit once the units fill the 1024 SIMDs and the longest unit no longer decides the launch.  Measured,
-  // whole / split: 1824 units of 10 steps 34.8 / 38.1 us, 12800 of 25 316 / 379; the other way 720 of 9 24.7 / 21.5,
-  // 1008 of 42 70.5 / 62.0, 1092 of 91 232 / 144.
+  // One wave per unit once the units fill the 1024 SIMDs several times over for their length; the results are the same.  Measured,
+  // us, whole / split: 2048 units of 2 steps (D = 64) 15.2 / 28.4, 800 of 10 (D = 128) 26.4 / 27.5, 16800 of 18 (D = 64) 306 / 385,
+  // 5632 of 44 (D = 128) 271 / 287; the other way 448 of 7 19.9 / 15.0, 504 of 21 42.5 / 26.1, 1092 of 91 177 / 118, 4000 of 125
+  // 525 / 474.  Near the line it can be wrong: 1140 of 10 (D = 64) 37.3 / 28.1, 3072 of 48 (D = 64) 208 / 154 go whole.
   const int steps = (a.S + 2048 / D - 1) / (2048 / D);      // 32 keys at D = 64, 16 at D = 128
   const long long total = (long long)units * a.Hkv * a.B;
   return total >= 480 + 30LL * steps ? launch_cfg<D, STEER, 1>(a, st, units, s) : launch_cfg<D, STEER, 4>(a, st, units, s);

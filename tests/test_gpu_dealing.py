@@ -87,3 +87,33 @@ def test_ragged_and_packed_equal_prompts(seka, B, S, Hq, Hkv, steered):
         o1, l1 = _attend(seka, one, slice(b, b + 1), steered, inp.scale)
         assert torch.equal(O[b:b + 1, :n], o1) and torch.equal(lse[b:b + 1, :, :n], l1), f"ragged prompt {b} of {n} tokens"
         assert torch.equal(Op[cu[b]:cu[b + 1]], o1[0]), f"packed prompt {b} of {n} tokens"
+
+
+# fp32: single prompts split a row's keys over four waves, the batches here give a row to one wave; up to 5, 9, 21 and 65 steps
+@pytest.mark.parametrize("B,S,Hq,Hkv,D,r", [(64, 33, 4, 1, 64, 8), (40, 130, 8, 2, 64, 20), (30, 143, 6, 2, 128, 8), (24, 333, 6, 2, 128, 40),
+                                            (6, 1033, 32, 8, 128, 8)])
+@pytest.mark.parametrize("steered", [False, True])
+def test_f32_prompts_do_not_depend_on_the_batch(seka, B, S, Hq, Hkv, D, r, steered):
+    import torch
+    print(f"dealing f32 B={B} S={S} {Hq}/{Hkv} D={D} rank {r} steered={steered}", flush=True)
+    inp = inputs.make_layer("dealing", "f32", B=B, S=S, Hq=Hq, Hkv=Hkv, D=D, M=1, r=r, gain=1.0, mask_recipe=("cover", 0.2, 0.2, 2), seed=B + S)
+    dev = H.DeviceInputs(inp)
+    lens = np.random.default_rng(S).integers(1, S + 1, size=B).astype(np.int32)
+    lens[B // 2] = S
+    O, lse = _attend(seka, dev, slice(0, B), steered, inp.scale)
+    Or, lr = _attend(seka, dev, slice(0, B), steered, inp.scale, lens=torch.from_numpy(lens).cuda())
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    pack = lambda x: torch.cat([x[b, :lens[b]] for b in range(B)]).contiguous()
+    Qp = pack(dev.Q)
+    Op = torch.full_like(Qp, float("nan"))
+    st = (dev.U, dev.gain, pack(dev.mask)) if steered else ()
+    seka.seka_attention_prefill_packed(Qp, pack(dev.K), pack(dev.V), Op, torch.from_numpy(cu).cuda(), S, *st, scale=inp.scale)
+    torch.cuda.synchronize()
+    for b in {0, 1, B // 2, B - 1}:
+        o1, l1 = _attend(seka, dev, slice(b, b + 1), steered, inp.scale)
+        assert torch.equal(O[b:b + 1], o1) and torch.equal(lse[b:b + 1], l1), f"prompt {b}"
+        n = int(lens[b])
+        one = type("Prompt", (), dict(Q=dev.Q[:, :n], K=dev.K[:, :n], V=dev.V[:, :n], mask=dev.mask[:, :n], U=dev.U, gain=dev.gain))
+        o1, l1 = _attend(seka, one, slice(b, b + 1), steered, inp.scale)
+        assert torch.equal(Or[b:b + 1, :n], o1) and torch.equal(lr[b:b + 1, :, :n], l1), f"ragged prompt {b} of {n} tokens"
+        assert torch.equal(Op[cu[b]:cu[b + 1]], o1[0]), f"packed prompt {b} of {n} tokens"
