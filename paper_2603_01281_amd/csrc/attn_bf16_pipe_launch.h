@@ -6,20 +6,19 @@
 #include <cstring>
 
 #include "attn_bf16_pipe_kernel.h"
+#include "compute_units.h"
 
 namespace seka {
 
-// Compute units of the current device (256 on MI355X), asked once.
+// Compute units of the current device (256 on MI355X).
 inline int pipe_compute_units() {
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1)
-      n = 256;
-    cus = n;
-  }
-  return cus;
+  static PerDeviceCount cus;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 256;
+  return cus.of(dev, [](int d) {
+    int n = 0;
+    return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, d) == hipSuccess && n > 0 ? n : 256;
+  });
 }
 
 struct PipeWidth {
