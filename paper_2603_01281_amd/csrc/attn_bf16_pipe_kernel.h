@@ -83,7 +83,9 @@ __device__ __forceinline__ float pipe_max3(float a, float b, float c) {
   return r;
 }
 
-// Direct-to-LDS load with a scalar 64-bit base and a 32-bit per-lane byte offset.
+// Direct-to-LDS load with a scalar 64-bit base and a 32-bit per-lane byte offset: the wave's 64 x 16 bytes land contiguously at
+// the (wave-uniform) LDS byte address.  Inline assembly keeps it outside the compiler's own vmcnt bookkeeping: the waits
+// are placed by hand.
 __device__ __forceinline__ void pipe_load_16B(const void* base, uint32_t lane_off, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(lane_off), "s"(base)
                : "memory", "m0");
@@ -161,7 +163,7 @@ template <int D>
 __host__ __device__ constexpr int pipe_v_swizzle(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 
 // HPW heads x RBW row groups = waves per workgroup; every wave owns RPW blocks of 32 consecutive query rows.
-// RPW = 2 (four waves, one per SIMD, 512-register budget) reads every K / V fragment once for two products.
+// The scheduled step is written for RPW = 1, and nothing else is instantiated.
 // NKR: rank of the concatenated basis in blocks of 32 columns (compile-time so that the edit is straight-line code).
 template <int D, int HPW, int RBW, int RPW, bool STEER, int NKR>
 __global__ __launch_bounds__(64 * HPW * RBW) __attribute__((amdgpu_waves_per_eu(2, D == 64 ? 2 : 8))) void
@@ -181,8 +183,8 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   constexpr int SPW = (SLOTS + NW - 1) / NW;             // load instructions per wave per tensor per tile
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  unsigned char* Kst = smem;                                     // [3][16 KB] swizzled K tiles
-  unsigned char* Vst = smem + DMA_STAGES * TB;                   // [3][16 KB] swizzled V tiles
+  unsigned char* Kst = smem;                                     // [3][TB] swizzled K tiles (16 KB each at D = 128, 8 KB at D = 64)
+  unsigned char* Vst = smem + DMA_STAGES * TB;                   // [3][TB] swizzled V tiles
   constexpr int Rpad = 32 * NKR, NP = pipe_edit_parts(D);
   constexpr bool DENSE = NKR >= 2;         // edit with the dense matrix g P (see attention_bf16_pipe_smem_bytes)
   constexpr bool kEventsInHot = STEER && (!DENSE || NW == 8);   // steering events handled inside the hot loop (see the tile loop)
@@ -253,7 +255,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   const uint32_t kst_base = (uint32_t)(uintptr_t)(dma_lds_void_ptr)Kst;
   const uint32_t vst_base = (uint32_t)(uintptr_t)(dma_lds_void_ptr)Vst;
   // V travels in units of half a tile, one half tile behind K: "shifted tile" t = rows [64 t - 32, 64 t + 32) = the
-  // 32-key blocks 2t - 1 and 2t, and block j lives at ring position j % 6 (8 KB each; tile t = positions 2t % 6,
+  // 32-key blocks 2t - 1 and 2t, and block j lives at ring position j % 6 (HB bytes each; tile t = positions 2t % 6,
   // 2t % 6 + 1 as before).  The PV product of a block runs one step after its softmax (see `step`), so the last
   // block of tile t is still being read while the loads of iteration t + 1 are in flight; shifting the unit by
   // half a tile makes every load overwrite only blocks that all waves are done with.

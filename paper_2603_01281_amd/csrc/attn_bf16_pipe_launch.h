@@ -52,7 +52,10 @@ inline PipeWidth pipe_width(int D, int nQB, int BQ, int nHC, int B, int cus) {
                           0.5 * (tiles + pipe_block_tiles(D) + pipe_start_tiles(D)));
     const double prompts = std::min((double)B, (double)cus / ((double)W * nHC));      // whose K and V an L2 serves at a time
     const double l2 = prompts * nQB * BQ * 4.0 * D / 4.2e6;
-    if (prompts > 1.01 && l2 > 1) cost *= 1 + 0.03 * std::log2(l2);                   // B=4 S=8192: 1934 against 1884 us
+    // Rank 32, D = 128, us, without this term / with it: B=4 S=8192 32 / 8 heads 1934 / 1902, B=8 S=8192 16 / 8 1960 / 1919, B=16
+    // S=4096 32 / 4 2080 / 2012, B=6 S=5000 32 / 8 1190 / 1163, B=16 S=6000 8 / 2 1112 / 1084, B=8 S=3000 32 / 32 728 / 665; no
+    // difference at B=2 S=8192 and B=4 S=4096 32 / 8 and B=4 S=12288 24 / 8; the other way at B=2 S=24576 28 / 4, 7298 / 7424.
+    if (prompts > 1.01 && l2 > 1) cost *= 1 + 0.03 * std::log2(l2);
     if (m == 0 || cost < best.cost) best = {W, cost};
   }
   return best;

@@ -18,7 +18,7 @@
 // products): four units that share their keys form a workgroup (KSPLIT = 1), and a wave takes the four parts of its keys
 // one after the other, which gives the bits of the split form (0 to 5 % of a short launch, none of a long one).  The form before this one (scalar FMAs, keys
 // and probabilities broadcast from LDS, the edit as dependent global loads) took 134 us at B=1 S=256 Hq=4 D=64 (one
-// call among others), this one 10; B=15 S=549 Hq=32 D=64 1898 -> 320 us; B=2 S=1446 Hq=6 D=128 1706 -> 144 us.
+// call among others), this one 8.3; B=15 S=549 Hq=32 D=64 1898 -> 306 us; B=2 S=1446 Hq=6 D=128 1706 -> 118 us.
 #include "common.h"
 
 namespace seka {

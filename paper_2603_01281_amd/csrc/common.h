@@ -35,7 +35,7 @@ struct AttnArgs {
   const int* lens;  // dev [B] valid tokens per prompt (clamped to [0, S]), or nullptr for S everywhere
   const int* cu;    // packed layout: dev [B + 1] token offsets (prompt b = tokens [cu[b], cu[b+1]) of `total`), else nullptr
   int total;        // packed layout: tokens in the tensors
-  // bf16, D = 128: how blocks of query rows are dealt to workgroups (set by the launcher, see attn_bf16_pipe_launch.h)
+  // pipelined bf16 kernel: how blocks of query rows are dealt to workgroups (set by its launcher, see attn_bf16_pipe_launch.h)
   int width;        // workgroups per prompt and head chunk
   int slots;        // prompts of different lengths: workgroups per head chunk that run at a time (width is then the
                     // number of workgroups per head chunk), or 0

@@ -260,7 +260,7 @@ __device__ __forceinline__ double lane_double(double v, int l) {
 // tournament of the blocks: D / 8 - 1 exchanges per sweep instead of one barrier per round of pairs).  Pairs inside a
 // block are rotated once per sweep.  A rotation is applied as three shears.  Sweeps repeat until one rotates nothing.
 // What bounds it: vector issue on the head's CU (about 140 instructions per round and wave, two waves per SIMD: 11 k
-// cycles per exchange of blocks).  8 heads, D = 128: 720 us (phase 1 78, phase 2 620 in 8 or 9 sweeps); the form before this
+// cycles per exchange of blocks).  8 heads, D = 128: 654 us (without phase 2 92; 8 or 9 sweeps); the form before this
 // one, Jacobi on Omega with a barrier after every 64 pairs and all columns in LDS, took 2730 us.
 template <typename T, int D>
 __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ gram, float gamma, float* __restrict__ U_out,

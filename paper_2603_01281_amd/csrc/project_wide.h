@@ -5,9 +5,11 @@
 // What bounds it: the matrix pipe and the LDS reads beside it.  A 64-wide slice of E is 2048 cycles of MFMA per SIMD,
 // 1536 cycles of LDS operand reads and 512 of tile writes.  Eight waves as 2 x 4; a wave owns 64 x 32 outputs in each
 // of the four quadrants of the tile (128 tokens x 128 features), so that operands of one half are kept in registers
-// for two quadrants.  A slice is four phases, one quadrant each; a phase is a memory part (the operands that the
-// phase adds, one half tile requested) and a matrix part (8 MFMAs) between barriers, and waves 4-7 run one part
-// behind waves 0-3: on every SIMD one wave multiplies while the other reads.
+// for two quadrants.  The schedule is the eight-wave ping-pong that is published for CDNA matrix products (HipKittens,
+// 2025): two groups of waves half a step apart, half tiles requested ahead.  A slice is four phases, one quadrant each;
+// a phase is a memory part (the operands that the phase adds, one half tile requested) and a matrix part (8 MFMAs)
+// between barriers, and waves 4-7 run one part behind waves 0-3: on every SIMD one wave multiplies while the other
+// reads.
 //
 //   phase   reads (16 bytes per lane)      requests             quadrant (A half, B half)
 //     0     A half 0 of slice k:     8     B half 1 of k + 1      (0, 0)
