@@ -89,14 +89,16 @@ def test_ragged_and_packed_equal_prompts(seka, B, S, Hq, Hkv, steered):
         assert torch.equal(Op[cu[b]:cu[b + 1]], o1[0]), f"packed prompt {b} of {n} tokens"
 
 
-# fp32: single prompts split a row's keys over four waves, the batches here give a row to one wave; up to 5, 9, 21 and 65 steps
-@pytest.mark.parametrize("B,S,Hq,Hkv,D,r", [(64, 33, 4, 1, 64, 8), (40, 130, 8, 2, 64, 20), (30, 143, 6, 2, 128, 8), (24, 333, 6, 2, 128, 40),
-                                            (6, 1033, 32, 8, 128, 8)])
+# fp32: single prompts split a row's keys over four waves, the batches here give a row to one wave; up to 5, 9, 21 and 65 steps.
+# bf16, D = 64: workgroups of 4 x 64, 2 x 128 and 1 x 256 rows, all on the pipelined kernel
+@pytest.mark.parametrize("dtype,B,S,Hq,Hkv,D,r", [
+    ("f32", 64, 33, 4, 1, 64, 8), ("f32", 40, 130, 8, 2, 64, 20), ("f32", 30, 143, 6, 2, 128, 8), ("f32", 24, 333, 6, 2, 128, 40),
+    ("f32", 6, 1033, 32, 8, 128, 8), ("bf16", 64, 150, 8, 2, 64, 32), ("bf16", 20, 700, 6, 3, 64, 64), ("bf16", 9, 1100, 3, 3, 64, 32)])
 @pytest.mark.parametrize("steered", [False, True])
-def test_f32_prompts_do_not_depend_on_the_batch(seka, B, S, Hq, Hkv, D, r, steered):
+def test_prompts_do_not_depend_on_the_batch(seka, dtype, B, S, Hq, Hkv, D, r, steered):
     import torch
-    print(f"dealing f32 B={B} S={S} {Hq}/{Hkv} D={D} rank {r} steered={steered}", flush=True)
-    inp = inputs.make_layer("dealing", "f32", B=B, S=S, Hq=Hq, Hkv=Hkv, D=D, M=1, r=r, gain=1.0, mask_recipe=("cover", 0.2, 0.2, 2), seed=B + S)
+    print(f"dealing {dtype} B={B} S={S} {Hq}/{Hkv} D={D} rank {r} steered={steered}", flush=True)
+    inp = inputs.make_layer("dealing", dtype, B=B, S=S, Hq=Hq, Hkv=Hkv, D=D, M=1, r=r, gain=1.0, mask_recipe=("cover", 0.2, 0.2, 2), seed=B + S)
     dev = H.DeviceInputs(inp)
     lens = np.random.default_rng(S).integers(1, S + 1, size=B).astype(np.int32)
     lens[B // 2] = S
