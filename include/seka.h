@@ -280,10 +280,9 @@ seka_status seka_attention_decode_static(const void* q, const void* K, const voi
  * U_packed   dev [Hkv,D,r_pad] tensor dtype or NULL: the first min(k_h, r_pad) columns of U_out[h], the remaining
  *            columns zero, ready to be seka_steer.U with M = 1, r = r_pad (1 <= r_pad <= D).
  * workspace  dev scratch of at least seka_learn_workspace_bytes(sh) bytes, 16-byte aligned.
- * fp32 accumulation of Omega; its Gram matrix is factored in fp64 and the factor's columns are orthogonalised in fp32
- * (one-sided Jacobi iteration to a relative off-diagonal of 2e-6); deterministic.
- * The decomposition runs one workgroup per head and is bound by its own latency, so a call costs about the
- * same for 8 heads as for 64: heads of several layers may be stacked along the head axis of one call (Hkv <=
+ * fp32 accumulation of Omega; its Gram matrix is decomposed in fp64 (tridiagonal form), and for a head with singular
+ * values that (nearly) coincide by an iteration in fp32 (one-sided Jacobi to a relative off-diagonal of 2e-6);
+ * deterministic.  Most of a call is latency of one workgroup per head, so 64 heads cost far less than eight times 8: heads of several layers may be stacked along the head axis of one call (Hkv <=
  * SEKA_MAX_KV_HEADS).
  *
  * seka_head_distance — the head-selection score of Sec. 3.4: D_out[h] = (1/n) sum_t || h_pos[t,h,:] -

@@ -6,12 +6,14 @@
 //   cov_partial_kernel   Omega in 16-row strips, the token range split into chunks (fp32 accumulation); bf16
 //                        tensors take cov_partial_mfma_kernel (exact products on the matrix cores, one pass).
 //   cov_reduce_kernel, gram_kernel   Omega from its partial sums, Omega Omega^T in fp64.
-//   svd_kernel           one workgroup per head: pivoted Cholesky of the Gram matrix (fp64), then one-sided (Hestenes)
-//                        Jacobi on its factor: plane rotations applied from the right make the columns mutually
-//                        orthogonal, L V = U Sigma, so at convergence column j is sigma_j u_j: the left singular
-//                        vectors come out directly, which is what Eq. 2 needs.
+//   tridiag_kernel, eig_kernel   (learn_eig.h) eigenvalues and vectors of the Gram matrix in fp64: singular values and left
+//                        singular vectors of Omega.
+//   svd_kernel           order, rank rule and packed basis; and where two singular values are too close for the above,
+//                        the vectors from a pivoted Cholesky factor (fp64) and one-sided (Hestenes) Jacobi: plane rotations
+//                        from the right make the factor's columns orthogonal, L V = U Sigma, whatever the gaps are.
 //   head_distance_*      token ranges per workgroup, 16-byte loads, partial sums merged in a fixed order.
 #include "common.h"
+#include "learn_eig.h"
 
 namespace seka {
 
@@ -227,26 +229,12 @@ __device__ __forceinline__ float reduce8(const float (&v)[8], int lane) {
   return r;
 }
 
-__device__ __forceinline__ unsigned wave_max(unsigned v) {
-  auto step = [&](unsigned u) __attribute__((always_inline)) { v = max(v, u); };
-  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));
-  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true));
-  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true));   // mirrored in 8
-  step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true));   // mirrored in 16
-  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  v = max(a[0], a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return (unsigned)__builtin_amdgcn_readfirstlane((int)max(b[0], b[1]));
-}
-__device__ __forceinline__ double lane_double(double v, int l) {
-  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, l), hi = (unsigned)__builtin_amdgcn_readlane((int)(u >> 32), l);
-  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
-}
-
-// Left singular vectors and singular values of one head's Omega, from its Gram matrix B = Omega Omega^T (fp64).
-// grid (Hkv), one workgroup of D / 16 waves per head (the heads are independent and a step of either phase needs
-// everything the step before it produced, so more workgroups would only add synchronisation).
+// Rank rule and packed basis of one head, and its singular values and vectors where the tridiagonal path cannot tell two
+// directions apart: squares closer than 1e-13 of the largest one (they come with about 1e-15) or than 1e-7 of themselves
+// (its vectors are then orthogonal to 1e-7 at worst).  Values of samples with noise are further apart by orders of magnitude
+// (smallest gap in 128 of them: 3e-3 of the value); equal ones are what the iteration is for.
+// grid (Hkv), one workgroup of D / 16 waves per head.  8 heads, D = 128: 12 us, and 107 + 54 for the two kernels before it;
+// with the iteration for every head, as it was: 654.
 //
 // Phase 1, Cholesky with diagonal pivoting, B = L L^T, in fp64: Omega and L have the same left singular vectors and
 // singular values (up to rotations from the right), and L, whose columns come out nearly sorted and nearly
@@ -260,10 +248,9 @@ __device__ __forceinline__ double lane_double(double v, int l) {
 // tournament of the blocks: D / 8 - 1 exchanges per sweep instead of one barrier per round of pairs).  Pairs inside a
 // block are rotated once per sweep.  A rotation is applied as three shears.  Sweeps repeat until one rotates nothing.
 // What bounds it: vector issue on the head's CU (about 140 instructions per round and wave, two waves per SIMD: 11 k
-// cycles per exchange of blocks).  8 heads, D = 128: 654 us (without phase 2 92; 8 or 9 sweeps); the form before this
-// one, Jacobi on Omega with a barrier after every 64 pairs and all columns in LDS, took 2730 us.
+// cycles per exchange of blocks; 8 or 9 sweeps).
 template <typename T, int D>
-__global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ gram, float gamma, float* __restrict__ U_out,
+__global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ gram, const float* __restrict__ omega, float gamma, float* __restrict__ U_out,
                                                     float* __restrict__ sigma_out, int* __restrict__ k_out,
                                                     T* __restrict__ U_packed, int r_pad) {
   constexpr int NW = D / 16, NT = 64 * NW;
@@ -288,8 +275,25 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
     }
   };
 
+  // ---- what the tridiagonal path found ----
+  typedef EigWork<D> W;
+  const double* work = reinterpret_cast<const double*>(omega + (size_t)h * D * D);
+  const bool finite = work[W::kStatus] == 0.0;
+  bool alike = !finite;                           // two directions that it cannot tell apart
+  if (finite) {
+    if (tid < D) {                                // thread r: the r-th largest
+      const double top = work[W::kLambda + D - 1], me = work[W::kLambda + D - 1 - tid];
+      const double next = tid < D - 1 ? work[W::kLambda + D - 2 - tid] : -top;
+      const bool kept = me > (double)kZeroSigma * kZeroSigma * top;
+      alike = kept && (me - next < fmax(1e-13 * top, 1e-7 * me) || reinterpret_cast<const int*>(work + W::kBad)[D - 1 - tid] != 0);
+      sig[tid] = me > 1e-14 * top ? (float)sqrt(me) : 0.f;         // below: rounding of the squares
+    }
+    alike = __syncthreads_or(alike);
+  }
+  float unit = finite ? (float)work[W::kUnit] : 0.f;
+  if (alike) {
   // ---- phase 1 ----
-  float unit;                                     // sqrt of B's largest element: L is scaled by its inverse
+  // unit: sqrt of B's largest element, L is scaled by its inverse
   int ncols = D;
   {
     constexpr int TR = D * D / NT / 4;            // a thread holds TR rows x 4 columns (8 or 4 rows)
@@ -299,7 +303,8 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
 #pragma unroll
     for (int i = 0; i < TR; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) a[i][j] = Bh[(size_t)(tr + i) * D + tc + j];
+      for (int j = 0; j < 4; ++j)                 // the lower triangle: reflectors stand in the other
+        a[i][j] = Bh[(size_t)max(tr + i, tc + j) * D + min(tr + i, tc + j)];
 #pragma unroll
     for (int x = 0; x < RPL; ++x) d[x] = Bh[(size_t)(lane + 64 * x) * (D + 1)];
     unsigned top = 0;                             // high word of the largest diagonal element (they are sums of squares)
@@ -497,6 +502,7 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
     if (lane == 0) sig[c] = sqrtf(s2);
   }
   __syncthreads();
+  }
   if (tid < D) {
     // compared as bits, which order non-negative values and leave no two of them unordered: every rank is written,
     // whatever the values are
@@ -534,6 +540,19 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
   static_assert(NT % D == 0, "a thread keeps its output column");
   const int r = tid % D, j = by_rank[r];
   const float s = sorted_s[r], s_inv = s > kZeroSigma * sorted_s[0] ? 1.f / s : 0.f;
+  if (!alike) {                                   // the columns are there
+    if (s_inv == 0.f)
+      for (int i = tid / D; i < D; i += NT / D) U_out[((size_t)h * D + i) * D + r] = 0.f;
+    if (U_packed) {
+#pragma unroll 4
+      for (int idx = tid; idx < D * r_pad; idx += NT) {
+        const int i = idx / r_pad, c = idx % r_pad;
+        const float u = U_out[((size_t)h * D + i) * D + c];
+        store_packed(i, c, c < k_sel && sorted_s[c] > kZeroSigma * sorted_s[0] ? u : 0.f);
+      }
+    }
+    return;
+  }
 #pragma unroll 8
   for (int i = tid / D; i < D; i += NT / D) {
     const float u = A[j * LD + i] * s_inv;
@@ -618,7 +637,9 @@ hipError_t launch_learn_td(const void* hn, const void* hs, int n, int Hkv, float
   auto kernel = svd_kernel<T, D>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(Hkv), dim3(4 * D), smem, s, gram, gamma, U_out, sigma_out, k_out, static_cast<T*>(U_packed), r_pad);
+  hipLaunchKernelGGL((tridiag_kernel<D>), dim3(Hkv), dim3(256), 0, s, gram, part);
+  hipLaunchKernelGGL((eig_kernel<D>), dim3(D / 4, Hkv), dim3(kEigThreads), 0, s, gram, part, U_out, 0.9 * kZeroSigma * kZeroSigma);
+  hipLaunchKernelGGL(kernel, dim3(Hkv), dim3(4 * D), smem, s, gram, part, gamma, U_out, sigma_out, k_out, static_cast<T*>(U_packed), r_pad);
   return hipGetLastError();
 }
 
