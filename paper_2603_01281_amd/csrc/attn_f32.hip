@@ -366,13 +366,17 @@ hipError_t launch_cfg(const AttnArgs& a, const SteerArgs& st, int units, hipStre
 template <int D, bool STEER>
 hipError_t launch_d(const AttnArgs& a, const SteerArgs& st, hipStream_t s) {
   const int units = (a.S + kUnitRows - 1) / kUnitRows * (a.Hq / a.Hkv);      // per (prompt, KV head)
-  // One wave per unit once the units fill the 1024 SIMDs several times over for their length; the results are the same.  Measured,
-  // us, whole / split: 2048 units of 2 steps (D = 64) 15.2 / 28.4, 800 of 10 (D = 128) 26.4 / 27.5, 16800 of 18 (D = 64) 306 / 385,
-  // 5632 of 44 (D = 128) 271 / 287; the other way 448 of 7 19.9 / 15.0, 504 of 21 42.5 / 26.1, 1092 of 91 177 / 118, 4000 of 125
-  // 525 / 474.  Near the line it can be wrong: 1140 of 10 (D = 64) 37.3 / 28.1, 3072 of 48 (D = 64) 208 / 154 go whole.
+  // One wave per unit or four; the results are the same.  Whole units win where they fill the 1024 SIMDs once, just, or often
+  // enough for their length that the last ones do not matter; a little over 1024 a second wave shares a few SIMDs and sets
+  // the time.  Measured, 8 / 2 heads, us, whole / split, units x steps.  D = 64: 552 x 12 28 / 16, 1008 x 3 11.5 / 15.2, 1056 x 6
+  // 23 / 21, 1140 x 10 36 / 27, 2024 x 12 42 / 45, 2160 x 23 70 / 70, 2160 x 45 138 / 107, 3072 x 48 206 / 156, 4320 x 45 229 / 201,
+  // 7920 x 45 358 / 358, 8280 x 12 120 / 154.  D = 128: 800 x 10 25 / 28, 1056 x 12 38 / 32, 2016 x 12 40 / 55, 3552 x 74 292 / 272,
+  // 4320 x 90 407 / 371, 5632 x 44 266 / 288, 7920 x 90 637 / 664.
   const int steps = (a.S + 2048 / D - 1) / (2048 / D);      // 32 keys at D = 64, 16 at D = 128
   const long long total = (long long)units * a.Hkv * a.B;
-  return total >= 480 + 30LL * steps ? launch_cfg<D, STEER, 1>(a, st, units, s) : launch_cfg<D, STEER, 4>(a, st, units, s);
+  const long long least = steps <= 4 ? 600 : total <= 1024 ? 480 + (D == 64 ? 60 : 30) * steps
+                                           : steps <= 24 ? 1800 : steps < 56 ? 1800 + 130 * (steps - 24) : 6000;
+  return total >= least ? launch_cfg<D, STEER, 1>(a, st, units, s) : launch_cfg<D, STEER, 4>(a, st, units, s);
 }
 
 }  // namespace
