@@ -266,7 +266,7 @@ size_t seka_decode_workspace_bytes(const seka_shape* sh) {
 }
 
 namespace {
-// Validation shared by the two generation-step entry points; *need = bytes of partial states the launch writes.
+// Validation shared by the two generation-step entry points; *need = bytes of partial states the launch cannot do without.
 seka_status check_decode(const void* q, const void* K, const void* V, void* O, float* lse, const int32_t* seq_lens,
                          const seka_shape* sh, size_t* need) {
   seka_status rc = check_shape(sh, true);
@@ -280,7 +280,7 @@ seka_status check_decode(const void* q, const void* K, const void* V, void* O, f
   const size_t nq = (size_t)sh->B * sh->Hq * sh->D * es;
   const size_t nk = (size_t)sh->B * sh->S * sh->Hkv * sh->D * es;
   if (ranges_overlap(O, nq, q, nq) || ranges_overlap(O, nq, K, nk) || ranges_overlap(O, nq, V, nk)) return SEKA_ERR_ALIAS;
-  *need = seka::decode_partial_bytes(sh->B, sh->S, sh->Hq, sh->Hkv, sh->D, sh->dtype);
+  *need = seka::decode_least_bytes(sh->B, sh->S, sh->Hq, sh->Hkv, sh->D, sh->dtype);
   return SEKA_OK;
 }
 }  // namespace
@@ -296,7 +296,7 @@ seka_status seka_attention_decode(const void* q, const void* K, const void* V, v
   const float scale = sh->softmax_scale > 0.0f ? sh->softmax_scale : 1.0f / std::sqrt((float)sh->D);
   (void)hipGetLastError();
   hipError_t e = seka::launch_decode(q, K, V, O, lse, seq_lens, sh->B, sh->S, sh->Hq, sh->Hkv, sh->D, sh->dtype, scale,
-                                     workspace, reinterpret_cast<hipStream_t>(hip_stream));
+                                     workspace, workspace_bytes, reinterpret_cast<hipStream_t>(hip_stream));
   return launch_status(e);
 }
 
@@ -312,7 +312,7 @@ seka_status seka_attention_decode_static(const void* q, const void* K, const voi
   if (e != hipSuccess) return launch_status(e);
   const float scale = sh->softmax_scale > 0.0f ? sh->softmax_scale : 1.0f / std::sqrt((float)sh->D);
   e = seka::launch_decode(q, K, V, O, lse, seq_lens, sh->B, sh->S, sh->Hq, sh->Hkv, sh->D, sh->dtype, scale, scratch_ptr,
-                          reinterpret_cast<hipStream_t>(hip_stream));
+                          seka::kDecodeStaticScratchBytes, reinterpret_cast<hipStream_t>(hip_stream));
   return launch_status(e);
 }
 

@@ -59,12 +59,12 @@ hipError_t launch_route(const void* Q, int B, int S, int Hq, int Hkv, int D, int
                         int window = 0);
 
 size_t decode_workspace_bytes(int B, int S, int Hq, int Hkv, int D, int dtype);   // what a caller is asked for
-size_t decode_partial_bytes(int B, int S, int Hq, int Hkv, int D, int dtype);     // what a launch of this size writes
+size_t decode_least_bytes(int B, int S, int Hq, int Hkv, int D, int dtype);       // what a launch of this size cannot do without
 constexpr size_t kDecodeStaticScratchBytes = (size_t)SEKA_DECODE_STATIC_MAX_BYTES;   // the library-owned buffer
 // Device address of the library-owned partial-state buffer on the current device (resolved once per device).
 hipError_t decode_static_scratch(void** out);
 hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, float* lse, const int* lens, int B, int S,
-                         int Hq, int Hkv, int D, int dtype, float scale, void* workspace, hipStream_t s);
+                         int Hq, int Hkv, int D, int dtype, float scale, void* workspace, size_t workspace_bytes, hipStream_t s);
 
 size_t learn_workspace_bytes(int Hkv, int D, int n);
 hipError_t launch_learn(const void* hn, const void* hs, int n, int Hkv, int D, int dtype, float gamma, float* U_out,

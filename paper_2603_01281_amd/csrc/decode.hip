@@ -564,7 +564,7 @@ static int decode_heads_per_wg(int G, int dtype) {
 // (128 at D = 64) where there are workgroups to spare (B=3 S=1408 28 / 4 heads 69 -> 15 us, B=1 S=4864 32 / 4 63 -> 19, B=8 S=700 32 / 8
 // 40 -> 13; nothing changes where the groups alone are enough).  Not more than the library's own buffer holds, unless
 // the 512-token ranges need that much.
-static int decode_splits_of(int B, int S, int Hq, int Hkv, int D, int dtype) {
+static int decode_least_splits(int B, int S, int Hq, int Hkv, int D, int dtype) {
   const int G = Hq / Hkv, groups = B * Hkv * (G / decode_heads_per_wg(G, dtype));
   const int splits = decode_splits(groups, S, kDecMinRows);
   if (dtype == SEKA_BF16) return splits;
@@ -572,23 +572,41 @@ static int decode_splits_of(int B, int S, int Hq, int Hkv, int D, int dtype) {
   return std::max(splits, (int)std::min((size_t)decode_splits(groups, S, kDecMinElemsF32 / D), fit));
 }
 
-size_t decode_partial_bytes(int B, int S, int Hq, int Hkv, int D, int dtype) {
-  return (size_t)B * Hq * decode_splits_of(B, S, Hq, Hkv, D, dtype) * (D + 2) * sizeof(float);
+static size_t decode_state_bytes(int B, int Hq, int D, int splits) { return (size_t)B * Hq * splits * (D + 2) * sizeof(float); }
+
+// bf16 caches of few groups at D = 128: as many ranges as give every compute unit a workgroup, down to 64 tokens each (a chain
+// of 512 tokens is 8 us by itself).  us, 512-token ranges / these: 32 / 8 heads B=1 S=1000 10.6 / 7.9, S=2500 14.1 / 9.7,
+// S=10000 16.8 / 15.3; B=3 S=1500 16.0 / 11.0; B=10 S=1000 16.9 / 14.5; 8 / 2 heads B=10 S=1500 15.3 / 9.7; 32 / 32 B=1
+// S=1000 15.5 / 9.1.  Not for a second range alone (28 / 4 heads B=30 S=1000 17.9 / 18.6), nor up to about 700 tokens (S=600
+// 7.9 in one range, 8.5 in nine), nor at D = 64, where a token is half the work (B=1 S=1000 7.1 / 8.8, B=1 S=3000 8 / 2
+// heads 8.7 / 9.2).  A workspace that was sized for the longer ranges gets those.
+constexpr int kDecOneRange = 700, kDecFineRows = 64, kDecFineWG = 256;
+static int decode_splits_of(int B, int S, int Hq, int Hkv, int D, int dtype, size_t workspace_bytes) {
+  const int least = decode_least_splits(B, S, Hq, Hkv, D, dtype);
+  if (dtype != SEKA_BF16 || D != 128 || S <= kDecOneRange) return least;
+  const int groups = B * Hkv * (Hq / Hkv / decode_heads_per_wg(Hq / Hkv, dtype));
+  const int fine = std::min({S / kDecFineRows, kDecFineWG / groups, kDecMaxSplits});
+  return fine > std::max(least, 2) && decode_state_bytes(B, Hq, D, fine) <= workspace_bytes ? fine : least;
+}
+
+size_t decode_least_bytes(int B, int S, int Hq, int Hkv, int D, int dtype) {
+  return decode_state_bytes(B, Hq, D, decode_least_splits(B, S, Hq, Hkv, D, dtype));
 }
 
 // A workspace that serves any smaller batch and any shorter cache too.  Fewer prompts may be cut into so many more ranges that
 // they need more than B do (fp32, 32 / 8 heads, D = 128, S = 1408: 22 prompts more than 23), hence the largest
 // need up to B; beyond kDecTargetWG prompts it only grows with B.  The need never falls with S.
 size_t decode_workspace_bytes(int B, int S, int Hq, int Hkv, int D, int dtype) {
-  size_t most = decode_partial_bytes(B, S, Hq, Hkv, D, dtype);
-  for (int b = std::min(B - 1, kDecTargetWG); b > 0; --b) most = std::max(most, decode_partial_bytes(b, S, Hq, Hkv, D, dtype));
+  auto need = [=](int b) { return decode_state_bytes(b, Hq, D, decode_splits_of(b, S, Hq, Hkv, D, dtype, SIZE_MAX)); };
+  size_t most = need(B);
+  for (int b = std::min(B - 1, kDecTargetWG); b > 0; --b) most = std::max(most, need(b));
   return most;
 }
 
 hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, float* lse, const int* lens, int B, int S,
-                         int Hq, int Hkv, int D, int dtype, float scale, void* workspace, hipStream_t s) {
+                         int Hq, int Hkv, int D, int dtype, float scale, void* workspace, size_t workspace_bytes, hipStream_t s) {
   const int G = Hq / Hkv, hp = decode_heads_per_wg(G, dtype);
-  const int splits = decode_splits_of(B, S, Hq, Hkv, D, dtype);
+  const int splits = decode_splits_of(B, S, Hq, Hkv, D, dtype, workspace_bytes);
   float* part = static_cast<float*>(workspace);
   if (dtype == SEKA_BF16) {
     const float c2 = scale * 1.4426950408889634f;

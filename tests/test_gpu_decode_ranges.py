@@ -13,7 +13,10 @@ pytestmark = pytest.mark.gpu
     ("bf16", 4, 4100, 12, 3, 128, [4100, 1, 0, 513]), ("bf16", 5, 2048, 8, 2, 64, [512, 2048, 0, 1536, 33]),
     ("bf16", 3, 1500, 8, 8, 128, [1500, 750, 749]), ("bf16", 2, 1000, 14, 2, 128, [1000, 129]), ("bf16", 1, 129, 4, 4, 64, None),
     ("f32", 3, 700, 14, 2, 128, [700, 64, 0]), ("f32", 2, 257, 6, 3, 64, [257, 65]), ("f32", 1, 4200, 8, 1, 128, None),
-    ("f32", 2, 127, 4, 4, 128, [127, 63])])
+    ("f32", 2, 127, 4, 4, 128, [127, 63]),
+    # bf16 caches of few groups at D = 128: one range up to 700 tokens, then one per compute unit, at least 64 tokens each
+    ("bf16", 1, 700, 8, 2, 128, None), ("bf16", 1, 701, 8, 2, 128, None), ("bf16", 2, 1000, 32, 8, 128, [1000, 65]),
+    ("bf16", 1, 4133, 6, 1, 128, None), ("bf16", 5, 1030, 14, 2, 128, [1030, 0, 1, 64, 700]), ("bf16", 33, 1100, 8, 8, 128, None)])
 def test_ranges(seka, dtype, B, S, Hq, Hkv, D, lens):
     import torch
     print(f"decode ranges {dtype} B={B} S={S} {Hq}/{Hkv} D={D}", flush=True)
@@ -39,3 +42,26 @@ def test_ranges(seka, dtype, B, S, Hq, Hkv, D, lens):
         H.assert_close_bf16(got_O[live], ref_O, "O")
         H.assert_lse_close_bf16(got_L[live], ref_L, "LSE", path="decode")
     assert np.all(got_O[~live] == 0.0) and np.all(np.isneginf(got_L[~live]))
+
+
+def test_small_workspace(seka):
+    """A workspace that holds the states of fewer, longer ranges than there would be: another order of sums, the same result."""
+    import torch
+    B, S, Hq, Hkv, D = 2, 2100, 8, 2, 128
+    print("decode small workspace", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    q, K, V = (torch.randn(shape, generator=g, device="cuda").bfloat16() for shape in ((B, Hq, D), (B, S, Hkv, D), (B, S, Hkv, D)))
+    most = seka.seka_decode_workspace_bytes(B, S, Hq, Hkv, D, seka.SEKA_BF16)
+    least = B * Hq * (S // 512) * (D + 2) * 4                 # ranges of 512 tokens and more
+    ref, _ = orc.decode_attention(H.to_f64(q), H.to_f64(K), H.to_f64(V), np.full(B, S, np.int32))
+    for nbytes in (most, least):
+        O = torch.full_like(q, float("nan"))
+        ws = torch.full((nbytes + 4096,), 0xa5, dtype=torch.uint8, device="cuda")
+        seka.seka_attention_decode(q, K, V, O, workspace=ws[:nbytes])
+        torch.cuda.synchronize()
+        assert bool((ws[nbytes:] == 0xa5).all())              # nothing behind it is written
+        H.assert_close_bf16(H.to_f64(O), ref, f"O with {nbytes} bytes")
+    assert least < most
+    with pytest.raises(seka.SekaError):
+        seka.seka_attention_decode(q, K, V, O, workspace=ws[:least - 16])
