@@ -1,0 +1,169 @@
+// Query projection in BM x BN tiles: Q[t, n] = sum_e X[t, e] W[n, e], bf16 in, fp32 accumulate, bf16 out, with the routing
+// sums of its outputs (project_wide.h has the sizes that fill the chip with 256 x 256 tiles).
+//
+// WM x WN waves, each TM x TN outputs.  64-wide slices of E travel straight into a ring of NS stages in LDS, NS of them ahead;
+// the operands of a slice are read one slice before its products.  One barrier per slice: behind barrier k slice k + 1 is in
+// LDS (every wave has waited for its own loads of it) and slice k in registers (and for its reads of it), so its stage
+// takes slice k + NS, and the reads of slice k + 1 run beside the products of slice k.
+#pragma once
+#include <type_traits>
+
+#include "project_wide.h"
+
+namespace seka {
+
+template <int BM, int BN, int WM, int WN, int NS, bool ROUTE>
+__global__ __launch_bounds__(64 * WM * WN) void project_route_tile_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
+                                                                          uint16_t* __restrict__ Qout, int E, long long tokens, int N,
+                                                                          int S, int G, int Hkv, float* __restrict__ workspace) {
+  constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, RBS = TM / 32, CBS = TN / 32;
+  constexpr int ROWS = BM + BN, STAGE = ROWS * kWideK * 2;         // a slice: BM rows of X, then BN rows of W, 128 bytes each
+  constexpr int LPW = ROWS / 8 / NW;                               // 1 KB loads per wave and slice
+  static_assert(ROWS / 8 % NW == 0 && TM == 64, "whole loads; a wave's routing sums are those of 64 tokens");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char tile_smem[];
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  // Each XCD takes a contiguous run of tiles, in groups of 8 token tiles x all feature tiles walked by columns.
+  const int nM = (int)((tokens + BM - 1) / BM), nN = (N + BN - 1) / BN;
+  const int tiles = nM * nN, per = (tiles + 7) / 8;
+  const int t = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || t >= tiles) return;         // workgroup-uniform, before any barrier
+  const int group = t / (8 * nN), in = t % (8 * nN), gm = min(8, nM - 8 * group);
+  const int mt = 8 * group + in % gm, nt = in / gm;
+  const size_t row0 = (size_t)mt * BM;
+  const int col0 = nt * BN;
+
+  // Load n of a wave: rows 8 (wave + NW n) .. + 7 of the stage, lane l chunk l % 8 of row l / 8; the 16-byte chunks of a row are
+  // swizzled (chunk ^ (row / 2) % 8) for conflict-free operand reads.  Rows past the tensors' ends repeat the last one.
+  const size_t rowbytes = (size_t)E * 2;
+  uint32_t off[LPW];
+  const int last_row = (int)min((long long)BM, tokens - (long long)row0) - 1, last_col = min(BN, N - col0) - 1;
+#pragma unroll
+  for (int n = 0; n < LPW; ++n) {
+    const int r = 8 * (wave + NW * n) + (lane >> 3);
+    const uint32_t chunk = 16u * ((lane & 7) ^ ((r >> 1) & 7));
+    off[n] = (uint32_t)(r < BM ? min(r, last_row) : min(r - BM, last_col)) * (uint32_t)rowbytes + chunk;
+  }
+  const unsigned char* Xb = reinterpret_cast<const unsigned char*>(X) + row0 * rowbytes;
+  const unsigned char* Wb = reinterpret_cast<const unsigned char*>(W) + (size_t)col0 * rowbytes;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(dma_lds_void_ptr)tile_smem;
+  const int nk = E / kWideK;
+  auto issue = [&](int k, int stage) __attribute__((always_inline)) {      // past the end: a slice nobody uses
+    const size_t at = (size_t)min(k, nk - 1) * (kWideK * 2);
+#pragma unroll
+    for (int n = 0; n < LPW; ++n)          // BM / 8 is a multiple of NW or the other way round: wave-uniform either way
+      wide_load_16B((8 * (wave + NW * n) < BM ? Xb : Wb) + at, off[n], lds0 + stage * STAGE + 1024 * (wave + NW * n));
+  };
+
+  typedef __attribute__((address_space(3))) const bf16x8* lds_frag;
+  uint32_t a_addr[4], b_addr[4];           // operand (row l32, elements 16 kk + 8 hf .. + 7) of the wave's rows in stage 0
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const uint32_t in_row = 16u * ((2 * kk + hf) ^ ((l32 >> 1) & 7));
+    a_addr[kk] = lds0 + (TM * wm + l32) * 128 + in_row;
+    b_addr[kk] = lds0 + (BM + TN * wn + l32) * 128 + in_row;
+  }
+  f32x16 acc[RBS][CBS];
+#pragma unroll
+  for (int i = 0; i < RBS; ++i)
+#pragma unroll
+    for (int j = 0; j < CBS; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  struct Operands { bf16x8 a[RBS][4], b[CBS][4]; };
+  Operands even, odd;
+  auto read = [&](Operands& f, int stage) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+#pragma unroll
+      for (int i = 0; i < RBS; ++i) f.a[i][kk] = *(lds_frag)(uintptr_t)(a_addr[kk] + stage * STAGE + 4096 * i);
+#pragma unroll
+      for (int j = 0; j < CBS; ++j) f.b[j][kk] = *(lds_frag)(uintptr_t)(b_addr[kk] + stage * STAGE + 4096 * j);
+    }
+  };
+  auto slice = [&](auto turn_c, int k) __attribute__((always_inline)) {      // turn_c: k modulo the unrolled turns
+    constexpr int TURN = decltype(turn_c)::value;
+    Operands &now = TURN % 2 ? odd : even, &next = TURN % 2 ? even : odd;
+    dma_wait_vmcnt<(NS - 2) * LPW>();
+    dma_barrier();
+    issue(k + NS, TURN % NS);
+    read(next, (TURN + 1) % NS);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int i = 0; i < RBS; ++i)
+#pragma unroll
+        for (int j = 0; j < CBS; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(now.a[i][kk], now.b[j][kk], acc[i][j], 0, 0, 0);
+  };
+#pragma unroll
+  for (int k = 0; k < NS; ++k) issue(k, k);
+  dma_wait_vmcnt<(NS - 1) * LPW>();
+  asm volatile("s_barrier" ::: "memory");
+  read(even, 0);
+  constexpr int TURNS = NS % 2 ? 2 * NS : NS;
+  int k = 0;
+  auto turns = [&](auto n_c) __attribute__((always_inline)) {
+    constexpr int LEFT = decltype(n_c)::value;                     // the first LEFT slices of a round of turns, as far as there are any
+    auto one = [&](auto i_c) __attribute__((always_inline)) {
+      constexpr int I = decltype(i_c)::value;
+      if constexpr (I < LEFT)
+        if (LEFT == TURNS || k + I < nk) slice(i_c, k + I);
+    };
+    one(std::integral_constant<int, 0>{});
+    one(std::integral_constant<int, 1>{});
+    one(std::integral_constant<int, 2>{});
+    one(std::integral_constant<int, 3>{});
+    one(std::integral_constant<int, 4>{});
+    one(std::integral_constant<int, 5>{});
+  };
+#pragma nounroll
+  for (; k + TURNS <= nk; k += TURNS) turns(std::integral_constant<int, TURNS>{});
+  turns(std::integral_constant<int, TURNS - 1>{});
+  dma_wait_vmcnt<0>();                     // the last requests still write to the ring
+  dma_barrier();
+
+  // ---- epilogue: round, sum for the routing, stage TM tokens x TN features per wave, store whole lines ----
+  typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+  constexpr int LINE = TN * 2, LC = LINE / 16;                     // bytes and 16-byte chunks of a staged row
+  unsigned char* const stage = tile_smem + TM * LINE * wave;       // chunks swizzled with the token
+  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+  const uint32_t sel = (l32 & 1) ? 0x03020706u : 0x05040100u;      // bytes of {neighbour, own}: see below
+  if (TM * wm > last_row || TN * wn > last_col) return;            // wave-uniform; no barrier follows
+#pragma unroll
+  for (int j = 0; j < CBS; ++j) {
+    float colsum = 0.f;
+#pragma unroll
+    for (int rb = 0; rb < RBS; ++rb)
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) {
+        // tokens m, m + 1 of feature column l32; an even lane keeps token m of columns l32, l32 + 1, an odd one token
+        // m + 1 of columns l32 - 1, l32
+        const bf16x2 own = {(__bf16)acc[rb][j][r], (__bf16)acc[rb][j][r + 1]};
+        colsum = __builtin_amdgcn_fdot2_f32_bf16(own, ones, colsum, false);
+        const uint32_t mine = __builtin_bit_cast(uint32_t, own);
+        const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+        const uint32_t pair = __builtin_amdgcn_perm(other, mine, sel);
+        const int m = 32 * rb + 8 * (r >> 2) + 4 * hf + (r & 3) + (l32 & 1), byte = 64 * j + 4 * (l32 >> 1);
+        *reinterpret_cast<uint32_t*>(stage + LINE * m + (byte ^ (16 * (m & (LC - 1))))) = pair;
+      }
+    if (ROUTE) {
+      // these 64 tokens lie in one prompt (S is a multiple of 128); feature -> (head, d)
+      const float tot = colsum + __shfl_xor(colsum, 32);
+      const size_t tok = row0 + TM * wm;
+      const int b = (int)(tok / S), tchunk = (int)(tok % S) / 64;
+      const int f = col0 + TN * wn + 32 * j + l32, hq = f / 128, h = hq / G, g = hq % G;
+      const int chunks = (S / 64) * G;
+      if (hf == 0) workspace[(((size_t)b * Hkv + h) * chunks + (size_t)tchunk * G + g) * 128 + f % 128] = tot;
+    }
+  }
+  asm volatile("" ::: "memory");           // a wave's LDS accesses complete in program order
+#pragma unroll
+  for (int it = 0; it < TM * LC / 64; ++it) {
+    const int m = (64 / LC) * it + lane / LC, c = lane % LC;
+    const u32x4 line = *reinterpret_cast<const u32x4*>(stage + LINE * m + ((16 * c) ^ (16 * (m & (LC - 1)))));
+    *reinterpret_cast<u32x4*>(Qout + (row0 + TM * wm + m) * (size_t)N + col0 + TN * wn + 8 * c) = line;
+  }
+}
+
+}  // namespace seka

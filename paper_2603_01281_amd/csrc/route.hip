@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "project_tile.h"
 #include "project_wide.h"
 
 namespace seka {
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(kFinishThreads) void route_finish_kernel(const floa
 // ---- query projection with the routing sums in its epilogue (Sec. 3.3: the routing query is a by-product of the
 // projection that produces Q, so it need not be read back) ----
 //
-// The sizes that project_route_wide_kernel does not take (rule in launch_project_route):
+// E of 2^22 and more, where the lane offsets of the kernels that load straight into LDS would leave 32 bits:
 // Q[t, n] = sum_e X[t, e] W[n, e]  (bf16 in, fp32 accumulate, bf16 out; W is the projection weight with one row per
 // output feature, the layout of a linear layer).  One workgroup = 128 tokens x 128 output features (one head at
 // D = 128), four waves of 64 x 64, v_mfma_f32_32x32x16_bf16; 64-wide slices of E go through two LDS stages, the
@@ -438,31 +439,62 @@ size_t project_route_workspace_bytes(int B, int S, int Hq) {
   return (size_t)B * Hq * (S / 64) * 128 * sizeof(float);
 }
 
+// Which tiles a projection takes: the least estimate of 3 us + (slices of E) x (sum over rounds of 256 workgroups of a slice's
+// time).  A slice costs more the more of the chip is busy (its power, HBM): measured, us at an eighth, half and all of the
+// compute units, 256 x 256 0.95 / 1.1 / 1.6, 256 x 128 0.69 / 0.75 / 0.94, 128 x 128 0.38 / 0.41 / 0.53, 128 x 64
+// 0.27 / 0.29 / 0.32.  us for E = 4096, N = 4096 in that order of tiles (128 x 128 register-staged before): 128 tokens
+// 60 / 46 / 27 / 20 (44), 512 62 / 48 / 29 / 24 (46), 1024 64 / 51 / 37 / 48 (51), 2048 69 / 63 / 72 / 89, 32768 811 with the
+// first; 1536 tokens E = 2880 48 / 40 / 46 / 51, 4096 x 1024 x 5120 82 / 67 / 44 / 57 (66).
+inline int project_tile_of(long long tokens, int N, int E) {
+  constexpr struct { int bm, bn; double alone, crowded; } kinds[4] = {{256, 256, 0.92, 0.66}, {256, 128, 0.68, 0.26}, {128, 128, 0.375, 0.155}, {128, 64, 0.27, 0.05}};
+  int best = 0;
+  double least = 0;
+  for (int i = 0; i < 4; ++i) {
+    const long long tiles = ((tokens + kinds[i].bm - 1) / kinds[i].bm) * ((N + kinds[i].bn - 1) / kinds[i].bn);
+    const long long full = (tiles - 1) / 256;
+    const double last = (double)(tiles - 256 * full) / 256;
+    const double cost = 3 + E / kWideK * (full * (kinds[i].alone + kinds[i].crowded) + kinds[i].alone + kinds[i].crowded * last * last);
+    if (i == 0 || cost < least) {
+      least = cost;
+      best = i;
+    }
+  }
+  return best;
+}
+
 hipError_t launch_project_route(const void* X, const void* W, int E, void* Qout, int B, int S, int Hq, int Hkv,
                                 const float* proto, int M, int mode, float tau, float* w_out, void* workspace,
                                 hipStream_t s) {
   const int N = Hq * 128, G = Hq / Hkv;
   const long long tokens = (long long)B * S;
-  const dim3 grid(N / kProjTile, (unsigned)(tokens / kProjTile));
   float* ws = static_cast<float*>(workspace);
   const uint16_t *x = static_cast<const uint16_t*>(X), *wq = static_cast<const uint16_t*>(W);
   uint16_t* q = static_cast<uint16_t*>(Qout);
-  const long long wide = ((tokens + kWideTile - 1) / kWideTile) * ((N + kWideTile - 1) / kWideTile);
-  // 128 x 128 tiles while there is at most one per compute unit (4 times as many as 256 x 256 ones), us for E = 4096,
-  // N = 4096, 128 / 256: 512 tokens 52 / 69, 1024 55 / 71, 2048 90 / 78, 4096 173 / 119, 32768 1336 / 811; 5120 x
-  // 1024 x 1024 (80 tiles) 33 / 29.  The lane offsets of the wide kernel are 32 bits: E below 2^22.
-  if (wide > 64 && E < (1 << 22)) {
-    auto kernel = w_out ? project_route_wide_kernel<true> : project_route_wide_kernel<false>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       8 * kWideHalf);
+  auto launch = [&](auto kernel, int bm, int bn, int threads, size_t smem) {
+    const long long tiles = ((tokens + bm - 1) / bm) * ((N + bn - 1) / bn);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((wide + 7) / 8 * 8)), dim3(512), 8 * kWideHalf, s, x, wq, q, E, tokens, N, S, G,
-                       Hkv, ws);
-  } else if (w_out != nullptr) {
-    hipLaunchKernelGGL((project_route_kernel<true>), grid, dim3(256), 0, s, x, wq, q, E, N, S, G, Hkv, ws);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(threads), smem, s, x, wq, q, E, tokens, N, S, G, Hkv, ws);
+    return hipSuccess;
+  };
+#define SEKA_PROJ_TILE(BM, BN, WM, WN)                                                                               \
+  launch(w_out ? project_route_tile_kernel<BM, BN, WM, WN, 3, true> : project_route_tile_kernel<BM, BN, WM, WN, 3, false>, BM, BN, \
+         64 * WM * WN, (size_t)3 * (BM + BN) * kWideK * 2)
+  hipError_t e = hipSuccess;
+  if (E >= (1 << 22)) {
+    const dim3 grid(N / kProjTile, (unsigned)(tokens / kProjTile));
+    if (w_out) hipLaunchKernelGGL((project_route_kernel<true>), grid, dim3(256), 0, s, x, wq, q, E, N, S, G, Hkv, ws);
+    else hipLaunchKernelGGL((project_route_kernel<false>), grid, dim3(256), 0, s, x, wq, q, E, N, S, G, Hkv, ws);
   } else {
-    hipLaunchKernelGGL((project_route_kernel<false>), grid, dim3(256), 0, s, x, wq, q, E, N, S, G, Hkv, ws);
+    switch (project_tile_of(tokens, N, E)) {
+      case 0: e = launch(w_out ? project_route_wide_kernel<true> : project_route_wide_kernel<false>, kWideTile, kWideTile, 512, (size_t)8 * kWideHalf); break;
+      case 1: e = SEKA_PROJ_TILE(256, 128, 4, 2); break;
+      case 2: e = SEKA_PROJ_TILE(128, 128, 2, 4); break;
+      default: e = SEKA_PROJ_TILE(128, 64, 2, 2); break;
+    }
   }
+#undef SEKA_PROJ_TILE
+  if (e != hipSuccess) return e;
   if (w_out != nullptr) {
     const float inv_count = 1.0f / ((float)S * (float)G);
     hipLaunchKernelGGL((route_finish_kernel<128>), dim3(B * Hkv), dim3(kFinishThreads), 0, s, ws, (S / 64) * G, inv_count,
