@@ -3,8 +3,8 @@
 // that keeps a fraction gamma of the singular-value mass (Eq. 3), and the head score D_h = mean ||h+ - h-||_2.
 //
 // Not on the inference path; deterministic throughout (every sum has a fixed order).
-//   cov_partial_kernel   Omega in 16-row strips, the token range split into chunks (fp32 accumulation); bf16
-//                        tensors take cov_partial_mfma_kernel (exact products on the matrix cores, one pass).
+//   cov_partial_f32_kernel, cov_partial_mfma_kernel   Omega on the matrix cores, the token range split into chunks (fp32
+//                        products and accumulation; exact products of bf16 values).
 //   cov_reduce_kernel, gram_kernel   Omega from its partial sums, Omega Omega^T in fp64.
 //   tridiag_kernel, eig_kernel   (learn_eig.h) eigenvalues and vectors of the Gram matrix in fp64: singular values and left
 //                        singular vectors of Omega.
@@ -20,7 +20,7 @@ namespace seka {
 namespace {
 
 constexpr int kLearnThreads = 256;
-constexpr int kCovTokens = 32;          // tokens staged per turn
+constexpr int kCovTokens = 16;          // fp32: tokens per turn
 constexpr int kMaxSweeps = 30;
 constexpr float kRotateTol = 2e-6f;     // rotate while |a_p . a_q| > tol |a_p| |a_q| (fp32 dot products of length d)
 constexpr float kZeroSigma = 1e-5f;     // sigma_c <= this share of sigma_1 is rounding noise: its direction is not determined
@@ -30,50 +30,57 @@ __host__ __device__ inline int learn_token_splits(int n) {
   return s < 1 ? 1 : (s > 32 ? 32 : s);
 }
 
-template <typename T> __device__ __forceinline__ float learn_load(const T* p);
-template <> __device__ __forceinline__ float learn_load<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float learn_load<uint16_t>(const uint16_t* p) { return bf16_bits_to_float(*p); }
-
-// grid (D/16, Hkv, splits); part[((split * Hkv + h) * D + i) * D + j] = sum over the split's tokens of hn[t,h,i] hs[t,h,j]
-template <typename T, int D>
-__global__ __launch_bounds__(kLearnThreads) void cov_partial_kernel(const T* __restrict__ hn, const T* __restrict__ hs,
-                                                                    int n, int Hkv, int splits, float* __restrict__ part) {
-  constexpr int RPT = 16 * D / kLearnThreads;        // strip rows per thread (one column each)
-  __shared__ float a_s[kCovTokens][16];
-  __shared__ float b_s[kCovTokens][D];
-  const int i0 = 16 * blockIdx.x, h = blockIdx.y, split = blockIdx.z;
+// Omega's partial sums of fp32 tensors: part[((split * Hkv + h) * D + i) * D + j] = sum over the split's tokens of
+// hn[t,h,i] hs[t,h,j].  grid ((D / 64)^2, Hkv, splits), four waves with a block of 32 x 32 each, on v_mfma_f32_32x32x2_f32: both
+// operands are a row of a block from each of two tokens, 128 bytes in a line, so they go from global memory straight into
+// operand registers (two loads per 64-cycle product), 16 tokens ahead of the products.  Bound by latency for a few hundred
+// samples (n = 717, 12 heads, D = 128: 77 us with vector FMAs and both views staged in LDS, 18 now), by the fp32 matrix
+// rate beyond.
+template <int D>
+__global__ __launch_bounds__(kLearnThreads) void cov_partial_f32_kernel(const float* __restrict__ hn, const float* __restrict__ hs,
+                                                                        int n, int Hkv, int splits, float* __restrict__ part) {
+  constexpr int QUADS = D / 64, STEPS = kCovTokens / 2;
+  const int h = blockIdx.y, split = blockIdx.z;
   const int per = (n + splits - 1) / splits;
   const int t0 = split * per, t1 = min(n, t0 + per);
-  const int j = threadIdx.x % D, rgrp = threadIdx.x / D;
-  float acc[RPT];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int i0 = 64 * (blockIdx.x / QUADS) + 32 * (wave >> 1), j0 = 64 * (blockIdx.x % QUADS) + 32 * (wave & 1);
+  f32x16 acc;
 #pragma unroll
-  for (int r = 0; r < RPT; ++r) acc[r] = 0.f;
-  for (int tb = t0; tb < t1; tb += kCovTokens) {
-    for (int idx = threadIdx.x; idx < kCovTokens * 16; idx += kLearnThreads) {
-      const int tt = idx / 16, ii = idx % 16, t = tb + tt;
-      a_s[tt][ii] = t < t1 ? learn_load(hn + ((size_t)t * Hkv + h) * D + i0 + ii) : 0.f;
-    }
-    for (int idx = threadIdx.x; idx < kCovTokens * D; idx += kLearnThreads) {
-      const int tt = idx / D, jj = idx % D, t = tb + tt;
-      b_s[tt][jj] = t < t1 ? learn_load(hs + ((size_t)t * Hkv + h) * D + jj) : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 4
-    for (int tt = 0; tt < kCovTokens; ++tt) {
-      const float bv = b_s[tt][j];
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  struct Tokens { float a[STEPS], b[STEPS]; };
+  auto fetch = [&](int tb, Tokens& x) __attribute__((always_inline)) {     // past the range: zeros, from a row that exists
 #pragma unroll
-      for (int r = 0; r < RPT; ++r) acc[r] = fmaf(a_s[tt][RPT * rgrp + r], bv, acc[r]);
+    for (int s = 0; s < STEPS; ++s) {
+      const int t = tb + 2 * s + hf;
+      const size_t row = ((size_t)min(t, n - 1) * Hkv + h) * D + l32;
+      const float a = hn[row + i0], b = hs[row + j0];
+      x.a[s] = t < t1 ? a : 0.f;
+      x.b[s] = t < t1 ? b : 0.f;
     }
-    __syncthreads();
+  };
+  auto multiply = [&](const Tokens& x) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[s], x.b[s], acc, 0, 0, 0);
+  };
+  Tokens x0, x1;
+  fetch(t0, x0);
+  for (int tb = t0; tb < t1; tb += 2 * kCovTokens) {
+    fetch(tb + kCovTokens, x1);
+    multiply(x0);
+    fetch(tb + 2 * kCovTokens, x0);
+    multiply(x1);
   }
 #pragma unroll
-  for (int r = 0; r < RPT; ++r)
-    part[(((size_t)split * Hkv + h) * D + i0 + RPT * rgrp + r) * D + j] = acc[r];
+  for (int r = 0; r < 16; ++r) {                 // element r of lane (l32, hf): row 8 (r / 4) + 4 hf + r % 4, column l32
+    const int i = i0 + 8 * (r >> 2) + 4 * hf + (r & 3), j = j0 + l32;
+    part[(((size_t)split * Hkv + h) * D + i) * D + j] = acc[r];
+  }
 }
 
 // The same partial sums for bf16 tensors on the matrix cores.  A product of two bf16 values is exact in fp32, so
 // v_mfma_f32_32x32x16_bf16 with its fp32 accumulation computes what the fp32 kernel above computes (up to the
-// order of the additions) and the kernel becomes a single pass over both views: grid (splits, Hkv), a workgroup
+// order of the additions) and the kernel is a single pass over both views: grid (splits, Hkv), a workgroup
 // stages 64 tokens x D of both views in LDS with 16-byte loads and every wave owns D*D/4096 blocks of 32 x 32 of
 // Omega.  Both MFMA operands run along the token axis, the strided one of the row-major [token][d] tiles, hence
 // the transposing LDS reads (rows padded by 64 bytes: four consecutive rows, of which 16 lanes read 32 bytes each, fall
@@ -626,8 +633,8 @@ hipError_t launch_learn_td(const void* hn, const void* hs, int n, int Hkv, float
     hipLaunchKernelGGL((cov_partial_mfma_kernel<D>), dim3(splits, Hkv), dim3(kLearnThreads), 0, s,
                        static_cast<const uint16_t*>(hn), static_cast<const uint16_t*>(hs), n, Hkv, splits, part);
   else
-    hipLaunchKernelGGL((cov_partial_kernel<T, D>), dim3(D / 16, Hkv, splits), dim3(kLearnThreads), 0, s,
-                       static_cast<const T*>(hn), static_cast<const T*>(hs), n, Hkv, splits, part);
+    hipLaunchKernelGGL((cov_partial_f32_kernel<D>), dim3((D / 64) * (D / 64), Hkv, splits), dim3(kLearnThreads), 0, s,
+                       static_cast<const float*>(hn), static_cast<const float*>(hs), n, Hkv, splits, part);
   const size_t elems = (size_t)Hkv * D * D;
   double* gram = reinterpret_cast<double*>(part + elems);          // over the other splits' slots (learn_workspace_bytes has room)
   hipLaunchKernelGGL(cov_reduce_kernel, dim3((unsigned)((elems / 4 + kLearnThreads - 1) / kLearnThreads)), dim3(kLearnThreads), 0, s,
