@@ -8,7 +8,8 @@
 // 16-byte loads (a row is 16 consecutive lanes for bf16 at D = 128, so one wave instruction fetches whole
 // rows) and scores them against all the query heads of its KV head (the GQA group shares every byte read),
 // keeping one online-softmax state per head with a lazily raised reference exponent: on the matrix cores for
-// bf16 caches (decode_partial_mfma_kernel), on the vector unit for fp32 ones (decode_partial_kernel).  Partial
+// bf16 caches (decode_partial_mfma_kernel) and fp32 ones of larger groups (decode_partial_f32_kernel), on the vector
+// unit for the other fp32 ones (decode_partial_kernel).  Partial
 // states are merged across lanes, waves (LDS) and splits (stage 2, fixed order, so the result does not depend on
 // scheduling).
 #include <algorithm>
@@ -32,10 +33,20 @@ constexpr float kNegBig = -1e30f;
 // split policy (measured on MI355X: more, smaller splits lose to the merge stage; fewer leave CUs idle)
 constexpr int kDecTargetWG = 4096, kDecMinRows = 512, kDecMinElemsF32 = 8192, kDecMaxSplits = 64;
 
-__host__ __device__ inline int decode_heads_per_group(int G) {
+// Query heads that one stage-1 workgroup serves: up to kDecMaxHeads of a KV head's group.
+constexpr int kDecMaxHeads = 16;
+inline int decode_heads_per_wg(int G) {
+  if (G <= kDecMaxHeads) return G;
+  for (int hp = kDecMaxHeads; hp > 1; --hp)
+    if (G % hp == 0) return hp;
+  return 1;
+}
+
+// Heads that count as one workgroup where fp32 ranges are cut: up to 8.
+inline int decode_heads_f32(int G) {
   if (G <= 8) return G;
-  for (int gp = 8; gp > 1; --gp)
-    if (G % gp == 0) return gp;
+  for (int hp = 8; hp > 1; --hp)
+    if (G % hp == 0) return hp;
   return 1;
 }
 
@@ -62,8 +73,9 @@ __device__ __forceinline__ float dec_dot2(uint32_t a, uint32_t b, float c) {
 template <> struct DecElem<float> {
   static constexpr int EPL = 4;
   __device__ static void load(const float* p, float (&out)[4]) {
-    const float4 v = *reinterpret_cast<const float4*>(p);
-    out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = v[i];
   }
   __device__ static void store(float* p, float v) { *p = v; }
 };
@@ -123,15 +135,15 @@ __device__ __forceinline__ void decode_emit(float mm, float ll, float oo, int b,
   }
 }
 
-// partial state of one (prompt, query head, split): D unnormalised outputs, then m (base-2 exponent), then l
-// (fp32 caches: every product on the vector unit, exactness over speed)
-template <typename T, int D, int GP>
-__global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const T* __restrict__ q, const T* __restrict__ K,
-                                                                     const T* __restrict__ V, const int* __restrict__ lens,
+// Partial state of one (prompt, query head, split): D unnormalised outputs, then m (base-2 exponent), then l.
+// Stage 1 for fp32 caches and groups of few heads: every product on the vector unit.
+template <int D, int GP>
+__global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const float* __restrict__ q, const float* __restrict__ K,
+                                                                     const float* __restrict__ V, const int* __restrict__ lens,
                                                                      int S, int Hq, int Hkv, float c2, int splits,
-                                                                     float* __restrict__ part, T* __restrict__ O,
+                                                                     float* __restrict__ part, float* __restrict__ O,
                                                                      float* __restrict__ lse) {
-  constexpr int EPL = DecElem<T>::EPL;
+  constexpr int EPL = DecElem<float>::EPL;
   constexpr int LPR = D / EPL;            // lanes per cached row
   constexpr int KPW = 64 / LPR;           // rows per wave load
   constexpr int UNR = 4;                  // row groups in flight per lane
@@ -152,7 +164,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const T* __
 
   float qv[GP][EPL];
 #pragma unroll
-  for (int g = 0; g < GP; ++g) DecElem<T>::load(q + ((size_t)b * Hq + hq0 + g) * D + c * EPL, qv[g]);
+  for (int g = 0; g < GP; ++g) DecElem<float>::load(q + ((size_t)b * Hq + hq0 + g) * D + c * EPL, qv[g]);
 
   float m[GP], l[GP], o[GP][EPL];
 #pragma unroll
@@ -164,8 +176,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const T* __
   }
 
   const size_t rowstride = (size_t)Hkv * D;
-  const T* Kb = K + ((size_t)b * S * Hkv + h) * D + c * EPL;
-  const T* Vb = V + ((size_t)b * S * Hkv + h) * D + c * EPL;
+  const float* Kb = K + ((size_t)b * S * Hkv + h) * D + c * EPL;
+  const float* Vb = V + ((size_t)b * S * Hkv + h) * D + c * EPL;
   const int step = kDecWaves * KPW;                      // rows per workgroup turn
   for (int turn = k0; turn < k1; turn += UNR * step) {      // workgroup-uniform trip count
     const int base = turn + wave * KPW + kk;
@@ -177,8 +189,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const T* __
         const int row = base + u * step;
         ok[u] = row < k1;
         const size_t r = (size_t)(ok[u] ? row : k1 - 1) * rowstride;
-        DecElem<T>::load(Kb + r, kf[u]);
-        DecElem<T>::load(Vb + r, vf[u]);
+        DecElem<float>::load(Kb + r, kf[u]);
+        DecElem<float>::load(Vb + r, vf[u]);
       }
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
@@ -238,7 +250,154 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const T* __
       ll += sm_ml[w][g][1] * aw;
       oo += sm_o[w][g][d] * aw;
     }
-    decode_emit<T, D>(mm, ll, oo, b, hq0 + g, d, Hq, splits, split, part, O, lse);
+    decode_emit<float, D>(mm, ll, oo, b, hq0 + g, d, Hq, splits, split, part, O, lse);
+  }
+}
+
+// Stage 1 for fp32 caches where decode_on_matrix_cores says so, on v_mfma_f32_16x16x4_f32 (fp32 products and
+// accumulation).  The query heads of a group (HP <= 16 of them, padded to the instruction's 16 columns) take the place that
+// 16 query rows have in the fp32 prefill kernel:
+//   S^T (16 keys x heads)  = K q^T        lane (head l % 16, g = l / 16) gets keys 4 g + i,
+//   O^T (D x heads)       += V^T P^T      for which it has the operand, and ends with d = 64 hh + 16 g + 4 i + db.
+// K and V go from global memory straight into operand registers with 16-byte loads, those of a wave's next 16 keys as soon
+// as its products with these are issued.  On the vector unit every head is a multiplication and an addition per element and
+// lane, and a token cost a workgroup 8.6 ns per head; the matrix cores take a whole group for what two or three heads cost
+// there.  us before / after (nothing cached): 28 / 4 heads, D = 128, B=1 S=100 15.3 / 6.6, S=9078 25.4 / 14.8, B=12 S=3000
+// 51.2 / 37.7 (3.9 TB/s); D = 64, B=1 S=777 13.5 / 8.6; 16 / 1 heads, D = 128, B=40 S=1137 43.6 / 18.4.
+// A score is shared by NCH accumulators and an output by two, so that the error against 64 bits is not above that of the vector
+// unit's sums (1.9e-7 against 2.0e-7 relative at S = 1137; one chain of 128 products per score 4.2e-7).  The registers for that
+// leave 2 waves per SIMD at D = 128 and 3 at D = 64 (4 spill: B=40 S=1137 32 / 8 heads 46.8 us instead of 44.3).
+template <int D>
+__global__ __launch_bounds__(kDecThreads, D == 64 ? 3 : 2) void decode_partial_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ K, const float* __restrict__ V, const int* __restrict__ lens, int S,
+    int Hq, int Hkv, int HP, float c2, int splits, float* __restrict__ part, float* __restrict__ O, float* __restrict__ lse) {
+  constexpr int NCH = 8;
+  constexpr int KI = D / 16, VH = D / 64;        // 16-byte pieces of a K row, of a V row per lane
+  constexpr int BK = 16, OLD = D + 4;            // keys per step; row stride of the merge area
+  __shared__ __attribute__((aligned(16))) float sm_o[kDecWaves][kDecMaxHeads][OLD];
+  __shared__ float sm_ml[kDecWaves][kDecMaxHeads][2];
+
+  const int G = Hq / Hkv, chunks = G / HP;
+  const int b = blockIdx.z, h = blockIdx.y / chunks, hq0 = h * G + (blockIdx.y % chunks) * HP;
+  const int split = decode_split_index(lens, splits);
+  const int n = lens ? min(max(lens[b], 0), S) : S;
+  const int per = (S + splits - 1) / splits;
+  const int k0 = split * per, k1 = min(n, k0 + per);
+  if (k0 >= k1 && splits > 1) return;            // workgroup-uniform; stage 2 knows which ranges are empty
+
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
+  f32x4 qv[KI];
+#pragma unroll
+  for (int i = 0; i < KI; ++i) {
+    qv[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (l16 < HP) qv[i] = *reinterpret_cast<const f32x4*>(q + ((size_t)b * Hq + hq0 + l16) * D + 16 * i + 4 * g);
+  }
+  const size_t rowstride = (size_t)Hkv * D;
+  const float* Kb = K + ((size_t)b * S * Hkv + h) * D + 4 * g;
+  const float* Vb = V + ((size_t)b * S * Hkv + h) * D + 4 * l16;
+  f32x4 kv[KI], vv[4][VH];
+  // rows clamped into the range: loads stay inside the cache
+  auto fetch_k = [&](int kb) __attribute__((always_inline)) {
+    const float* kp = Kb + (size_t)min(kb + l16, k1 - 1) * rowstride;
+#pragma unroll
+    for (int i = 0; i < KI; ++i) kv[i] = *reinterpret_cast<const f32x4*>(kp + 16 * i);
+  };
+  auto fetch_v = [&](int kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* vp = Vb + (size_t)min(kb + 4 * g + i, k1 - 1) * rowstride;
+#pragma unroll
+      for (int hh = 0; hh < VH; ++hh) vv[i][hh] = *reinterpret_cast<const f32x4*>(vp + 64 * hh);
+    }
+  };
+
+  f32x4 o[2][D / 16];                            // keys 4 g + i of even and of odd i
+#pragma unroll
+  for (int x = 0; x < D / 16; ++x) o[0][x] = o[1][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = kNegBig, l = 0.f;                    // l: this lane's keys only, until the end
+  constexpr int TURN = kDecWaves * BK;
+  int kb = k0 + wave * BK;
+  if (kb < k1) {
+    fetch_k(kb);
+    fetch_v(kb);
+  }
+  for (; kb < k1; kb += TURN) {
+    const bool more = kb + TURN < k1;
+    f32x4 acc[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < KI; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        acc[(4 * i + e) % NCH] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[i][e], qv[i][e], acc[(4 * i + e) % NCH], 0, 0, 0);
+    if (more) fetch_k(kb + TURN);
+#pragma unroll
+    for (int half = NCH / 2; half; half /= 2)
+#pragma unroll
+      for (int c = 0; c < half; ++c) acc[c] += acc[c + half];
+    f32x4 t = acc[0] * c2;
+    float bmax = kNegBig;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (kb + 4 * g + i >= k1) t[i] = -INFINITY;
+      bmax = fmaxf(bmax, t[i]);
+    }
+    bmax = fmaxf(bmax, __shfl_xor(bmax, 16));
+    bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+    const bool raise = bmax > m + kDecSlack;     // the same in a head's four lanes
+    if (__any(raise)) {                          // rare after the first steps
+      const float alpha = raise ? __builtin_amdgcn_exp2f(m - bmax) : 1.f;
+      if (raise) m = bmax;
+      l *= alpha;
+#pragma unroll
+      for (int x = 0; x < D / 16; ++x) {
+        o[0][x] *= alpha;
+        o[1][x] *= alpha;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float p = __builtin_amdgcn_exp2f(t[i] - m);
+      l += p;
+#pragma unroll
+      for (int x = 0; x < D / 16; ++x)
+        o[i & 1][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][x / 4][x % 4], p, o[i & 1][x], 0, 0, 0);
+    }
+    if (more) fetch_v(kb + TURN);
+  }
+
+  // ---- merge the waves ----
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+#pragma unroll
+  for (int x = 0; x < D / 16; ++x) o[0][x] += o[1][x];
+  if (l16 < HP) {
+#pragma unroll
+    for (int hh = 0; hh < VH; ++hh)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<f32x4*>(&sm_o[wave][l16][64 * hh + 16 * g + 4 * i]) = 
+            f32x4{o[0][4 * hh][i], o[0][4 * hh + 1][i], o[0][4 * hh + 2][i], o[0][4 * hh + 3][i]};
+    if (g == 0) {
+      sm_ml[wave][l16][0] = m;
+      sm_ml[wave][l16][1] = l;
+    }
+  }
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < HP * D; idx += kDecThreads) {
+    const int hd = idx / D, d = idx % D;
+    float mm = sm_ml[0][hd][0];
+#pragma unroll
+    for (int w = 1; w < kDecWaves; ++w) mm = fmaxf(mm, sm_ml[w][hd][0]);
+    float ll = 0.f, oo = 0.f;
+#pragma unroll
+    for (int w = 0; w < kDecWaves; ++w) {
+      const float aw = __builtin_amdgcn_exp2f(sm_ml[w][hd][0] - mm);
+      ll += sm_ml[w][hd][1] * aw;
+      oo += sm_o[w][hd][d] * aw;
+    }
+    decode_emit<float, D>(mm, ll, oo, b, hq0 + hd, d, Hq, splits, split, part, O, lse);
   }
 }
 
@@ -255,15 +414,6 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const T* __
 // on the current ones.  Waves take the 32-key blocks of the workgroup's range in turn and never synchronise
 // before the final merge.  Probabilities are rounded to bf16 once; that value feeds the row sum and the product.
 typedef __attribute__((address_space(3))) s16x4* dec_lds_s16x4_ptr;
-constexpr int kDecMfmaMaxHeads = 16;
-
-__host__ __device__ inline int decode_heads_per_group_mfma(int G) {
-  if (G <= kDecMfmaMaxHeads) return G;
-  for (int hp = kDecMfmaMaxHeads; hp > 1; --hp)
-    if (G % hp == 0) return hp;
-  return 1;
-}
-
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const uint16_t* __restrict__ q,
                                                                           const uint16_t* __restrict__ K,
@@ -281,9 +431,9 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const u
   constexpr int KS = D / 16, NB = D / 32;
   constexpr int CPR = D / 8, RPI = 64 / CPR, NV = BK / RPI;   // V rows: 16-byte chunks per row, rows per load, loads
   constexpr int kTileBytes = BK * LD * 2;
-  constexpr int kMergeBytes = kDecMfmaMaxHeads * OLD * 4;
+  constexpr int kMergeBytes = kDecMaxHeads * OLD * 4;
   __shared__ __attribute__((aligned(16))) unsigned char smem[NW * (kTileBytes > kMergeBytes ? kTileBytes : kMergeBytes)];
-  __shared__ float sm_ml[NW][kDecMfmaMaxHeads][2];
+  __shared__ float sm_ml[NW][kDecMaxHeads][2];
 
   const int G = Hq / Hkv;
   const int chunks = G / HP;
@@ -409,7 +559,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const u
   // ---- merge the waves: lane (head l32, hf) holds O[head][32 i + 8 (r / 4) + 4 hf + r % 4] ----
   l += __shfl_xor(l, 32);
   __syncthreads();                         // every wave is done with its V tile: the area becomes the merge area
-  float* sm_o = reinterpret_cast<float*>(smem) + (size_t)wave * kDecMfmaMaxHeads * OLD;
+  float* sm_o = reinterpret_cast<float*>(smem) + (size_t)wave * kDecMaxHeads * OLD;
   if (l32 < HP) {
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -434,7 +584,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const u
     for (int w = 0; w < NW; ++w) {
       const float aw = __builtin_amdgcn_exp2f(sm_ml[w][g][0] - mm);
       ll += sm_ml[w][g][1] * aw;
-      oo += sm_all[((size_t)w * kDecMfmaMaxHeads + g) * OLD + d] * aw;
+      oo += sm_all[((size_t)w * kDecMaxHeads + g) * OLD + d] * aw;
     }
     decode_emit<uint16_t, D>(mm, ll, oo, b, hq0 + g, d, Hq, splits, split, part, O, lse);
   }
@@ -507,30 +657,33 @@ void launch_decode_finish(const float* part, const int* lens, int B, int S, int 
   else hipLaunchKernelGGL((decode_finish_kernel<T, D, (kDecMaxSplits + NJ - 1) / NJ>), grid, block, 0, s, part, lens, S, Hq, splits, O, lse);
 }
 
-template <typename T, int D, int GP>
-hipError_t launch_decode_gp(const void* q, const void* K, const void* V, void* O, float* lse, const int* lens, int B,
-                            int S, int Hq, int Hkv, float scale, float* part, int splits, hipStream_t s) {
-  const int chunks = (Hq / Hkv) / GP;
-  const float c2 = scale * 1.4426950408889634f;
-  hipLaunchKernelGGL((decode_partial_kernel<T, D, GP>), dim3(splits, Hkv * chunks, B), dim3(kDecThreads), 0, s,
-                     static_cast<const T*>(q), static_cast<const T*>(K), static_cast<const T*>(V), lens, S, Hq, Hkv, c2,
-                     splits, part, static_cast<T*>(O), lse);
-  if (splits > 1)
-    launch_decode_finish<T, D>(part, lens, B, S, Hq, splits, static_cast<T*>(O), lse, s);
-  return hipGetLastError();
+// Whether an fp32 call goes to the matrix cores.  Groups of five heads and more do; one or two heads are too few for an
+// instruction of 16 (32 / 16 heads, D = 128, B=1 S=9078: vector unit 33.9 us, matrix cores 37.0; D = 64, B=6 S=1137 16.2 /
+// 17.1); three and four do while the call is a chain of loads and products and not yet memory's: up to 64 MB of cache at
+// D = 128, 128 MB at D = 64 (24 / 8 heads, D = 128: B=6 S=1137, 56 MB, 20.2 / 16.6, B=16 S=560, 73 MB, 20.4 / 22.8; 32 / 8
+// heads: B=6 S=1137 22.4 / 16.6, B=100 S=400 69.5 / 72.8; D = 64, B=16 S=560, 37 MB, 14.4 / 12.8, B=100 S=400, 164 MB,
+// 43.1 / 44.4).
+bool decode_on_matrix_cores(int B, int S, int Hkv, int D, int hp) {
+  if (hp <= 2 || hp > 4) return hp > 4;
+  return 2.0 * sizeof(float) * B * S * Hkv * D * D <= 64e6 * 128;
 }
 
-template <typename T, int D>
-hipError_t launch_decode_td(const void* q, const void* K, const void* V, void* O, float* lse, const int* lens, int B,
-                            int S, int Hq, int Hkv, float scale, float* part, int splits, hipStream_t s) {
-  switch (decode_heads_per_group(Hq / Hkv)) {
-#define SEKA_DEC_CASE(GP) \
-    case GP: return launch_decode_gp<T, D, GP>(q, K, V, O, lse, lens, B, S, Hq, Hkv, scale, part, splits, s)
-    SEKA_DEC_CASE(1); SEKA_DEC_CASE(2); SEKA_DEC_CASE(3); SEKA_DEC_CASE(4);
-    SEKA_DEC_CASE(5); SEKA_DEC_CASE(6); SEKA_DEC_CASE(7); SEKA_DEC_CASE(8);
-#undef SEKA_DEC_CASE
-    default: return hipErrorNotSupported;
+template <int D>
+hipError_t launch_decode_f32(const float* q, const float* K, const float* V, float* O, float* lse, const int* lens, int B, int S,
+                             int Hq, int Hkv, float scale, float* part, int splits, hipStream_t s) {
+  const int G = Hq / Hkv, hp = decode_heads_per_wg(G);
+  const float c2 = scale * 1.4426950408889634f;
+  const dim3 grid(splits, Hkv * (G / hp), B);
+  if (decode_on_matrix_cores(B, S, Hkv, D, hp)) {
+    hipLaunchKernelGGL(decode_partial_f32_kernel<D>, grid, dim3(kDecThreads), 0, s, q, K, V, lens, S, Hq, Hkv, hp, c2, splits, part, O,
+                       lse);
+  } else {
+    auto kernel = hp == 1 ? decode_partial_kernel<D, 1> : hp == 2 ? decode_partial_kernel<D, 2>
+                : hp == 3 ? decode_partial_kernel<D, 3> : decode_partial_kernel<D, 4>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kDecThreads), 0, s, q, K, V, lens, S, Hq, Hkv, c2, splits, part, O, lse);
   }
+  if (splits > 1) launch_decode_finish<float, D>(part, lens, B, S, Hq, splits, O, lse, s);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -555,17 +708,11 @@ hipError_t decode_static_scratch(void** out) {
   return hipSuccess;
 }
 
-// query heads that one stage-1 workgroup serves: the bf16 kernel takes up to 16 per KV head, the fp32 one up to 8
-static int decode_heads_per_wg(int G, int dtype) {
-  return dtype == SEKA_BF16 ? decode_heads_per_group_mfma(G) : decode_heads_per_group(G);
-}
-
-// The fp32 kernel multiplies on the vector unit, about 60 ns per token and workgroup at seven heads: ranges of 64 tokens
-// (128 at D = 64) where there are workgroups to spare (B=3 S=1408 28 / 4 heads 69 -> 15 us, B=1 S=4864 32 / 4 63 -> 19, B=8 S=700 32 / 8
-// 40 -> 13; nothing changes where the groups alone are enough).  Not more than the library's own buffer holds, unless
+// fp32: ranges of 64 tokens (128 at D = 64) where there are workgroups to spare; 64 tokens are one turn of the matrix-core
+// kernel's waves.  Nothing changes where the groups alone are enough.  Not more than the library's own buffer holds, unless
 // the 512-token ranges need that much.
 static int decode_least_splits(int B, int S, int Hq, int Hkv, int D, int dtype) {
-  const int G = Hq / Hkv, groups = B * Hkv * (G / decode_heads_per_wg(G, dtype));
+  const int G = Hq / Hkv, groups = B * Hkv * (G / (dtype == SEKA_BF16 ? decode_heads_per_wg(G) : decode_heads_f32(G)));
   const int splits = decode_splits(groups, S, kDecMinRows);
   if (dtype == SEKA_BF16) return splits;
   const size_t fit = kDecodeStaticScratchBytes / ((size_t)B * Hq * (D + 2) * sizeof(float));
@@ -584,7 +731,7 @@ constexpr int kDecOneRange = 700, kDecFineRows = 64, kDecFineWG = 256;
 static int decode_splits_of(int B, int S, int Hq, int Hkv, int D, int dtype, size_t workspace_bytes) {
   const int least = decode_least_splits(B, S, Hq, Hkv, D, dtype);
   if (dtype != SEKA_BF16 || D != 128 || S <= kDecOneRange) return least;
-  const int groups = B * Hkv * (Hq / Hkv / decode_heads_per_wg(Hq / Hkv, dtype));
+  const int groups = B * Hkv * (Hq / Hkv / decode_heads_per_wg(Hq / Hkv));
   const int fine = std::min({S / kDecFineRows, kDecFineWG / groups, kDecMaxSplits});
   return fine > std::max(least, 2) && decode_state_bytes(B, Hq, D, fine) <= workspace_bytes ? fine : least;
 }
@@ -605,8 +752,15 @@ size_t decode_workspace_bytes(int B, int S, int Hq, int Hkv, int D, int dtype) {
 
 hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, float* lse, const int* lens, int B, int S,
                          int Hq, int Hkv, int D, int dtype, float scale, void* workspace, size_t workspace_bytes, hipStream_t s) {
-  const int G = Hq / Hkv, hp = decode_heads_per_wg(G, dtype);
-  const int splits = decode_splits_of(B, S, Hq, Hkv, D, dtype, workspace_bytes);
+  const int G = Hq / Hkv, hp = decode_heads_per_wg(G);
+  int splits = decode_splits_of(B, S, Hq, Hkv, D, dtype, workspace_bytes);
+  if (dtype != SEKA_BF16 && splits > 1 && decode_on_matrix_cores(B, S, Hkv, D, hp)) {
+    // the four waves of that kernel take 64 tokens per turn: whole turns, in fewer ranges (D = 128, S=1137 in 13 ranges of 88
+    // or 9 of 127: 32 / 8 heads B=6 21.9 -> 16.6 us, 28 / 4 B=40 52.2 -> 44.3, 16 / 1 B=40 26.6 -> 18.4)
+    constexpr int kTurn = kDecWaves * 16;
+    const int per = ((S + splits - 1) / splits + kTurn - 1) / kTurn * kTurn;
+    splits = (S + per - 1) / per;
+  }
   float* part = static_cast<float*>(workspace);
   if (dtype == SEKA_BF16) {
     const float c2 = scale * 1.4426950408889634f;
@@ -634,8 +788,9 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
 #undef SEKA_DEC_LAUNCH
     return hipGetLastError();
   }
-  return D == 128 ? launch_decode_td<float, 128>(q, K, V, O, lse, lens, B, S, Hq, Hkv, scale, part, splits, s)
-                  : launch_decode_td<float, 64>(q, K, V, O, lse, lens, B, S, Hq, Hkv, scale, part, splits, s);
+  const float *q32 = static_cast<const float*>(q), *K32 = static_cast<const float*>(K), *V32 = static_cast<const float*>(V);
+  auto launch = D == 128 ? launch_decode_f32<128> : launch_decode_f32<64>;
+  return launch(q32, K32, V32, static_cast<float*>(O), lse, lens, B, S, Hq, Hkv, scale, part, splits, s);
 }
 
 }  // namespace seka
