@@ -59,6 +59,13 @@ inline int decode_splits(int groups, int S, int min_rows) {
   return want < 1 ? 1 : want;
 }
 
+// A 16-byte load of the cache.  NT: without keeping a place for it in the caches (decode_streams).
+template <bool NT, typename V>
+__device__ __forceinline__ V dec_load(const V* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+
 template <typename T> struct DecElem;
 template <> struct DecElem<uint16_t> {
   __device__ static void store(uint16_t* p, float v) {
@@ -72,8 +79,9 @@ __device__ __forceinline__ float dec_dot2(uint32_t a, uint32_t b, float c) {
 
 template <> struct DecElem<float> {
   static constexpr int EPL = 4;
+  template <bool NT = false>
   __device__ static void load(const float* p, float (&out)[4]) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(p);
+    const f32x4 v = dec_load<NT>(reinterpret_cast<const f32x4*>(p));
 #pragma unroll
     for (int i = 0; i < 4; ++i) out[i] = v[i];
   }
@@ -137,7 +145,7 @@ __device__ __forceinline__ void decode_emit(float mm, float ll, float oo, int b,
 
 // Partial state of one (prompt, query head, split): D unnormalised outputs, then m (base-2 exponent), then l.
 // Stage 1 for fp32 caches and groups of few heads: every product on the vector unit.
-template <int D, int GP>
+template <int D, int GP, bool NT>
 __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const float* __restrict__ q, const float* __restrict__ K,
                                                                      const float* __restrict__ V, const int* __restrict__ lens,
                                                                      int S, int Hq, int Hkv, float c2, int splits,
@@ -189,8 +197,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const float
         const int row = base + u * step;
         ok[u] = row < k1;
         const size_t r = (size_t)(ok[u] ? row : k1 - 1) * rowstride;
-        DecElem<float>::load(Kb + r, kf[u]);
-        DecElem<float>::load(Vb + r, vf[u]);
+        DecElem<float>::load<NT>(Kb + r, kf[u]);
+        DecElem<float>::load<NT>(Vb + r, vf[u]);
       }
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
@@ -267,7 +275,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const float
 // A score is shared by NCH accumulators and an output by two, so that the error against 64 bits is not above that of the vector
 // unit's sums (1.9e-7 against 2.0e-7 relative at S = 1137; one chain of 128 products per score 4.2e-7).  The registers for that
 // leave 2 waves per SIMD at D = 128 and 3 at D = 64 (4 spill: B=40 S=1137 32 / 8 heads 46.8 us instead of 44.3).
-template <int D>
+template <int D, bool NT>
 __global__ __launch_bounds__(kDecThreads, D == 64 ? 3 : 2) void decode_partial_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ K, const float* __restrict__ V, const int* __restrict__ lens, int S,
     int Hq, int Hkv, int HP, float c2, int splits, float* __restrict__ part, float* __restrict__ O, float* __restrict__ lse) {
@@ -307,7 +315,7 @@ __global__ __launch_bounds__(kDecThreads, D == 64 ? 3 : 2) void decode_partial_f
     for (int i = 0; i < 4; ++i) {
       const float* vp = Vb + (size_t)min(kb + 4 * g + i, k1 - 1) * rowstride;
 #pragma unroll
-      for (int hh = 0; hh < VH; ++hh) vv[i][hh] = *reinterpret_cast<const f32x4*>(vp + 64 * hh);
+      for (int hh = 0; hh < VH; ++hh) vv[i][hh] = dec_load<NT>(reinterpret_cast<const f32x4*>(vp + 64 * hh));
     }
   };
 
@@ -414,7 +422,7 @@ __global__ __launch_bounds__(kDecThreads, D == 64 ? 3 : 2) void decode_partial_f
 // on the current ones.  Waves take the 32-key blocks of the workgroup's range in turn and never synchronise
 // before the final merge.  Probabilities are rounded to bf16 once; that value feeds the row sum and the product.
 typedef __attribute__((address_space(3))) s16x4* dec_lds_s16x4_ptr;
-template <int D, int NW>
+template <int D, int NW, bool NT>
 __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const uint16_t* __restrict__ q,
                                                                           const uint16_t* __restrict__ K,
                                                                           const uint16_t* __restrict__ V,
@@ -467,8 +475,8 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const u
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const size_t rv = (size_t)min(kb + RPI * i + lane / CPR, k1 - 1) * rowstride + 8 * (lane % CPR);
-      kr[i] = *reinterpret_cast<const u32x4*>(Kb + rv);
-      vr[i] = *reinterpret_cast<const u32x4*>(Vb + rv);
+      kr[i] = dec_load<NT>(reinterpret_cast<const u32x4*>(Kb + rv));
+      vr[i] = dec_load<NT>(reinterpret_cast<const u32x4*>(Vb + rv));
     }
   };
   // transposing read of a V^T fragment (32 values of d x 16 keys): lanes address key 4 hf + li / 4 (+ 8) of the
@@ -668,18 +676,30 @@ bool decode_on_matrix_cores(int B, int S, int Hkv, int D, int hp) {
   return 2.0 * sizeof(float) * B * S * Hkv * D * D <= 64e6 * 128;
 }
 
-template <int D>
+// Whether a call reads past the caches: each byte once, and so many of them that the next call over the same cache would find
+// little of them in the 256 MB of the memory-side cache either.  The line is at 300 MB, with the call repeated on one cache: up
+// to 290 MB plain loads are the better by up to 10 %, from 310 MB on nontemporal ones, by 1 to 14 %.  us, plain / nontemporal,
+// D = 128: bf16 32 / 8 heads B=16, 290 MB, 49.8 / 50.7, 310 MB 55.2 / 54.0; 32 / 32 heads B=6 S=9078, 892 MB, 154.4 / 137.6
+// (6.5 TB/s); fp32 28 / 4 heads B=4 S=32000, 524 MB, 104.5 / 81.9; 32 / 16 heads B=40 S=1137, 745 MB, 136.6 / 123.0.
+// The lengths of a ragged batch are on the device: a quarter of the allocation is taken for them (lengths spread over 1 : 16
+// by ratio fill a third).
+bool decode_streams(int B, int S, int Hkv, int D, int dtype, bool ragged, int chunks) {
+  const double bytes = 2.0 * (dtype == SEKA_BF16 ? 2 : 4) * B * S * Hkv * D;
+  return chunks == 1 && bytes * (ragged ? 0.25 : 1.0) > 300e6;
+}
+
+template <int D, bool NT>
 hipError_t launch_decode_f32(const float* q, const float* K, const float* V, float* O, float* lse, const int* lens, int B, int S,
                              int Hq, int Hkv, float scale, float* part, int splits, hipStream_t s) {
   const int G = Hq / Hkv, hp = decode_heads_per_wg(G);
   const float c2 = scale * 1.4426950408889634f;
   const dim3 grid(splits, Hkv * (G / hp), B);
   if (decode_on_matrix_cores(B, S, Hkv, D, hp)) {
-    hipLaunchKernelGGL(decode_partial_f32_kernel<D>, grid, dim3(kDecThreads), 0, s, q, K, V, lens, S, Hq, Hkv, hp, c2, splits, part, O,
+    hipLaunchKernelGGL((decode_partial_f32_kernel<D, NT>), grid, dim3(kDecThreads), 0, s, q, K, V, lens, S, Hq, Hkv, hp, c2, splits, part, O,
                        lse);
   } else {
-    auto kernel = hp == 1 ? decode_partial_kernel<D, 1> : hp == 2 ? decode_partial_kernel<D, 2>
-                : hp == 3 ? decode_partial_kernel<D, 3> : decode_partial_kernel<D, 4>;
+    auto kernel = hp == 1 ? decode_partial_kernel<D, 1, NT> : hp == 2 ? decode_partial_kernel<D, 2, NT>
+                : hp == 3 ? decode_partial_kernel<D, 3, NT> : decode_partial_kernel<D, 4, NT>;
     hipLaunchKernelGGL(kernel, grid, dim3(kDecThreads), 0, s, q, K, V, lens, S, Hq, Hkv, c2, splits, part, O, lse);
   }
   if (splits > 1) launch_decode_finish<float, D>(part, lens, B, S, Hq, splits, O, lse, s);
@@ -762,34 +782,36 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
     splits = (S + per - 1) / per;
   }
   float* part = static_cast<float*>(workspace);
+  const bool streams = decode_streams(B, S, Hkv, D, dtype, lens != nullptr, G / hp);
   if (dtype == SEKA_BF16) {
     const float c2 = scale * 1.4426950408889634f;
     const dim3 grid(splits, Hkv * (G / hp), B);
     const uint16_t *q16 = static_cast<const uint16_t*>(q), *K16 = static_cast<const uint16_t*>(K), *V16 = static_cast<const uint16_t*>(V);
     uint16_t* O16 = static_cast<uint16_t*>(O);
-#define SEKA_DEC_LAUNCH(DD, NW)                                                                                              \
-    hipLaunchKernelGGL((decode_partial_mfma_kernel<DD, NW>), grid, dim3(64 * NW), 0, s, q16, K16, V16, lens, S, Hq, Hkv, hp, \
+#define SEKA_DEC_LAUNCH(DD, NW, NT)                                                                                              \
+    hipLaunchKernelGGL((decode_partial_mfma_kernel<DD, NW, NT>), grid, dim3(64 * NW), 0, s, q16, K16, V16, lens, S, Hq, Hkv, hp, \
                        c2, splits, part, O16, lse)
     if (splits > 1) {
       if (D == 128) {
-        SEKA_DEC_LAUNCH(128, 4);
+        if (streams) SEKA_DEC_LAUNCH(128, 4, true); else SEKA_DEC_LAUNCH(128, 4, false);
         launch_decode_finish<uint16_t, 128>(part, lens, B, S, Hq, splits, O16, lse, s);
       } else {
-        SEKA_DEC_LAUNCH(64, 4);
+        if (streams) SEKA_DEC_LAUNCH(64, 4, true); else SEKA_DEC_LAUNCH(64, 4, false);
         launch_decode_finish<uint16_t, 64>(part, lens, B, S, Hq, splits, O16, lse, s);
       }
     } else if (S > 128 && (long long)B * Hkv * (G / hp) <= 256) {
       // A short cache is one workgroup's chain of blocks, half as long with twice the waves: 12.0 -> 10.3 us at S = 1000,
       // 32 / 8 heads.  Only one such workgroup fits a compute unit (LDS): at 512 workgroups 17.5 us became 20.1.
-      if (D == 128) SEKA_DEC_LAUNCH(128, 8); else SEKA_DEC_LAUNCH(64, 8);
+      if (D == 128) SEKA_DEC_LAUNCH(128, 8, false); else SEKA_DEC_LAUNCH(64, 8, false);
     } else {
-      if (D == 128) SEKA_DEC_LAUNCH(128, 4); else SEKA_DEC_LAUNCH(64, 4);
+      if (D == 128) SEKA_DEC_LAUNCH(128, 4, false); else SEKA_DEC_LAUNCH(64, 4, false);
     }
 #undef SEKA_DEC_LAUNCH
     return hipGetLastError();
   }
   const float *q32 = static_cast<const float*>(q), *K32 = static_cast<const float*>(K), *V32 = static_cast<const float*>(V);
-  auto launch = D == 128 ? launch_decode_f32<128> : launch_decode_f32<64>;
+  auto launch = D == 128 ? (streams ? launch_decode_f32<128, true> : launch_decode_f32<128, false>)
+                         : (streams ? launch_decode_f32<64, true> : launch_decode_f32<64, false>);
   return launch(q32, K32, V32, static_cast<float*>(O), lse, lens, B, S, Hq, Hkv, scale, part, splits, s);
 }
 
