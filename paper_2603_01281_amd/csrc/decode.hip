@@ -756,6 +756,16 @@ static int decode_splits_of(int B, int S, int Hq, int Hkv, int D, int dtype, siz
   return fine > std::max(least, 2) && decode_state_bytes(B, Hq, D, fine) <= workspace_bytes ? fine : least;
 }
 
+// bf16 caches whose groups alone give more than half of the compute units a workgroup of eight waves, and none two: one range
+// up to S = 1535, and up to 2047 from 192 groups on.  Two or three ranges are workgroups of four waves, of which some compute
+// units get two and others one.  us, ranges / one, 32 / 8 heads: D = 128 S=1100 160 groups 26.0 / 20.7, 256 groups 32.0 / 27.6;
+// S=2000 192 groups 43.8 / 38.8, 256 56.4 / 47.8; D = 64 S=1300 160 groups 20.5 / 15.6; ragged B=32 S=1100 20.2 / 15.0.  Not at 128
+// groups (S=1300 21.7 / 21.7, S=2000 30.3 / 31.1) nor longer (192 groups S=3500 60.1 / 64.9), nor for a few prompts of their own
+// lengths, where the longest is all (B=6 32 / 32 heads S=2000 25.3 / 28.2).
+static bool decode_one_range(int B, int S, int groups, bool ragged) {
+  return groups <= 256 && (groups >= 192 ? S < 2048 : groups > 128 && S < 1536) && (!ragged || B >= 8);
+}
+
 size_t decode_least_bytes(int B, int S, int Hq, int Hkv, int D, int dtype) {
   return decode_state_bytes(B, Hq, D, decode_least_splits(B, S, Hq, Hkv, D, dtype));
 }
@@ -774,6 +784,8 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
                          int Hq, int Hkv, int D, int dtype, float scale, void* workspace, size_t workspace_bytes, hipStream_t s) {
   const int G = Hq / Hkv, hp = decode_heads_per_wg(G);
   int splits = decode_splits_of(B, S, Hq, Hkv, D, dtype, workspace_bytes);
+  const int groups = B * Hkv * (G / hp);
+  if (dtype == SEKA_BF16 && splits > 1 && decode_one_range(B, S, groups, lens != nullptr)) splits = 1;
   if (dtype != SEKA_BF16 && splits > 1 && decode_on_matrix_cores(B, S, Hkv, D, hp)) {
     // the four waves of that kernel take 64 tokens per turn: whole turns, in fewer ranges (D = 128, S=1137 in 13 ranges of 88
     // or 9 of 127: 32 / 8 heads B=6 21.9 -> 16.6 us, 28 / 4 B=40 52.2 -> 44.3, 16 / 1 B=40 26.6 -> 18.4)
@@ -799,7 +811,7 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
         if (streams) SEKA_DEC_LAUNCH(64, 4, true); else SEKA_DEC_LAUNCH(64, 4, false);
         launch_decode_finish<uint16_t, 64>(part, lens, B, S, Hq, splits, O16, lse, s);
       }
-    } else if (S > 128 && (long long)B * Hkv * (G / hp) <= 256) {
+    } else if (S > 128 && groups <= 256) {
       // A short cache is one workgroup's chain of blocks, half as long with twice the waves: 12.0 -> 10.3 us at S = 1000,
       // 32 / 8 heads.  Only one such workgroup fits a compute unit (LDS): at 512 workgroups 17.5 us became 20.1.
       if (D == 128) SEKA_DEC_LAUNCH(128, 8, false); else SEKA_DEC_LAUNCH(64, 8, false);

@@ -20,7 +20,9 @@ pytestmark = pytest.mark.gpu
     ("f32", 3, 4000, 7, 1, 128, [129, 4000, 3937]), ("f32", 16, 500, 32, 8, 128, None),
     # bf16 caches of few groups at D = 128: one range up to 700 tokens, then one per compute unit, at least 64 tokens each
     ("bf16", 1, 700, 8, 2, 128, None), ("bf16", 1, 701, 8, 2, 128, None), ("bf16", 2, 1000, 32, 8, 128, [1000, 65]),
-    ("bf16", 1, 4133, 6, 1, 128, None), ("bf16", 5, 1030, 14, 2, 128, [1030, 0, 1, 64, 700]), ("bf16", 33, 1100, 8, 8, 128, None)])
+    ("bf16", 1, 4133, 6, 1, 128, None), ("bf16", 5, 1030, 14, 2, 128, [1030, 0, 1, 64, 700]), ("bf16", 33, 1100, 8, 8, 128, None),
+    # one range of eight waves for 129 to 256 groups
+    ("bf16", 17, 1535, 8, 8, 64, None), ("bf16", 17, 1536, 8, 8, 64, None), ("bf16", 8, 2047, 24, 24, 64, [2047, 0, 1, 33, 512, 1024, 257, 700])])
 def test_ranges(seka, dtype, B, S, Hq, Hkv, D, lens):
     import torch
     print(f"decode ranges {dtype} B={B} S={S} {Hq}/{Hkv} D={D}", flush=True)
