@@ -88,6 +88,27 @@ template <> struct DecElem<float> {
   __device__ static void store(float* p, float v) { *p = v; }
 };
 
+// Maximum and sum over the lanes with the same index in a half (HALVES = 2) or a row of 16 (4); the same bits in all of them.
+// Lane swaps on the vector unit: a shuffle through LDS is some 120 cycles in a chain that every step of a range waits for
+// (us, shuffles / swaps: bf16 32 / 8 heads D = 128 B=1 S=1000 9.0 / 8.5, D = 64 7.3 / 7.0; fp32 D = 64 S=600 8.8 / 8.4).
+template <int PARTS, typename F>
+__device__ __forceinline__ float across(float v, F join) {
+  if (PARTS == 4) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = join(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  }
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return join(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+template <int PARTS>
+__device__ __forceinline__ float across_max(float v) {
+  return across<PARTS>(v, [](float x, float y) __attribute__((always_inline)) { return fmaxf(x, y); });
+}
+template <int PARTS>
+__device__ __forceinline__ float across_sum(float v) {
+  return across<PARTS>(v, [](float x, float y) __attribute__((always_inline)) { return x + y; });
+}
+
 // Sum over the LPR consecutive lanes that hold one row; every one of them receives the total.
 template <int LPR>
 __device__ __forceinline__ float row_sum(float v) {
@@ -274,7 +295,8 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial_kernel(const float
 // 51.2 / 37.7 (3.9 TB/s); D = 64, B=1 S=777 13.5 / 8.6; 16 / 1 heads, D = 128, B=40 S=1137 43.6 / 18.4.
 // A score is shared by NCH accumulators and an output by two, so that the error against 64 bits is not above that of the vector
 // unit's sums (1.9e-7 against 2.0e-7 relative at S = 1137; one chain of 128 products per score 4.2e-7).  The registers for that
-// leave 2 waves per SIMD at D = 128 and 3 at D = 64 (4 spill: B=40 S=1137 32 / 8 heads 46.8 us instead of 44.3).
+// leave 2 waves per SIMD at D = 128 and 4 at D = 64 (where holding the compiler to 4 made it spill: B=40 S=1137 32 / 8 heads
+// 46.8 us instead of 44.3).
 template <int D, bool NT>
 __global__ __launch_bounds__(kDecThreads, D == 64 ? 3 : 2) void decode_partial_f32_kernel(
     const float* __restrict__ q, const float* __restrict__ K, const float* __restrict__ V, const int* __restrict__ lens, int S,
@@ -351,8 +373,7 @@ __global__ __launch_bounds__(kDecThreads, D == 64 ? 3 : 2) void decode_partial_f
       if (kb + 4 * g + i >= k1) t[i] = -INFINITY;
       bmax = fmaxf(bmax, t[i]);
     }
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 16));
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+    bmax = across_max<4>(bmax);
     const bool raise = bmax > m + kDecSlack;     // the same in a head's four lanes
     if (__any(raise)) {                          // rare after the first steps
       const float alpha = raise ? __builtin_amdgcn_exp2f(m - bmax) : 1.f;
@@ -376,8 +397,7 @@ __global__ __launch_bounds__(kDecThreads, D == 64 ? 3 : 2) void decode_partial_f
   }
 
   // ---- merge the waves ----
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
+  l = across_sum<4>(l);
 #pragma unroll
   for (int x = 0; x < D / 16; ++x) o[0][x] += o[1][x];
   if (l16 < HP) {
@@ -535,7 +555,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const u
     float bmax = t[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) bmax = fmaxf(bmax, t[r]);
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+    bmax = across_max<2>(bmax);
     const bool raise = bmax > m + kDecSlack;
     if (__any(raise)) {                    // rare after the first blocks
       const float alpha = raise ? __builtin_amdgcn_exp2f(m - bmax) : 1.f;
@@ -565,7 +585,7 @@ __global__ __launch_bounds__(64 * NW, 2) void decode_partial_mfma_kernel(const u
   }
 
   // ---- merge the waves: lane (head l32, hf) holds O[head][32 i + 8 (r / 4) + 4 hf + r % 4] ----
-  l += __shfl_xor(l, 32);
+  l = across_sum<2>(l);
   __syncthreads();                         // every wave is done with its V tile: the area becomes the merge area
   float* sm_o = reinterpret_cast<float*>(smem) + (size_t)wave * kDecMaxHeads * OLD;
   if (l32 < HP) {
