@@ -292,7 +292,7 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
       const double top = work[W::kLambda + D - 1], me = work[W::kLambda + D - 1 - tid];
       const double next = tid < D - 1 ? work[W::kLambda + D - 2 - tid] : -top;
       const bool kept = me > (double)kZeroSigma * kZeroSigma * top;
-      alike = kept && (me - next < fmax(1e-13 * top, 1e-7 * me) || reinterpret_cast<const int*>(work + W::kBad)[D - 1 - tid] != 0);
+      alike = !is_finite(me) || (kept && (me - next < fmax(1e-13 * top, 1e-7 * me) || reinterpret_cast<const int*>(work + W::kBad)[D - 1 - tid] != 0));
       sig[tid] = me > 1e-14 * top ? (float)sqrt(me) : 0.f;         // below: rounding of the squares
     }
     alike = __syncthreads_or(alike);

@@ -16,6 +16,14 @@ struct EigWork {
   static_assert((kBad + D) * 2 <= D * D, "fits the slot");
 };
 
+// What counts as nothing of a sum of squares beside T's diagonal, of a matrix whose largest element is 1 to 4: 1e-20 of it is
+// below its rounding by four orders.  (In what is left of a matrix of exactly low rank every further step is some 1e-16 of the
+// one before, and 1 / h^2 leaves fp64 when n2 passes 1e-154.)
+constexpr double kEigNothing = 1e-40;
+
+__device__ __forceinline__ bool is_finite(double v) {               // by its bits
+  return ((unsigned)(__builtin_bit_cast(unsigned long long, v) >> 32) & 0x7ff00000u) != 0x7ff00000u;
+}
 __device__ __forceinline__ unsigned wave_max(unsigned v) {
   auto step = [&](unsigned u) __attribute__((always_inline)) { v = max(v, u); };
   step((unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true));
@@ -197,8 +205,9 @@ __global__ __launch_bounds__(256) void tridiag_kernel(double* gram, float* omega
       total += dpp_double<0xB1>(total);
       n2 = row_sum(n2);
       // v = x - alpha e_{k+1}, h = v.v / 2; nothing right of the diagonal: H = I
-      const double alpha = n2 > 0.0 ? -copysign(n2 * fast_rsqrt(n2), x0) : 0.0, v1 = x0 - alpha;
-      const double inv = n2 > 0.0 ? fast_reciprocal(__builtin_fma(-alpha, x0, n2)) : 0.0;      // 1 / h
+      const bool some = n2 > kEigNothing;
+      const double alpha = some ? -copysign(n2 * fast_rsqrt(n2), x0) : 0.0, v1 = x0 - alpha;
+      const double inv = some ? fast_reciprocal(__builtin_fma(-alpha, x0, n2)) : 0.0;      // 1 / h
       if ((lane & (16 / NC - 1)) == 0) ybuf[buf][row_at + row] = total;
       if (ti == (k1 & 15)) {
         const bool here = P + 1 >= NC || k1 >> 4 == P;
@@ -235,7 +244,7 @@ __global__ __launch_bounds__(256) void tridiag_kernel(double* gram, float* omega
           if (j > P || 16 * P + tj > k) B[(size_t)k * D + tj + 16 * j] = x[j];
         if (tj == 0) {
           work[W::kMinor + 2 * k] = dk;
-          work[W::kMinor + 2 * k + 3] = fmax(alpha * alpha, 1e-40);      // never 0: a zero minor is followed by one that is not
+          work[W::kMinor + 2 * k + 3] = fmax(alpha * alpha, kEigNothing);      // never 0: a zero minor is followed by one that is not
           work[W::kOff + k] = alpha;
           work[W::kTau + k] = inv;
         }
@@ -265,7 +274,7 @@ __global__ __launch_bounds__(256) void tridiag_kernel(double* gram, float* omega
   }
   if (tid == 255 - 15) {                          // ti = tj = 15: the last 2 x 2
     work[W::kMinor + 2 * (D - 2)] = dk;
-    work[W::kMinor + 2 * (D - 2) + 3] = fmax(x[NC - 1] * x[NC - 1], 1e-40);
+    work[W::kMinor + 2 * (D - 2) + 3] = fmax(x[NC - 1] * x[NC - 1], kEigNothing);
     work[W::kOff + D - 2] = x[NC - 1];
     work[W::kOff + D - 1] = 0.0;
     work[W::kMinor + 2 * (D - 1)] = a[NC - 1][NC - 1];
@@ -488,7 +497,7 @@ __global__ __launch_bounds__(kEigThreads) void eig_kernel(const double* __restri
       } else if (l16 == 0) {
         zz_s[who] = zz;
         r_s[who] = r;
-        bad_s[who] = !(fabs(mu - lam - delta) <= delta && fabs(pivot) <= 1e-13 * norm * sqrt(zz));
+        bad_s[who] = !(is_finite(zz) && fabs(mu - lam - delta) <= delta && fabs(pivot) <= 1e-13 * norm * sqrt(zz));
       }
     }
   }

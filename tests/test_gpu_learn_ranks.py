@@ -113,3 +113,42 @@ def test_all_of_the_mass(seka, D, n):
         assert 1 <= got_k[h] <= np.count_nonzero(got_S[h]), (h, got_k[h], np.count_nonzero(got_S[h]))
         # a value is absorbed if it is below half an ulp of the sum so far, at most 2^-24 of the total; D of them at most
         assert got_S[h, got_k[h]:].sum() <= D * 2.0 ** -24 * got_S[h].sum()
+
+
+def _few_valued(kind, n, Hkv, D, g):
+    """Samples that take few values, as quantised keys do: what is left of their exactly low-rank Gram matrix, behind the last
+    step of the reduction that has something to reduce, shrinks by a factor of 1e-16 and more per step."""
+    if kind == "fixed":
+        return np.tile((np.arange(D) % 7 - 4).astype(np.float32), (n, Hkv, 1)), np.ones((n, Hkv, D), np.float32)
+    if kind == "bits":
+        return tuple(g.integers(0, 2, (n, Hkv, D)).astype(np.float32) for _ in range(2))
+    if kind == "signs":
+        return tuple((2.0 * g.integers(0, 2, (n, Hkv, D)) - 1.0).astype(np.float32) for _ in range(2))
+    return tuple(np.round(2.0 * g.standard_normal((n, Hkv, D))).astype(np.float32) for _ in range(2))
+
+
+# copies: the same tokens 64 times over, which is the same Omega
+@pytest.mark.parametrize("copies", [1, 64])
+@pytest.mark.parametrize("kind,n,D,dtype", [("fixed", 1, 64, "f32"), ("fixed", 1, 128, "f32")] + [
+    (kind, n, D, "bf16" if n == 3 else "f32") for kind in ("bits", "signs", "integers") for n in (1, 2, 3, 4) for D in (64, 128)])
+def test_few_valued_samples(seka, kind, n, D, dtype, copies):
+    import torch
+    print(f"learn few values {kind} n={n} D={D} {dtype} copies={copies}", flush=True)
+    Hkv = 32
+    ha, hb = _few_valued(kind, n, Hkv, D, np.random.default_rng(1000 * D + n))
+    U, sig, k, Up = _learn(seka, np.repeat(ha, copies, axis=0), np.repeat(hb, copies, axis=0), 0.9, dtype)
+    got_U, got_S = H.to_f64(U), H.to_f64(sig)
+    assert torch.isfinite(U).all() and torch.isfinite(sig).all() and torch.isfinite(Up.float()).all()
+    for h in range(Hkv):
+        omega = ha[:, h].astype(np.float64).T @ hb[:, h].astype(np.float64) / n
+        s = np.linalg.svd(omega, compute_uv=False)
+        assert np.abs(got_S[h] - s).max() <= 2e-5 * s[0] and np.all(np.diff(got_S[h]) <= 0)       # bounds as above
+        rank = int(np.sum(s > 1e-4 * s[0]))      # integers: the next value is Omega's rounding to fp32
+        live = got_S[h] > 1e-5 * got_S[h, 0]
+        assert live.sum() == rank and np.all(got_U[h][:, ~live] == 0.0)
+        G = got_U[h][:, live].T @ got_U[h][:, live]
+        assert rank == 0 or np.abs(G - np.eye(rank)).max() <= 1e-4
+        assert rank == 0 or np.abs(np.linalg.norm(got_U[h][:, live].T @ omega, axis=1) - s[:rank]).max() <= 1e-4 * s[0]
+        frac = np.cumsum(s) / s.sum() if rank else np.ones(D)
+        if np.abs(frac - 0.9).min() > 1e-4:
+            assert int(k[h]) == int(np.sum(frac < 0.9)) + 1
