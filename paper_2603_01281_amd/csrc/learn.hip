@@ -22,7 +22,10 @@ namespace {
 constexpr int kLearnThreads = 256;
 constexpr int kCovTokens = 16;          // fp32: tokens per turn
 constexpr int kMaxSweeps = 30;
-constexpr float kRotateTol = 2e-6f;     // rotate while |a_p . a_q| > tol |a_p| |a_q| (fp32 dot products of length d)
+constexpr float kRotateTol = 2e-6f;     // sweeps go on while |a_p . a_q| > tol |a_p| |a_q| (fp32 dot products of length d)
+// Few samples: they rotate what is above this as well, so that the last one leaves the columns orthogonal to the rounding of the
+// sums (2.7e-7 instead of 2e-6, for less than a microsecond; 3 to 8 % of a sweep over all columns).
+constexpr float kRotateFewTol = 2e-7f;
 constexpr float kZeroSigma = 1e-5f;     // sigma_c <= this share of sigma_1 is rounding noise: its direction is not determined
 
 __host__ __device__ inline int learn_token_splits(int n) {
@@ -253,13 +256,13 @@ __device__ __forceinline__ float reduce8(const float (&v)[8], int lane) {
 // lane) in registers and rotates all pairs across them (8 rounds of 8 disjoint pairs, registers named at compile
 // time, the 8 dot products of a round reduced together); then blocks change partners through LDS (a round-robin
 // tournament of the blocks: D / 8 - 1 exchanges per sweep instead of one barrier per round of pairs).  Pairs inside a
-// block are rotated once per sweep.  A rotation is applied as three shears.  Sweeps repeat until one rotates nothing.
+// block are rotated once per sweep.  A rotation is applied as three shears.  Sweeps repeat until one finds nothing above kRotateTol.
 // What bounds it: vector issue on the head's CU (about 140 instructions per round and wave, two waves per SIMD: 11 k
 // cycles per exchange of blocks; 8 or 9 sweeps).
 template <typename T, int D>
 __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ gram, const float* __restrict__ omega, float gamma, float* __restrict__ U_out,
                                                     float* __restrict__ sigma_out, int* __restrict__ k_out,
-                                                    T* __restrict__ U_packed, int r_pad) {
+                                                    T* __restrict__ U_packed, int r_pad, int few) {
   constexpr int NW = D / 16, NT = 64 * NW;
   constexpr int RPL = D / 64;                     // rows per lane
   constexpr int LD = D + RPL;                     // column stride in floats
@@ -285,9 +288,9 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
   // ---- what the tridiagonal path found ----
   typedef EigWork<D> W;
   const double* work = reinterpret_cast<const double*>(omega + (size_t)h * D * D);
-  const bool finite = work[W::kStatus] == 0.0;
-  bool alike = !finite;                           // two directions that it cannot tell apart
-  if (finite) {
+  const bool known = !few && work[W::kStatus] == 0.0;              // it ran, on an Omega that is finite
+  bool alike = !known;                            // two directions that it cannot tell apart
+  if (known) {
     if (tid < D) {                                // thread r: the r-th largest
       const double top = work[W::kLambda + D - 1], me = work[W::kLambda + D - 1 - tid];
       const double next = tid < D - 1 ? work[W::kLambda + D - 2 - tid] : -top;
@@ -297,7 +300,7 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
     }
     alike = __syncthreads_or(alike);
   }
-  float unit = finite ? (float)work[W::kUnit] : 0.f;
+  float unit = known ? (float)work[W::kUnit] : 0.f;
   if (alike) {
   // ---- phase 1 ----
   // unit: sqrt of B's largest element, L is scaled by its inverse
@@ -310,8 +313,10 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
 #pragma unroll
     for (int i = 0; i < TR; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)                 // the lower triangle: reflectors stand in the other
-        a[i][j] = Bh[(size_t)max(tr + i, tc + j) * D + min(tr + i, tc + j)];
+      for (int j = 0; j < 4; ++j) {               // the lower triangle: reflectors stand in the other, if there are any
+        const int r = tr + i, c = tc + j;
+        a[i][j] = Bh[few ? r * D + c : max(r, c) * D + min(r, c)];
+      }
 #pragma unroll
     for (int x = 0; x < RPL; ++x) d[x] = Bh[(size_t)(lane + 64 * x) * (D + 1)];
     unsigned top = 0;                             // high word of the largest diagonal element (they are sums of squares)
@@ -399,6 +404,7 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
 
   // ---- phase 2 ----
   const int nblk = max(2, ((ncols + 7) / 8 + 1) & ~1);           // blocks that take part (even)
+  const float rotate_tol2 = few ? kRotateFewTol * kRotateFewTol : kRotateTol * kRotateTol;
   for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
     int rotated = 0;
     for (int step = 0; step < nblk - 1; ++step) {
@@ -419,9 +425,10 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
           return s;
         };
         // rotation of the lane's pair from its norms and dot product; returns t (0: leave the pair alone), sine and
-        // tangent of half the angle
-        auto angle = [&](float al, float be, float ga, float& sn, float& th) __attribute__((always_inline)) -> float {
-          const bool rot = ga * ga > (kRotateTol * kRotateTol) * (al * be);      // norms are 0 or in [1e-7, 1]
+        // tangent of half the angle, and whether another sweep is asked for
+        auto angle = [&](float al, float be, float ga, float& sn, float& th, int& more) __attribute__((always_inline)) -> float {
+          const bool rot = ga * ga > rotate_tol2 * (al * be);      // norms are 0 or in [1e-7, 1]
+          more |= __any(ga * ga > (kRotateTol * kRotateTol) * (al * be));
           const float df = be - al, g2 = ga + ga;
           float t = g2 * __builtin_amdgcn_rcpf(df + copysignf(__builtin_amdgcn_sqrtf(__builtin_fmaf(df, df, g2 * g2)), df));
           t = rot ? t : 0.f;
@@ -460,8 +467,7 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
             }
             const float al = reduce8(va, lane), be = reduce8(vb, lane), ga = reduce8(vg, lane);
             float sn, th;
-            const float t = angle(al, be, ga, sn, th);
-            rotated |= __any(t != 0.f);
+            angle(al, be, ga, sn, th, rotated);
 #pragma unroll
             for (int j = 0; j < 8; ++j) apply(P[j], Q[j], lane_value(sn, j), lane_value(th, j));
           }
@@ -480,9 +486,8 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
           for (int j = 0; j < 8; ++j) vg[j] = dot(j, 8 + ((j + r) & 7));
           const float ga = reduce8(vg, lane);
           float sn, th;
-          const float t = angle(al, be, ga, sn, th);
-          if (__any(t != 0.f)) {                  // the last sweeps rotate few pairs, the very last none
-            rotated = 1;
+          const float t = angle(al, be, ga, sn, th, rotated);
+          if (__any(t != 0.f)) {                  // the last sweeps rotate few pairs
             al = fmaxf(__builtin_fmaf(-t, ga, al), 0.f);
             be = fmaxf(__builtin_fmaf(t, ga, be), 0.f);
 #pragma unroll
@@ -568,6 +573,17 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
   }
 }
 
+// Samples up to which every head goes straight to the iteration.  Omega of n samples has no more than n directions, columns of
+// the pivoted factor that the iteration's time grows with; that of the tridiagonal form grows with the heads alone.  Rounding
+// Omega to fp32 leaves fp32 samples further columns, bf16 samples fewer.  us, iteration / tridiagonal form: D = 128, 8 heads, fp32
+// n = 1 34 / 178, 16 101 / 178, 24 169 / 178, 32 221 / 179, bf16 32 119 / 178, 48 201 / 178; 64 heads fp32 32 239 / 514, 56 508 / 514,
+// bf16 64 245 / 514; D = 64, 8 heads fp32 12 51 / 81, 20 86 / 81, 64 heads 40 141 / 157, 44 176 / 157.
+inline int learn_few(int Hkv, int D, bool bf16) {
+  const int heads = 3 * Hkv / 8;
+  if (D == 64) return Hkv <= 16 ? 16 : (bf16 ? 20 : 10) + heads;
+  return bf16 ? 40 + Hkv / 2 : 22 + heads;
+}
+
 // grid (splits, Hkv): part[h * splits + split] = sum over the split's tokens of || hp[t,h,:] - hm[t,h,:] ||_2.
 // A row is D / 8 (bf16) or D / 4 (fp32) consecutive lanes with one 16-byte load each; fixed-order merges throughout.
 template <typename T, int D>
@@ -644,9 +660,12 @@ hipError_t launch_learn_td(const void* hn, const void* hs, int n, int Hkv, float
   auto kernel = svd_kernel<T, D>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((tridiag_kernel<D>), dim3(Hkv), dim3(256), 0, s, gram, part);
-  hipLaunchKernelGGL((eig_kernel<D>), dim3(D / 4, Hkv), dim3(kEigThreads), 0, s, gram, part, U_out, 0.9 * kZeroSigma * kZeroSigma);
-  hipLaunchKernelGGL(kernel, dim3(Hkv), dim3(4 * D), smem, s, gram, part, gamma, U_out, sigma_out, k_out, static_cast<T*>(U_packed), r_pad);
+  const bool few = n <= learn_few(Hkv, D, sizeof(T) == 2);
+  if (!few) {
+    hipLaunchKernelGGL((tridiag_kernel<D>), dim3(Hkv), dim3(256), 0, s, gram, part);
+    hipLaunchKernelGGL((eig_kernel<D>), dim3(D / 4, Hkv), dim3(kEigThreads), 0, s, gram, part, U_out, 0.9 * kZeroSigma * kZeroSigma);
+  }
+  hipLaunchKernelGGL(kernel, dim3(Hkv), dim3(4 * D), smem, s, gram, part, gamma, U_out, sigma_out, k_out, static_cast<T*>(U_packed), r_pad, (int)few);
   return hipGetLastError();
 }
 

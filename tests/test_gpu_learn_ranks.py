@@ -152,3 +152,31 @@ def test_few_valued_samples(seka, kind, n, D, dtype, copies):
         frac = np.cumsum(s) / s.sum() if rank else np.ones(D)
         if np.abs(frac - 0.9).min() > 1e-4:
             assert int(k[h]) == int(np.sum(frac < 0.9)) + 1
+
+
+# the last number of samples that goes straight to the iteration, and the first that does not
+@pytest.mark.parametrize("dtype,D,Hkv,line", [("f32", 128, 2, 22), ("f32", 128, 8, 25), ("bf16", 128, 4, 42), ("f32", 64, 8, 16), ("bf16", 64, 3, 16),
+                                              ("f32", 64, 40, 25), ("bf16", 64, 32, 32)])
+def test_few_samples(seka, dtype, D, Hkv, line):
+    import torch
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    for n in (line, line + 1):
+        print(f"learn few samples {dtype} D={D} Hkv={Hkv} n={n}", flush=True)
+        g = np.random.default_rng(D + n)
+        ha, hb = (torch.from_numpy(g.standard_normal((n, Hkv, D)).astype(np.float32)).to(dt).float().numpy() for _ in range(2))
+        U, sig, k, _ = _learn(seka, ha, hb, 0.9, dtype)
+        got_U, got_S = H.to_f64(U), H.to_f64(sig)
+        for h in range(Hkv):
+            omega = ha[:, h].astype(np.float64).T @ hb[:, h].astype(np.float64) / n
+            s = np.linalg.svd(omega, compute_uv=False)
+            assert np.abs(got_S[h] - s).max() <= 2e-5 * s[0] and np.all(np.diff(got_S[h]) <= 0)       # bounds as above
+            live = got_S[h] > 1e-5 * got_S[h, 0]
+            assert live.sum() == n and np.all(got_U[h][:, ~live] == 0.0)
+            G = got_U[h][:, live].T @ got_U[h][:, live]
+            # pairs above 2e-7 are rotated, seen through sums of D fp32 products (7 or 8 additions deep: 2^-24 each), and U is
+            # rounded to fp32 (2^-24 per column)
+            assert np.abs(G - np.eye(n)).max() <= 2e-7 + (8 + 2) * 2.0 ** -24
+            assert np.abs(np.linalg.norm(got_U[h][:, live].T @ omega, axis=1) - s[:n]).max() <= 1e-4 * s[0]
+            frac = np.cumsum(s) / s.sum()
+            if np.abs(frac - 0.9).min() > 1e-4:
+                assert int(k[h]) == int(np.sum(frac < 0.9)) + 1
