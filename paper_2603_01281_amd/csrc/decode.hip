@@ -691,9 +691,20 @@ void launch_decode_finish(const float* part, const int* lens, int B, int S, int 
 // D = 128, 128 MB at D = 64 (24 / 8 heads, D = 128: B=6 S=1137, 56 MB, 20.2 / 16.6, B=16 S=560, 73 MB, 20.4 / 22.8; 32 / 8
 // heads: B=6 S=1137 22.4 / 16.6, B=100 S=400 69.5 / 72.8; D = 64, B=16 S=560, 37 MB, 14.4 / 12.8, B=100 S=400, 164 MB,
 // 43.1 / 44.4).
-bool decode_on_matrix_cores(int B, int S, int Hkv, int D, int hp) {
+// `ranges` of `turns` times 64 tokens for each of B Hkv chunks groups: above one workgroup per compute unit three heads, and four
+// in ranges of a single turn, are not always enough either.  Three lose where the last workgroups share only a few compute
+// units, where a range is a single turn, and at D = 64 with two to a unit.  us, vector unit / matrix cores, 3 heads: D = 128,
+// S=128 264 groups 11.5 / 13.9, S=300 96 groups 10.8 / 12.3, 160 groups 15.4 / 14.0, 184 groups 16.5 / 18.7, S=600 72 groups
+// 15.1 / 13.5; D = 64, S=100 640 groups 7.3 / 8.1, S=300 144 groups 9.5 / 10.2, 300 groups 15.8 / 15.1, S=900 84 groups
+// 13.2 / 11.1; 4 heads, D = 128, S=384 84 groups 11.1 / 10.3, 112 groups 14.4 / 15.8.
+bool decode_on_matrix_cores(int B, int S, int Hkv, int chunks, int D, int hp, int ranges, int turns) {
   if (hp <= 2 || hp > 4) return hp > 4;
-  return 2.0 * sizeof(float) * B * S * Hkv * D * D <= 64e6 * 128;
+  if (2.0 * sizeof(float) * B * S * Hkv * D * D > 64e6 * 128) return false;
+  const int wg = B * Hkv * chunks * ranges;
+  if (wg <= 256) return true;
+  if (hp == 4) return D == 64 || turns > 1 || wg <= 512;
+  if (D == 64) return S >= 128 && wg > 448 - std::max(S - 600, 0) / 10;
+  return turns > 1 && (S < 120 || S >= 192) && (wg - 1) % 256 >= (S < 350 ? 80 : 60);
 }
 
 // Whether a call reads past the caches: each byte once, and so many of them that the next call over the same cache would find
@@ -710,11 +721,11 @@ bool decode_streams(int B, int S, int Hkv, int D, int dtype, bool ragged, int ch
 
 template <int D, bool NT>
 hipError_t launch_decode_f32(const float* q, const float* K, const float* V, float* O, float* lse, const int* lens, int B, int S,
-                             int Hq, int Hkv, float scale, float* part, int splits, hipStream_t s) {
+                             int Hq, int Hkv, float scale, float* part, int splits, bool on_matrix_cores, hipStream_t s) {
   const int G = Hq / Hkv, hp = decode_heads_per_wg(G);
   const float c2 = scale * 1.4426950408889634f;
   const dim3 grid(splits, Hkv * (G / hp), B);
-  if (decode_on_matrix_cores(B, S, Hkv, D, hp)) {
+  if (on_matrix_cores) {
     hipLaunchKernelGGL((decode_partial_f32_kernel<D, NT>), grid, dim3(kDecThreads), 0, s, q, K, V, lens, S, Hq, Hkv, hp, c2, splits, part, O,
                        lse);
   } else {
@@ -806,12 +817,15 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
   int splits = decode_splits_of(B, S, Hq, Hkv, D, dtype, workspace_bytes);
   const int groups = B * Hkv * (G / hp);
   if (dtype == SEKA_BF16 && splits > 1 && decode_one_range(B, S, groups, lens != nullptr)) splits = 1;
-  if (dtype != SEKA_BF16 && splits > 1 && decode_on_matrix_cores(B, S, Hkv, D, hp)) {
+  bool on_matrix_cores = false;
+  if (dtype != SEKA_BF16) {
     // the four waves of that kernel take 64 tokens per turn: whole turns, in fewer ranges (D = 128, S=1137 in 13 ranges of 88
     // or 9 of 127: 32 / 8 heads B=6 21.9 -> 16.6 us, 28 / 4 B=40 52.2 -> 44.3, 16 / 1 B=40 26.6 -> 18.4)
     constexpr int kTurn = kDecWaves * 16;
-    const int per = ((S + splits - 1) / splits + kTurn - 1) / kTurn * kTurn;
-    splits = (S + per - 1) / per;
+    const int turns = ((S + splits - 1) / splits + kTurn - 1) / kTurn;
+    const int ranges = splits > 1 ? (S + turns * kTurn - 1) / (turns * kTurn) : 1;
+    on_matrix_cores = decode_on_matrix_cores(B, S, Hkv, G / hp, D, hp, ranges, turns);
+    if (on_matrix_cores) splits = ranges;
   }
   float* part = static_cast<float*>(workspace);
   const bool streams = decode_streams(B, S, Hkv, D, dtype, lens != nullptr, G / hp);
@@ -844,7 +858,7 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
   const float *q32 = static_cast<const float*>(q), *K32 = static_cast<const float*>(K), *V32 = static_cast<const float*>(V);
   auto launch = D == 128 ? (streams ? launch_decode_f32<128, true> : launch_decode_f32<128, false>)
                          : (streams ? launch_decode_f32<64, true> : launch_decode_f32<64, false>);
-  return launch(q32, K32, V32, static_cast<float*>(O), lse, lens, B, S, Hq, Hkv, scale, part, splits, s);
+  return launch(q32, K32, V32, static_cast<float*>(O), lse, lens, B, S, Hq, Hkv, scale, part, splits, on_matrix_cores, s);
 }
 
 }  // namespace seka

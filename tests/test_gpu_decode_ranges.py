@@ -18,6 +18,9 @@ pytestmark = pytest.mark.gpu
     ("f32", 3, 1500, 32, 8, 128, [1500, 64, 1]), ("f32", 2, 1137, 9, 1, 64, [1137, 0]), ("f32", 2, 15, 20, 1, 64, [15, 1]),
     ("f32", 1, 65, 16, 1, 128, None), ("f32", 5, 200, 6, 2, 128, [200, 17, 16, 0, 193]), ("f32", 2, 333, 6, 2, 64, [333, 79]),
     ("f32", 3, 4000, 7, 1, 128, [129, 4000, 3937]), ("f32", 16, 500, 32, 8, 128, None),
+    # three and four heads with more than one workgroup per compute unit: on the vector unit, on the matrix cores, ...
+    ("f32", 48, 300, 6, 2, 128, None), ("f32", 80, 300, 6, 2, 128, [300, 129] * 40), ("f32", 72, 300, 6, 2, 64, None),
+    ("f32", 160, 300, 6, 2, 64, [300, 1] * 80), ("f32", 28, 384, 16, 4, 128, None),
     # bf16 caches of few groups at D = 128: one range up to 700 tokens, then one per compute unit, at least 64 tokens each
     ("bf16", 1, 700, 8, 2, 128, None), ("bf16", 1, 701, 8, 2, 128, None), ("bf16", 2, 1000, 32, 8, 128, [1000, 65]),
     ("bf16", 1, 4133, 6, 1, 128, None), ("bf16", 5, 1030, 14, 2, 128, [1030, 0, 1, 64, 700]), ("bf16", 33, 1100, 8, 8, 128, None),
