@@ -19,6 +19,8 @@
 // one after the other, which gives the bits of the split form (0 to 5 % of a short launch, none of a long one).  The form before this one (scalar FMAs, keys
 // and probabilities broadcast from LDS, the edit as dependent global loads) took 134 us at B=1 S=256 Hq=4 D=64 (one
 // call among others), this one 8.3; B=15 S=549 Hq=32 D=64 1898 -> 306 us; B=2 S=1446 Hq=6 D=128 1706 -> 118 us.
+#include <algorithm>
+
 #include "common.h"
 
 namespace seka {
@@ -368,15 +370,18 @@ hipError_t launch_d(const AttnArgs& a, const SteerArgs& st, hipStream_t s) {
   const int units = (a.S + kUnitRows - 1) / kUnitRows * (a.Hq / a.Hkv);      // per (prompt, KV head)
   // One wave per unit or four; the results are the same.  Whole units win where they fill the 1024 SIMDs once, just, or often
   // enough for their length that the last ones do not matter; a little over 1024 a second wave shares a few SIMDs and sets
-  // the time.  Measured, 8 / 2 heads, us, whole / split, units x steps.  D = 64: 552 x 12 28 / 16, 1008 x 3 11.5 / 15.2, 1056 x 6
-  // 23 / 21, 1140 x 10 36 / 27, 2024 x 12 42 / 45, 2160 x 23 70 / 70, 2160 x 45 138 / 107, 3072 x 48 206 / 156, 4320 x 45 229 / 201,
-  // 7920 x 45 358 / 358, 8280 x 12 120 / 154.  D = 128: 800 x 10 25 / 28, 1056 x 12 38 / 32, 2016 x 12 40 / 55, 3552 x 74 292 / 272,
-  // 4320 x 90 407 / 371, 5632 x 44 266 / 288, 7920 x 90 637 / 664.
+  // the time.  The fewer steps a unit has, the more the split form's merge weighs: up to 4 steps at D = 64 and 7 at D = 128 whole
+  // units win over 1024 as well.  `whole` counts the idle waves of a last workgroup.
+  // Measured, us, whole / split, units x steps.  D = 64: 544 x 1 5.4 / 9.6, 480 x 3 10.7 / 8.1, 600 x 3 10.6 / 12.5, 588 x 4 13.6 / 13.8,
+  // 1136 x 2 12.3 / 18.4, 1056 x 6 22 / 20, 1140 x 10 36 / 27, 2024 x 12 42 / 45, 2160 x 45 138 / 107, 4320 x 45 229 / 201.  D = 128: 576 x 3
+  // 13.0 / 16.2, 800 x 10 25 / 28, 1140 x 5 25 / 28, 1728 x 6 28 / 38, 1056 x 12 38 / 32, 2016 x 12 40 / 55, 2016 x 36 104 / 93, 4032 x 56
+  // 283 / 264, 4320 x 90 407 / 371, 5632 x 44 266 / 288, 7920 x 90 637 / 664.
   const int steps = (a.S + 2048 / D - 1) / (2048 / D);      // 32 keys at D = 64, 16 at D = 128
-  const long long total = (long long)units * a.Hkv * a.B;
-  const long long least = steps <= 4 ? 600 : total <= 1024 ? 480 + (D == 64 ? 60 : 30) * steps
-                                           : steps <= 24 ? 1800 : steps < 56 ? 1800 + 130 * (steps - 24) : 6000;
-  return total >= least ? launch_cfg<D, STEER, 1>(a, st, units, s) : launch_cfg<D, STEER, 4>(a, st, units, s);
+  const long long total = (long long)units * a.Hkv * a.B, whole = (long long)((units + 3) / 4 * 4) * a.Hkv * a.B;
+  const int rise = D == 64 ? std::min(60 * std::min(steps - 4, 11) + 350 * std::max(steps - 15, 0), 6800)
+                           : std::min(55 * std::min(steps - 7, 41) + 320 * std::max(steps - 48, 0), 5800);
+  const long long least = whole <= 1024 ? (D == 64 ? 375 + 70 * steps : 400 + 35 * steps) : rise <= 0 ? 0 : rise + (D == 64 ? 1215 : 1180);
+  return (whole <= 1024 ? total : whole) >= least ? launch_cfg<D, STEER, 1>(a, st, units, s) : launch_cfg<D, STEER, 4>(a, st, units, s);
 }
 
 }  // namespace

@@ -11,7 +11,10 @@ pytestmark = pytest.mark.gpu
 
 # (B, S, Hq, Hkv, D, M, r): the first five take the split form, the last three fill the chip (a unit per wave)
 CASES = [(1, 1, 2, 1, 64, 1, 1), (1, 16, 2, 2, 128, 1, 16), (2, 33, 3, 1, 64, 1, 17), (1, 130, 4, 2, 128, 2, 64), (1, 257, 2, 1, 64, 4, 16),
-         (40, 17, 6, 2, 128, 1, 9), (32, 47, 7, 1, 64, 3, 40), (12, 97, 10, 2, 128, 1, 33)]
+         (40, 17, 6, 2, 128, 1, 9), (32, 47, 7, 1, 64, 3, 40), (12, 97, 10, 2, 128, 1, 33),
+         # both sides of a line between the forms: few steps and about 500 units, few steps and over 1024, more steps and over 1024
+         (3, 67, 32, 8, 64, 1, 8), (15, 66, 8, 2, 64, 1, 8), (71, 49, 4, 2, 64, 1, 16), (3, 162, 32, 8, 64, 1, 8), (19, 70, 12, 2, 128, 1, 8),
+         (17, 129, 12, 3, 128, 1, 8)]
 
 
 @pytest.mark.parametrize("B,S,Hq,Hkv,D,M,r", CASES)
