@@ -1,6 +1,6 @@
 // Query projection in 256 x 256 tiles: Q[t, n] = sum_e X[t, e] W[n, e], bf16 in, fp32 accumulate, bf16 out, with the
-// routing sums of its outputs (see project_route_kernel, which takes the sizes whose 256 x 256 tiles would leave the
-// chip idle).
+// routing sums of its outputs (project_tile.h has the smaller tiles, for sizes whose 256 x 256 ones would leave the chip
+// idle).
 //
 // What bounds it: the matrix pipe and the LDS reads beside it.  A 64-wide slice of E is 2048 cycles of MFMA per SIMD,
 // 1536 cycles of LDS operand reads and 512 of tile writes.  Eight waves as 2 x 4; a wave owns 64 x 32 outputs in each

@@ -1,4 +1,4 @@
-"""GPU parity of seka_project_route: the query projection with the routing sums in its epilogue."""
+"""GPU parity of seka_project_route: the query projection with the routing sums in its epilogue, at small sizes (128 x 64 tiles)."""
 import numpy as np
 import pytest
 
@@ -9,7 +9,7 @@ from tests import helpers as H
 pytestmark = pytest.mark.gpu
 
 
-# E / 64 slices: 3, 1 and 5 (loop ends in its tail), 2, 4 and 8 (even counts: the loop ends without a tail, as at E = 4096)
+# E / 64 slices: 3, 1, 5, 2, 4 and 8
 @pytest.mark.parametrize("shape", [(2, 256, 8, 2, 192), (1, 384, 4, 4, 64), (3, 128, 6, 3, 320),
                                    (1, 256, 4, 2, 128), (2, 128, 8, 2, 256), (1, 128, 4, 1, 512)])
 def test_project_route(seka, shape):
