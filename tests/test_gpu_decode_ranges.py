@@ -76,23 +76,30 @@ def test_small_workspace(seka):
         seka.seka_attention_decode(q, K, V, O, workspace=ws[:least - 16])
 
 
-@pytest.mark.parametrize("dtype,B,S,Hq,Hkv,D", [("bf16", 74, 1000, 32, 8, 128), ("bf16", 148, 1001, 8, 8, 64), ("f32", 37, 1000, 32, 8, 128),
-                                                ("f32", 73, 1017, 56, 8, 64)])
-def test_larger_than_the_caches(seka, dtype, B, S, Hq, Hkv, D):
-    """More than 300 MB of keys and values, which are then read without keeping a place for them; the first, a middle and the last prompt."""
+# bf16 in a single range (plain loads); in several, also ragged; fp32 on the matrix cores and on the vector unit
+@pytest.mark.parametrize("dtype,B,S,Hq,Hkv,D,ragged", [
+    ("bf16", 74, 1000, 32, 8, 128, False), ("bf16", 148, 1001, 8, 8, 64, False), ("bf16", 37, 2000, 32, 8, 128, False),
+    ("bf16", 74, 2003, 8, 8, 64, False), ("bf16", 148, 2100, 32, 8, 128, True), ("f32", 37, 1000, 32, 8, 128, False),
+    ("f32", 73, 1017, 56, 8, 64, False), ("f32", 37, 1001, 40, 8, 128, False), ("f32", 148, 1050, 40, 8, 128, True)])
+def test_larger_than_the_caches(seka, dtype, B, S, Hq, Hkv, D, ragged):
+    """More than 300 MB of keys and values (of a ragged batch four times that), which launches of several ranges and all fp32
+    ones read without keeping a place for them; the first, a middle and the last prompt."""
     import torch
-    print(f"decode large {dtype} B={B} S={S} {Hq}/{Hkv} D={D}", flush=True)
-    assert 2 * B * S * Hkv * D * (2 if dtype == "bf16" else 4) > 300e6
+    print(f"decode large {dtype} B={B} S={S} {Hq}/{Hkv} D={D} ragged={ragged}", flush=True)
+    assert 2 * B * S * Hkv * D * (2 if dtype == "bf16" else 4) * (0.25 if ragged else 1) > 300e6
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     g = torch.Generator(device="cuda")
     g.manual_seed(S)
     q, K, V = (torch.randn(shape, generator=g, device="cuda").to(dt) for shape in ((B, Hq, D), (B, S, Hkv, D), (B, S, Hkv, D)))
+    lens = np.full(B, S, np.int32)
+    if ragged:
+        lens[:] = np.random.default_rng(S).integers(1, S, B)
     O = torch.full_like(q, float("nan"))
     ws = torch.full((seka.seka_decode_workspace_bytes(B, S, Hq, Hkv, D, seka.SEKA_BF16 if dtype == "bf16" else seka.SEKA_F32),), 0xff,
                     dtype=torch.uint8, device="cuda")
-    seka.seka_attention_decode(q, K, V, O, workspace=ws)
+    seka.seka_attention_decode(q, K, V, O, seq_lens=torch.from_numpy(lens).cuda() if ragged else None, workspace=ws)
     for b in (0, B // 2, B - 1):
-        ref, _ = orc.decode_attention(H.to_f64(q[b:b + 1]), H.to_f64(K[b:b + 1]), H.to_f64(V[b:b + 1]), np.full(1, S, np.int32))
+        ref, _ = orc.decode_attention(H.to_f64(q[b:b + 1]), H.to_f64(K[b:b + 1]), H.to_f64(V[b:b + 1]), lens[b:b + 1])
         if dtype == "f32":
             H.assert_close_f32(H.to_f64(O[b:b + 1]), ref, "O", tol=1e-5)
         else:
