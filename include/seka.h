@@ -233,9 +233,11 @@ seka_status seka_attention_prefill_packed(const void* Q, const void* K, const vo
  *           cached token gets O = 0 and lse = -inf.
  * workspace dev scratch of at least seka_decode_workspace_bytes(sh) bytes, 16-byte aligned; contents on return
  *           are unspecified; calls sharing it must be ordered by their stream.  The size never falls with B or S:
- *           one allocated for the largest batch and cache serves the smaller ones.  A smaller workspace is accepted
- *           as long as the call can be cut into fewer, longer ranges that fit it.  (Caches short enough to be taken in
- *           one piece per head group, S <= 700 in bf16, are one kernel that does not touch it.)
+ *           one allocated for the largest batch and cache serves the smaller ones.  bf16 calls also accept a smaller
+ *           one that holds the states of ranges of 512 tokens and more; they are then cut into those, and the order of
+ *           the sums, with it the last bits of O and lse, is that of the ranges.  fp32 calls have no such choice.
+ *           (Caches short enough to be taken in one piece per head group, S <= 700 in bf16, are one kernel that does not
+ *           touch it.)
  */
 size_t seka_decode_workspace_bytes(const seka_shape* sh);
 seka_status seka_attention_decode(const void* q, const void* K, const void* V, void* O, float* lse,

@@ -90,7 +90,8 @@ template <> struct DecElem<float> {
 
 // Maximum and sum over the lanes with the same index in a half (HALVES = 2) or a row of 16 (4); the same bits in all of them.
 // Lane swaps on the vector unit: a shuffle through LDS is some 120 cycles in a chain that every step of a range waits for
-// (us, shuffles / swaps: bf16 32 / 8 heads D = 128 B=1 S=1000 9.0 / 8.5, D = 64 7.3 / 7.0; fp32 D = 64 S=600 8.8 / 8.4).
+// (us, shuffles / swaps, kernels of a graph on one cache: bf16 32 / 8 heads B=1 S=1000 D = 128 6.8 / 6.7, D = 64 7.0 / 6.8; fp32 D = 64
+// S=600 7.4 / 7.2).
 template <int PARTS, typename F>
 __device__ __forceinline__ float across(float v, F join) {
   if (PARTS == 4) {
@@ -775,11 +776,12 @@ static int decode_least_splits(int B, int S, int Hq, int Hkv, int D, int dtype) 
 static size_t decode_state_bytes(int B, int Hq, int D, int splits) { return (size_t)B * Hq * splits * (D + 2) * sizeof(float); }
 
 // bf16 caches of few groups at D = 128: as many ranges as give every compute unit a workgroup, down to 64 tokens each (a chain
-// of 512 tokens is 8 us by itself).  us, 512-token ranges / these: 32 / 8 heads B=1 S=1000 10.6 / 7.9, S=2500 14.1 / 9.7,
-// S=10000 16.8 / 15.3; B=3 S=1500 16.0 / 11.0; B=10 S=1000 16.9 / 14.5; 8 / 2 heads B=10 S=1500 15.3 / 9.7; 32 / 32 B=1
-// S=1000 15.5 / 9.1.  Not for a second range alone (28 / 4 heads B=30 S=1000 17.9 / 18.6), nor up to about 700 tokens (S=600
-// 7.9 in one range, 8.5 in nine), nor at D = 64, where a token is half the work (B=1 S=1000 7.1 / 8.8, B=1 S=3000 8 / 2
-// heads 8.7 / 9.2).  A workspace that was sized for the longer ranges gets those.
+// of 512 tokens is 8 us by itself).  us, 512-token ranges / these, in a graph on caches that are not cached: 32 / 8 heads B=1 S=1000
+// 15.5 / 8.2 (on one cache over and over 10.6 / 6.7; called one by one from the host 14.4 / 9.8, the host's time for two launches),
+// S=2500 14.8 / 10.1, S=10000 17.4 / 15.9; B=3 S=1500 16.7 / 11.2; B=10 S=1000 18.7 / 15.0; 8 / 2 heads B=10 S=1500 15.7 / 10.1;
+// 32 / 32 B=1 S=1000 16.1 / 9.5.  Not for a second range alone (28 / 4 heads B=30 S=1000 18.6 / 19.5), nor up to about 700 tokens and at
+// D = 64, where one range is one launch: called one by one on one cache S=600 7.9 / 9.9, D = 64 B=1 S=1000 7.5 / 9.8, while in a graph on
+// caches that are not cached 11.0 / 8.1 and 10.8 / 6.9.  A workspace that was sized for the longer ranges gets those.
 constexpr int kDecOneRange = 700, kDecFineRows = 64, kDecFineWG = 256;
 static int decode_splits_of(int B, int S, int Hq, int Hkv, int D, int dtype, size_t workspace_bytes) {
   const int least = decode_least_splits(B, S, Hq, Hkv, D, dtype);
@@ -791,10 +793,10 @@ static int decode_splits_of(int B, int S, int Hq, int Hkv, int D, int dtype, siz
 
 // bf16 caches whose groups alone give more than half of the compute units a workgroup of eight waves, and none two: one range
 // up to S = 1535, and up to 2047 from 192 groups on.  Two or three ranges are workgroups of four waves, of which some compute
-// units get two and others one.  us, ranges / one, 32 / 8 heads: D = 128 S=1100 160 groups 26.0 / 20.7, 256 groups 32.0 / 27.6;
-// S=2000 192 groups 43.8 / 38.8, 256 56.4 / 47.8; D = 64 S=1300 160 groups 20.5 / 15.6; ragged B=32 S=1100 20.2 / 15.0.  Not at 128
-// groups (S=1300 21.7 / 21.7, S=2000 30.3 / 31.1) nor longer (192 groups S=3500 60.1 / 64.9), nor for a few prompts of their own
-// lengths, where the longest is all (B=6 32 / 32 heads S=2000 25.3 / 28.2).
+// units get two and others one.  us, ranges / one, in a graph on caches that are not cached, 32 / 8 heads: D = 128 S=1100 160 groups
+// 28.1 / 22.8, 256 groups 34.0 / 29.3; S=2000 192 groups 45.6 / 41.3, 256 60.0 / 50.2; D = 64 S=1300 160 groups 21.6 / 16.8; ragged B=32
+// S=1100 23.6 / 19.3.  Not at 128 groups (S=1300 23.4 / 23.8, S=2000 32.1 / 34.0) nor longer (192 groups S=3500 61.9 / 67.1), nor for a
+// few prompts of their own lengths, where the longest is all (B=6 32 / 32 heads S=2000 29.6 / 33.2).
 static bool decode_one_range(int B, int S, int groups, bool ragged) {
   return groups <= 256 && (groups >= 192 ? S < 2048 : groups > 128 && S < 1536) && (!ragged || B >= 8);
 }
