@@ -21,6 +21,9 @@ struct EigWork {
 // one before, and 1 / h^2 leaves fp64 when n2 passes 1e-154.)
 constexpr double kEigNothing = 1e-40;
 
+// Off-diagonal elements below this share of what their rows and columns are: a matrix that is diagonal already.
+constexpr double kEigApart = 2e-7;
+
 __device__ __forceinline__ bool is_finite(double v) {               // by its bits
   return ((unsigned)(__builtin_bit_cast(unsigned long long, v) >> 32) & 0x7ff00000u) != 0x7ff00000u;
 }
@@ -145,7 +148,7 @@ __global__ __launch_bounds__(256) void tridiag_kernel(double* gram, float* omega
   const int e = top && finite ? ((int)(top >> 20) - 1023) & ~1 : 0;
   if (tid == 0) {
     work[W::kUnit] = __builtin_bit_cast(double, (unsigned long long)(1023 + e / 2) << 52);
-    work[W::kStatus] = finite ? 0.0 : 1.0;
+    work[W::kStatus] = finite ? 0.0 : 1.0;       // 2: diagonal, with eigenvalues too close for what follows
     work[W::kMinor + 1] = 0.0;
   }
   if (!finite) return;                            // the same in every wave
@@ -158,6 +161,39 @@ __global__ __launch_bounds__(256) void tridiag_kernel(double* gram, float* omega
   }
   dk *= down;
   x0 *= down;
+  // A matrix that is diagonal with equal elements would come back from all of this with directions that cannot be told apart,
+  // and have the iteration before it, which finds nothing to rotate there (D = 128, 8 heads: 318 -> 172 us; 0.2 us for the
+  // others, which row 0 rules out).  Row 0 is in every wave, so all of them go the same way.
+  bool some_off = false;
+  double dc[NC];
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    dc[j] = B[(size_t)(tj + 16 * j) * (D + 1)] * down;
+    some_off |= tj + 16 * j > 0 && x[j] * x[j] > kEigApart * kEigApart * dk * dc[j];
+  }
+  if (!__any(some_off)) {
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const double dr = B[(size_t)(ti + 16 * i) * (D + 1)] * down;
+#pragma unroll
+      for (int j = 0; j < NC; ++j) some_off |= ti + 16 * i != tj + 16 * j && a[i][j] * a[i][j] > kEigApart * kEigApart * dr * dc[j];
+    }
+    if (tid < 16) {
+#pragma unroll
+      for (int j = 0; j < NC; ++j) ybuf[0][tj + 16 * j] = dc[j];
+    }
+    some_off = __syncthreads_or(some_off);
+    bool twins = false;                           // the limits are those of svd_kernel, a little tighter
+    if (tid < D && !some_off) {
+      const double me = ybuf[0][tid], limit = 0.9 * fmax(1e-13, 1e-7 * me);
+#pragma unroll 8
+      for (int i = 0; i < D; ++i) twins |= i != tid && me > 1e-9 && fabs(ybuf[0][i] - me) < limit;
+    }
+    if (__syncthreads_or(twins)) {
+      if (tid == 0) work[W::kStatus] = 2.0;
+      return;
+    }
+  }
   unsigned up8 = -(lane >> 3 & 1), up4 = -(lane >> 2 & 1), up2 = -(lane >> 1 & 1);
   asm("" : "+v"(up8), "+v"(up4), "+v"(up2));     // or they become comparisons again
   const int row = NC == 8 ? ((lane >> 3 & 1) << 2) + ((lane >> 2 & 1) << 1) + (lane >> 1 & 1) : ((lane >> 3 & 1) << 1) + (lane >> 2 & 1);
@@ -287,8 +323,9 @@ __global__ __launch_bounds__(256) void tridiag_kernel(double* gram, float* omega
 //  1. Multisection: the signs of det(T_i - x), i = 1 .. D, change as often as there are eigenvalues below x (the recurrence
 //     of the leading minors, no division; rescaled every 8 steps); 64 lanes cut the interval in 65, nine times.  T comes by
 //     scalar loads (from LDS the four waves wait for its one port: 41 cycles per row instead of 25).
-//  2. The vectors: forward and backward factorisation of L Delta L^T - lambda, joined where the pivot is smallest, twice,
-//     with the eigenvalue corrected in between.  Chains of D steps: wave 0 runs all eight of them in lanes 0 - 7 (a wave
+//  2. The vectors: forward and backward factorisation of L Delta L^T - lambda, joined where the pivot is smallest (the twisted
+//     factorisation of Parlett and Dhillon, Linear Algebra and its Applications 267, 1997, and 387, 2004), twice, with the
+//     eigenvalue corrected in between.  Chains of D steps: wave 0 runs all eight of them in lanes 0 - 7 (a wave
 //     per eigenvalue has four times the LDS instructions and takes twice as long).  On the factored form vectors of
 //     eigenvalues that differ by a fraction r of themselves are orthogonal to about D 2^-53 / r, whatever lies between
 //     them and the largest one (on T itself the tail of the spectrum would lose its directions).
@@ -314,8 +351,8 @@ __global__ __launch_bounds__(kEigThreads) void eig_kernel(const double* __restri
   const int h = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   double* work = reinterpret_cast<double*>(omega + (size_t)h * D * D);
-  const eig_const_ptr T = (eig_const_ptr)(work + W::kMinor), E = (eig_const_ptr)(work + W::kOff);
-  if (work[W::kStatus] != 0.0) return;                             // Omega is not finite: nothing here reads on
+  const eig_const_ptr T = (eig_const_ptr)(work + W::kMinor);
+  if (work[W::kStatus] != 0.0) return;                             // nothing here reads on
   double norm = 0.0, largest = 0.0;                                // Gershgorin bound of T, largest diagonal element
 #pragma unroll
   for (int x = 0; x < RPL; ++x) {
