@@ -1,5 +1,6 @@
-"""Offline stage on prescribed singular values: spread ones take the tridiagonal path, equal and nearly equal ones (and
-the matrices that fall apart into blocks) the iteration that needs no gaps; around the threshold between them."""
+"""Offline stage on prescribed singular values: spread ones take the tridiagonal path and are held to its accuracy, which the
+iteration does not reach; equal and nearly equal ones the iteration, which needs no gaps (or either, where the samples'
+rounding separates them); around the threshold between them; matrices that are diagonal already."""
 import numpy as np
 import pytest
 
@@ -53,7 +54,9 @@ def test_prescribed_singular_values(seka, name, D, rotated):
         live = got_S[h] > 1e-5 * got_S[h, 0]
         assert np.all(got_U[h][:, ~live] == 0.0)
         G = got_U[h][:, live].T @ got_U[h][:, live]
-        assert np.abs(G - np.eye(int(live.sum()))).max() <= 1e-4
+        # Spread: relative gaps r of the squares are 1.5e-2 and more, where the vectors in fp64 are orthogonal to D 2^-53 / r < 1e-12;
+        # rounding U_out to fp32 moves a dot product by at most 2 x 2^-24 sum |u_i u_j| <= 2^-23.  The iteration stops at 2e-6.
+        assert np.abs(G - np.eye(int(live.sum()))).max() <= (2.0 ** -23 + 1e-9 if name in ("spread", "geometric") else 1e-4)
         # columns are left singular vectors: u_i^T Omega has length sigma_i, and different ones are orthogonal.  The iteration
         # stops at |u_i . u_j| = 2e-6, and u_i^T Omega Omega^T u_j is at most sigma_1^2 times what both of u_i and u_j are off
         # their directions: 2 x 2e-6, and rounding of U_out to fp32; 1e-5 covers both
