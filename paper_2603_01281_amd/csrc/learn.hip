@@ -574,14 +574,17 @@ __global__ __launch_bounds__(4 * D) void svd_kernel(const double* __restrict__ g
 }
 
 // Samples up to which every head goes straight to the iteration.  Omega of n samples has no more than n directions, columns of
-// the pivoted factor that the iteration's time grows with; that of the tridiagonal form grows with the heads alone.  Rounding
-// Omega to fp32 leaves fp32 samples further columns, bf16 samples fewer.  us, iteration / tridiagonal form: D = 128, 8 heads, fp32
-// n = 1 34 / 178, 16 101 / 178, 24 169 / 178, 32 221 / 179, bf16 32 119 / 178, 48 201 / 178; 64 heads fp32 32 239 / 514, 56 508 / 514,
-// bf16 64 245 / 514; D = 64, 8 heads fp32 12 51 / 81, 20 86 / 81, 64 heads 40 141 / 157, 44 176 / 157.
+// the pivoted factor that the iteration's time grows with; that of the tridiagonal form grows with the rounds that eig_kernel's D / 4
+// workgroups per head make on the 256 compute units.  Rounding Omega to fp32 leaves fp32 samples further columns, bf16 samples
+// fewer; the line for fp32 lies between that of samples whose spectrum decays (first figure) and of gaussian ones.  us,
+// iteration / tridiagonal form: D = 128, 8 heads fp32 n = 1 38 / 184, n = 28 161, 185 / 185, n = 32 165, 227 / 185, bf16 n = 44
+// 187, 173 / 185; 12 heads fp32 n = 32 177, 228 / 230, n = 40 187, 261 / 232; 32 heads fp32 n = 44 242, 410 / 336, bf16 n = 64 250, 249 /
+// 336; 64 heads fp32 n = 64 416, 539 / 530, bf16 n = 80 490, 492 / 532; D = 64, 8 heads fp32 n = 16 79, 80 / 85, 64 heads bf16 n = 48
+// 146, 146 / 165.
 inline int learn_few(int Hkv, int D, bool bf16) {
-  const int heads = 3 * Hkv / 8;
-  if (D == 64) return Hkv <= 16 ? 16 : (bf16 ? 20 : 10) + heads;
-  return bf16 ? 40 + Hkv / 2 : 22 + heads;
+  const int rounds = (Hkv * (D / 4) + 255) / 256;
+  if (D == 64) return bf16 ? 12 + 10 * rounds : 10 + 8 * rounds;
+  return bf16 ? 40 + 6 * rounds : 26 + 5 * rounds;
 }
 
 // grid (splits, Hkv): part[h * splits + split] = sum over the split's tokens of || hp[t,h,:] - hm[t,h,:] ||_2.

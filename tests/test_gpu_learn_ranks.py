@@ -155,8 +155,8 @@ def test_few_valued_samples(seka, kind, n, D, dtype, copies):
 
 
 # the last number of samples that goes straight to the iteration, and the first that does not
-@pytest.mark.parametrize("dtype,D,Hkv,line", [("f32", 128, 2, 22), ("f32", 128, 8, 25), ("bf16", 128, 4, 42), ("f32", 64, 8, 16), ("bf16", 64, 3, 16),
-                                              ("f32", 64, 40, 25), ("bf16", 64, 32, 32)])
+@pytest.mark.parametrize("dtype,D,Hkv,line", [("f32", 128, 2, 31), ("f32", 128, 9, 36), ("f32", 128, 40, 51), ("bf16", 128, 4, 46), ("f32", 64, 8, 18),
+                                              ("bf16", 64, 3, 22), ("f32", 64, 40, 34), ("bf16", 64, 32, 32)])
 def test_few_samples(seka, dtype, D, Hkv, line):
     import torch
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
