@@ -283,10 +283,11 @@ seka_status seka_attention_decode_static(const void* q, const void* K, const voi
  * U_packed   dev [Hkv,D,r_pad] tensor dtype or NULL: the first min(k_h, r_pad) columns of U_out[h], the remaining
  *            columns zero, ready to be seka_steer.U with M = 1, r = r_pad (1 <= r_pad <= D).
  * workspace  dev scratch of at least seka_learn_workspace_bytes(sh) bytes, 16-byte aligned.
- * fp32 accumulation of Omega; its Gram matrix is decomposed in fp64 (tridiagonal form), and for a head with singular
- * values that (nearly) coincide by an iteration in fp32 (one-sided Jacobi to a relative off-diagonal of 2e-6);
- * deterministic.  Most of a call is latency of one workgroup per head, so 64 heads cost far less than eight times 8: heads of several layers may be stacked along the head axis of one call (Hkv <=
- * SEKA_MAX_KV_HEADS).
+ * fp32 accumulation of Omega; its Gram matrix is decomposed in fp64 (tridiagonal form).  A head with singular values that
+ * (nearly) coincide takes an iteration in fp32 instead (one-sided Jacobi to a relative off-diagonal of 2e-6), and so does
+ * every head of a call on few samples (up to some tens, to 3e-7 there).  Deterministic.  Most of a call is latency of one
+ * workgroup per head, so 64 heads cost far less than eight times 8: heads of several layers may be stacked along the
+ * head axis of one call (Hkv <= SEKA_MAX_KV_HEADS).
  *
  * seka_head_distance — the head-selection score of Sec. 3.4: D_out[h] = (1/n) sum_t || h_pos[t,h,:] -
  * h_neg[t,h,:] ||_2 over the n = B*S sample tokens; heads whose score clears a threshold are given a nonzero

@@ -8,8 +8,8 @@
 //   cov_reduce_kernel, gram_kernel   Omega from its partial sums, Omega Omega^T in fp64.
 //   tridiag_kernel, eig_kernel   (learn_eig.h) eigenvalues and vectors of the Gram matrix in fp64: singular values and left
 //                        singular vectors of Omega.
-//   svd_kernel           order, rank rule and packed basis; and where two singular values are too close for the above,
-//                        the vectors from a pivoted Cholesky factor (fp64) and one-sided (Hestenes) Jacobi: plane rotations
+//   svd_kernel           order, rank rule and packed basis; and where two singular values are too close for the above, or the
+//                        samples few (learn_few), the vectors from a pivoted Cholesky factor (fp64) and one-sided (Hestenes) Jacobi: plane rotations
 //                        from the right make the factor's columns orthogonal, L V = U Sigma, whatever the gaps are.
 //   head_distance_*      token ranges per workgroup, 16-byte loads, partial sums merged in a fixed order.
 #include "common.h"
