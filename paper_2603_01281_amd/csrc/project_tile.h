@@ -1,7 +1,9 @@
 // Query projection in BM x BN tiles: Q[t, n] = sum_e X[t, e] W[n, e], bf16 in, fp32 accumulate, bf16 out, with the routing
 // sums of its outputs (project_wide.h has the sizes that fill the chip with 256 x 256 tiles).
 //
-// WM x WN waves, each TM x TN outputs.  64-wide slices of E travel straight into a ring of NS stages in LDS, NS of them ahead;
+// WM x WN waves, each TM x TN outputs, on v_mfma_f32_16x16x32_bf16 (see project_wide.h).  64-wide slices of E travel straight
+// into a ring of NS stages in LDS, NS of them ahead (three where a slice is 32 or 48 KB; six of the 24 KB slices of 128 x 64
+// tiles, whose one wave per SIMD finishes a slice before the third one ahead has come: 24.4 -> 22.7 us at 128 tokens, E = N = 4096);
 // the operands of a slice are read one slice before its products.  One barrier per slice: behind barrier k slice k + 1 is in
 // LDS (every wave has waited for its own loads of it) and slice k in registers (and for its reads of it), so its stage
 // takes slice k + NS, and the reads of slice k + 1 run beside the products of slice k.
@@ -16,12 +18,12 @@ template <int BM, int BN, int WM, int WN, int NS, bool ROUTE>
 __global__ __launch_bounds__(64 * WM * WN) void project_route_tile_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
                                                                           uint16_t* __restrict__ Qout, int E, long long tokens, int N,
                                                                           int S, int G, int Hkv, float* __restrict__ workspace) {
-  constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, RBS = TM / 32, CBS = TN / 32;
+  constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, RBS = TM / 16, CBS = TN / 16;
   constexpr int ROWS = BM + BN, STAGE = ROWS * kWideK * 2;         // a slice: BM rows of X, then BN rows of W, 128 bytes each
   constexpr int LPW = ROWS / 8 / NW;                               // 1 KB loads per wave and slice
   static_assert(ROWS / 8 % NW == 0 && TM == 64, "whole loads; a wave's routing sums are those of 64 tokens");
   extern __shared__ __attribute__((aligned(1024))) unsigned char tile_smem[];
-  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN;
   // Each XCD takes a contiguous run of tiles, in groups of 8 token tiles x all feature tiles walked by columns.
@@ -49,58 +51,63 @@ __global__ __launch_bounds__(64 * WM * WN) void project_route_tile_kernel(const 
   const unsigned char* Wb = reinterpret_cast<const unsigned char*>(W) + (size_t)col0 * rowbytes;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(dma_lds_void_ptr)tile_smem;
   const int nk = E / kWideK;
-  auto issue = [&](int k, int stage) __attribute__((always_inline)) {      // past the end: a slice nobody uses
-    const size_t at = (size_t)min(k, nk - 1) * (kWideK * 2);
-#pragma unroll
-    for (int n = 0; n < LPW; ++n)          // BM / 8 is a multiple of NW or the other way round: wave-uniform either way
-      wide_load_16B((8 * (wave + NW * n) < BM ? Xb : Wb) + at, off[n], lds0 + stage * STAGE + 1024 * (wave + NW * n));
+  auto issue_one = [&](int n, size_t at, int stage) __attribute__((always_inline)) {
+    // BM / 8 is a multiple of NW or the other way round: wave-uniform either way
+    wide_load_16B((8 * (wave + NW * n) < BM ? Xb : Wb) + at, off[n], lds0 + stage * STAGE + 1024 * (wave + NW * n));
   };
+  auto at_of = [&](int k) __attribute__((always_inline)) { return (size_t)min(k, nk - 1) * (kWideK * 2); };     // past the end: a slice nobody uses
 
   typedef __attribute__((address_space(3))) const bf16x8* lds_frag;
-  uint32_t a_addr[4], b_addr[4];           // operand (row l32, elements 16 kk + 8 hf .. + 7) of the wave's rows in stage 0
+  constexpr int KK = kWideK / 32;          // products of a slice
+  uint32_t a_addr[KK], b_addr[KK];         // operand (row l16, elements 32 kk + 8 grp .. + 7) of the wave's rows in stage 0
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const uint32_t in_row = 16u * ((2 * kk + hf) ^ ((l32 >> 1) & 7));
-    a_addr[kk] = lds0 + (TM * wm + l32) * 128 + in_row;
-    b_addr[kk] = lds0 + (BM + TN * wn + l32) * 128 + in_row;
+  for (int kk = 0; kk < KK; ++kk) {
+    const uint32_t in_row = 16u * ((4 * kk + grp) ^ ((l16 >> 1) & 7));
+    a_addr[kk] = lds0 + (TM * wm + l16) * 128 + in_row;
+    b_addr[kk] = lds0 + (BM + TN * wn + l16) * 128 + in_row;
   }
-  f32x16 acc[RBS][CBS];
+  f32x4 acc[RBS][CBS];
 #pragma unroll
   for (int i = 0; i < RBS; ++i)
 #pragma unroll
     for (int j = 0; j < CBS; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  struct Operands { bf16x8 a[RBS][4], b[CBS][4]; };
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+  struct Operands { bf16x8 a[RBS][KK], b[CBS][KK]; };
   Operands even, odd;
-  auto read = [&](Operands& f, int stage) __attribute__((always_inline)) {
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-#pragma unroll
-      for (int i = 0; i < RBS; ++i) f.a[i][kk] = *(lds_frag)(uintptr_t)(a_addr[kk] + stage * STAGE + 4096 * i);
-#pragma unroll
-      for (int j = 0; j < CBS; ++j) f.b[j][kk] = *(lds_frag)(uintptr_t)(b_addr[kk] + stage * STAGE + 4096 * j);
-    }
+  constexpr int PER_KK = RBS + CBS, READS = KK * PER_KK, PRODUCTS = KK * RBS * CBS;
+  auto read_one = [&](Operands& f, int i, int stage) __attribute__((always_inline)) {
+    const int kk = i / PER_KK, r = i % PER_KK;
+    if (r < RBS) f.a[r][kk] = *(lds_frag)(uintptr_t)(a_addr[kk] + stage * STAGE + 2048 * r);
+    else f.b[r - RBS][kk] = *(lds_frag)(uintptr_t)(b_addr[kk] + stage * STAGE + 2048 * (r - RBS));
   };
+  // One slice, in program order: a product, then an operand read of the next slice, then a request, until all are issued.
+  // Left to itself the compiler moves the reads to the end of the slice, in front of the products that wait for them (E = N =
+  // 4096: 1024 tokens 40.3 -> 35.9 us, 2048 67.2 -> 60.2, 128 26.0 -> 24.4).
   auto slice = [&](auto turn_c, int k) __attribute__((always_inline)) {      // turn_c: k modulo the unrolled turns
     constexpr int TURN = decltype(turn_c)::value;
     Operands &now = TURN % 2 ? odd : even, &next = TURN % 2 ? even : odd;
     dma_wait_vmcnt<(NS - 2) * LPW>();
     dma_barrier();
-    issue(k + NS, TURN % NS);
-    read(next, (TURN + 1) % NS);
+    const size_t at = at_of(k + NS);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-      for (int i = 0; i < RBS; ++i)
-#pragma unroll
-        for (int j = 0; j < CBS; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(now.a[i][kk], now.b[j][kk], acc[i][j], 0, 0, 0);
+    for (int p = 0; p < PRODUCTS; ++p) {
+      const int kk = p / (RBS * CBS), i = p / CBS % RBS, j = p % CBS;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(now.a[i][kk], now.b[j][kk], acc[i][j], 0, 0, 0);
+      if (p < READS) read_one(next, p, (TURN + 1) % NS);
+      if (p < LPW) issue_one(p, at, TURN % NS);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
 #pragma unroll
-  for (int k = 0; k < NS; ++k) issue(k, k);
+  for (int k = 0; k < NS; ++k)
+#pragma unroll
+    for (int n = 0; n < LPW; ++n) issue_one(n, at_of(k), k);
   dma_wait_vmcnt<(NS - 1) * LPW>();
   asm volatile("s_barrier" ::: "memory");
-  read(even, 0);
+#pragma unroll
+  for (int i = 0; i < READS; ++i) read_one(even, i, 0);
   constexpr int TURNS = NS % 2 ? 2 * NS : NS;
   int k = 0;
   auto turns = [&](auto n_c) __attribute__((always_inline)) {
@@ -128,7 +135,7 @@ __global__ __launch_bounds__(64 * WM * WN) void project_route_tile_kernel(const 
   constexpr int LINE = TN * 2, LC = LINE / 16;                     // bytes and 16-byte chunks of a staged row
   unsigned char* const stage = tile_smem + TM * LINE * wave;       // chunks swizzled with the token
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-  const uint32_t sel = (l32 & 1) ? 0x03020706u : 0x05040100u;      // bytes of {neighbour, own}: see below
+  const uint32_t sel = (l16 & 1) ? 0x03020706u : 0x05040100u;      // bytes of {neighbour, own}: see below
   if (TM * wm > last_row || TN * wn > last_col) return;            // wave-uniform; no barrier follows
 #pragma unroll
   for (int j = 0; j < CBS; ++j) {
@@ -136,25 +143,26 @@ __global__ __launch_bounds__(64 * WM * WN) void project_route_tile_kernel(const 
 #pragma unroll
     for (int rb = 0; rb < RBS; ++rb)
 #pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        // tokens m, m + 1 of feature column l32; an even lane keeps token m of columns l32, l32 + 1, an odd one token
-        // m + 1 of columns l32 - 1, l32
+      for (int r = 0; r < 4; r += 2) {
+        // tokens m, m + 1 of feature column l16; an even lane keeps token m of columns l16, l16 + 1, an odd one token
+        // m + 1 of columns l16 - 1, l16
         const bf16x2 own = {(__bf16)acc[rb][j][r], (__bf16)acc[rb][j][r + 1]};
         colsum = __builtin_amdgcn_fdot2_f32_bf16(own, ones, colsum, false);
         const uint32_t mine = __builtin_bit_cast(uint32_t, own);
         const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xf, 0xf, true);   // lane ^ 1
         const uint32_t pair = __builtin_amdgcn_perm(other, mine, sel);
-        const int m = 32 * rb + 8 * (r >> 2) + 4 * hf + (r & 3) + (l32 & 1), byte = 64 * j + 4 * (l32 >> 1);
+        const int m = 16 * rb + 4 * grp + r + (l16 & 1), byte = 32 * j + 4 * (l16 >> 1);
         *reinterpret_cast<uint32_t*>(stage + LINE * m + (byte ^ (16 * (m & (LC - 1))))) = pair;
       }
     if (ROUTE) {
       // these 64 tokens lie in one prompt (S is a multiple of 128); feature -> (head, d)
+      colsum += __shfl_xor(colsum, 16);
       const float tot = colsum + __shfl_xor(colsum, 32);
       const size_t tok = row0 + TM * wm;
       const int b = (int)(tok / S), tchunk = (int)(tok % S) / 64;
-      const int f = col0 + TN * wn + 32 * j + l32, hq = f / 128, h = hq / G, g = hq % G;
+      const int f = col0 + TN * wn + 16 * j + l16, hq = f / 128, h = hq / G, g = hq % G;
       const int chunks = (S / 64) * G;
-      if (hf == 0) workspace[(((size_t)b * Hkv + h) * chunks + (size_t)tchunk * G + g) * 128 + f % 128] = tot;
+      if (grp == 0) workspace[(((size_t)b * Hkv + h) * chunks + (size_t)tchunk * G + g) * 128 + f % 128] = tot;
     }
   }
   asm volatile("" ::: "memory");           // a wave's LDS accesses complete in program order

@@ -2,8 +2,11 @@
 // routing sums of its outputs (project_tile.h has the smaller tiles, for sizes whose 256 x 256 ones would leave the chip
 // idle).
 //
-// What bounds it: the matrix pipe and the LDS reads beside it.  A 64-wide slice of E is 2048 cycles of MFMA per SIMD,
-// 1536 cycles of LDS operand reads and 512 of tile writes.  Eight waves as 2 x 4; a wave owns 64 x 32 outputs in each
+// What bounds it: the matrix pipe under the chip's power limit, and the LDS reads beside it.  A 64-wide slice of E is 2048
+// cycles of MFMA per SIMD, 1536 cycles of LDS operand reads and 512 of tile writes.  The products are
+// v_mfma_f32_16x16x32_bf16: an MFMA of that shape reads and writes half as much accumulator per multiply-add as
+// v_mfma_f32_32x32x16_bf16, and alone, on random operands, the chip sustains 2.05 PFLOP/s of it against 1.76 (the clock is
+// what gives; nothing else changes, operand bytes and register counts are the same).  Eight waves as 2 x 4; a wave owns 64 x 32 outputs in each
 // of the four quadrants of the tile (128 tokens x 128 features), so that operands of one half are kept in registers
 // for two quadrants.  The schedule is the eight-wave ping-pong that is published for CDNA matrix products (HipKittens,
 // 2025): two groups of waves half a step apart, half tiles requested ahead.  A slice is four phases, one quadrant each;
@@ -23,8 +26,8 @@
 // of waves are done with it, and it is requested four to six phases before it is read.  The loads return in order:
 // before the barrier that a read relies on, every wave waits until only the requests after that half are left.
 //
-// Measured at 32768 tokens, E = 4096, N = 4096 with the routing sums: 811 us (1356 TFLOP/s) against 1336 us of the
-// 128 x 128 kernel; the sums come out with the same bits.
+// Measured at 32768 tokens, E = 4096, N = 4096 with the routing sums: 759 us (1449 TFLOP/s), 806 with 32 x 32 x 16 products in
+// the same schedule on the same box, 1336 with the register-staged 128 x 128 kernel; the outputs come out with the same bits.
 #pragma once
 #include <type_traits>
 
@@ -43,7 +46,7 @@ __global__ __launch_bounds__(512) void project_route_wide_kernel(const uint16_t*
                                                                  uint16_t* __restrict__ Qout, int E, long long tokens, int N,
                                                                  int S, int G, int Hkv, float* __restrict__ workspace) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char wide_smem[];     // A: [2 slices][2 halves], then B
-  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
   // Workgroups go round-robin over the 8 XCDs: each XCD takes a contiguous run of tiles, in groups of 8 token tiles x
@@ -88,43 +91,51 @@ __global__ __launch_bounds__(512) void project_route_wide_kernel(const uint16_t*
   };
 
   typedef __attribute__((address_space(3))) const bf16x8* lds_frag;
-  uint32_t a_addr[4], b_addr[4];           // operand (row l32, elements 16 kk + 8 hf .. + 7) of the wave's rows in buffer 0, half 0
+  constexpr int KK = kWideK / 32;          // products of a slice
+  uint32_t a_addr[KK], b_addr[KK];         // operand (row l16, elements 32 kk + 8 grp .. + 7) of the wave's rows in buffer 0, half 0
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const uint32_t in_row = 16u * ((2 * kk + hf) ^ ((l32 >> 1) & 7));
-    a_addr[kk] = lds0 + (64 * wm + l32) * 128 + in_row;
-    b_addr[kk] = ldsB + (32 * wn + l32) * 128 + in_row;
+  for (int kk = 0; kk < KK; ++kk) {
+    const uint32_t in_row = 16u * ((4 * kk + grp) ^ ((l16 >> 1) & 7));
+    a_addr[kk] = lds0 + (64 * wm + l16) * 128 + in_row;
+    b_addr[kk] = ldsB + (32 * wn + l16) * 128 + in_row;
   }
-  f32x16 acc[2][2][2];                     // [A half][B half][block of 32 tokens]
+  f32x4 acc[2][2][4][2];                   // [A half][B half][block of 16 tokens][block of 16 features]
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 32; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i >> 2][(i >> 1) & 1][i & 1][r] = 0.f;
-  bf16x8 a[2][4], b0[4], b1[4];
+    for (int r = 0; r < 4; ++r) acc[i >> 4][(i >> 3) & 1][(i >> 1) & 3][i & 1][r] = 0.f;
+  struct OperandB { bf16x8 f[2][KK]; };
+  bf16x8 a[4][KK];
+  OperandB b0, b1;
   auto read_a = [&](int off) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) a[rb][kk] = *(lds_frag)(uintptr_t)(a_addr[kk] + off + 4096 * rb);
+      for (int rb = 0; rb < 4; ++rb) a[rb][kk] = *(lds_frag)(uintptr_t)(a_addr[kk] + off + 2048 * rb);
   };
-  auto read_b = [&](bf16x8 (&b)[4], int off) __attribute__((always_inline)) {
+  auto read_b = [&](OperandB& b, int off) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) b[kk] = *(lds_frag)(uintptr_t)(b_addr[kk] + off);
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) b.f[cb][kk] = *(lds_frag)(uintptr_t)(b_addr[kk] + off + 2048 * cb);
   };
-  auto multiply = [&](f32x16 (&c)[2], const bf16x8 (&b)[4]) __attribute__((always_inline)) {
+  auto multiply = [&](f32x4 (&c)[4][2], const OperandB& b) __attribute__((always_inline)) {
     asm volatile("s_barrier" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) c[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[rb][kk], b[kk], c[rb], 0, 0, 0);
+      for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+          c[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rb][kk], b.f[cb][kk], c[rb][cb], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_barrier" ::: "memory");
   };
   // One slice; B half 0 is in bc on entry, B half 0 of the next slice in bn on return.
-  auto slice = [&](auto buf_c, int k, bf16x8 (&bc)[4], bf16x8 (&bn)[4]) __attribute__((always_inline)) {
+  auto slice = [&](auto buf_c, int k, OperandB& bc, OperandB& bn) __attribute__((always_inline)) {
     constexpr int C = decltype(buf_c)::value;
     read_a(2 * C * kWideHalf);
     issue_b(1, k + 1, C ^ 1);
@@ -168,36 +179,40 @@ __global__ __launch_bounds__(512) void project_route_wide_kernel(const uint16_t*
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
   unsigned char* const stage = wide_smem + 16384 * wave;           // [2][64 tokens][128 bytes], chunks swizzled with the token
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-  const uint32_t sel = (l32 & 1) ? 0x03020706u : 0x05040100u;      // bytes of {neighbour, own}: see below
+  const uint32_t sel = (l16 & 1) ? 0x03020706u : 0x05040100u;      // bytes of {neighbour, own}: see below
   const bool cols = cols_hi || wn < 2;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if ((i == 1 && !rows_hi) || !cols) continue;                   // wave-uniform
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      float colsum = 0.f;
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
+      for (int cb = 0; cb < 2; ++cb) {
+        float colsum = 0.f;
 #pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          // tokens m, m + 1 of feature column l32; an even lane keeps token m of columns l32, l32 + 1, an odd one
-          // token m + 1 of columns l32 - 1, l32
-          const bf16x2 own = {(__bf16)acc[i][j][rb][r], (__bf16)acc[i][j][rb][r + 1]};
-          colsum = __builtin_amdgcn_fdot2_f32_bf16(own, ones, colsum, false);
-          const uint32_t mine = __builtin_bit_cast(uint32_t, own);
-          const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xf, 0xf, true);   // lane ^ 1
-          const uint32_t pair = __builtin_amdgcn_perm(other, mine, sel);
-          const int m = 32 * rb + 8 * (r >> 2) + 4 * hf + (r & 3) + (l32 & 1), byte = 64 * j + 4 * (l32 >> 1);
-          *reinterpret_cast<uint32_t*>(stage + 8192 * i + 128 * m + (byte ^ (16 * (m & 7)))) = pair;
+        for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+          for (int r = 0; r < 4; r += 2) {
+            // tokens m, m + 1 of feature column l16; an even lane keeps token m of columns l16, l16 + 1, an odd one
+            // token m + 1 of columns l16 - 1, l16
+            const bf16x2 own = {(__bf16)acc[i][j][rb][cb][r], (__bf16)acc[i][j][rb][cb][r + 1]};
+            colsum = __builtin_amdgcn_fdot2_f32_bf16(own, ones, colsum, false);
+            const uint32_t mine = __builtin_bit_cast(uint32_t, own);
+            const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+            const uint32_t pair = __builtin_amdgcn_perm(other, mine, sel);
+            const int m = 16 * rb + 4 * grp + r + (l16 & 1), byte = 64 * j + 32 * cb + 4 * (l16 >> 1);
+            *reinterpret_cast<uint32_t*>(stage + 8192 * i + 128 * m + (byte ^ (16 * (m & 7)))) = pair;
+          }
+        if (ROUTE) {
+          // these 64 tokens lie in one prompt (S is a multiple of 128); feature -> (head, d)
+          colsum += __shfl_xor(colsum, 16);
+          const float tot = colsum + __shfl_xor(colsum, 32);
+          const size_t tok = row0 + 128 * i + 64 * wm;
+          const int b = (int)(tok / S), tchunk = (int)(tok % S) / 64;
+          const int f = col0 + 64 * wn + 32 * j + 16 * cb + l16, hq = f / 128, h = hq / G, g = hq % G;
+          const int chunks = (S / 64) * G;
+          if (grp == 0) workspace[(((size_t)b * Hkv + h) * chunks + (size_t)tchunk * G + g) * 128 + f % 128] = tot;
         }
-      if (ROUTE) {
-        // these 64 tokens lie in one prompt (S is a multiple of 128); feature -> (head, d)
-        const float tot = colsum + __shfl_xor(colsum, 32);
-        const size_t tok = row0 + 128 * i + 64 * wm;
-        const int b = (int)(tok / S), tchunk = (int)(tok % S) / 64;
-        const int f = col0 + 64 * wn + 32 * j + l32, hq = f / 128, h = hq / G, g = hq % G;
-        const int chunks = (S / 64) * G;
-        if (hf == 0) workspace[(((size_t)b * Hkv + h) * chunks + (size_t)tchunk * G + g) * 128 + f % 128] = tot;
       }
     }
     asm volatile("" ::: "memory");         // a wave's LDS accesses complete in program order
