@@ -3,26 +3,36 @@
 // blended P of AdaSEKA).  Flash-style: scores and edited keys never leave the CU.  Software-pipelined,
 // 32 query rows per wave; attn_bf16_lds_dma.h describes how the tiles travel.
 //
-// Math mapping: S^T = K Q^T on v_mfma_f32_32x32x16_bf16 with A = K rows from LDS and B = Q fragments resident
-// in registers, so each lane owns one query row and 16 of a block's 32 keys (row maximum and sum are in-lane
-// plus one exchange with lane ^ 32); O^T = V^T P^T with B = P^T taken straight from the S^T accumulators (the
+// Math mapping: S^T = K Q^T on v_mfma_f32_16x16x32_bf16 with A = K rows from LDS and B = Q fragments resident
+// in registers, in tiles of 16 keys x 16 query rows: each lane owns one query row of each of its wave's two row tiles and
+// 8 of a block's 32 keys; O^T = V^T P^T with B = P^T taken straight from the S^T accumulators (the
 // contraction order over keys is permuted identically on the V side) and A = V^T fetched from the row-major V
 // tile with the transposing LDS read ds_read_b64_tr_b16.  A workgroup is HPW query heads of one KV group x
 // RBW blocks of 32 query rows, all sharing the K/V tiles (and the edit) of that KV head.
 //
-// What bounds this kernel on gfx950 is the SIMD's vector issue port and, behind it, the chip's power limit, not the
-// matrix pipe alone: a 32x32x16 bf16 MFMA keeps the port from issuing other vector work for about 22 of its 32
-// cycles, a plain vector instruction takes 3 to 5 cycles of it, the transcendental unit accepts one exponential
-// about every 10 cycles, and the two waves of a SIMD queue on the same port.  Consequences:
+// What bounds this kernel on gfx950 is the chip's power limit and the SIMD's issue port, not the matrix pipe alone: with
+// everything but the MFMAs removed a 64-key tile of a workgroup takes 0.99 us, the LDS operand reads add 0.15, the softmax
+// 0.3, tile loads and barrier 0.1 (a stand-alone loop of this step, all compute units busy; each at its own clock).
+// Consequences:
+//   * the products are 16 x 16 x 32 and not 32 x 32 x 16: half the accumulator traffic per multiply-add, and on random operands
+//     the chip sustains 2.05 PFLOP/s of them against 1.76.  With four plain vector instructions beside each 32 cycles of
+//     MFMA that is 17.7 ns against 20.2;
+//   * the row sums are products too (one more output tile, of ones): as v_dot2c_f32_bf16 of the packed probabilities, eight per
+//     32-key block, they took 2.3 of 20.6 ns, as two MFMAs they take 1.0;
 //   * every vector instruction in the loop that is not softmax arithmetic is removed: LDS read addresses
 //     are a register plus an immediate (the loop is unrolled over the three ring stages so that stage
 //     offsets are compile-time constants), tile loads take a scalar base plus a per-lane offset computed
-//     once, and the common case of a step computes no row maximum at all (see `step`): 48 vector instructions
-//     per 16 MFMAs;
+//     once, and the common case of a step computes no row maximum at all (see `step`): 44 vector instructions
+//     per 34 MFMAs;
 //   * MFMAs and vector instructions alternate in program order, and every MFMA has vector work beside it:
 //     a step handles three consecutive 32-key blocks at once: the S^T products of the next block, the softmax
 //     of the current one and the PV products of the previous one (whose probabilities were formed one step
-//     earlier), with one exponential per MFMA.
+//     earlier), with one exponential for every second MFMA.
+// Measured, us, 32 x 32 x 16 products with sums by dot products / now, launches of one box in turns: B=4 S=8192 32 / 8 heads D = 128
+// plain 1800 / 1703, rank 32 1892 / 1801; B=1 S=4096 124 / 118; B=1 S=32768 28 / 4 heads rank 64 6364 / 6060; B=4 S=700 rank 32
+// 32.9 / 32.7; D = 64 B=4 S=4096 plain 292 / 285, rank 32 310 / 312.
+// Tried: 64 query rows per wave, one wave per SIMD, outputs and queries in accumulation registers (half the LDS reads):
+// 1.6 % slower in the stand-alone loop and 15 % in the kernel, whose barrier and branches nothing overlaps then.
 // The softmax runs per 32-key block (half a tile), which halves the score registers the pipeline needs.
 // K tiles live in a ring of three LDS stages; V in a ring of six half tiles that runs half a tile behind K
 // (see the tile loads).  K(t+2) and the V blocks 2t+3, 2t+4 are requested during iteration t (in the hot loop
@@ -32,6 +42,7 @@
 // U^T q afterwards (score-side form, the tile itself stays as loaded); at larger ranks the keys are edited in LDS.
 #pragma once
 #include <type_traits>
+#include <utility>
 
 #include "attn_bf16_lds_dma.h"
 
@@ -47,9 +58,10 @@ namespace seka {
 // g P = U_cat diag(c) U_cat^T, built once per workgroup; at rank >= 64 one product with it moves no more operand
 // bytes than two low-rank products and has no intermediate.  Either way the operands are stored in the order the
 // MFMAs read them (one 16-byte LDS read per lane and operand).
+constexpr int PIPE_RA = 8;                          // MFMAs between an operand read from LDS and its use (5, 7 and 10 within 1 %)
 constexpr int PIPE_Z_LD = 80;                       // bytes per key in a coordinate buffer
 constexpr int PIPE_Z_BYTES = DMA_BK * PIPE_Z_LD;    // one buffer
-constexpr int PIPE_QT_BYTES = 2048;                 // U^T q of one wave: [2 k-slices][64 lanes][8] bf16
+constexpr int PIPE_QT_BYTES = 2048;                 // U^T q of one wave: [2 row tiles][64 lanes][8] bf16
 // bf16 parts of an element of g P (dense form).  One part rounds it to 2^-9, at D = 128 less than the edited key's own
 // rounding adds; a full-rank projector at D = 64 (whose diagonal is g) was further from the exact result than the form with
 // two low-rank products (4.2e-3 against 3.3e-3, 2-norms), so there a second part carries the remainder.
@@ -69,12 +81,27 @@ inline size_t attention_bf16_pipe_smem_bytes(int D, int S, bool steer, int nkr, 
 
 typedef __attribute__((address_space(3))) const bf16x8* pipe_lds_bf16x8_ptr;
 
-// The compiler does not insert, before inline assembly, the wait states an MFMA result needs before a vector
-// instruction may read it.  pipe_max3 is only used on scores whose MFMAs are provably far behind: in the
-// pipelined loop they belong to the previous step (a scheduling barrier and eight MFMAs apart); elsewhere
-// pipe_mfma_result_guard() is placed between the product and the maximum.
-__device__ __forceinline__ void pipe_mfma_result_guard(f32x16& acc) {
-  asm volatile("s_nop 15\n\ts_nop 15" : "+v"(acc));
+// The products of the tile loop are inline assembly: with the builtin the compiler takes other registers for a product's result than
+// for its accumulator, and then waits before it lets anything else into the registers that became free.  It does not know what
+// they are, so the waits that the instruction needs are placed by hand: a product's result may be read by a vector
+// instruction 11 wait states after it was issued at the earliest (mfma_result_guard; in the pipelined loop 16 other products lie
+// between), and a register that a vector instruction wrote may be read by a product after 2 (mfma_operand_guard).
+__device__ __forceinline__ void pipe_mfma_first(f32x4& d, const bf16x8& a, const bf16x8& b) {      // d = a b
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void pipe_mfma(f32x4& d, const bf16x8& a, const bf16x8& b) {            // d += a b
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void pipe_mfma_result_guard(f32x4 (&s)[2][2]) {
+  asm volatile("s_nop 11" : "+v"(s[0][0]), "+v"(s[0][1]), "+v"(s[1][0]), "+v"(s[1][1]));
+}
+__device__ __forceinline__ void pipe_mfma_operand_guard(bf16x8 (&p)[2]) { asm volatile("s_nop 3" : "+v"(p[0]), "+v"(p[1])); }
+// What vector instructions made of the accumulators is complete here; the compiler may not move them past it.
+template <int N>
+__device__ __forceinline__ void pipe_pin_acc(f32x4 (&o)[N][2], f32x4 (&l)[2]) {
+#pragma unroll
+  for (int i = 0; i < N; i += 2) asm volatile("" : "+v"(o[i][0]), "+v"(o[i][1]), "+v"(o[i + 1][0]), "+v"(o[i + 1][1]));
+  asm volatile("" : "+v"(l[0]), "+v"(l[1]));
 }
 
 __device__ __forceinline__ float pipe_max3(float a, float b, float c) {
@@ -87,7 +114,7 @@ __device__ __forceinline__ float pipe_max3(float a, float b, float c) {
 // the (wave-uniform) LDS byte address.  Inline assembly keeps it outside the compiler's own vmcnt bookkeeping: the waits
 // are placed by hand.
 __device__ __forceinline__ void pipe_load_16B(const void* base, uint32_t lane_off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(lane_off), "s"(base)
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(lane_off), "s"(base)
                : "memory", "m0");
 }
 
@@ -156,27 +183,42 @@ __device__ __forceinline__ bool pipe_ragged_item(const AttnArgs& a, int item, in
 }
 
 // The 16-byte chunk of tile row `row` that lies at position p is p ^ swizzle: conflict-free 16-byte reads of one chunk
-// of 16 consecutive rows (K), and conflict-free transposing reads of four consecutive rows x 64 bytes (V).
+// of 16 consecutive rows (K), and conflict-free transposing reads of eight consecutive rows x 32 bytes (V).
 template <int D>
 __host__ __device__ constexpr int pipe_k_swizzle(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
 template <int D>
-__host__ __device__ constexpr int pipe_v_swizzle(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+__host__ __device__ constexpr int pipe_v_swizzle(int row) { return D == 128 ? 4 * (row & 3) + 2 * ((row >> 2) & 1) : 2 * ((row >> 1) & 3); }
 
-// HPW heads x RBW row groups = waves per workgroup; every wave owns RPW blocks of 32 consecutive query rows.
-// The scheduled step is written for RPW = 1, and nothing else is instantiated.
+template <class F, int... I>
+__device__ __forceinline__ void pipe_static_for_impl(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void pipe_static_for(F&& f) { pipe_static_for_impl(f, std::make_integer_sequence<int, N>{}); }
+
+// Which K fragment a step reads behind its MFMA m, and which of a lane's 16 scores it takes up there (-1: none); see `step`.
+constexpr int pipe_kfrag_at(int m, int ks, int ahead) {
+  for (int f = 2; f < 2 * ks; ++f)
+    if (m == (2 * f - ahead < f - 2 ? f - 2 : 2 * f - ahead)) return f;
+  return -1;
+}
+constexpr int pipe_element_at(int m, int mfmas) {
+  for (int e = 0; e < 16; ++e)
+    if (m == e * (mfmas >= 34 ? mfmas - 3 : 16) / 16) return e;
+  return -1;
+}
+
+// HPW heads x RBW row groups = waves per workgroup; every wave owns 32 consecutive query rows, two row tiles of 16.
 // NKR: rank of the concatenated basis in blocks of 32 columns (compile-time so that the edit is straight-line code).
-template <int D, int HPW, int RBW, int RPW, bool STEER, int NKR>
+template <int D, int HPW, int RBW, bool STEER, int NKR>
 __global__ __launch_bounds__(64 * HPW * RBW) __attribute__((amdgpu_waves_per_eu(2, D == 64 ? 2 : 8))) void
 attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   static_assert(D == 64 || D == 128, "head dimensions of the tile layouts");
   constexpr int NW = HPW * RBW;
   constexpr int NT = 64 * NW;
-  constexpr int WR = 32 * RPW;
+  constexpr int WR = 32;
   constexpr int BQ = WR * RBW;
   constexpr int BK = DMA_BK;
-  constexpr int KS = D / 16;
-  constexpr int DB = D / 32;
-  constexpr int KS2 = D / 32;
+  constexpr int KS = D / 32;                             // slices of the head dimension that a product contracts
+  constexpr int DT = D / 16;                             // output tiles of 16 columns
   constexpr int RB = 2 * D, CH = D / 8;                  // bytes and 16-byte chunks of a tile row
   constexpr int TB = BK * RB;                            // bytes of a tile
   constexpr int SLOTS = TB / 1024;
@@ -234,12 +276,12 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, hf = lane >> 5;
+  const int l16 = lane & 15, grp = lane >> 4;
   const int hq = hq0 + wave / RBW;
   // Waves w and w + 4 share a SIMD: their row blocks are chosen to end on different tiles or halves of a tile.
   const int rb = RBW == 1 ? 0 : RBW == 2 ? (wave ^ (wave >> 2)) & 1 : RBW == 4 ? (wave & 3) ^ (wave >> 2 ? 3 : 0) : wave < 4 ? wave : 11 - wave;
   int qw = qb * BQ + WR * rb;    // first query row of this wave
-  int qi0 = qw + l32;                      // this lane's query row in row block 0 (block rp: + 32 rp)
+  int qi0 = qw + l16;                      // this lane's query row in row tile 0 (tile 1: + 16)
 
   const float gain = STEER ? st.gain[h] : 0.f;
   const float kscale = STEER ? st.kscale[h] : 1.f;
@@ -260,17 +302,23 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // block of tile t is still being read while the loads of iteration t + 1 are in flight; shifting the unit by
   // half a tile makes every load overwrite only blocks that all waves are done with.
   constexpr int HB = TB / 2;              // bytes of a 32-key block
-  int slot_row[SPW];          // first LDS row of this lane in slot n
-  uint32_t koff[SPW], voff[SPW], slot_lds[SPW], vslot_lds[SPW];
-  bool vslot_hi[SPW];         // slot n belongs to the second block of a shifted tile (wave-uniform)
+  // Load n of a wave fills slot wave + NW n (surplus loads repeat the last slot, same bytes).
+  auto slot_of = [&](int w, int n) __attribute__((always_inline)) { return SLOTS % NW == 0 ? w + NW * n : min(w + NW * n, SLOTS - 1); };
+  auto slot_lds = [&](int w, int n) __attribute__((always_inline)) { return 1024u * slot_of(w, n); };
+  // of a shifted tile of V: the block that slot n belongs to, and where it lies in it
+  auto vslot_hi = [&](int w, int n) __attribute__((always_inline)) { return NW == SLOTS / 2 ? n == 1 : slot_of(w, n) >= SLOTS / 2; };
+  auto vslot_lds = [&](int w, int n) __attribute__((always_inline)) { return NW == SLOTS / 2 ? 1024u * w : 1024u * (slot_of(w, n) & (SLOTS / 2 - 1)); };
+  auto slot_row = [&](int n) __attribute__((always_inline)) { return (64 / CH) * slot_of(wave, n) + lane / CH; };   // this lane's row in it
+  // (the wave's index passes through an opaque copy at every request: the LDS addresses of all stages would be kept in scalar registers)
+  auto opaque_wave = [&]() __attribute__((always_inline)) {
+    int w = wave;
+    asm volatile("" : "+s"(w));
+    return w;
+  };
+  uint32_t koff[SPW], voff[SPW];
 #pragma unroll
   for (int n = 0; n < SPW; ++n) {
-    const int slot = min(wave + NW * n, SLOTS - 1);      // surplus slots repeat the last one (same bytes)
-    const int row = (64 / CH) * slot + lane / CH;
-    slot_row[n] = row;
-    slot_lds[n] = 1024u * slot;
-    vslot_lds[n] = 1024u * (slot & (SLOTS / 2 - 1));
-    vslot_hi[n] = slot >= SLOTS / 2;
+    const int row = slot_row(n);
     koff[n] = row * rowbytes + 16u * ((lane & (CH - 1)) ^ pipe_k_swizzle<D>(row));
     voff[n] = row * rowbytes + 16u * ((lane & (CH - 1)) ^ pipe_v_swizzle<D>(row));
   }
@@ -283,34 +331,38 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // Otherwise rows past the prompt's end repeat its last key (finite data that the causal mask hides); offsets
   // are then taken from token 0 so that they never go negative.
   auto issue_k_to = [&](auto full_c, int t, uint32_t lds_stage_base) __attribute__((always_inline)) {
+    const int w = opaque_wave();
     if (decltype(full_c)::value || t * BK + BK <= S) {
       const unsigned char* tile = Kbytes + (size_t)t * BK * rowbytes;
 #pragma unroll
-      for (int n = 0; n < SPW; ++n) pipe_load_16B(tile, koff[n], lds_stage_base + slot_lds[n]);
+      for (int n = 0; n < SPW; ++n) pipe_load_16B(tile, koff[n], lds_stage_base + slot_lds(w, n));
     } else {
 #pragma unroll
       for (int n = 0; n < SPW; ++n) {
         uint32_t ko = koff[n];
-        asm volatile("" : "+v"(ko));     // formed here, not hoisted out of the tile loops into a register (or scratch slot) of its own
-        pipe_load_16B(Kbytes, ko + (uint32_t)(min(t * BK + slot_row[n], S - 1) - slot_row[n]) * rowbytes,
-                      lds_stage_base + slot_lds[n]);
+        int row = slot_row(n);
+        asm volatile("" : "+v"(ko), "+v"(row));     // formed here, not hoisted out of the loops into a register (or scratch slot) of its own
+        pipe_load_16B(Kbytes, ko + (uint32_t)(min(t * BK + row, S - 1) - row) * rowbytes,
+                      lds_stage_base + slot_lds(w, n));
       }
     }
   };
   // Shifted V tile t: block 2t - 1 to ring byte offset posA, block 2t to posB.
   auto issue_v_to = [&](auto full_c, int t, uint32_t posA, uint32_t posB) __attribute__((always_inline)) {
+    const int w = opaque_wave();
     const int first = t * BK - BK / 2;
     if (decltype(full_c)::value || (first >= 0 && first + BK <= S)) {
       const unsigned char* tile = Vbytes + (size_t)first * rowbytes;
 #pragma unroll
-      for (int n = 0; n < SPW; ++n) pipe_load_16B(tile, voff[n], vst_base + (vslot_hi[n] ? posB : posA) + vslot_lds[n]);
+      for (int n = 0; n < SPW; ++n) pipe_load_16B(tile, voff[n], vst_base + (vslot_hi(w, n) ? posB : posA) + vslot_lds(w, n));
     } else {
 #pragma unroll
       for (int n = 0; n < SPW; ++n) {
         uint32_t vo = voff[n];
-        asm volatile("" : "+v"(vo));
-        pipe_load_16B(Vbytes, vo + (uint32_t)(min(max(first + slot_row[n], 0), S - 1) - slot_row[n]) * rowbytes,
-                      vst_base + (vslot_hi[n] ? posB : posA) + vslot_lds[n]);
+        int row = slot_row(n);
+        asm volatile("" : "+v"(vo), "+v"(row));
+        pipe_load_16B(Vbytes, vo + (uint32_t)(min(max(first + row, 0), S - 1) - row) * rowbytes,
+                      vst_base + (vslot_hi(w, n) ? posB : posA) + vslot_lds(w, n));
       }
     }
   };
@@ -320,20 +372,26 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // 4 KB per wave for turning Q rows into operands and the output accumulators into rows: the third stage of the K
   // ring and positions 3 and 4 of the V ring, which a block's first loads do not touch (at D = 64 an area of its own).  32 rows x 128 bytes; the
   // 16-byte chunk of a row is swizzled with the row (chunk ^ row % 8).
-  static_assert(RPW == 1 && NW <= 8, "one 4 KB staging area per wave");
+  static_assert(NW <= 8, "one 4 KB staging area per wave");
   unsigned char* const stg = D == 64    ? smem + 2 * DMA_STAGES * TB + 4096 * wave
                              : wave < 4 ? Kst + 2 * TB + 4096 * wave
                                         : Vst + 3 * HB + 4096 * (wave - 4);
   typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
-  auto stg_line = [&](int i) __attribute__((always_inline)) -> u32x4* {     // chunk lane % 8 of row 8 i + lane / 8
-    return reinterpret_cast<u32x4*>(stg + 1024 * i + 128 * (lane >> 3) + 16 * ((lane & 7) ^ (lane >> 3)));
+  // (the lane index passes through an opaque copy where they are used: addresses formed from it would be kept over the tile loops)
+  auto opaque_lane = [&]() __attribute__((always_inline)) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    return ln;
   };
-  auto stg_row = [&](int chunk) __attribute__((always_inline)) -> unsigned char* {     // of row l32
-    return stg + 128 * l32 + 16 * (chunk ^ (l32 & 7));
+  auto stg_line = [&](int ln, int i) __attribute__((always_inline)) -> u32x4* {     // chunk ln % 8 of row 8 i + ln / 8
+    return reinterpret_cast<u32x4*>(stg + 1024 * i + 128 * (ln >> 3) + 16 * ((ln & 7) ^ (ln >> 3)));
+  };
+  auto stg_row = [&](int ln, int rt, int chunk) __attribute__((always_inline)) -> unsigned char* {     // of row 16 rt + ln % 16
+    return stg + 2048 * rt + 128 * (ln & 15) + 16 * (chunk ^ (ln & 7));
   };
 
-  // ---- Q fragments: B operand of S^T = K Q^T, lane (col = row qi, k = 16 ks + 8 hf + e) ----
-  bf16x8 qf[RPW][KS];
+  // ---- Q fragments: B operand of S^T = K Q^T, lane (col = row 16 rt + l16, k = 32 ks + 8 grp + e) at rt KS + ks ----
+  bf16x8 qf[2 * KS];
   // First loads of a block of query rows: K tiles 0 and 1, V blocks -1 (a copy of row 0: the first step's PV
   // product multiplies it by zero probabilities, so it only has to be finite) to 2, then the wave's Q rows.
   auto begin_block = [&]() __attribute__((always_inline)) {
@@ -345,26 +403,29 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     // covers eight whole 128-byte lines; q_operands() turns them into operands through LDS.  (Fetched in operand
     // order, 32 rows x 32 bytes per load, the address unit took 3 cycles per row: 6000 cycles per block.)
 #pragma unroll
-    for (int i = 0; i < KS; ++i) {        // rows past the end read row 0 (finite data, results never stored):
+    for (int i = 0; i < 2 * KS; ++i) {    // rows past the end read row 0 (finite data, results never stored):
       const int qi = qw + 8 * (i & 3) + (lane >> 3);                                          // no branch, no wait here
       const uint16_t* qp = Qg + ((tok0 + (qi < S ? qi : 0)) * a.Hq + hq) * D + 64 * (i >> 2) + 8 * (lane & 7);
-      qf[0][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qp));
+      qf[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qp));
     }
   };
   auto q_operands = [&]() __attribute__((always_inline)) {
-    bf16x8 qn[KS];
+    bf16x8 qn[2 * KS];
+    const int ln = opaque_lane();
 #pragma unroll
     for (int half = 0; half < D / 64; ++half) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) *stg_line(i) = __builtin_bit_cast(u32x4, qf[0][4 * half + i]);
+      for (int i = 0; i < 4; ++i) *stg_line(ln, i) = __builtin_bit_cast(u32x4, qf[4 * half + i]);
       asm volatile("" ::: "memory");       // a wave's LDS accesses complete in program order: no wait needed
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        qn[4 * half + ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(stg_row(2 * ks + hf)));
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+          qn[rt * KS + 2 * half + ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(stg_row(ln, rt, 4 * ks + (ln >> 4))));
       asm volatile("" ::: "memory");
     }
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[0][ks] = qn[ks];
+    for (int i = 0; i < 2 * KS; ++i) qf[i] = qn[i];
   };
   begin_block();
 
@@ -481,7 +542,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const int r = r0 + i;
-          U1[((((r >> 4) * KS2 + s1) * 64) + g1 * 16 + (r & 15)) * 8 + e1] = e16[i];
+          U1[((((r >> 4) * KS + s1) * 64) + g1 * 16 + (r & 15)) * 8 + e1] = e16[i];
         }
       }
     };
@@ -534,7 +595,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
           }
           // this lane holds T[y = 16 strip + 4 g + i][x = 16 ct + j], i = 0..3
           const int x = 16 * ct + j, xl = x & 31, y0 = 16 * strip + 4 * g;
-          const int frag = ((x >> 5) * 2 + ((xl >> 2) & 1)) * KS2 + (y0 >> 5);           // (s_out, half, ks)
+          const int frag = ((x >> 5) * 2 + ((xl >> 2) & 1)) * KS + (y0 >> 5);           // (s_out, half, ks)
           const int flane = 16 * ((y0 & 31) >> 3) + 4 * (xl >> 3) + (xl & 3);          // lane (g', j') of the edit
           bf16x4 o4;
 #pragma unroll
@@ -571,25 +632,25 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     const unsigned bits16 = (unsigned)((bits >> (16 * (kblk & 3))) & 0xffffull);
     if (kblk >= BK / 16 || bits16 == 0) return;           // wave-uniform
     unsigned char* krow = Kb + (16 * kblk + j) * RB;
-    bf16x8 kreg[KS2];   // K^T as B operand: lane (col = key j, k = d = 32 s + 8 g + e) = logical chunk 4 s + g
+    bf16x8 kreg[KS];   // K^T as B operand: lane (col = key j, k = d = 32 s + 8 g + e) = logical chunk 4 s + g
 #pragma unroll
-    for (int s = 0; s < KS2; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j)));
+    for (int s = 0; s < KS; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j)));
     const float mbit = ((bits16 >> j) & 1u) ? 1.f : 0.f;
     const float ksc = 1.f + mbit * (kscale - 1.f);        // a for highlighted keys, exactly 1 otherwise
     // k' = a k + mask (g P) k: output rows d are permuted so that each result lands in the lane that holds that
     // element of k
 #pragma unroll
-    for (int s = 0; s < KS2; ++s) {
+    for (int s = 0; s < KS; ++s) {
       float outv[8];
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
         f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int ks = 0; ks < KS2; ++ks) {
-          const bf16x8 ua = *reinterpret_cast<const bf16x8*>(AP + (((s * 2 + half) * KS2 + ks) * 64 + ln) * 8);
+        for (int ks = 0; ks < KS; ++ks) {
+          const bf16x8 ua = *reinterpret_cast<const bf16x8*>(AP + (((s * 2 + half) * KS + ks) * 64 + ln) * 8);
           acc[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua, kreg[ks], acc[ks & 1], 0, 0, 0);
           if (NP == 2) {
-            const bf16x8 ul = *reinterpret_cast<const bf16x8*>(AP + D * D + (((s * 2 + half) * KS2 + ks) * 64 + ln) * 8);
+            const bf16x8 ul = *reinterpret_cast<const bf16x8*>(AP + D * D + (((s * 2 + half) * KS + ks) * 64 + ln) * 8);
             acc[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ul, kreg[ks], acc[ks & 1], 0, 0, 0);
           }
         }
@@ -608,8 +669,8 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // Score-side form (rank <= 32): the coordinates c .* (U_cat^T k) of the 64 keys of the (swizzled, unchanged) K
   // tile at Kb, zero for keys that are not highlighted, into the buffer at zdst; wave w < 4 owns the 16-key block w
   // (a block without highlights only stores zeros).  A key's 32 coordinates are stored in the order the score
-  // correction contracts them: k-slice ks2, half hf, slot e  <->  r = 16 ks2 + 4 hf + 8 (e / 4) + e % 4, which is
-  // the order in which a lane of the 32 x 32 accumulator holds U^T q of its query row (see make_qt).
+  // correction contracts them: lane group grp, slot e  <->  r = 16 (e / 4) + 4 grp + e % 4, which is the order in which
+  // a lane of the 16 x 16 accumulators holds U^T q of its query row.
   auto coords_tile = [&](const unsigned char* Kb, unsigned long long bits, unsigned char* zdst) __attribute__((always_inline)) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
@@ -617,193 +678,173 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     const int kblk = wave;
     if (kblk >= BK / 16) return;                          // wave-uniform
     const unsigned bits16 = (unsigned)((bits >> (16 * kblk)) & 0xffffull);
-    // this lane's results: key 16 kblk + j, coordinates r = 16 half + 4 g + i  ->  k-slice half, hf = g & 1, slots 4 (g / 2) + i
-    unsigned char* zrow = zdst + (16 * kblk + j) * PIPE_Z_LD + 16 * (g & 1) + 8 * (g >> 1);
+    // this lane's results: key 16 kblk + j, coordinates r = 16 half + 4 g + i  ->  group g, slots 4 half + i
+    unsigned char* zrow = zdst + (16 * kblk + j) * PIPE_Z_LD + 16 * g;
     if (bits16 == 0) {
-      *reinterpret_cast<uint2*>(zrow) = make_uint2(0, 0);
-      *reinterpret_cast<uint2*>(zrow + 32) = make_uint2(0, 0);
+      *reinterpret_cast<uint4*>(zrow) = make_uint4(0, 0, 0, 0);
       return;
     }
     const unsigned char* krow = Kb + (16 * kblk + j) * RB;
-    bf16x8 kreg[KS2];   // K^T as B operand: lane (col = key j, k = d = 32 s + 8 g + e) = logical chunk 4 s + g
+    bf16x8 kreg[KS];   // K^T as B operand: lane (col = key j, k = d = 32 s + 8 g + e) = logical chunk 4 s + g
 #pragma unroll
-    for (int s = 0; s < KS2; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j)));
+    for (int s = 0; s < KS; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j)));
     const float mbit = ((bits16 >> j) & 1u) ? 1.f : 0.f;
+    bf16x8 z8;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // two chains: even and odd slices of d
 #pragma unroll
-      for (int s = 0; s < KS2; ++s) {
-        const bf16x8 ua = *reinterpret_cast<const bf16x8*>(U1 + ((half * KS2 + s) * 64 + ln) * 8);
+      for (int s = 0; s < KS; ++s) {
+        const bf16x8 ua = *reinterpret_cast<const bf16x8*>(U1 + ((half * KS + s) * 64 + ln) * 8);
         acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua, kreg[s], acc[s & 1], 0, 0, 0);
       }
       const f32x4 c4 = *reinterpret_cast<const f32x4*>(cvec + 16 * half + 4 * g);
-      bf16x4 z4;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) z4[i] = (__bf16)((acc[0][i] + acc[1][i]) * (c4[i] * mbit));
-      *reinterpret_cast<uint2*>(zrow + 32 * half) = __builtin_bit_cast(uint2, z4);
+      for (int i = 0; i < 4; ++i) z8[4 * half + i] = (__bf16)((acc[0][i] + acc[1][i]) * (c4[i] * mbit));
     }
+    *reinterpret_cast<bf16x8*>(zrow) = z8;
   };
 
   for (int pass = 0;; ++pass) {      // one turn per block of query rows (indentation of the body kept flat)
   // ---- math pieces ----
-  f32x16 oacc[RPW][DB];
+  f32x4 oacc[DT][2], lacc[2];              // O^T tiles (16 columns x 16 rows) and, in all four elements alike, the row sums
 #pragma unroll
-  for (int rp = 0; rp < RPW; ++rp)
+  for (int rt = 0; rt < 2; ++rt) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[rp][db][r] = 0.f;
+    for (int dt = 0; dt < DT; ++dt) oacc[dt][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    lacc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  pipe_pin_acc(oacc, lacc);
   const float c2 = a.scale * 1.4426950408889634f;   // probabilities are exp2(s * c2 - m)
-  // m_run: reference exponent of the row (in units of s * c2).  It follows the row maximum lazily: it is only
-  // raised when the maximum has moved more than kSlack above it, so probabilities stay below 2^kSlack and the
-  // output accumulators are rescaled a handful of times per row instead of once per block.
-  constexpr float kSlack = 8.f;
-  float m_run[RPW], l_run[RPW];
-#pragma unroll
-  for (int rp = 0; rp < RPW; ++rp) { m_run[rp] = -1e30f; l_run[rp] = 0.f; }
+  // m_run: reference exponent of the row (in units of s * c2).  It follows the row maximum lazily: when it is raised it is put
+  // kLead above the maximum, and it is raised only where a probability reaches 2, or (in the wave's last tile, which takes
+  // its maxima anyway) where the maximum has moved more than kSlack since; so probabilities stay below 2 and the output
+  // accumulators are rescaled a handful of times per row instead of once per block.
+  constexpr float kLead = 11.f, kSlack = 8.f;
+  float m_run[2] = {-1e30f, -1e30f};
   // The tile loops live in a (generic, always inlined) lambda of their own.  This changes nothing in what is
   // computed; the compiler allocates the loop's registers differently for it, and the launch is 3 % faster.
   auto run_block = [&](auto) __attribute__((always_inline)) {
 
-  // LDS byte addresses of this lane's operands inside stage 0 (stage and row-block offsets are immediates):
-  // K: row l32 (+32), logical chunk 2 ks + hf, physical chunk (2 ks + hf) ^ (l32 & 15)
-  // V: row 16 kb + 4 hf + (li >> 2) (+8), logical chunk 4 db + 2 (grp & 1) + ((li & 3) >> 1), physical chunk 4 (db ^ q) + low
-  uint32_t kaddr[KS], vaddr[DB];
+  // LDS byte addresses of this lane's operands inside stage 0 (stage, key-tile and row offsets are immediates):
+  // K: row l16 (+ 16), logical chunk 4 ks + grp
+  // V: row 4 grp + (l16 >> 2) (+ 16), logical chunk 2 dt + ((l16 & 3) >> 1)
+  uint32_t kaddr[KS], vaddr[DT];
   {
-    const int kfix = l32 * RB + 16 * (hf ^ pipe_k_swizzle<D>(l32));
+    const int kfix = l16 * RB + 16 * (grp ^ pipe_k_swizzle<D>(l16));
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) kaddr[ks] = kst_base + (uint32_t)(kfix ^ (ks << 5));
-    const int li = lane & 15, grp = lane >> 4;
-    const int vfix = (4 * hf + (li >> 2)) * RB + 16 * (pipe_v_swizzle<D>(li >> 2) + 2 * (grp & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
+    for (int ks = 0; ks < KS; ++ks) kaddr[ks] = kst_base + (uint32_t)(kfix ^ (ks << 6));
+    const int vrow = 4 * grp + (l16 >> 2);
+    const int vfix = vrow * RB + 16 * (((l16 & 3) >> 1) ^ pipe_v_swizzle<D>(vrow)) + 8 * (l16 & 1);
 #pragma unroll
-    for (int db = 0; db < DB; ++db) vaddr[db] = vst_base + (uint32_t)(vfix ^ (db << 6));
+    for (int dt = 0; dt < DT; ++dt) vaddr[dt] = vst_base + (uint32_t)(vfix ^ (dt << 5));
   }
+  const bf16x8 zeros8 = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+  bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+  asm volatile("" : "+v"(ones));           // kept in registers
 
-  // Part [KS0, KS1) of one 32-key block of S^T (32 keys x 32 RPW rows) = K rows . Q^T ; off = LDS byte offset
-  // of the block's first row.  Each K fragment is read once and used for every row block of the wave.
-  auto qk_part = [&](auto ks0_c, auto ks1_c, int off, f32x16 (&sn)[RPW]) __attribute__((always_inline)) {
-    constexpr int KS0 = decltype(ks0_c)::value, KS1 = decltype(ks1_c)::value;
-    if (KS0 == 0) {
+  // Scores of one 32-key block: S^T tiles [key tile][row tile]; off = LDS byte offset of the block's first row.
+  auto kfrag = [&](int i, int off) __attribute__((always_inline)) -> bf16x8 {        // fragment i: slice i / 2, key tile i % 2
+    return *(pipe_lds_bf16x8_ptr)(uintptr_t)(kaddr[i >> 1] + off + 16 * (i & 1) * RB);
+  };
+  auto qk_one = [&](int i, const bf16x8& k, f32x4 (&sn)[2][2]) __attribute__((always_inline)) {
 #pragma unroll
-      for (int rp = 0; rp < RPW; ++rp)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sn[rp][r] = 0.f;
+    for (int rt = 0; rt < 2; ++rt) {
+      if (i < 2) pipe_mfma_first(sn[i & 1][rt], k, qf[rt * KS + (i >> 1)]);
+      else pipe_mfma(sn[i & 1][rt], k, qf[rt * KS + (i >> 1)]);
     }
+  };
+  auto qk_block = [&](int off, f32x4 (&sn)[2][2]) __attribute__((always_inline)) {
+    bf16x8 kf[2 * KS];
 #pragma unroll
-    for (int ks = KS0; ks < KS1; ++ks) {
-      const bf16x8 a0 = *(pipe_lds_bf16x8_ptr)(uintptr_t)(kaddr[ks] + off);
+    for (int i = 0; i < 2 * KS; ++i) kf[i] = kfrag(i, off);
+    __builtin_amdgcn_sched_barrier(0);     // all of them on their way before the first product
 #pragma unroll
-      for (int rp = 0; rp < RPW; ++rp) sn[rp] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, qf[rp][ks], sn[rp], 0, 0, 0);
-    }
+    for (int i = 0; i < 2 * KS; ++i) qk_one(i, kf[i], sn);
   };
   using IC0 = std::integral_constant<int, 0>;
-  using ICH = std::integral_constant<int, KS / 2>;
-  using ICK = std::integral_constant<int, KS>;
-  // causal mask of the 32-key block starting at key j0, row block rp
-  auto causal_mask = [&](int j0, int rp, f32x16& sv) __attribute__((always_inline)) {
-    const int jbase = j0 + 4 * hf, qi = qi0 + 32 * rp;
+  // causal mask of the 32-key block starting at key j0
+  auto causal_mask = [&](int j0, f32x4 (&sv)[2][2]) __attribute__((always_inline)) {
+    const int jbase = j0 + 4 * grp;
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
-      if (jbase + 8 * (r >> 2) + (r & 3) > qi) sv[r] = -INFINITY;
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (jbase + 16 * kt + i > qi0 + 16 * rt) sv[kt][rt][i] = -INFINITY;
   };
-  // Softmax of one 32-key block, first part: row maximum (of s * c2) over the block, both halves of the row.
-  auto block_max = [&](const f32x16& sv) __attribute__((always_inline)) -> float {
-    float mx = pipe_max3(sv[0], sv[1], sv[2]);
-#pragma unroll
-    for (int r = 3; r < 15; r += 2) mx = pipe_max3(mx, sv[r], sv[r + 1]);
-    mx = fmaxf(mx, sv[15]) * c2;
-    // the other 16 keys of this query row live in lane ^ 32
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-    return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  // Row maximum (of s * c2) over one 32-key block, all lanes of the row.
+  auto block_max = [&](int rt, const f32x4 (&sv)[2][2]) __attribute__((always_inline)) -> float {
+    float mx = pipe_max3(sv[0][rt][0], sv[0][rt][1], sv[0][rt][2]);
+    mx = pipe_max3(mx, sv[0][rt][3], sv[1][rt][0]);
+    mx = pipe_max3(mx, sv[1][rt][1], sv[1][rt][2]);
+    mx = fmaxf(mx, sv[1][rt][3]) * c2;
+    // the other 24 keys of this query row live in lanes ^ 16, ^ 32 and ^ 48
+    const auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = fmaxf(__uint_as_float(s16[0]), __uint_as_float(s16[1]));
+    const auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
   };
-  // Raise the reference exponent of the rows whose maximum ran away from it, and rescale their sums.  The output
-  // accumulators are rescaled by rescale_outputs(), which the caller runs once every PV product whose
-  // probabilities were formed against the old reference has been accumulated.
-  float alpha_pend[RPW];
-  bool rescale_pend[RPW];                // wave-uniform
+  // Raise the reference exponent of the rows whose maximum over the block ran away from it, and rescale their outputs and sums
+  // (every PV product whose probabilities were formed against the old reference has been accumulated).
+  auto raise_reference = [&](const f32x4 (&sv)[2][2], bool empty = false) __attribute__((always_inline)) {
+    const float mx[2] = {block_max(0, sv) + kLead, block_max(1, sv) + kLead};
+    const bool need0 = mx[0] > m_run[0] + kSlack, need1 = mx[1] > m_run[1] + kSlack;
+    if (__any(need0 | need1)) {    // a handful of times per row
+      const float m0 = need0 ? mx[0] : m_run[0], m1 = need1 ? mx[1] : m_run[1];
+      const float alpha[2] = {__builtin_amdgcn_exp2f(m_run[0] - m0), __builtin_amdgcn_exp2f(m_run[1] - m1)};
+      m_run[0] = m0;
+      m_run[1] = m1;
+      if (empty) return;             // nothing accumulated yet
+      // (the maxima and exponentials above lie between the last PV product and these)
 #pragma unroll
-  for (int rp = 0; rp < RPW; ++rp) { alpha_pend[rp] = 1.f; rescale_pend[rp] = false; }
-  auto raise_reference = [&](int rp, float mfull) __attribute__((always_inline)) {
-    const bool need = mfull > m_run[rp] + kSlack;
-    if (__any(need)) {   // a handful of times per row
-      const float m_new = need ? mfull : m_run[rp];
-      const float alpha = __builtin_amdgcn_exp2f(m_run[rp] - m_new);
-      m_run[rp] = m_new;
-      l_run[rp] *= alpha;
-      alpha_pend[rp] = alpha;            // rescale_outputs() has run since the last raise of this row block
-      rescale_pend[rp] = true;
+      for (int rt = 0; rt < 2; ++rt) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) oacc[dt][rt][i] *= alpha[rt];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lacc[rt][i] *= alpha[rt];
+      }
+      pipe_pin_acc(oacc, lacc);
     }
   };
-  auto rescale_outputs = [&]() __attribute__((always_inline)) {
+  // Probabilities of one block, packed as P^T operands (lane group grp, slot e <-> key 16 (e / 4) + 4 grp + e % 4).
+  // Returns the bits of all of them or-ed together: they are not negative, so bit 14 or 30 is set if and only if one
+  // of them is 2 or more (or not a number).
+  auto block_exp = [&](const f32x4 (&sv)[2][2], bf16x8 (&pb)[2]) __attribute__((always_inline)) -> uint32_t {
+    uint32_t bits = 0;
 #pragma unroll
-    for (int rp = 0; rp < RPW; ++rp)
-      if (rescale_pend[rp]) {
+    for (int rt = 0; rt < 2; ++rt) {
+      const float mneg = -m_run[rt];
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) oacc[rp][db][r] *= alpha_pend[rp];
-        rescale_pend[rp] = false;
-      }
-  };
-  // Second part: probabilities, packed P^T, row sum of the rounded probabilities (the values the PV product uses).
-  auto block_exp = [&](int rp, f32x16& sv, bf16x8 (&pb)[2]) __attribute__((always_inline)) {
-    const float mneg = -m_run[rp];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) sv[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], c2, mneg));
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      pb[0][e] = (__bf16)sv[e];
-      pb[1][e] = (__bf16)sv[8 + e];
+      for (int e = 0; e < 8; ++e) pb[rt][e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sv[e >> 2][rt][e & 3], c2, mneg));
+      const u32x4 w = __builtin_bit_cast(u32x4, pb[rt]);
+      bits = (w[0] | w[1] | bits);
+      bits = (w[2] | w[3] | bits);
     }
-    float lsum = l_run[rp];
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int e = 0; e < 8; e += 2) {
-        const bf16x2 pp = {pb[kb][e], pb[kb][e + 1]};
-        lsum = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, lsum, false);
-      }
-    l_run[rp] = lsum;
+    return bits;
   };
-  // The same for the schedule without a per-block maximum: the scores are left untouched, the sum of the rounded
-  // probabilities is returned instead of being added to the row's running sum.
-  auto block_exp_sum = [&](const f32x16& sv, bf16x8 (&pb)[2], float& lsum) __attribute__((always_inline)) {
-    const float mneg = -m_run[0];
-    float pv[16];
+  // O^T += V^T P^T for one 32-key block, and the row sums of P^T (the rounded probabilities, those that the products use)
+  // as one more output tile whose V^T is all ones; off = LDS byte offset of the block's first row
+  auto pv_block = [&](int off, bf16x8 (&pb)[2]) __attribute__((always_inline)) {
+    s16x4 lo[DT], hi[DT];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) pv[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], c2, mneg));
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      pb[0][e] = (__bf16)pv[e];
-      pb[1][e] = (__bf16)pv[8 + e];
+    for (int dt = 0; dt < DT; ++dt) {
+      lo[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)(vaddr[dt] + off));
+      hi[dt] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)(vaddr[dt] + off + 16 * RB));
     }
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    float acc = 0.f;
+    __builtin_amdgcn_sched_barrier(0);     // all of them on their way before the first product
+    pipe_mfma_operand_guard(pb);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+    for (int rt = 0; rt < 2; ++rt) pipe_mfma(lacc[rt], ones, pb[rt]);
 #pragma unroll
-      for (int e = 0; e < 8; e += 2) {
-        const bf16x2 pp = {pb[kb][e], pb[kb][e + 1]};
-        acc = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, acc, false);
-      }
-    lsum = acc;
-  };
-  // O^T += V^T P^T for one 32-key block; off = LDS byte offset of the block's first row
-  auto pv_half = [&](int off, const bf16x8 (&pb)[RPW][2]) __attribute__((always_inline)) {
+    for (int dt = 0; dt < DT; ++dt) {
+      const bf16x4 lo4 = __builtin_bit_cast(bf16x4, lo[dt]), hi4 = __builtin_bit_cast(bf16x4, hi[dt]);
+      const bf16x8 va = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)(vaddr[db] + off + (16 * kb) * RB));
-        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)(vaddr[db] + off + (16 * kb + 8) * RB));
-        const bf16x4 lo4 = __builtin_bit_cast(bf16x4, lo), hi4 = __builtin_bit_cast(bf16x4, hi);
-        const bf16x8 va = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
-#pragma unroll
-        for (int rp = 0; rp < RPW; ++rp)
-          oacc[rp][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[rp][kb], oacc[rp][db], 0, 0, 0);
-      }
+      for (int rt = 0; rt < 2; ++rt) pipe_mfma(oacc[dt][rt], va, pb[rt]);
     }
   };
 
@@ -814,9 +855,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   dma_wait_vmcnt<0>();   // also covers the Q, U and mask loads issued after the tile loads
   q_operands();
 #pragma unroll
-  for (int rp = 0; rp < RPW; ++rp)
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[rp][ks]));   // pin the compiler's own wait for Q here, not in the loop
+  for (int i = 0; i < 2 * KS; ++i) asm volatile("" : "+v"(qf[i]));   // pin the compiler's own wait for Q here, not in the loop
   dma_barrier();
   unsigned long long anyw = 0ull;      // bit i: tile 64 (t / 64) + i holds a highlighted key (0 when not steering)
   // Next tile index at which the loop has something to do besides attention: a tile with highlighted keys, or
@@ -829,27 +868,25 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   int tile_evt = 0x7fffffff;
   int ztile = -1;                      // score-side form: the tile whose coordinates were computed last
   if (STEER && !DENSE) {
-    // U^T q of this wave's 32 query rows: (U_cat^T Q^T)[r][row] on the 32 x 32 MFMA, A = U_cat^T rows r = l32 taken
-    // from the operand store of U_cat^T K^T (entry (rb, s), lane (g, j) with r = 16 rb + j, d = 32 s + 8 g + e),
-    // B = the Q fragments.  A lane ends up with its query row's coordinates r = 8 (i / 4) + 4 hf + i % 4, i = 0..15:
-    // converted to bf16 they are the two B operands of the score correction as they stand, kept in LDS (each lane
-    // reads back what it wrote: no barrier).
+    // U^T q of this wave's 32 query rows: (U_cat^T Q^T)[r][row], A = the operand store of U_cat^T K^T as it stands, B = the Q
+    // fragments.  A lane ends up with its query rows' coordinates r = 16 rb + 4 grp + i: converted to bf16 they are the
+    // B operands of the score correction, kept in LDS (each lane reads back what it wrote: no barrier).
     if (steer_on) {
-      f32x16 qt;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) qt[r] = 0.f;
+      for (int rt = 0; rt < 2; ++rt) {
+        bf16x8 q8;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const bf16x8 ua = *reinterpret_cast<const bf16x8*>(
-            U1 + ((((l32 >> 4) * KS2 + (ks >> 1)) * 64) + (2 * (ks & 1) + hf) * 16 + (l32 & 15)) * 8);
-        qt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ua, qf[0][ks], qt, 0, 0, 0);
+        for (int rb2 = 0; rb2 < 2; ++rb2) {
+          f32x4 qt = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks)
+            qt = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8*>(U1 + ((rb2 * KS + ks) * 64 + lane) * 8),
+                                                         qf[rt * KS + ks], qt, 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) q8[4 * rb2 + i] = (__bf16)qt[i];
+        }
+        *reinterpret_cast<bf16x8*>(qtbuf + wave * PIPE_QT_BYTES + 1024 * rt + lane * 16) = q8;
       }
-      bf16x8 q8[2];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) { q8[0][e] = (__bf16)qt[e]; q8[1][e] = (__bf16)qt[8 + e]; }
-      unsigned char* qp = qtbuf + wave * PIPE_QT_BYTES + lane * 16;
-      *reinterpret_cast<bf16x8*>(qp) = q8[0];
-      *reinterpret_cast<bf16x8*>(qp + PIPE_QT_BYTES / 2) = q8[1];
     }
     anyw = any_word(0);
     if (anyw & 1ull) {
@@ -868,36 +905,37 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     tile_evt = next_event(1);
   }
   // Score correction of one 32-key block of S^T (keys keyoff .. keyoff + 31 of `tile`): += Z (32 keys x 32 r) . (U^T q)^T,
-  // two MFMAs; A = the keys' coordinates from the tile's buffer, B = this wave's U^T q operands.
-  auto corr = [&](int tile, int keyoff, f32x16 (&sv)[RPW]) __attribute__((always_inline)) {
-    const unsigned char* zp = zbuf + (tile & 1) * PIPE_Z_BYTES + (keyoff + l32) * PIPE_Z_LD + 16 * hf;
+  // four MFMAs; A = the keys' coordinates from the tile's buffer, B = this wave's U^T q operands.
+  auto corr = [&](int tile, int keyoff, f32x4 (&sv)[2][2]) __attribute__((always_inline)) {
+    const unsigned char* zp = zbuf + (tile & 1) * PIPE_Z_BYTES + (keyoff + l16) * PIPE_Z_LD + 16 * grp;
     const unsigned char* qp = qtbuf + wave * PIPE_QT_BYTES + lane * 16;
+    const bf16x8 qb[2] = {*reinterpret_cast<const bf16x8*>(qp), *reinterpret_cast<const bf16x8*>(qp + 1024)};
 #pragma unroll
-    for (int k2 = 0; k2 < 2; ++k2) {
-      const bf16x8 za = *reinterpret_cast<const bf16x8*>(zp + 32 * k2);
-      const bf16x8 qb = *reinterpret_cast<const bf16x8*>(qp + (PIPE_QT_BYTES / 2) * k2);
-      sv[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(za, qb, sv[0], 0, 0, 0);
+    for (int kt = 0; kt < 2; ++kt) {
+      const bf16x8 za = *reinterpret_cast<const bf16x8*>(zp + 16 * kt * PIPE_Z_LD);
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) pipe_mfma(sv[kt][rt], za, qb[rt]);
     }
+    pipe_mfma_result_guard(sv);
   };
 
-  bf16x8 pb[RPW][2];           // probabilities (P^T operand) of the block whose PV product is next; none at first
+  bf16x8 pb[2] = {zeros8, zeros8};   // probabilities (P^T operands) of the block whose PV product is next; none at first
+  f32x4 sc0[2][2], sc1[2][2];  // scores of keys 0..31 / 32..63 of the current tile
 #pragma unroll
-  for (int rp = 0; rp < RPW; ++rp)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { pb[rp][0][e] = (__bf16)0.f; pb[rp][1][e] = (__bf16)0.f; }
-  f32x16 sc0[RPW], sc1[RPW];   // scores of keys 0..31 / 32..63 of the current tile, per row block
-#pragma unroll
-  for (int rp = 0; rp < RPW; ++rp)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) { sc0[rp][r] = 0.f; sc1[rp][r] = 0.f; }
+  for (int i = 0; i < 4; ++i) sc0[i >> 1][i & 1] = sc1[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
   bf16x8 kpre[2];              // first two K fragments of the block the next step scores (see `step`)
   if (0 <= tw_last) {
-    qk_part(IC0{}, ICK{}, 0, sc0);
+    qk_block(0, sc0);
+    pipe_mfma_result_guard(sc0);
+    // The first reference of rows that see the whole block: its maximum (before the score correction, if it gets one).  Rows that
+    // start with a masked block take theirs after the mask.
+    if (0 < tw_last) {
 #pragma unroll
-    for (int rp = 0; rp < RPW; ++rp) pipe_mfma_result_guard(sc0[rp]);
+      for (int rt = 0; rt < 2; ++rt) m_run[rt] = fmaxf(block_max(rt, sc0) + kLead, m_run[rt]);
+    }
   }
 #pragma unroll
-  for (int i = 0; i < 2; ++i) kpre[i] = *(pipe_lds_bf16x8_ptr)(uintptr_t)(kaddr[i] + HB);
+  for (int i = 0; i < 2; ++i) kpre[i] = kfrag(i, HB);
 
   // `top` of iteration t: request K(t+2), then the V blocks 2t+3 and 2t+4; their ring slots are free since the
   // barrier of iteration t - 1.  Bottom: everything but those two V blocks must have landed before the next
@@ -947,7 +985,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
           edit_tile(Kst + (tn % 3) * TB, hlbits[tn]);
           dma_barrier();
 #pragma unroll
-          for (int i = 0; i < 2; ++i) kp[i] = *(pipe_lds_bf16x8_ptr)(uintptr_t)(kaddr[i] + knext_off);
+          for (int i = 0; i < 2; ++i) kp[i] = kfrag(i, knext_off);
         }
       }
     }
@@ -963,84 +1001,77 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // the block at KNEXT, the one the following step scores.
   //
   // No row maximum in the common case.  The probabilities of `cur` are formed against the row's reference exponent
-  // as it stands; their sum over the block tells whether that was safe: a sum beyond kSumLimit (or one that is not
-  // a number) means some score ran far ahead of the reference, and only then is the block's maximum computed, the
+  // as it stands, and their bits tell whether that was safe: a probability of 2 or more (or one that is not a number)
+  // means some score ran far ahead of the reference, and only then is the block's maximum computed, the
   // reference raised and the block's probabilities formed again (a handful of times per row; the first block of a
   // row always takes this turn, its reference starts at -1e30).  The common case is 16 multiply-adds, 16
-  // exponentials, 8 packings and 8 dot products per 16 MFMAs: no three-input maxima, no cross-lane exchange, no
-  // raise test.
-  auto kfrag = [&](int ks, int off) __attribute__((always_inline)) -> bf16x8 {
-    return *(pipe_lds_bf16x8_ptr)(uintptr_t)(kaddr[ks] + off);
-  };
-  auto qk_one = [&](int ks, const bf16x8& a0, f32x16 (&sn)[RPW]) __attribute__((always_inline)) {
-#pragma unroll
-    for (int rp = 0; rp < RPW; ++rp) sn[rp] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, qf[rp][ks], sn[rp], 0, 0, 0);
-  };
-  constexpr float kSumLimit = 4096.f;          // probabilities stay below 2^12
-  auto step = [&](auto koff_c, uint32_t knext0, uint32_t knext1, auto voff_c, f32x16 (&cur)[RPW], f32x16 (&next)[RPW], bf16x8 (&pb)[RPW][2],
+  // exponentials, 8 packings and 4 ors per 34 MFMAs: no three-input maxima, no cross-lane exchange, no raise test, and
+  // the row sums are two of the MFMAs (as dot products with ones, eight per step, they took a ninth of the step's time).
+  auto step = [&](auto koff_c, uint32_t knext, auto voff_c, f32x4 (&cur)[2][2], f32x4 (&next)[2][2], bf16x8 (&pb)[2],
                   bf16x8 (&kpre)[2]) __attribute__((always_inline)) {
-    static_assert(RPW == 1, "the schedule below is written for one row block per wave");
     const int KOFF = koff_c, VOFF = voff_c;
+    // Program order, one MFMA per slot: the scores of the next block (two per K fragment), the row sums and the outputs of the block before
+    // (two per V fragment).  Behind an MFMA comes its share of the LDS reads, issued RA MFMAs ahead of their use, and of the softmax:
+    // the multiply-add and the exponential of an element in turn (a run of exponentials stalls the wave in front of the next
+    // MFMA), a packing for every second element.
+    constexpr int NQ = 4 * KS, NM = NQ + 2 + 2 * DT;        // MFMAs: scores, all
+    constexpr int RA = PIPE_RA;
+    static_assert(RA <= NQ + 1, "reads start in the step itself");
+    bf16x8 kf[2 * KS];
+    s16x4 vlo[DT], vhi[DT];
+    float x[16], pr[16];
+    bf16x2 pk[8];
+    kf[0] = kpre[0];
+    kf[1] = kpre[1];
+    __builtin_amdgcn_sched_barrier(0);
+    pipe_static_for<NM>([&](auto m_c) __attribute__((always_inline)) {
+      constexpr int m = decltype(m_c)::value;
+      if constexpr (m < NQ) {
+        constexpr int f = m >> 1, kt = f & 1, rt = m & 1;
+        if constexpr (f < 2) pipe_mfma_first(next[kt][rt], kf[f], qf[rt * KS + (f >> 1)]);
+        else pipe_mfma(next[kt][rt], kf[f], qf[rt * KS + (f >> 1)]);
+      } else if constexpr (m < NQ + 2) {
+        pipe_mfma(lacc[m - NQ], ones, pb[m - NQ]);
+      } else {
+        constexpr int dt = (m - NQ - 2) >> 1, rt = m & 1;
+        const bf16x4 lo4 = __builtin_bit_cast(bf16x4, vlo[dt]), hi4 = __builtin_bit_cast(bf16x4, vhi[dt]);
+        const bf16x8 va = __builtin_shufflevector(lo4, hi4, 0, 1, 2, 3, 4, 5, 6, 7);
+        pipe_mfma(oacc[dt][rt], va, pb[rt]);
+      }
+      constexpr int f = pipe_kfrag_at(m, KS, RA);
+      if constexpr (f >= 0) kf[f] = kfrag(f, KOFF);
+      constexpr int v = m - (NQ + 2 - RA - 1);
+      if constexpr (v >= 0 && v < 2 * DT) {
+        const uint32_t ad = vaddr[v >> 1] + VOFF;
+        if constexpr (v & 1) vhi[v >> 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)(ad + 16 * RB));
+        else vlo[v >> 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((dma_lds_s16x4_ptr)(uintptr_t)ad);
+      }
+      if constexpr (m == NM - 4) kpre[0] = *(pipe_lds_bf16x8_ptr)(uintptr_t)knext;
+      if constexpr (m == NM - 2) kpre[1] = *(pipe_lds_bf16x8_ptr)(uintptr_t)(knext + 16 * RB);
+      constexpr int e0 = pipe_element_at(m, NM), e1 = pipe_element_at(m - 1, NM), e2 = pipe_element_at(m - 2, NM);
+      // (volatile: the compiler would form all of them at the first one's place)
+      if constexpr (e0 >= 0) asm volatile("v_fma_f32 %0, %1, %2, -%3" : "=v"(x[e0]) : "v"(cur[(e0 >> 2) & 1][e0 >> 3][e0 & 3]), "s"(c2), "v"(m_run[e0 >> 3]));
+      if constexpr (e1 >= 0) pr[e1] = __builtin_amdgcn_exp2f(x[e1]);
+      if constexpr (e2 >= 0 && (e2 & 1)) pk[e2 >> 1] = bf16x2{(__bf16)pr[e2 - 1], (__bf16)pr[e2]};
+      __builtin_amdgcn_sched_barrier(0);
+    });
     bf16x8 pn[2];
-    float lb;
+    uint32_t bits = 0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) next[0][r] = 0.f;
-    qk_one(0, kpre[0], next);
-    qk_one(1, kpre[1], next);
-    const bf16x8 k2 = kfrag(2, KOFF), k3 = kfrag(3, KOFF);
-    qk_one(2, k2, next);
-    qk_one(3, k3, next);
-    if constexpr (KS == 8) {
-      const bf16x8 k4 = kfrag(4, KOFF), k5 = kfrag(5, KOFF);
-      qk_one(4, k4, next);
-      qk_one(5, k5, next);
-      const bf16x8 k6 = kfrag(6, KOFF), k7 = kfrag(7, KOFF);
-      qk_one(6, k6, next);
-      qk_one(7, k7, next);
-    }
-    pv_half(VOFF, pb);
-    kpre[0] = *(pipe_lds_bf16x8_ptr)(uintptr_t)knext0;
-    kpre[1] = *(pipe_lds_bf16x8_ptr)(uintptr_t)knext1;
-    block_exp_sum(cur[0], pn, lb);
-    // Program order: every MFMA is followed by its share of the 24 LDS reads, two plain vector instructions and
-    // (from the second MFMA on, when the first multiply-adds have been issued) one exponential: the transcendental
-    // unit takes one instruction about every ten cycles, and a run of exponentials stalls the wave in front of
-    // the next MFMA.
-    __builtin_amdgcn_sched_group_barrier(0x100, 2, 2);          // fragments 2 and 3
-    if constexpr (KS == 8) {
+    for (int e = 0; e < 16; ++e) pn[e >> 3][e & 7] = pk[e >> 1][e & 1];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 2);
-        if (i < 14 && !(i & 1)) __builtin_amdgcn_sched_group_barrier(0x100, 2, 2);
-        if (i < 15 && ((i & 1) || i == 14)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 2);
-        __builtin_amdgcn_sched_group_barrier(0x002, 2, 2);
-        if (i >= 1) __builtin_amdgcn_sched_group_barrier(0x400, 1, 2);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x400, 1, 2);
-    } else {       // half the MFMAs for the same softmax: twice the vector work beside each
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 2);
-        if (i < 4) __builtin_amdgcn_sched_group_barrier(0x100, 2, 2);
-        if (i == 4 || i == 5) __builtin_amdgcn_sched_group_barrier(0x100, 1, 2);
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 2);
-        if (i >= 1) __builtin_amdgcn_sched_group_barrier(0x400, 2, 2);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x400, 2, 2);
-    }
+    for (int k = 0; k < 8; k += 2) bits = __builtin_bit_cast(uint32_t, pk[k]) | __builtin_bit_cast(uint32_t, pk[k + 1]) | bits;
     // The probabilities are first used by the next step: without a use here their whole computation is sunk
     // into that step, away from the MFMAs it is meant to share the issue port with.
-    asm volatile("" : "+v"(pn[0]), "+v"(pn[1]), "+v"(lb));
+    asm volatile("" : "+v"(pn[0]), "+v"(pn[1]), "+v"(bits));
     __builtin_amdgcn_sched_barrier(0);
-    if (__builtin_expect(__any(!(lb <= kSumLimit)), 0)) {
+    if (__builtin_expect(__any((bits & 0x40004000u) != 0u), 0)) {
       // `cur` was produced by the previous step's MFMAs: far enough behind for the inline-assembly maxima
-      raise_reference(0, block_max(cur[0]));
-      block_exp_sum(cur[0], pn, lb);
-      rescale_outputs();       // after this step's PV product, whose probabilities were formed against the old reference
+      raise_reference(cur);    // after this step's PV product, whose probabilities were formed against the old reference
+      block_exp(cur, pn);
     }
-    l_run[0] += lb;
-    pb[0][0] = pn[0];
-    pb[0][1] = pn[1];
+    pb[0] = pn[0];
+    pb[1] = pn[1];
   };
   // One tile every row of this wave sees in full; ST = t % 3 is compile-time so that every LDS read address is
   // a register plus an immediate.  Enters with S(t, keys 0..31) in sc0 and the probabilities of the block before
@@ -1054,12 +1085,12 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(kaddr[ks]));
 #pragma unroll
-    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(vaddr[db]));
-    step(integral_constant<int, ST * TB + HB>{}, kaddr[0] + ((ST + 1) % 3) * TB, kaddr[1] + ((ST + 1) % 3) * TB, integral_constant<int, ((2 * ST + 5) % 6) * HB>{}, sc0, sc1, pb, kpre);
+    for (int dt = 0; dt < DT; ++dt) asm volatile("" : "+v"(vaddr[dt]));
+    step(integral_constant<int, ST * TB + HB>{}, kaddr[0] + ((ST + 1) % 3) * TB, integral_constant<int, ((2 * ST + 5) % 6) * HB>{}, sc0, sc1, pb, kpre);
     if (STEER && !DENSE && __builtin_expect(ztile == t, 0)) corr(t, 32, sc1);
     top(std::true_type{}, st_c, t);
     if (kEventsInHot) events(t, ((ST + 1) % 3) * TB, kpre);
-    step(integral_constant<int, ((ST + 1) % 3) * TB>{}, kaddr[0] + ((ST + 1) % 3) * TB + HB, kaddr[1] + ((ST + 1) % 3) * TB + HB, integral_constant<int, 2 * ST * HB>{}, sc1, sc0, pb, kpre);
+    step(integral_constant<int, ((ST + 1) % 3) * TB>{}, kaddr[0] + ((ST + 1) % 3) * TB + HB, integral_constant<int, 2 * ST * HB>{}, sc1, sc0, pb, kpre);
     bottom(std::true_type{}, t);
   };
 
@@ -1073,17 +1104,17 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
       asm volatile("" : "+v"(kaddr[ks]));
     }
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      vaddr[db] += dv;
-      asm volatile("" : "+v"(vaddr[db]));
+    for (int dt = 0; dt < DT; ++dt) {
+      vaddr[dt] += dv;
+      asm volatile("" : "+v"(vaddr[dt]));
     }
   };
-  auto ring_step = [&](int koff, int knext, int voff, f32x16 (&cur)[RPW], f32x16 (&next)[RPW]) __attribute__((always_inline)) {
-    uint32_t k0 = kaddr[0] + knext, k1 = kaddr[1] + knext;
-    asm volatile("" : "+v"(k0), "+v"(k1));
+  auto ring_step = [&](int koff, int knext, int voff, f32x4 (&cur)[2][2], f32x4 (&next)[2][2]) __attribute__((always_inline)) {
+    uint32_t k0 = kaddr[0] + knext;
+    asm volatile("" : "+v"(k0));
     move_addr(koff, voff);
     __builtin_amdgcn_sched_barrier(0);
-    step(IC0{}, k0, k1, IC0{}, cur, next, pb, kpre);
+    step(IC0{}, k0, IC0{}, cur, next, pb, kpre);
     move_addr(-koff, -voff);
   };
 
@@ -1100,6 +1131,15 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   while (t < tw_last) {
     if (t % 3 == 0) {
       using std::integral_constant;
+      // what the loop reads is in registers here (a reload from scratch memory that is first used in the loop is waited for in
+      // every turn of it, and with it the tile loads)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(kaddr[ks]));
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) asm volatile("" : "+v"(vaddr[dt]));
+#pragma unroll
+      for (int n = 0; n < SPW; ++n) asm volatile("" : "+v"(koff[n]), "+v"(voff[n]));
+      asm volatile("" : "+v"(ones), "+v"(m_run[0]), "+v"(m_run[1]));
 #pragma nounroll
       for (; t + 3 <= t_hot && (!STEER || kEventsInHot || tile_evt > t + 3); t += 3) {
         hot(integral_constant<int, 0>{}, t);
@@ -1129,7 +1169,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     const bool zt = STEER && !DENSE && ztile == t;     // before the event of tile t + 1 moves ztile on
     events(t, 0, kpre);                     // this wave scores nothing further; other waves may (kpre is dead here)
     if (owed) {
-      pv_half(owed_off, pb);
+      pv_block(owed_off, pb);
       owed = false;
     }
     if (t == tw_last) {
@@ -1137,31 +1177,28 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
       // last 32 sees all of its first.
       const int off = (t % 3) * TB;
       const bool second = (qw & 32) != 0;      // wave-uniform
-      if (second) qk_part(IC0{}, ICK{}, off + HB, sc1);
+      if (second) qk_block(off + HB, sc1);
       if (zt) {
         corr(t, 0, sc0);
         if (second) corr(t, 32, sc1);
       }
-      if (t > 0) pv_half((int)vpos(2 * t - 1), pb);      // the block before this tile (its softmax ran in the last step)
-      pipe_mfma_result_guard(sc0[0]);
-      if (!second) causal_mask(t * BK, 0, sc0[0]);
-      raise_reference(0, block_max(sc0[0]));
-      rescale_outputs();
-      block_exp(0, sc0[0], pb[0]);
-      pv_half((int)vpos(2 * t), pb);
+      if (t > 0) pv_block((int)vpos(2 * t - 1), pb);     // the block before this tile (its softmax ran in the last step)
+      auto last_block = [&](bool masked, bool empty, int j0, f32x4 (&sv)[2][2]) __attribute__((always_inline)) {
+        if (masked) causal_mask(j0, sv);
+        raise_reference(sv, empty);
+        block_exp(sv, pb);
+      };
+      last_block(!second, t == 0, t * BK, sc0);
+      pv_block((int)vpos(2 * t), pb);
       if (second) {
-        pipe_mfma_result_guard(sc1[0]);
-        causal_mask(t * BK + 32, 0, sc1[0]);
-        raise_reference(0, block_max(sc1[0]));
-        rescale_outputs();
-        block_exp(0, sc1[0], pb[0]);
+        last_block(true, false, t * BK + 32, sc1);
         owed = true;
         owed_off = (int)vpos(2 * t + 1);
       }
     }
     bottom(std::false_type{}, t);
   }
-  if (owed) pv_half(owed_off, pb);
+  if (owed) pv_block(owed_off, pb);
   };
   run_block(std::false_type{});
 
@@ -1174,7 +1211,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     dma_barrier();
     qb = nblocks - 1 - dealt;
     qw = qb * BQ + WR * rb;
-    qi0 = qw + l32;
+    qi0 = qw + l16;
     last_key = min(S, qb * BQ + BQ) - 1;
     ntiles = last_key / BK + 1;
     begin_block();
@@ -1182,29 +1219,35 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   if (!more) dma_barrier();    // the staging areas belong to the rings
   // Output: through the staging area, 64 of the 128 columns at a time, so that every store covers eight whole
   // 128-byte lines (straight from the accumulators a store is 32 pieces of 16 bytes: 13000 cycles per block).
-  const float l_tot = l_run[0] + __shfl_xor(l_run[0], 32);
-  const float inv = 1.f / l_tot;
+  asm volatile("s_nop 15" ::: "memory");   // the last PV product
+  pipe_pin_acc(oacc, lacc);
+  const int ln = opaque_lane();
+  const float inv[2] = {1.f / lacc[0][0], 1.f / lacc[1][0]};
 #pragma unroll
   for (int half = 0; half < D / 64; ++half) {
 #pragma unroll
-    for (int c4 = 0; c4 < 8; ++c4) {       // columns 64 half + 8 c4 + 4 hf .. + 3
-      bf16x4 o4;
+    for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[0][2 * half + c4 / 4][4 * (c4 & 3) + e] * inv);
-      *reinterpret_cast<uint2*>(stg_row(c4) + 8 * hf) = __builtin_bit_cast(uint2, o4);
-    }
+      for (int c = 0; c < 4; ++c) {        // columns 64 half + 16 c + 4 grp .. + 3
+        bf16x4 o4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(oacc[4 * half + c][rt][e] * inv[rt]);
+        *reinterpret_cast<uint2*>(stg_row(ln, rt, 2 * c + (ln >> 5)) + 8 * ((ln >> 4) & 1)) = __builtin_bit_cast(uint2, o4);
+      }
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int qi = qw_out + 8 * i + (lane >> 3);
-      const u32x4 line = *stg_line(i);
-      if (qi < S) *reinterpret_cast<u32x4*>(Og + ((tok0 + qi) * a.Hq + hq) * D + 64 * half + 8 * (lane & 7)) = line;
+      const int qi = qw_out + 8 * i + (ln >> 3);
+      const u32x4 line = *stg_line(ln, i);
+      if (qi < S) *reinterpret_cast<u32x4*>(Og + ((tok0 + qi) * a.Hq + hq) * D + 64 * half + 8 * (ln & 7)) = line;
     }
     asm volatile("" ::: "memory");
   }
-  // m_run is the reference exponent in units of s * scale * log2(e); l_tot is relative to it
-  if (a.lse && hf == 0 && qw_out + l32 < S)
-    a.lse[lse_index(a, b, hq, tok0, qw_out + l32)] = m_run[0] * 0.6931471805599453f + logf(l_tot);
+  // m_run is the reference exponent in units of s * scale * log2(e); the sums are relative to it
+  if (a.lse && grp < 2) {                  // lane group rt writes row tile rt
+    const int qi = qw_out + lane;
+    if (qi < S) a.lse[lse_index(a, b, hq, tok0, qi)] = (grp ? m_run[1] : m_run[0]) * 0.6931471805599453f + logf(grp ? lacc[1][0] : lacc[0][0]);
+  }
   if (!more) break;
   }   // for pass
 }

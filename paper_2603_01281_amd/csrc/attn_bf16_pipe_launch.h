@@ -66,7 +66,7 @@ hipError_t launch_attention_bf16_pipe_cfg(AttnArgs a, const SteerArgs* steer, hi
   constexpr int BQ = 32 * RBW;
   const size_t smem = attention_bf16_pipe_smem_bytes(D, a.S, STEER, NKR, HPW * RBW);
   if (smem > 160 * 1024) return hipErrorNotSupported;
-  auto kernel = attention_bf16_pipe_kernel<D, HPW, RBW, 1, STEER, NKR>;
+  auto kernel = attention_bf16_pipe_kernel<D, HPW, RBW, STEER, NKR>;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   if (e != hipSuccess) return e;

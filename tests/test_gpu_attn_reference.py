@@ -1,0 +1,57 @@
+"""bf16 attention where the softmax reference has to move: one key far above everything before it, at every position within a
+tile, and keys that are not numbers."""
+import numpy as np
+import pytest
+
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+
+def _reference(Q, K, V):
+    q, k, v = (x.double().cpu() for x in (Q, K, V))
+    B, S, Hq, D = q.shape
+    k, v = (x.repeat_interleave(Hq // k.shape[2], dim=2) for x in (k, v))
+    s = (q.permute(0, 2, 1, 3).contiguous() @ k.permute(0, 2, 3, 1).contiguous()) * D ** -0.5
+    mask = np.triu(np.ones((S, S), dtype=bool), 1)
+    s.masked_fill_(__import__("torch").from_numpy(mask), float("-inf"))
+    return (s.softmax(-1) @ v.permute(0, 2, 1, 3).contiguous()).permute(0, 2, 1, 3).numpy()
+
+
+@pytest.mark.parametrize("D,Hq,Hkv", [(128, 8, 2), (128, 2, 2), (128, 7, 1), (64, 8, 2)])
+def test_late_raise(seka, D, Hq, Hkv):
+    import torch
+    S = 456                                              # seven full tiles and eight keys
+    for j in (0, 5, 17, 31, 32, 63, 64, 100, 191, 192, 250, 383, 447, 448, 455):
+        print(f"late raise D={D} heads {Hq}/{Hkv} key {j}", flush=True)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(j)
+        Q, K, V = (torch.randn((1, S, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+        K[:, j] = (3.0 * Q[:, S // 2].reshape(1, Hkv, Hq // Hkv, D)[:, :, 0]).bfloat16()     # some rows score it 2^40 above the rest
+        O = torch.full_like(Q, float("nan"))
+        seka.seka_attention_plain(Q, K, V, O)
+        torch.cuda.synchronize()
+        H.assert_close_bf16(H.to_f64(O), _reference(Q, K, V), f"late raise at {j}")
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_keys_that_are_not_numbers(seka, D, bad):
+    """Rows before such a key are untouched; rows from it on are not numbers (an infinite key scores inf or -inf by the sign of
+    the query, and a row of -inf and finite scores is an ordinary one)."""
+    import torch
+    S, Hq, Hkv, j = 300, 8, 2, 170
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    Q, K, V = (torch.randn((1, S, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    clean = torch.empty_like(Q)
+    seka.seka_attention_plain(Q, K, V, clean)
+    K[:, j, :, 3] = bad
+    O = torch.empty_like(Q)
+    seka.seka_attention_plain(Q, K, V, O)
+    torch.cuda.synchronize()
+    assert torch.equal(O[:, :j], clean[:, :j])
+    tail = O[:, j:].float()
+    hit = torch.ones_like(tail, dtype=torch.bool) if bad != bad else (Q[:, j:, :, 3:4].float() > 0).expand_as(tail)
+    assert torch.isnan(tail[hit]).all()
+    assert torch.isfinite(tail[~hit]).all()
