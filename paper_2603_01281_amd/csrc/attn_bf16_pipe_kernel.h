@@ -619,51 +619,74 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     return __ballot(v != 0ull);
   };
 
-  // Dense form (rank > 32): edit the highlighted 16-key blocks of the (swizzled) K tile at Kb in place; wave w < 4
-  // owns block w.  What bounds the edit is LDS traffic for its matrix operand (every block reads all of it), so
-  // blocks are not split further.
-  auto edit_tile = [&](unsigned char* Kb, unsigned long long bits) __attribute__((always_inline)) {
+  // Dense form (rank > 32): edit the highlighted 16-key blocks of (swizzled) K tile `tile` at Kb in place; wave w < 4
+  // owns block w.  Every block reads all of the matrix operand (32 KB at D = 128), so blocks are not split further.  The
+  // output rows go in 2 KS groups of 16: the operand of a group is read while the group before it is multiplied, and a
+  // group is finished (scaled, added) while the next one is multiplied; the wave's keys and the first operand are on their way
+  // before it knows whether its block has highlighted keys.  (One group at a time, reads, products and the rest in a row, an
+  // event cost an editing wave 2050 cycles, all of it latency.)
+  auto edit_tile = [&](unsigned char* Kb, int tile) __attribute__((always_inline)) {
     // The lane index is re-derived behind an opaque copy so that none of the per-lane operand addresses below
     // is hoisted out of the tile loop: they would occupy registers the attention pipeline needs.
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int j = ln & 15, g = ln >> 4;
     const int kblk = wave;
-    const unsigned bits16 = (unsigned)((bits >> (16 * (kblk & 3))) & 0xffffull);
-    if (kblk >= BK / 16 || bits16 == 0) return;           // wave-uniform
+    if (kblk >= BK / 16) return;                          // wave-uniform
+    const unsigned long long bits = hlbits[tile];
     unsigned char* krow = Kb + (16 * kblk + j) * RB;
     bf16x8 kreg[KS];   // K^T as B operand: lane (col = key j, k = d = 32 s + 8 g + e) = logical chunk 4 s + g
 #pragma unroll
     for (int s = 0; s < KS; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j)));
-    const float mbit = ((bits16 >> j) & 1u) ? 1.f : 0.f;
-    const float ksc = 1.f + mbit * (kscale - 1.f);        // a for highlighted keys, exactly 1 otherwise
-    // k' = a k + mask (g P) k: output rows d are permuted so that each result lands in the lane that holds that
-    // element of k
+    struct Operand { bf16x8 u[NP][KS]; };     // of a group of 16 output rows
+    auto part = [&](int g8, int p, int ks) __attribute__((always_inline)) {
+      return *reinterpret_cast<const bf16x8*>(AP + p * D * D + ((g8 * KS + ks) * 64 + ln) * 8);
+    };
+    Operand ua;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      float outv[8];
+    for (int i = 0; i < NP * KS; ++i) ua.u[i / KS][i % KS] = part(0, i / KS, i % KS);
+    const unsigned bits16 = __builtin_amdgcn_readfirstlane((unsigned)((bits >> (16 * kblk)) & 0xffffull));
+    if (bits16 == 0) return;                              // wave-uniform
+    const bool lit = (bits16 >> j) & 1u;
+    // k' = a k + (g P) k: output rows d are permuted so that each result lands in the lane that holds that
+    // element of k, and the products are added to a k there.  Keys that are not highlighted keep their bits.
+    f32x4 c[3];
+    auto start = [&](int g8) __attribute__((always_inline)) {
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+      for (int i = 0; i < 4; ++i) c[g8 % 3][i] = (float)kreg[g8 >> 1][4 * (g8 & 1) + i] * kscale;
+      if (g8 < 2) asm volatile("s_nop 1" : "+v"(c[g8 % 3]));      // behind the others comes a `finish` before their products
+      else asm volatile("" : "+v"(c[g8 % 3]));
+    };
+    uint2 out[2];
+    auto finish = [&](int g8) __attribute__((always_inline)) {
+      const int s = g8 >> 1, half = g8 & 1;
+      asm volatile("s_nop 3" : "+v"(c[g8 % 3]));        // with the next group's products and reads: 11 states
+      bf16x4 o;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          const bf16x8 ua = *reinterpret_cast<const bf16x8*>(AP + (((s * 2 + half) * KS + ks) * 64 + ln) * 8);
-          acc[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua, kreg[ks], acc[ks & 1], 0, 0, 0);
-          if (NP == 2) {
-            const bf16x8 ul = *reinterpret_cast<const bf16x8*>(AP + D * D + (((s * 2 + half) * KS + ks) * 64 + ln) * 8);
-            acc[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ul, kreg[ks], acc[ks & 1], 0, 0, 0);
-          }
+      for (int i = 0; i < 4; ++i) o[i] = (__bf16)c[g8 % 3][i];
+      const uint2 ob = __builtin_bit_cast(uint2, o);
+      const uint4 kb = __builtin_bit_cast(uint4, kreg[s]);
+      out[half] = make_uint2(lit ? ob.x : half ? kb.z : kb.x, lit ? ob.y : half ? kb.w : kb.y);
+      if (half) *reinterpret_cast<uint4*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j))) = make_uint4(out[0].x, out[0].y, out[1].x, out[1].y);
+    };
+    start(0);
+#pragma unroll
+    for (int g8 = 0; g8 < 2 * KS; ++g8) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          pipe_mfma(c[g8 % 3], ua.u[p][ks], kreg[ks]);
+          __builtin_amdgcn_sched_barrier(0);
+          if (g8 + 1 < 2 * KS) ua.u[p][ks] = part(g8 + 1, p, ks);
+          __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          outv[4 * half + i] = (float)kreg[s][4 * half + i] * ksc + mbit * (acc[0][i] + acc[1][i]);
-        __builtin_amdgcn_sched_barrier(0);     // keeps the operand reads of later row groups from piling up in registers
-      }
-      bf16x8 o;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] = (__bf16)outv[e];
-      *reinterpret_cast<bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j))) = o;
+      if (g8 + 1 < 2 * KS) start(g8 + 1);
+      if (g8 > 0) finish(g8 - 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    asm volatile("s_nop 7" : "+v"(c[(2 * KS - 1) % 3]));
+    finish(2 * KS - 1);
   };
 
   // Score-side form (rank <= 32): the coordinates c .* (U_cat^T k) of the 64 keys of the (swizzled, unchanged) K
@@ -898,8 +921,8 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   } else if (STEER) {
     anyw = any_word(0);
     if (anyw & 3ull) {
-      if (anyw & 1ull) edit_tile(Kst, hlbits[0]);
-      if (anyw & 2ull) edit_tile(Kst + TB, hlbits[1]);
+      if (anyw & 1ull) edit_tile(Kst, 0);
+      if (anyw & 2ull) edit_tile(Kst + TB, 1);
       dma_barrier();
     }
     tile_evt = next_event(1);
@@ -982,7 +1005,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
           coords_tile(Kst + (tn % 3) * TB, hlbits[tn], zbuf + (tn & 1) * PIPE_Z_BYTES);
           ztile = tn;                    // first read after the barrier at the bottom of this iteration
         } else {
-          edit_tile(Kst + (tn % 3) * TB, hlbits[tn]);
+          edit_tile(Kst + (tn % 3) * TB, tn);
           dma_barrier();
 #pragma unroll
           for (int i = 0; i < 2; ++i) kp[i] = kfrag(i, knext_off);
