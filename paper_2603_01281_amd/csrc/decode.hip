@@ -714,9 +714,9 @@ bool decode_on_matrix_cores(int B, int S, int Hkv, int chunks, int D, int hp, in
 // D = 128: bf16 32 / 8 heads B=16, 290 MB, 49.8 / 50.7, 310 MB 55.2 / 54.0; 32 / 32 heads B=6 S=9078, 892 MB, 154.4 / 137.6
 // (6.5 TB/s); fp32 28 / 4 heads B=4 S=32000, 524 MB, 104.5 / 81.9; 32 / 16 heads B=40 S=1137, 745 MB, 136.6 / 123.0.
 // The lengths of a ragged batch are on the device: a quarter of the allocation is taken for them (lengths spread over 1 : 16
-// by ratio fill a third).  Two kinds of loads stay plain whatever this says: those of bf16 launches of a single range per head
-// group, and K in decode_partial_f32_kernel, whose lines are asked for by two loads each (us, plain / nontemporal K: 40 / 8 heads
-// B=15 S=4050 D = 128 84.4 / 95.5, 16 / 1 B=148 S=3417 91.8 / 110.2, 32 / 4 B=222 S=1114 192.9 / 200.7; up to 20 % slower, never faster).
+// by ratio fill a third).  One kind of loads stays plain whatever this says: K in decode_partial_f32_kernel, whose lines are asked
+// for by two loads each (us, plain / nontemporal K: 40 / 8 heads B=15 S=4050 D = 128 84.4 / 95.5, 16 / 1 B=148 S=3417 91.8 / 110.2,
+// 32 / 4 B=222 S=1114 192.9 / 200.7; up to 20 % slower, never faster).
 bool decode_streams(int B, int S, int Hkv, int D, int dtype, bool ragged, int chunks) {
   const double bytes = 2.0 * (dtype == SEKA_BF16 ? 2 : 4) * B * S * Hkv * D;
   return chunks == 1 && bytes * (ragged ? 0.25 : 1.0) > 300e6;
@@ -854,7 +854,11 @@ hipError_t launch_decode(const void* q, const void* K, const void* V, void* O, f
       // 32 / 8 heads.  Only one such workgroup fits a compute unit (LDS): at 512 workgroups 17.5 us became 20.1.
       if (D == 128) SEKA_DEC_LAUNCH(128, 8, false); else SEKA_DEC_LAUNCH(64, 8, false);
     } else {
-      if (D == 128) SEKA_DEC_LAUNCH(128, 4, false); else SEKA_DEC_LAUNCH(64, 4, false);
+      if (D == 128) {
+        if (streams) SEKA_DEC_LAUNCH(128, 4, true); else SEKA_DEC_LAUNCH(128, 4, false);
+      } else {
+        if (streams) SEKA_DEC_LAUNCH(64, 4, true); else SEKA_DEC_LAUNCH(64, 4, false);
+      }
     }
 #undef SEKA_DEC_LAUNCH
     return hipGetLastError();

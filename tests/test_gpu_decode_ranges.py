@@ -76,14 +76,15 @@ def test_small_workspace(seka):
         seka.seka_attention_decode(q, K, V, O, workspace=ws[:least - 16])
 
 
-# bf16 in a single range (plain loads); in several, also ragged; fp32 on the matrix cores and on the vector unit
+# bf16 in a single range, of less than a turn of the four waves too; in several, also ragged; fp32 on the matrix cores and on the
+# vector unit
 @pytest.mark.parametrize("dtype,B,S,Hq,Hkv,D,ragged", [
-    ("bf16", 74, 1000, 32, 8, 128, False), ("bf16", 148, 1001, 8, 8, 64, False), ("bf16", 37, 2000, 32, 8, 128, False),
+    ("bf16", 770, 97, 32, 8, 128, False), ("bf16", 74, 1000, 32, 8, 128, False), ("bf16", 148, 1001, 8, 8, 64, False), ("bf16", 37, 2000, 32, 8, 128, False),
     ("bf16", 74, 2003, 8, 8, 64, False), ("bf16", 148, 2100, 32, 8, 128, True), ("f32", 37, 1000, 32, 8, 128, False),
     ("f32", 73, 1017, 56, 8, 64, False), ("f32", 37, 1001, 40, 8, 128, False), ("f32", 148, 1050, 40, 8, 128, True)])
 def test_larger_than_the_caches(seka, dtype, B, S, Hq, Hkv, D, ragged):
-    """More than 300 MB of keys and values (of a ragged batch four times that), which launches of several ranges and all fp32
-    ones read without keeping a place for them; the first, a middle and the last prompt."""
+    """More than 300 MB of keys and values (of a ragged batch four times that), which are read without keeping a place for
+    them; the first, a middle and the last prompt."""
     import torch
     print(f"decode large {dtype} B={B} S={S} {Hq}/{Hkv} D={D} ragged={ragged}", flush=True)
     assert 2 * B * S * Hkv * D * (2 if dtype == "bf16" else 4) * (0.25 if ragged else 1) > 300e6
