@@ -2,8 +2,10 @@
 // sums of its outputs (project_wide.h has the sizes that fill the chip with 256 x 256 tiles).
 //
 // WM x WN waves, each TM x TN outputs, on v_mfma_f32_16x16x32_bf16 (see project_wide.h).  64-wide slices of E travel straight
-// into a ring of NS stages in LDS, NS of them ahead (three where a slice is 32 or 48 KB; six of the 24 KB slices of 128 x 64
-// tiles, whose one wave per SIMD finishes a slice before the third one ahead has come: 24.4 -> 22.7 us at 128 tokens, E = N = 4096);
+// into a ring of NS stages in LDS, NS of them ahead (three where a slice is 32 or 48 KB; four of the 24 KB slices of 128 x 64
+// tiles, whose one wave per SIMD finishes a slice before the third one ahead has come.  Against three with 32 x 32 x 16 products,
+// 28 shapes of up to 240 such tiles, geometric means at E = 512, 1024, 2048, 4096: four 0.99 / 0.98 / 0.95 / 0.93, six 1.02 / 1.00 /
+// 0.98 / 0.95);
 // the operands of a slice are read one slice before its products.  One barrier per slice: behind barrier k slice k + 1 is in
 // LDS (every wave has waited for its own loads of it) and slice k in registers (and for its reads of it), so its stage
 // takes slice k + NS, and the reads of slice k + 1 run beside the products of slice k.
@@ -137,6 +139,7 @@ __global__ __launch_bounds__(64 * WM * WN) void project_route_tile_kernel(const 
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
   const uint32_t sel = (l16 & 1) ? 0x03020706u : 0x05040100u;      // bytes of {neighbour, own}: see below
   if (TM * wm > last_row || TN * wn > last_col) return;            // wave-uniform; no barrier follows
+  float* const sums = ROUTE ? project_sums(workspace, row0 + TM * wm, col0 + TN * wn, S, G, Hkv) : nullptr;
 #pragma unroll
   for (int j = 0; j < CBS; ++j) {
     float colsum = 0.f;
@@ -155,14 +158,9 @@ __global__ __launch_bounds__(64 * WM * WN) void project_route_tile_kernel(const 
         *reinterpret_cast<uint32_t*>(stage + LINE * m + (byte ^ (16 * (m & (LC - 1))))) = pair;
       }
     if (ROUTE) {
-      // these 64 tokens lie in one prompt (S is a multiple of 128); feature -> (head, d)
       colsum += __shfl_xor(colsum, 16);
       const float tot = colsum + __shfl_xor(colsum, 32);
-      const size_t tok = row0 + TM * wm;
-      const int b = (int)(tok / S), tchunk = (int)(tok % S) / 64;
-      const int f = col0 + TN * wn + 16 * j + l16, hq = f / 128, h = hq / G, g = hq % G;
-      const int chunks = (S / 64) * G;
-      if (grp == 0) workspace[(((size_t)b * Hkv + h) * chunks + (size_t)tchunk * G + g) * 128 + f % 128] = tot;
+      if (grp == 0) sums[16 * j + l16] = tot;
     }
   }
   asm volatile("" ::: "memory");           // a wave's LDS accesses complete in program order

@@ -41,6 +41,16 @@ __device__ __forceinline__ void wide_load_16B(const void* base, uint32_t lane_of
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
 }
 
+// Where a wave's routing sums go: those of 64 tokens from `tok` on (they lie in one prompt, S is a multiple of 128) and of up to
+// 64 features from `col` on (of one head, D = 128).  Wave-uniform, one scalar division by S and one by G.  (Where the sums are
+// formed, for every 16 features, they were vector code, the one by S of 64 bits: 8 of the 18 KB of the wide kernel, and 0.5
+// to 1 us per launch: 32 / 8 heads, E = 512, 128 tokens 9.8 -> 9.1 us.)
+__device__ __forceinline__ float* project_sums(float* workspace, size_t tok, int col, int S, int G, int Hkv) {
+  const unsigned block = (unsigned)(tok >> 6), blocks = (unsigned)S >> 6, b = block / blocks, tchunk = block % blocks;
+  const unsigned hq = (unsigned)col >> 7, h = hq / (unsigned)G, g = hq % (unsigned)G;
+  return workspace + ((((size_t)b * Hkv + h) * blocks + tchunk) * G + g) * 128 + (col & 127);
+}
+
 template <bool ROUTE>
 __global__ __launch_bounds__(512) void project_route_wide_kernel(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
                                                                  uint16_t* __restrict__ Qout, int E, long long tokens, int N,
@@ -184,6 +194,7 @@ __global__ __launch_bounds__(512) void project_route_wide_kernel(const uint16_t*
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     if ((i == 1 && !rows_hi) || !cols) continue;                   // wave-uniform
+    float* const sums = ROUTE ? project_sums(workspace, row0 + 128 * i + 64 * wm, col0 + 64 * wn, S, G, Hkv) : nullptr;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
 #pragma unroll
@@ -204,14 +215,9 @@ __global__ __launch_bounds__(512) void project_route_wide_kernel(const uint16_t*
             *reinterpret_cast<uint32_t*>(stage + 8192 * i + 128 * m + (byte ^ (16 * (m & 7)))) = pair;
           }
         if (ROUTE) {
-          // these 64 tokens lie in one prompt (S is a multiple of 128); feature -> (head, d)
           colsum += __shfl_xor(colsum, 16);
           const float tot = colsum + __shfl_xor(colsum, 32);
-          const size_t tok = row0 + 128 * i + 64 * wm;
-          const int b = (int)(tok / S), tchunk = (int)(tok % S) / 64;
-          const int f = col0 + 64 * wn + 32 * j + 16 * cb + l16, hq = f / 128, h = hq / G, g = hq % G;
-          const int chunks = (S / 64) * G;
-          if (grp == 0) workspace[(((size_t)b * Hkv + h) * chunks + (size_t)tchunk * G + g) * 128 + f % 128] = tot;
+          if (grp == 0) sums[32 * j + 16 * cb + l16] = tot;
         }
       }
     }

@@ -492,7 +492,7 @@ hipError_t launch_project_route(const void* X, const void* W, int E, void* Qout,
       case 0: e = launch(w_out ? project_route_wide_kernel<true> : project_route_wide_kernel<false>, kWideTile, kWideTile, 512, (size_t)8 * kWideHalf); break;
       case 1: e = SEKA_PROJ_TILE(256, 128, 4, 2, 3); break;
       case 2: e = SEKA_PROJ_TILE(128, 128, 2, 4, 3); break;
-      default: e = SEKA_PROJ_TILE(128, 64, 2, 2, 6); break;
+      default: e = SEKA_PROJ_TILE(128, 64, 2, 2, 4); break;
     }
   }
 #undef SEKA_PROJ_TILE

@@ -1,5 +1,5 @@
 """GPU parity of seka_project_route over its four tile sizes: half tiles at the edges, counts of slices of E that end in
-every turn of the three-stage ring (1 to 7 and 11) and of the six-stage ring (1 to 7 and 11 to 13); and over the kernel for rows of 2^22 elements and more."""
+every turn of the three-stage ring (1 to 7 and 11) and of the four-stage ring (1 to 7 and 11 to 13); and over the kernel for rows of 2^22 elements and more."""
 import pytest
 
 from paper_2603_01281_amd import inputs
