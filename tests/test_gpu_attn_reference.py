@@ -55,3 +55,31 @@ def test_keys_that_are_not_numbers(seka, D, bad):
     hit = torch.ones_like(tail, dtype=torch.bool) if bad != bad else (Q[:, j:, :, 3:4].float() > 0).expand_as(tail)
     assert torch.isnan(tail[hit]).all()
     assert torch.isfinite(tail[~hit]).all()
+
+
+@pytest.mark.parametrize("D,r,Hq,Hkv", [(128, 32, 8, 2), (128, 8, 2, 2), (64, 16, 8, 2), (64, 32, 2, 1), (128, 64, 8, 2)])
+@pytest.mark.parametrize("j", [0, 17, 31])
+def test_first_reference_of_highlighted_keys(seka, D, r, Hq, Hkv, j):
+    """A highlighted key of the first block that is all of a row: its probability is a power of two (against a reference without the
+    edit it is rounded to bf16, 2^-9 of the sum).  Scores are exact here; the other keys are e^-15 of the sum, exp2 and the
+    logarithm of a number near 20 are good to 4e-6."""
+    import torch
+    S = 200
+    for top in (14.0, 14.375, 15.0, 15.5):               # 8 significant bits; the edit doubles the key's score
+        print(f"first reference D={D} r={r} heads {Hq}/{Hkv} key {j} score {top}", flush=True)
+        Q, K = torch.zeros((1, S, Hq, D), device="cuda"), torch.zeros((1, S, Hkv, D), device="cuda")
+        Q[..., 0] = 8.0
+        K[:, j, :, 0] = top / 2
+        V = torch.randn((1, S, Hkv, D), device="cuda")
+        U = torch.zeros((Hkv, 1, D, r), device="cuda")
+        U[:, 0, torch.arange(r), torch.arange(r)] = 1.0
+        Q, K, V, U = (x.bfloat16() for x in (Q, K, V, U))
+        mask = torch.zeros((1, S), dtype=torch.uint8, device="cuda")
+        mask[:, j] = 1
+        O, lse = torch.empty_like(Q), torch.empty((1, Hq, S), device="cuda")
+        seka.seka_attention_prefill(Q, K, V, O, U, [1.0] * Hkv, mask, scale=0.125, lse=lse)
+        torch.cuda.synchronize()
+        i = np.arange(S)
+        ref = np.where(i < j, np.log(i + 1.0), np.log(i + np.exp(top)))
+        d = np.abs(lse.double().cpu().numpy() - ref)
+        assert d.max() <= 1e-5, f"{d.max():.3g} at row {int(d.max((0, 1)).argmax())}"
