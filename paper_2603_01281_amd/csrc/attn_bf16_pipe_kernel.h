@@ -110,12 +110,9 @@ __device__ __forceinline__ float pipe_max3(float a, float b, float c) {
   return r;
 }
 
-// Direct-to-LDS load with a scalar 64-bit base and a 32-bit per-lane byte offset: the wave's 64 x 16 bytes land contiguously at
-// the (wave-uniform) LDS byte address.  Inline assembly keeps it outside the compiler's own vmcnt bookkeeping: the waits
-// are placed by hand.
+// (the LDS address is wave-uniform, which the compiler does not always see)
 __device__ __forceinline__ void pipe_load_16B(const void* base, uint32_t lane_off, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(lane_off), "s"(base)
-               : "memory", "m0");
+  dma_load_16B(base, lane_off, __builtin_amdgcn_readfirstlane(lds_base));
 }
 
 // Sum / maximum over the 64 lanes (all active), the same value in all of them.

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(64 * WM * WN) void project_route_tile_kernel(const 
   const int nk = E / kWideK;
   auto issue_one = [&](int n, size_t at, int stage) __attribute__((always_inline)) {
     // BM / 8 is a multiple of NW or the other way round: wave-uniform either way
-    wide_load_16B((8 * (wave + NW * n) < BM ? Xb : Wb) + at, off[n], lds0 + stage * STAGE + 1024 * (wave + NW * n));
+    dma_load_16B((8 * (wave + NW * n) < BM ? Xb : Wb) + at, off[n], lds0 + stage * STAGE + 1024 * (wave + NW * n));
   };
   auto at_of = [&](int k) __attribute__((always_inline)) { return (size_t)min(k, nk - 1) * (kWideK * 2); };     // past the end: a slice nobody uses
 

@@ -37,10 +37,6 @@ namespace seka {
 
 constexpr int kWideTile = 256, kWideK = 64, kWideHalf = 128 * kWideK * 2;     // bytes of a half tile
 
-__device__ __forceinline__ void wide_load_16B(const void* base, uint32_t lane_off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory", "m0");
-}
-
 // Where a wave's routing sums go: those of 64 tokens from `tok` on (they lie in one prompt, S is a multiple of 128) and of up to
 // 64 features from `col` on (of one head, D = 128).  Wave-uniform, one scalar division by S and one by G.  (Where the sums are
 // formed, for every 16 features, they were vector code, the one by S of 64 bits: 8 of the 18 KB of the wide kernel, and 0.5
@@ -92,12 +88,12 @@ __global__ __launch_bounds__(512) void project_route_wide_kernel(const uint16_t*
   auto issue_a = [&](int half, int k, int buf) __attribute__((always_inline)) {     // past the end: a slice nobody uses
     const unsigned char* src = Xb + (half ? a_half : 0) + (size_t)min(k, nk - 1) * (kWideK * 2);
 #pragma unroll
-    for (int s = 0; s < 2; ++s) wide_load_16B(src, aoff[s], lds0 + (2 * buf + half) * kWideHalf + slot_lds[s]);
+    for (int s = 0; s < 2; ++s) dma_load_16B(src, aoff[s], lds0 + (2 * buf + half) * kWideHalf + slot_lds[s]);
   };
   auto issue_b = [&](int half, int k, int buf) __attribute__((always_inline)) {
     const unsigned char* src = Wb + (half ? b_half : 0) + (size_t)min(k, nk - 1) * (kWideK * 2);
 #pragma unroll
-    for (int s = 0; s < 2; ++s) wide_load_16B(src, boff[s], ldsB + (2 * buf + half) * kWideHalf + slot_lds[s]);
+    for (int s = 0; s < 2; ++s) dma_load_16B(src, boff[s], ldsB + (2 * buf + half) * kWideHalf + slot_lds[s]);
   };
 
   typedef __attribute__((address_space(3))) const bf16x8* lds_frag;
