@@ -52,15 +52,13 @@ namespace seka {
 // 64-bit highlight word per tile and, for rank <= 32, the buffers of the score-side form.
 // Rank <= 32 (nkr == 1): the edit is applied to the scores, s_ij = q_i . k_j + (U^T q_i) . (c .* U^T k_j) for
 // highlighted j (paper Sec. 2, the equivalence of key-side and score-side control, Eq. 5): U_cat is stored once, as
-// the operand of U_cat^T K^T; the coordinates c .* U^T k of a tile's keys go to one of two 64 x 32 bf16 buffers
-// (rows padded to 80 bytes: conflict-free 16-byte row reads), and every wave keeps U^T q of its 32 rows as two
-// MFMA operands (2 KB).  Larger ranks: the keys themselves are edited with the dense D x D matrix
+// the operand of U_cat^T K^T; the coordinates c .* U^T k of a tile's keys go to one of two 64 x 32 bf16 buffers,
+// and every wave keeps U^T q of its 32 rows as two MFMA operands (2 KB).  Larger ranks: the keys themselves are edited with the dense D x D matrix
 // g P = U_cat diag(c) U_cat^T, built once per workgroup; at rank >= 64 one product with it moves no more operand
 // bytes than two low-rank products and has no intermediate.  Either way the operands are stored in the order the
 // MFMAs read them (one 16-byte LDS read per lane and operand).
 constexpr int PIPE_RA = 8;                          // MFMAs between an operand read from LDS and its use (5, 7 and 10 within 1 %)
-constexpr int PIPE_Z_LD = 80;                       // bytes per key in a coordinate buffer
-constexpr int PIPE_Z_BYTES = DMA_BK * PIPE_Z_LD;    // one buffer
+constexpr int PIPE_Z_BYTES = DMA_BK * 64;           // one coordinate buffer: [4 blocks of 16 keys][64 lanes][8] bf16
 constexpr int PIPE_QT_BYTES = 2048;                 // U^T q of one wave: [2 row tiles][64 lanes][8] bf16
 // bf16 parts of an element of g P (dense form).  One part rounds it to 2^-9, at D = 128 less than the edited key's own
 // rounding adds; a full-rank projector at D = 64 (whose diagonal is g) was further from the exact result than the form with
@@ -231,7 +229,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   uint16_t* U1 = UN;                       // low rank: operand (rb, s) of U_cat^T K^T: [2][4][64 lanes][8]
   uint16_t* AP = UN;                       // dense: operand (s_out, half, ks) of (g P) K^T: [NP][D/32][2][D/32][64 lanes][8]
   float* cvec = reinterpret_cast<float*>(UN + (DENSE ? (size_t)NP * D * D : (size_t)D * Rpad));   // [Rpad]
-  unsigned char* zbuf = reinterpret_cast<unsigned char*>(cvec + Rpad);     // low rank: [2][64 keys][80 B] coordinates
+  unsigned char* zbuf = reinterpret_cast<unsigned char*>(cvec + Rpad);     // low rank: [2][4 blocks][64 lanes][8] coordinates
   unsigned char* qtbuf = zbuf + 2 * PIPE_Z_BYTES;                          // low rank: [NW][2][64 lanes][8] U^T q
   unsigned long long* hlbits = reinterpret_cast<unsigned long long*>(      // [tiles] (STEER)
       DENSE ? reinterpret_cast<unsigned char*>(cvec + Rpad) : qtbuf + NW * PIPE_QT_BYTES);
@@ -292,7 +290,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // chunk position l % CH, and fetches the logical chunk that the swizzle assigns to that position.
   const uint32_t rowbytes = (uint32_t)a.Hkv * D * 2;
   const uint32_t kst_base = (uint32_t)(uintptr_t)(dma_lds_void_ptr)Kst;
-  const uint32_t vst_base = (uint32_t)(uintptr_t)(dma_lds_void_ptr)Vst;
+  const uint32_t vst_base = kst_base + DMA_STAGES * TB;      // (Vst itself, a generic pointer, would be compared with null at every request)
   // V travels in units of half a tile, one half tile behind K: "shifted tile" t = rows [64 t - 32, 64 t + 32) = the
   // 32-key blocks 2t - 1 and 2t, and block j lives at ring position j % 6 (HB bytes each; tile t = positions 2t % 6,
   // 2t % 6 + 1 as before).  The PV product of a block runs one step after its softmax (see `step`), so the last
@@ -330,7 +328,8 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   auto issue_k_to = [&](auto full_c, int t, uint32_t lds_stage_base) __attribute__((always_inline)) {
     const int w = opaque_wave();
     if (decltype(full_c)::value || t * BK + BK <= S) {
-      const unsigned char* tile = Kbytes + (size_t)t * BK * rowbytes;
+      // (a product of 32-bit factors: of 64-bit ones it took five scalar instructions more per tile)
+      const unsigned char* tile = Kbytes + (uint64_t)(uint32_t)(t * BK) * rowbytes;
 #pragma unroll
       for (int n = 0; n < SPW; ++n) pipe_load_16B(tile, koff[n], lds_stage_base + slot_lds(w, n));
     } else {
@@ -349,7 +348,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     const int w = opaque_wave();
     const int first = t * BK - BK / 2;
     if (decltype(full_c)::value || (first >= 0 && first + BK <= S)) {
-      const unsigned char* tile = Vbytes + (size_t)first * rowbytes;
+      const unsigned char* tile = Vbytes + (uint64_t)(uint32_t)first * rowbytes;
 #pragma unroll
       for (int n = 0; n < SPW; ++n) pipe_load_16B(tile, voff[n], vst_base + (vslot_hi(w, n) ? posB : posA) + vslot_lds(w, n));
     } else {
@@ -628,7 +627,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int j = ln & 15, g = ln >> 4;
-    const int kblk = wave;
+    const int kblk = opaque_wave();
     if (kblk >= BK / 16) return;                          // wave-uniform
     const unsigned long long bits = hlbits[tile];
     unsigned char* krow = Kb + (16 * kblk + j) * RB;
@@ -686,43 +685,59 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     finish(2 * KS - 1);
   };
 
-  // Score-side form (rank <= 32): the coordinates c .* (U_cat^T k) of the 64 keys of the (swizzled, unchanged) K
-  // tile at Kb, zero for keys that are not highlighted, into the buffer at zdst; wave w < 4 owns the 16-key block w
+  // Score-side form (rank <= 32): the coordinates c .* (U_cat^T k) of the 64 keys of (swizzled, unchanged) K tile `tile`
+  // at Kb, zero for keys that are not highlighted, into the buffer at zdst; wave w < 4 owns the 16-key block w
   // (a block without highlights only stores zeros).  A key's 32 coordinates are stored in the order the score
   // correction contracts them: lane group grp, slot e  <->  r = 16 (e / 4) + 4 grp + e % 4, which is the order in which
-  // a lane of the 16 x 16 accumulators holds U^T q of its query row.
-  auto coords_tile = [&](const unsigned char* Kb, unsigned long long bits, unsigned char* zdst) __attribute__((always_inline)) {
+  // a lane of the 16 x 16 accumulators holds U^T q of its query row.  The operands are on their way before the wave knows
+  // whether its block has highlighted keys.  What bounds an event is latency: of LDS, and of scalar registers that come back from
+  // vector lanes.  With the operands read one after the other here and in `corr`, and the event's tests on 64-bit values whose
+  // halves were spilled, short steered prompts at D = 64 took 3.8 % longer (12 shapes, few workgroups or many highlighted keys; 32 / 4 heads
+  // S=1220 28.2 -> 27.2 us, 8 / 2 heads S=9875 165.4 -> 158.4).
+  auto coords_tile = [&](const unsigned char* Kb, int tile, unsigned char* zdst) __attribute__((always_inline)) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int j = ln & 15, g = ln >> 4;
-    const int kblk = wave;
+    const int kblk = opaque_wave();
     if (kblk >= BK / 16) return;                          // wave-uniform
-    const unsigned bits16 = (unsigned)((bits >> (16 * kblk)) & 0xffffull);
-    // this lane's results: key 16 kblk + j, coordinates r = 16 half + 4 g + i  ->  group g, slots 4 half + i
-    unsigned char* zrow = zdst + (16 * kblk + j) * PIPE_Z_LD + 16 * g;
-    if (bits16 == 0) {
-      *reinterpret_cast<uint4*>(zrow) = make_uint4(0, 0, 0, 0);
-      return;
-    }
+    const unsigned long long bits = hlbits[tile];
     const unsigned char* krow = Kb + (16 * kblk + j) * RB;
     bf16x8 kreg[KS];   // K^T as B operand: lane (col = key j, k = d = 32 s + 8 g + e) = logical chunk 4 s + g
 #pragma unroll
     for (int s = 0; s < KS; ++s) kreg[s] = *reinterpret_cast<const bf16x8*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j)));
-    const float mbit = ((bits16 >> j) & 1u) ? 1.f : 0.f;
-    bf16x8 z8;
+    constexpr int AHEAD = D == 64 ? 2 * KS : KS;          // of the 2 KS operands (all of them at D = 128: 8 registers spilled)
+    auto operand = [&](int i) __attribute__((always_inline)) { return *reinterpret_cast<const bf16x8*>(U1 + (i * 64 + ln) * 8); };
+    bf16x8 ua[2 * KS];
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // two chains: even and odd slices of d
+    for (int i = 0; i < AHEAD; ++i) ua[i] = operand(i);
+    auto coefficients = [&](int half) __attribute__((always_inline)) { return *reinterpret_cast<const f32x4*>(cvec + 16 * half + 4 * g); };
+    f32x4 c4[2];
+    if (D == 64) c4[0] = coefficients(0), c4[1] = coefficients(1);
+    __builtin_amdgcn_sched_barrier(0);
+    const unsigned bits16 = __builtin_amdgcn_readfirstlane((unsigned)((bits >> (16 * kblk)) & 0xffffull));
+    // this lane's results: key 16 kblk + j, coordinates r = 16 half + 4 g + i  ->  lane of the operand, slots 4 half + i
+    u32x4* const zrow = reinterpret_cast<u32x4*>(zdst + 1024 * kblk + 16 * ln);
+    u32x4 z = {0u, 0u, 0u, 0u};
+    if (bits16 != 0) {                                    // wave-uniform
+      bf16x8 z8;
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const bf16x8 ua = *reinterpret_cast<const bf16x8*>(U1 + ((half * KS + s) * 64 + ln) * 8);
-        acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua, kreg[s], acc[s & 1], 0, 0, 0);
+      for (int half = 0; half < 2; ++half) {
+        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // two chains: even and odd slices of d
+#pragma unroll
+        for (int s = 0; s < KS; ++s) acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ua[half * KS + s], kreg[s], acc[s & 1], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (D == 128) c4[half] = coefficients(half);
+#pragma unroll
+        for (int i = AHEAD; i < (half == 0 ? 2 * KS : 0); ++i) ua[i] = operand(i);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z8[4 * half + i] = (__bf16)((acc[0][i] + acc[1][i]) * c4[half][i]);
       }
-      const f32x4 c4 = *reinterpret_cast<const f32x4*>(cvec + 16 * half + 4 * g);
+      const u32x4 w = __builtin_bit_cast(u32x4, z8);
+      const bool lit = (bits16 >> j) & 1u;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) z8[4 * half + i] = (__bf16)((acc[0][i] + acc[1][i]) * (c4[i] * mbit));
+      for (int i = 0; i < 4; ++i) z[i] = lit ? w[i] : 0u;
     }
-    *reinterpret_cast<bf16x8*>(zrow) = z8;
+    *zrow = z;
   };
 
   for (int pass = 0;; ++pass) {      // one turn per block of query rows (indentation of the body kept flat)
@@ -910,7 +925,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     }
     anyw = any_word(0);
     if (anyw & 1ull) {
-      coords_tile(Kst, hlbits[0], zbuf);
+      coords_tile(Kst, 0, zbuf);
       dma_barrier();
       ztile = 0;
     }
@@ -925,18 +940,22 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     tile_evt = next_event(1);
   }
   // Score correction of one 32-key block of S^T (keys keyoff .. keyoff + 31 of `tile`): += Z (32 keys x 32 r) . (U^T q)^T,
-  // four MFMAs; A = the keys' coordinates from the tile's buffer, B = this wave's U^T q operands.
-  auto corr = [&](int tile, int keyoff, f32x4 (&sv)[2][2]) __attribute__((always_inline)) {
-    const unsigned char* zp = zbuf + (tile & 1) * PIPE_Z_BYTES + (keyoff + l16) * PIPE_Z_LD + 16 * grp;
+  // four MFMAs; A = the keys' coordinates from the tile's buffer, B = this wave's U^T q operands.  before_step: the next vector
+  // instruction that reads the scores is that of a step.
+  auto corr = [&](auto before_step_c, int tile, int keyoff, f32x4 (&sv)[2][2]) __attribute__((always_inline)) {
+    const unsigned char* zp = zbuf + (tile & 1) * PIPE_Z_BYTES + keyoff * 64 + lane * 16;
     const unsigned char* qp = qtbuf + wave * PIPE_QT_BYTES + lane * 16;
+    const bf16x8 za[2] = {*reinterpret_cast<const bf16x8*>(zp), *reinterpret_cast<const bf16x8*>(zp + 1024)};
     const bf16x8 qb[2] = {*reinterpret_cast<const bf16x8*>(qp), *reinterpret_cast<const bf16x8*>(qp + 1024)};
+    __builtin_amdgcn_sched_barrier(0);     // all four on their way before the first product
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) {
-      const bf16x8 za = *reinterpret_cast<const bf16x8*>(zp + 16 * kt * PIPE_Z_LD);
+    for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) pipe_mfma(sv[kt][rt], za, qb[rt]);
-    }
-    pipe_mfma_result_guard(sv);
+      for (int kt = 0; kt < 2; ++kt) pipe_mfma(sv[kt][rt], za[kt], qb[rt]);
+    // a step reads sv[0][0] behind its first product, the other tiles in this order four elements apart: with the three products behind
+    // each, eight states and more
+    if (decltype(before_step_c)::value) asm volatile("s_nop 3" : "+v"(sv[0][0]), "+v"(sv[0][1]), "+v"(sv[1][0]), "+v"(sv[1][1]));
+    else pipe_mfma_result_guard(sv);
   };
 
   bf16x8 pb[2] = {zeros8, zeros8};   // probabilities (P^T operands) of the block whose PV product is next; none at first
@@ -960,7 +979,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) sv[i >> 1][i & 1] = sc0[i >> 1][i & 1];
         asm volatile("s_nop 1" : "+v"(sv[0][0]), "+v"(sv[0][1]), "+v"(sv[1][0]), "+v"(sv[1][1]));
-        corr(0, 0, sv);
+        corr(std::false_type{}, 0, 0, sv);
         first_reference(sv);
       } else {
         first_reference(sc0);
@@ -1002,7 +1021,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // block) and ztile tells the next iteration which scores to correct.  No barrier of its own: the coordinates are
   // first read after the barrier at the bottom of the iteration, by the corrections of the two score blocks of
   // that tile at the top of the next iteration and after its first step.
-  auto events = [&](int t, int knext_off, bf16x8 (&kp)[2]) __attribute__((always_inline)) {
+  auto events = [&](int t, int koff, bf16x8 (&kp)[2]) __attribute__((always_inline)) {
     if (!STEER) return;
     // one scalar compare in the common case; tiles past the end and unsteered heads have no bit set
     const int tn = t + 1;
@@ -1010,15 +1029,15 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
       const unsigned sh = tn & 63;
       if (sh == 0u) anyw = any_word(tn);
       tile_evt = next_event(tn);
-      if ((anyw >> sh) & 1ull) {
+      if ((unsigned)(anyw >> sh) & 1u) {      // (of 32 bits: as a 64-bit test it kept four more scalar registers)
         if (!DENSE) {                    // score-side: the tile stays as it is, its coordinates go to a buffer
-          coords_tile(Kst + (tn % 3) * TB, hlbits[tn], zbuf + (tn & 1) * PIPE_Z_BYTES);
+          coords_tile(Kst + koff, tn, zbuf + (tn & 1) * PIPE_Z_BYTES);
           ztile = tn;                    // first read after the barrier at the bottom of this iteration
         } else {
-          edit_tile(Kst + (tn % 3) * TB, tn);
+          edit_tile(Kst + koff, tn);
           dma_barrier();
 #pragma unroll
-          for (int i = 0; i < 2; ++i) kp[i] = kfrag(i, knext_off);
+          for (int i = 0; i < 2; ++i) kp[i] = kfrag(i, koff);
         }
       }
     }
@@ -1114,13 +1133,13 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     using std::integral_constant;
     // The operand addresses pass through an opaque copy once per tile: otherwise every "address + stage offset"
     // below is hoisted out of the loop into a register of its own (dozens), instead of being an immediate.
-    if (STEER && !DENSE && __builtin_expect(ztile == t, 0)) corr(t, 0, sc0);
+    if (STEER && !DENSE && __builtin_expect(ztile == t, 0)) corr(std::true_type{}, t, 0, sc0);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(kaddr[ks]));
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) asm volatile("" : "+v"(vaddr[dt]));
     step(integral_constant<int, ST * TB + HB>{}, kaddr[0] + ((ST + 1) % 3) * TB, integral_constant<int, ((2 * ST + 5) % 6) * HB>{}, sc0, sc1, pb, kpre);
-    if (STEER && !DENSE && __builtin_expect(ztile == t, 0)) corr(t, 32, sc1);
+    if (STEER && !DENSE && __builtin_expect(ztile == t, 0)) corr(std::true_type{}, t, 32, sc1);
     top(std::true_type{}, st_c, t);
     if (kEventsInHot) events(t, ((ST + 1) % 3) * TB, kpre);
     step(integral_constant<int, ((ST + 1) % 3) * TB>{}, kaddr[0] + ((ST + 1) % 3) * TB + HB, integral_constant<int, 2 * ST * HB>{}, sc1, sc0, pb, kpre);
@@ -1183,9 +1202,9 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     }
     top(std::false_type{}, IC0{}, t);
     const int off = (t % 3) * TB, offn = ((t + 1) % 3) * TB;
-    if (STEER && !DENSE && ztile == t) corr(t, 0, sc0);
+    if (STEER && !DENSE && ztile == t) corr(std::true_type{}, t, 0, sc0);
     ring_step(off + HB, offn, (int)vpos(2 * t - 1), sc0, sc1);
-    if (STEER && !DENSE && ztile == t) corr(t, 32, sc1);
+    if (STEER && !DENSE && ztile == t) corr(std::true_type{}, t, 32, sc1);
     events(t, offn, kpre);
     ring_step(offn, offn + HB, (int)vpos(2 * t), sc1, sc0);
     bottom(std::false_type{}, t);
@@ -1200,7 +1219,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   for (; t < ntiles; ++t) {
     top(std::false_type{}, IC0{}, t);
     const bool zt = STEER && !DENSE && ztile == t;     // before the event of tile t + 1 moves ztile on
-    events(t, 0, kpre);                     // this wave scores nothing further; other waves may (kpre is dead here)
+    events(t, ((t + 1) % 3) * TB, kpre);                     // this wave scores nothing further; other waves may (kpre is dead here)
     if (owed) {
       pv_block(owed_off, pb);
       owed = false;
@@ -1212,8 +1231,8 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
       const bool second = (qw & 32) != 0;      // wave-uniform
       if (second) qk_block(off + HB, sc1);
       if (zt) {
-        corr(t, 0, sc0);
-        if (second) corr(t, 32, sc1);
+        corr(std::false_type{}, t, 0, sc0);
+        if (second) corr(std::false_type{}, t, 32, sc1);
       }
       if (t > 0) pv_block((int)vpos(2 * t - 1), pb);     // the block before this tile (its softmax ran in the last step)
       auto last_block = [&](bool masked, bool empty, int j0, f32x4 (&sv)[2][2]) __attribute__((always_inline)) {

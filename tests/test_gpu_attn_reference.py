@@ -83,3 +83,28 @@ def test_first_reference_of_highlighted_keys(seka, D, r, Hq, Hkv, j):
         ref = np.where(i < j, np.log(i + 1.0), np.log(i + np.exp(top)))
         d = np.abs(lse.double().cpu().numpy() - ref)
         assert d.max() <= 1e-5, f"{d.max():.3g} at row {int(d.max((0, 1)).argmax())}"
+
+
+@pytest.mark.parametrize("D,r", [(128, 16), (128, 64), (64, 16), (64, 64)])
+def test_infinite_key_beside_a_highlighted_one(seka, D, r):
+    """A key that is not highlighted gets no correction, not even 0 times what its products with the basis are."""
+    import torch
+    S, Hq, Hkv, j = 300, 8, 2, 170
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    Q, K, V = (torch.randn((1, S, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+    U = torch.zeros((Hkv, 1, D, r), device="cuda")
+    U[:, 0, torch.arange(r), torch.arange(r)] = 1.0
+    mask = torch.zeros((1, S), dtype=torch.uint8, device="cuda")
+    mask[:, j - 1] = 1                                   # one of the same 16 keys
+    out = []
+    for K3 in (K[:, j, :, 3].clone(), float("inf")):
+        K[:, j, :, 3] = K3
+        O = torch.empty_like(Q)
+        seka.seka_attention_prefill(Q, K, V, O, U.bfloat16(), [0.5] * Hkv, mask)
+        torch.cuda.synchronize()
+        out.append(O)
+    assert torch.equal(out[1][:, :j], out[0][:, :j])
+    low = (Q[:, j:, :, 3:4].float() < 0).expand_as(out[1][:, j:])       # scores of -inf: ordinary rows
+    assert torch.isfinite(out[1][:, j:].float()[low]).all()
+    assert torch.isnan(out[1][:, j:].float()[~low]).all()
