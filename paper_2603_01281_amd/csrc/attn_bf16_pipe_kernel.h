@@ -81,9 +81,10 @@ typedef __attribute__((address_space(3))) const bf16x8* pipe_lds_bf16x8_ptr;
 
 // The products of the tile loop are inline assembly: with the builtin the compiler takes other registers for a product's result than
 // for its accumulator, and then waits before it lets anything else into the registers that became free.  It does not know what
-// they are, so the waits that the instruction needs are placed by hand: a product's result may be read by a vector
-// instruction 11 wait states after it was issued at the earliest (mfma_result_guard; in the pipelined loop 16 other products lie
-// between), and a register that a vector instruction wrote may be read by a product after 2 (mfma_operand_guard).
+// they are, so the waits that the instruction needs are placed by hand: a product's result may be read or overwritten by a vector
+// instruction 8 wait states after it was issued at the earliest (4 passes and 4, which is what the compiler keeps behind its own;
+// mfma_result_guard is 12; in the pipelined loop the products of the outputs and sums lie between, 18 at D = 128, 10 at D = 64),
+// and a register that a vector instruction wrote may be read by a product after 2 (mfma_operand_guard).
 __device__ __forceinline__ void pipe_mfma_first(f32x4& d, const bf16x8& a, const bf16x8& b) {      // d = a b
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
 }
@@ -656,7 +657,9 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     uint2 out[2];
     auto finish = [&](int g8) __attribute__((always_inline)) {
       const int s = g8 >> 1, half = g8 & 1;
-      asm volatile("s_nop 3" : "+v"(c[g8 % 3]));        // with the next group's products and reads: 11 states
+      // 8 states and more: with the four products of the next group, and behind all but the last but one their reads and four multiplications
+      if (g8 == 2 * KS - 2) asm volatile("s_nop 7" : "+v"(c[g8 % 3]));
+      else asm volatile("s_nop 3" : "+v"(c[g8 % 3]));
       bf16x4 o;
 #pragma unroll
       for (int i = 0; i < 4; ++i) o[i] = (__bf16)c[g8 % 3][i];
