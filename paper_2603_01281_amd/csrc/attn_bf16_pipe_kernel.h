@@ -621,8 +621,10 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // output rows go in 2 KS groups of 16: the operand of a group is read while the group before it is multiplied, and a
   // group is finished (scaled, added) while the next one is multiplied; the wave's keys and the first operand are on their way
   // before it knows whether its block has highlighted keys.  (One group at a time, reads, products and the rest in a row, an
-  // event cost an editing wave 2050 cycles, all of it latency.)
-  auto edit_tile = [&](unsigned char* Kb, int tile) __attribute__((always_inline)) {
+  // event cost an editing wave 2050 cycles, all of it latency.)  ahead_c false: one group at a time all the same, for the turns behind
+  // a wave's last tile at D = 128, where the reads ahead spilled 17 to 25 registers (no slower: ratios of time for B=8 S=4096 32 / 8 heads rank 128, a ragged batch of rank 48
+  // and one prompt of 32k tokens at rank 64 0.999 to 1.001; 110 shapes 0.998).
+  auto edit_tile = [&](auto ahead_c, unsigned char* Kb, int tile) __attribute__((always_inline)) {
     // The lane index is re-derived behind an opaque copy so that none of the per-lane operand addresses below
     // is hoisted out of the tile loop: they would occupy registers the attention pipeline needs.
     int ln = lane;
@@ -668,6 +670,25 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
       out[half] = make_uint2(lit ? ob.x : half ? kb.z : kb.x, lit ? ob.y : half ? kb.w : kb.y);
       if (half) *reinterpret_cast<uint4*>(krow + 16 * ((4 * s + g) ^ pipe_k_swizzle<D>(j))) = make_uint4(out[0].x, out[0].y, out[1].x, out[1].y);
     };
+    if (!decltype(ahead_c)::value) {       // one group after the other
+#pragma unroll
+      for (int g8 = 0; g8 < 2 * KS; ++g8) {
+        if (g8 > 0) {
+#pragma unroll
+          for (int i = 0; i < NP * KS; ++i) ua.u[i / KS][i % KS] = part(g8, i / KS, i % KS);
+        }
+        start(g8);
+        asm volatile("s_nop 1" : "+v"(c[g8 % 3]));
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int p = 0; p < NP; ++p) pipe_mfma(c[g8 % 3], ua.u[p][ks], kreg[ks]);
+        asm volatile("s_nop 7" : "+v"(c[g8 % 3]));
+        finish(g8);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      return;
+    }
     start(0);
 #pragma unroll
     for (int g8 = 0; g8 < 2 * KS; ++g8) {
@@ -936,8 +957,8 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   } else if (STEER) {
     anyw = any_word(0);
     if (anyw & 3ull) {
-      if (anyw & 1ull) edit_tile(Kst, 0);
-      if (anyw & 2ull) edit_tile(Kst + TB, 1);
+      if (anyw & 1ull) edit_tile(std::true_type{}, Kst, 0);
+      if (anyw & 2ull) edit_tile(std::true_type{}, Kst + TB, 1);
       dma_barrier();
     }
     tile_evt = next_event(1);
@@ -1024,7 +1045,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // block) and ztile tells the next iteration which scores to correct.  No barrier of its own: the coordinates are
   // first read after the barrier at the bottom of the iteration, by the corrections of the two score blocks of
   // that tile at the top of the next iteration and after its first step.
-  auto events = [&](int t, int koff, bf16x8 (&kp)[2]) __attribute__((always_inline)) {
+  auto events = [&](auto ahead_c, int t, int koff, bf16x8 (&kp)[2]) __attribute__((always_inline)) {
     if (!STEER) return;
     // one scalar compare in the common case; tiles past the end and unsteered heads have no bit set
     const int tn = t + 1;
@@ -1037,7 +1058,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
           coords_tile(Kst + koff, tn, zbuf + (tn & 1) * PIPE_Z_BYTES);
           ztile = tn;                    // first read after the barrier at the bottom of this iteration
         } else {
-          edit_tile(Kst + koff, tn);
+          edit_tile(ahead_c, Kst + koff, tn);
           dma_barrier();
 #pragma unroll
           for (int i = 0; i < 2; ++i) kp[i] = kfrag(i, koff);
@@ -1144,7 +1165,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     step(integral_constant<int, ST * TB + HB>{}, kaddr[0] + ((ST + 1) % 3) * TB, integral_constant<int, ((2 * ST + 5) % 6) * HB>{}, sc0, sc1, pb, kpre);
     if (STEER && !DENSE && __builtin_expect(ztile == t, 0)) corr(std::true_type{}, t, 32, sc1);
     top(std::true_type{}, st_c, t);
-    if (kEventsInHot) events(t, ((ST + 1) % 3) * TB, kpre);
+    if (kEventsInHot) events(std::true_type{}, t, ((ST + 1) % 3) * TB, kpre);
     step(integral_constant<int, ((ST + 1) % 3) * TB>{}, kaddr[0] + ((ST + 1) % 3) * TB + HB, integral_constant<int, 2 * ST * HB>{}, sc1, sc0, pb, kpre);
     bottom(std::true_type{}, t);
   };
@@ -1208,7 +1229,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     if (STEER && !DENSE && ztile == t) corr(std::true_type{}, t, 0, sc0);
     ring_step(off + HB, offn, (int)vpos(2 * t - 1), sc0, sc1);
     if (STEER && !DENSE && ztile == t) corr(std::true_type{}, t, 32, sc1);
-    events(t, offn, kpre);
+    events(std::true_type{}, t, offn, kpre);
     ring_step(offn, offn + HB, (int)vpos(2 * t), sc1, sc0);
     bottom(std::false_type{}, t);
     ++t;
@@ -1222,7 +1243,7 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   for (; t < ntiles; ++t) {
     top(std::false_type{}, IC0{}, t);
     const bool zt = STEER && !DENSE && ztile == t;     // before the event of tile t + 1 moves ztile on
-    events(t, ((t + 1) % 3) * TB, kpre);                     // this wave scores nothing further; other waves may (kpre is dead here)
+    events(std::bool_constant<D == 64>{}, t, ((t + 1) % 3) * TB, kpre);                     // this wave scores nothing further; other waves may (kpre is dead here)
     if (owed) {
       pv_block(owed_off, pb);
       owed = false;

@@ -9,6 +9,9 @@ writes a register.
   result of a 16 x 16 x 32 product  -> anything but a product that accumulates   8 (4 passes; what the compiler keeps for its own)
                                        onto the same registers
 
+And, from the same code objects: the pipelined attention kernels keep every vector register (a reload waits for all loads before it, the
+tiles in flight too).
+
 Needs the LLVM tools of ROCm and the built library, and no GPU."""
 import os
 import re
@@ -19,6 +22,7 @@ import pytest
 from paper_2603_01281_amd import build
 
 OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
+READELF = os.path.join(os.path.dirname(OBJDUMP), "llvm-readelf")
 KINDS = {"v": 0, "a": 1 << 9, "s": 1 << 10}
 NAMED = {"m0": {KINDS["s"] + 200}, "vcc": {KINDS["s"] + 106, KINDS["s"] + 107}, "vcc_lo": {KINDS["s"] + 106}, "vcc_hi": {KINDS["s"] + 107},
          "exec": {KINDS["s"] + 126, KINDS["s"] + 127}}
@@ -202,3 +206,17 @@ def test_compiled_kernels_keep_them(code_objects):
                 bad.append(f"{name}: {len(found)}\n  " + "\n  ".join(found[:4]))
     assert seen > 1000, "the products of the attention kernels"
     assert not bad, "\n".join(bad)
+
+
+def test_pipelined_kernels_spill_no_vector_registers(code_objects):
+    spills = {}
+    for path in code_objects:
+        notes = subprocess.run([READELF, "--notes", path], check=True, capture_output=True, text=True).stdout
+        kernel = ""
+        for key, value in re.findall(r"\.(symbol|vgpr_spill_count):\s+(\S+)", notes):
+            if key == "symbol":
+                kernel = value
+            elif "attention_bf16_pipe_kernel" in kernel:
+                spills[kernel] = int(value)
+    assert len(spills) == 32, sorted(spills)
+    assert not any(spills.values()), {k: v for k, v in spills.items() if v}
