@@ -61,10 +61,13 @@ hipError_t launch_attention_bf16_group(const AttnArgs& a, const SteerArgs* steer
 template <int D, bool STEER>
 hipError_t launch_attention_bf16_any(const AttnArgs& a, const SteerArgs* steer, hipStream_t s) {
   // Many prompts of one block of rows of one or two heads: the register-staged kernel at D = 64 runs two workgroups per
-  // compute unit and hides their starts behind each other (32 / 32 heads, rank 32, us, this / pipelined: B=64 S=64
-  // 34 / 49, B=64 S=203 123 / 130, B=14 S=203 31 / 35; at S=300 the other way, 237 / 201; four heads x 64 rows never).
+  // compute unit and hides their starts behind each other.  Plain calls take it at every such length (32 / 32 heads, us, this / pipelined:
+  // B=64 S=64 21 / 35, S=128 41 / 54, S=256 75 / 87).  Steered ones only with a whole tile of keys (rank 64, B=64 S=64 37 / 53; 16 / 8
+  // heads B=256 56 / 61) or a few keys (S=8 37 / 47): of a mask whose rows are not aligned it forms the highlight words byte by byte (S=24
+  // B=18 22 / 18, S=100 B=64 94 / 67, S=203 138 / 96), and over several tiles the pipelined kernel's events cost less (8 / 8 heads B=64 S=128
+  // 22 / 21, 16 / 8 heads B=256 98 / 78, 32 / 32 heads B=64 S=256 126 / 103).  Four heads x 64 rows never.
   const int G = a.Hq / a.Hkv, heads = G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
-  const bool staged = D == 64 && heads < 4 && a.S <= 256 / heads && (long long)a.B * (a.Hq / heads) > 256;
+  const bool staged = D == 64 && heads < 4 && a.S <= 256 / heads && (!STEER || a.S == 64 || a.S <= 8) && (long long)a.B * (a.Hq / heads) > 256;
   if (!staged) {
     const hipError_t e = launch_attention_bf16_pipe<D>(a, steer, s);
     if (e != hipErrorNotSupported) return e;     // highlight bitmap too large for LDS at this S: register-staged kernel

@@ -445,8 +445,8 @@ size_t project_route_workspace_bytes(int B, int S, int Hq) {
 // 0.27 / 0.29 / 0.32.  us for E = 4096, N = 4096 in that order of tiles (128 x 128 register-staged before): 128 tokens
 // 60 / 46 / 27 / 20 (44), 512 62 / 48 / 29 / 24 (46), 1024 64 / 51 / 37 / 48 (51), 2048 69 / 63 / 72 / 89, 32768 811 with the
 // first; 1536 tokens E = 2880 48 / 40 / 46 / 51, 4096 x 1024 x 5120 82 / 67 / 44 / 57 (66).  Those are figures of 32 x 32 x 16
-// products; with 16 x 16 x 32 ones all four are up to 10 % faster and the rule still takes a kind within 0.15 % of the best one
-// (geometric mean over 5000 shapes timed with each).
+// products and three stages; with 16 x 16 x 32 ones and four stages for 128 x 64 all four are up to 10 % faster and the rule still takes a kind
+// within 0.11 % of the best one (geometric mean over 260 shapes timed with each, at most 2.5 %; always 128 x 128 14 %).
 inline int project_tile_of(long long tokens, int N, int E) {
   constexpr struct { int bm, bn; double alone, crowded; } kinds[4] = {{256, 256, 0.92, 0.66}, {256, 128, 0.68, 0.26}, {128, 128, 0.375, 0.155}, {128, 64, 0.27, 0.05}};
   int best = 0;

@@ -10,10 +10,11 @@ pytestmark = pytest.mark.gpu
 
 
 # every workgroup shape (4 x 64, 2 x 128, 1 x 256, 7 x 32 rows), both forms of the edit, one tile to several turns of the
-# ring, and (80 prompts) the sizes that stay with the register-staged kernel
+# ring, and (80 prompts and more) the sizes that stay with the register-staged kernel: plain up to 256 / heads rows, steered at 64 and up to 8
 @pytest.mark.parametrize("B,S,Hq,Hkv,M,r", [
     (1, 1, 4, 1, 1, 8), (2, 64, 8, 2, 1, 32), (1, 65, 4, 2, 1, 40), (1, 129, 3, 3, 4, 8), (2, 257, 6, 2, 2, 64), (1, 448, 14, 2, 1, 16),
-    (1, 900, 4, 1, 2, 16), (1, 833, 7, 1, 4, 32), (1, 1100, 2, 1, 1, 64), (80, 130, 4, 4, 1, 32), (80, 260, 4, 4, 3, 32)])
+    (1, 900, 4, 1, 2, 16), (1, 833, 7, 1, 4, 32), (1, 1100, 2, 1, 1, 64), (80, 130, 4, 4, 1, 32), (80, 260, 4, 4, 3, 32),
+    (80, 64, 4, 4, 1, 32), (140, 64, 4, 2, 2, 32), (80, 8, 4, 4, 1, 64), (80, 9, 4, 4, 1, 32), (80, 65, 4, 4, 1, 64), (140, 128, 4, 2, 1, 16)])
 @pytest.mark.parametrize("scaled", [False, True])
 def test_d64(seka, B, S, Hq, Hkv, M, r, scaled):
     import torch
