@@ -775,10 +775,11 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   }
   pipe_pin_acc(oacc, lacc);
   const float c2 = a.scale * 1.4426950408889634f;   // probabilities are exp2(s * c2 - m)
-  // m_run: reference exponent of the row (in units of s * c2).  It follows the row maximum lazily: when it is raised it is put
-  // kLead above the maximum, and it is raised only where a probability reaches 2, or (in the wave's last tile, which takes
-  // its maxima anyway) where the maximum has moved more than kSlack since; so probabilities stay below 2 and the output
-  // accumulators are rescaled a handful of times per row instead of once per block.
+  // m_run: reference exponent of the row (in units of s * c2).  It follows the row maximum lazily.  A row's first one is put kLead
+  // above the maximum of its first block.  It is put there again where a probability of any row of the wave reaches 2, and
+  // then in every row of the wave whose maximum has moved more than kSlack since; so too in the wave's last tile, which
+  // takes its maxima anyway.  So probabilities stay below 2 and the output accumulators are rescaled a handful of times
+  // per row instead of once per block.
   constexpr float kLead = 11.f, kSlack = 8.f;
   float m_run[2] = {-1e30f, -1e30f};
   // The tile loops live in a (generic, always inlined) lambda of their own.  This changes nothing in what is
@@ -870,20 +871,13 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
     }
   };
   // Probabilities of one block, packed as P^T operands (lane group grp, slot e <-> key 16 (e / 4) + 4 grp + e % 4).
-  // Returns the bits of all of them or-ed together: they are not negative, so bit 14 or 30 is set if and only if one
-  // of them is 2 or more (or not a number).
-  auto block_exp = [&](const f32x4 (&sv)[2][2], bf16x8 (&pb)[2]) __attribute__((always_inline)) -> uint32_t {
-    uint32_t bits = 0;
+  auto block_exp = [&](const f32x4 (&sv)[2][2], bf16x8 (&pb)[2]) __attribute__((always_inline)) {
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
       const float mneg = -m_run[rt];
 #pragma unroll
       for (int e = 0; e < 8; ++e) pb[rt][e] = (__bf16)__builtin_amdgcn_exp2f(__builtin_fmaf(sv[e >> 2][rt][e & 3], c2, mneg));
-      const u32x4 w = __builtin_bit_cast(u32x4, pb[rt]);
-      bits = (w[0] | w[1] | bits);
-      bits = (w[2] | w[3] | bits);
     }
-    return bits;
   };
   // O^T += V^T P^T for one 32-key block, and the row sums of P^T (the rounded probabilities, those that the products use)
   // as one more output tile whose V^T is all ones; off = LDS byte offset of the block's first row
@@ -1077,10 +1071,11 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
   // the block at KNEXT, the one the following step scores.
   //
   // No row maximum in the common case.  The probabilities of `cur` are formed against the row's reference exponent
-  // as it stands, and their bits tell whether that was safe: a probability of 2 or more (or one that is not a number)
+  // as it stands, and their bits tell whether that was safe: they are not negative, so bit 14 or 30 of a packed pair is set if and
+  // only if one of them is 2 or more (or not a number), and that
   // means some score ran far ahead of the reference, and only then is the block's maximum computed, the
-  // reference raised and the block's probabilities formed again (a handful of times per row; the first block of a
-  // row always takes this turn, its reference starts at -1e30).  The common case is 16 multiply-adds, 16
+  // reference raised and the block's probabilities formed again (a handful of times per row; not for its first block, whose
+  // maximum the first reference was taken from before the loop, unless that was -inf).  The common case is 16 multiply-adds, 16
   // exponentials, 8 packings and 4 ors per 34 MFMAs: no three-input maxima, no cross-lane exchange, no raise test, and
   // the row sums are two of the MFMAs (as dot products with ones, eight per step, they took a ninth of the step's time).
   auto step = [&](auto koff_c, uint32_t knext, auto voff_c, f32x4 (&cur)[2][2], f32x4 (&next)[2][2], bf16x8 (&pb)[2],
