@@ -108,3 +108,57 @@ def test_infinite_key_beside_a_highlighted_one(seka, D, r):
     low = (Q[:, j:, :, 3:4].float() < 0).expand_as(out[1][:, j:])       # scores of -inf: ordinary rows
     assert torch.isfinite(out[1][:, j:].float()[low]).all()
     assert torch.isnan(out[1][:, j:].float()[~low]).all()
+
+
+@pytest.mark.parametrize("D,r,Hq,Hkv", [(128, 16, 8, 2), (128, 32, 7, 1), (128, 64, 8, 2), (64, 16, 8, 2), (64, 64, 2, 2)])
+def test_late_raise_by_a_highlighted_key(seka, D, r, Hq, Hkv):
+    """The edit doubles the key that is far above everything before it: scores of both sides of the reference come from the correction
+    (rank <= 32) or from the edited tile."""
+    import torch
+    S = 456
+    U = torch.zeros((Hkv, 1, D, r), device="cuda")
+    U[:, 0, torch.arange(r), torch.arange(r)] = 1.0
+    for j in (17, 32, 63, 64, 100, 191, 250, 383, 447, 448, 455):
+        print(f"late raise, highlighted D={D} r={r} heads {Hq}/{Hkv} key {j}", flush=True)
+        g = torch.Generator(device="cuda")
+        g.manual_seed(100 + j)
+        Q, K, V = (torch.randn((1, S, h, D), generator=g, device="cuda").bfloat16() for h in (Hq, Hkv, Hkv))
+        q = Q[:, S // 2].reshape(1, Hkv, Hq // Hkv, D)[:, :, 0].float()
+        q[..., r:] = 0                                   # all of it in the basis: the edit doubles it exactly
+        K[:, j] = (1.5 * q * (D / r) ** 0.5).bfloat16()
+        mask = torch.zeros((1, S), dtype=torch.uint8, device="cuda")
+        mask[:, j] = 1
+        Ke = K.clone()
+        Ke[:, j] *= 2
+        O = torch.full_like(Q, float("nan"))
+        seka.seka_attention_prefill(Q, K, V, O, U.bfloat16(), [1.0] * Hkv, mask)
+        torch.cuda.synchronize()
+        H.assert_close_bf16(H.to_f64(O), _reference(Q, Ke, V), f"late raise, highlighted key {j}")
+
+
+@pytest.mark.parametrize("D,Hq,Hkv,r", [(128, 8, 2, 0), (128, 2, 2, 0), (128, 7, 1, 0), (128, 3, 3, 0), (64, 8, 2, 0), (64, 7, 1, 0),
+                                        (128, 8, 2, 16), (128, 8, 2, 64), (64, 8, 2, 16), (64, 2, 1, 64)])
+def test_row_sums_of_long_rows(seka, D, Hq, Hkv, r):
+    """Keys that all score the same: every probability is the power of two that the reference leaves (kept exactly in bf16), so row i's sum is
+    that of i + 1 equal terms, exact in fp32, and its log-sum-exp is the score + log(i + 1).  What is left is the rounding of numbers below
+    16, the reference and the logarithm: a few times 2^-21.  Highlighted keys are orthogonal to the basis: the edit changes nothing."""
+    import torch
+    S, score = 8231, 1.375
+    Q, K = torch.zeros((1, S, Hq, D), device="cuda"), torch.zeros((1, S, Hkv, D), device="cuda")
+    Q[..., 0] = 8.0
+    K[..., 0] = score
+    V = torch.ones((1, S, Hkv, D), device="cuda")
+    Q, K, V = (x.bfloat16() for x in (Q, K, V))
+    O, lse = torch.full_like(Q, float("nan")), torch.empty((1, Hq, S), device="cuda")
+    if r:
+        U = torch.zeros((Hkv, 1, D, r), device="cuda")
+        U[:, 0, torch.arange(1, r + 1) % D, torch.arange(r)] = 1.0
+        U[:, 0, 0] = 0.0
+        mask = (torch.arange(S, device="cuda")[None] % 3 == 1).to(torch.uint8).contiguous()
+        seka.seka_attention_prefill(Q, K, V, O, U.bfloat16(), [1.0] * Hkv, mask, scale=0.125, lse=lse)
+    else:
+        seka.seka_attention_plain(Q, K, V, O, lse=lse, scale=0.125)
+    torch.cuda.synchronize()
+    d = np.abs(lse.double().cpu().numpy() - (score + np.log(np.arange(S) + 1.0)))
+    assert d.max() <= 5e-6, f"{d.max():.3g} at row {int(d.max((0, 1)).argmax())}"
+    assert (O == 1).all()
