@@ -15,7 +15,7 @@
 // 0.3, tile loads and barrier 0.1 (a stand-alone loop of this step, all compute units busy; each at its own clock).
 // Consequences:
 //   * the products are 16 x 16 x 32 and not 32 x 32 x 16: half the accumulator traffic per multiply-add, and on random operands
-//     the chip sustains 2.05 PFLOP/s of them against 1.76.  With four plain vector instructions beside each 32 cycles of
+//     the chip sustains 1.95 PFLOP/s of them against 1.76 (mfma_rate_probe.hip).  With four plain vector instructions beside each 32 cycles of
 //     MFMA that is 17.7 ns against 20.2;
 //   * the row sums are products too (one more output tile, of ones): as v_dot2c_f32_bf16 of the packed probabilities, eight per
 //     32-key block, they took 2.3 of 20.6 ns, as two MFMAs they take 1.0;
@@ -126,10 +126,12 @@ __device__ __forceinline__ int pipe_wave_max(int v) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
-// What a block of query rows and a workgroup cost beside their key tiles, in units of one 64-key tile (2700 cycles at
-// D = 128):
-// a block waits for its first tiles, runs its last ones outside the unrolled loop and writes its output; a workgroup
-// starts and prepares the edit.
+// What a block of query rows and a workgroup cost beside their key tiles, in units of one 64-key tile (2800 cycles at
+// D = 128, 1900 at D = 64):
+// a block waits for its first tiles, runs its last ones outside the unrolled loop and writes its output (stamps: 4.7 tiles at D = 128,
+// 5.4 at D = 64); a workgroup starts and prepares the edit (plain 2.4 and 2.1, rank <= 32 3.3 and 3.4, above 4.1).  Little hangs on
+// them: over 330 drawn shapes at D = 128 and 140 at D = 64, each timed at all five widths that are considered, the widths chosen with
+// half or twice these values are within 0.8 % of those chosen with these.
 constexpr float pipe_block_tiles(int D) { return 4.f * 128 / D; }
 constexpr float pipe_start_tiles(int D) { return 3.f * 128 / D; }
 
@@ -1167,7 +1169,8 @@ attention_bf16_pipe_kernel(AttnArgs a, SteerArgs st) {
 
   // A step at run-time ring offsets.  The operand addresses are moved there before the step and back after it: an
   // address formed inside the step is a vector instruction that the order asked for has no place for, and the
-  // step's MFMAs then end up in a row in front of its exponentials (4100 cycles per tile instead of the loop's 2700).
+  // step's MFMAs then end up in a row in front of its exponentials (4100 cycles per tile instead of the loop's 2700, with 32 x 32 x 16
+  // products).
   auto move_addr = [&](uint32_t dk, uint32_t dv) __attribute__((always_inline)) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {

@@ -5,7 +5,7 @@
 // What bounds it: the matrix pipe under the chip's power limit, and the LDS reads beside it.  A 64-wide slice of E is 2048
 // cycles of MFMA per SIMD, 1536 cycles of LDS operand reads and 512 of tile writes.  The products are
 // v_mfma_f32_16x16x32_bf16: an MFMA of that shape reads and writes half as much accumulator per multiply-add as
-// v_mfma_f32_32x32x16_bf16, and alone, on random operands, the chip sustains 2.05 PFLOP/s of it against 1.76 (the clock is
+// v_mfma_f32_32x32x16_bf16, and alone, on random operands, the chip sustains 1.95 PFLOP/s of it against 1.76 (mfma_rate_probe.hip; the clock is
 // what gives; nothing else changes, operand bytes and register counts are the same).  Eight waves as 2 x 4; a wave owns 64 x 32 outputs in each
 // of the four quadrants of the tile (128 tokens x 128 features), so that operands of one half are kept in registers
 // for two quadrants.  The schedule is the eight-wave ping-pong that is published for CDNA matrix products (HipKittens,
