@@ -30,7 +30,7 @@
 //     earlier), with one exponential for every second MFMA.
 // Measured, us, 32 x 32 x 16 products with sums by dot products / now, launches of one box in turns: B=4 S=8192 32 / 8 heads D = 128
 // plain 1800 / 1703, rank 32 1892 / 1801; B=1 S=4096 124 / 118; B=1 S=32768 28 / 4 heads rank 64 6364 / 6060; B=4 S=700 rank 32
-// 32.9 / 32.7; D = 64 B=4 S=4096 plain 292 / 285, rank 32 310 / 312.
+// 32.9 / 32.7; D = 64 B=4 S=4096 plain 305 / 293, rank 32 317 / 305.
 // Tried: 64 query rows per wave, one wave per SIMD, outputs and queries in accumulation registers (half the LDS reads):
 // 1.6 % slower in the stand-alone loop and 15 % in the kernel, whose barrier and branches nothing overlaps then.
 // The softmax runs per 32-key block (half a tile), which halves the score registers the pipeline needs.
